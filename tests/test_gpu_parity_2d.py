@@ -335,3 +335,31 @@ def test_full_size_gradient_matrix_sampled(gpu, ref):
             _same_floats(_host(dd[4 * bi: 4 * bi + 4]), ref.decompress(want_c, 4, cols, rate),
                          "full r%d rows from %d" % (rate, 4 * bi))
         del dc, dd
+
+
+@pytest.mark.parametrize("cols", (257, 258, 259, 1022))
+def test_rows_aligned_to_their_elements_only(gpu, ref, cols):
+    """Column counts that are no multiple of 4: every row but each fourth (or second) starts off a
+    16-byte boundary, blocks inside the matrix move whole rows, the last block column and row stick
+    out.  fp32 and half precision, both directions, the reduce and the ring hops."""
+    import torch
+    rows = 70
+    x = _matrix(rows, cols, seed=cols % 5)
+    y = _matrix(rows, cols, seed=cols % 5 + 1)
+    for rate in (2, 8):
+        print("unaligned rows", cols, rate, flush=True)
+        _round_trip(gpu, ref, x, rate, "%d columns r%d" % (cols, rate))
+        cx, cy = ref.compress(x, rate), ref.compress(y, rate)
+        got = gpu.zc2d_reduce_compressed([_dev(cx), _dev(cy)], rows, cols, rate)
+        _same_bytes(_host(got), ref.reduce_compressed([cx, cy], rows, cols, rate), rate, "reduce")
+        got = gpu.zc2d_reduce_mixed([_dev(cx)], _dev(y), rows, cols, rate)
+        _same_bytes(_host(got), ref.reduce_mixed([cx], y, rows, cols, rate), rate, "reduce_mixed")
+        got = gpu.zc2d_reduce_decompress([_dev(cx)], _dev(y), rows, cols, rate)
+        _same_floats(_host(got), ref.reduce_decompress([cx], y, rows, cols, rate), "reduce_decompress")
+        for dtype in (torch.bfloat16, torch.float16):
+            h = _dev(x).to(dtype)
+            c = gpu.zc2d_compress_half(h, rate)
+            _same_bytes(_host(c), ref.compress(_host(h.float()), rate), rate, "compress_half")
+            # the narrowing is torch's: round to nearest even
+            back = gpu.zc2d_decompress_half(c, rows, cols, rate, dtype)
+            assert torch.equal(back.view(torch.int16), gpu.zc2d_decompress(c, rows, cols, rate).to(dtype).view(torch.int16))
