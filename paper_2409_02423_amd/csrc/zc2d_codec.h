@@ -15,20 +15,19 @@
 //     that far within its budget, which low rates rarely do;
 //   * the plane loop is unrolled, uniform over the wavefront, and ends when no lane has
 //     budget left;
-//   * encoder: the group tests of a plane are computed without a loop.  In the stream
-//     the newly significant coefficient of index p (counted from the first coefficient
-//     not yet significant) and rank j (1-based) ends its token at bit p + j, and every
-//     token starts one bit after the previous one ended, so the code is the pattern
-//     with each one moved up by its rank (two look-ups in a 256-entry table) plus that
-//     word shifted by one;
+//   * encoder: a plane is one code word, formed without a loop.  Past the coefficients
+//     already significant, a zero is one bit 0 and a newly significant coefficient two
+//     bits 1 (the end of its token and the next group bit), which two look-ups in a
+//     256-entry table per byte write down; the topmost of these bits is a group bit 0;
 //   * decoder: a table indexed by the next 9 stream bits and by how far the last
 //     coefficient is (whose token has no closing one) decodes all the tokens that lie
-//     whole within those bits; it is used when its result stays inside the budget,
-//     otherwise one token is decoded by count-trailing-zeros with the limits applied.
-//     A budget cut inside a run places the decoded one after the zeros read so far, which
-//     is the lowest index still possible.  A lane's progress through a plane is one state
-//     word that table entries are added to; lanes whose plane is closed read an all-zero
-//     row, so that a step needs no per-lane case distinction;
+//     whole within those bits.  The window is zero past the budget, which decodes to
+//     what unseen bits are but for a run cut by the budget (its one goes to the lowest
+//     index still possible); entries where that can matter are marked, and where it
+//     does, one token is decoded by count-trailing-zeros with the limits applied.  A
+//     lane's progress through a plane is one state word that table entries are added to;
+//     lanes whose plane is closed read an all-zero row, so that a step needs no per-lane
+//     case distinction;
 //   * after the planes, the usual case (at most 16 planes read, starting within the top
 //     16) turns each coefficient's 16-bit pattern into its word with one shift.
 #ifndef ZC2D_CODEC_H
@@ -42,6 +41,7 @@ using zc::alignbit;
 using zc::umin;
 using zc::umax;
 using zc::count_leading_zeros;
+using zc::count_leading_zeros_nonzero;
 using zc::count_trailing_zeros;
 
 constexpr int kFractionBits = 27;
@@ -103,16 +103,27 @@ ZC_DEV constexpr void transpose_halves(uint32_t (&a)[8]) {
 }
 
 // ---- tables --------------------------------------------------------------------------
-// Encoder: v[c] has, for each one of c at position p with 1-based rank j, bit p + j set.
-struct ExpandTable { uint32_t v[256]; };
+// Encoder.  Behind a plane's first group bit, a coefficient that is still zero is one bit 0 and
+// one that becomes significant is two bits 1: the end of its token and the next group bit.  Both
+// tables hold that expansion X(c) of eight coefficients c, for the two bytes of what a plane has
+// past the coefficients already significant.  v[c], the lower byte: bit 0 the first group bit (a
+// one), X(c) from bit 1 up (17 bits in all), and in the upper half how far the upper byte's
+// expansion moves up to follow it, 1 + 8 + (ones of c), from bit 20 up.  v[256 + c], the upper
+// byte: X(c).
+constexpr int kExpandEntries = 512;
+constexpr uint32_t kExpandBits = 0x1FFFFu;
+constexpr int kExpandShift = 20;
+struct ExpandTable { uint32_t v[kExpandEntries]; };
 constexpr ExpandTable build_expand_table() {
   ExpandTable t{};
   for (int c = 0; c < 256; ++c) {
-    uint32_t e = 0;
-    int rank = 0;
-    for (int p = 0; p < 8; ++p)
-      if ((c >> p) & 1) { ++rank; e |= 1u << (p + rank); }
-    t.v[c] = e;
+    uint32_t e = 0, at = 0;
+    for (int p = 0; p < 8; ++p) {
+      if ((c >> p) & 1) e |= 3u << at++;
+      ++at;
+    }
+    t.v[c] = 1u | e << 1 | (at + 1) << kExpandShift;
+    t.v[256 + c] = e;
   }
   return t;
 }
@@ -128,13 +139,20 @@ constexpr ExpandTable build_expand_table() {
 // An entry holds all the tokens that lie whole within the look-ahead: group bit, zeros,
 // closing one; a run that reaches the last coefficient needs no closing one, and the plane is
 // closed after it; a group bit 0 closes the plane.
-// Bits 0..9: the ones, as positions past the current coefficient; bits 10..14: how many
-// coefficients were passed; bit 15: the plane is closed (bits 10..15 are added to s);
-// bits 20..23: how many stream bits were used; bit 31: no token ends within the look-ahead
-// (so that entry >> 20 exceeds any budget, and the decoder reads one token on its own).
+// Byte 0: how many stream bits were used; byte 1, which is added to s: how many coefficients were
+// passed, bit 13: the plane is closed; upper half: the ones, as positions past the current
+// coefficient, nine at most, and in its top bit whether the budget matters to this entry.
+// Bits past the budget are zeros in the decoder's window, and what they decode to there is right
+// everywhere but in one place: zeros after a group bit 1 would put the one on the last
+// coefficient, where a run cut by the budget has it at the lowest index still possible.  So an
+// entry has bit 31 set if it holds a run that reaches the last coefficient without a closing one,
+// or no whole token at all (no bits used), and only these are ever checked against the budget.
+// (Such a run's entry belongs to an index of 7 or more, which moves bit 31 past the sixteen bits of
+// a plane when it is applied as it is.)
 constexpr int kLookahead = 9;
 constexpr int kTokenRows = 11;
 constexpr uint32_t kTokenFirstRowState = 6, kTokenIdleState = 16;
+constexpr uint32_t kTokenChecked = 1u << 31;
 struct TokenTable { uint32_t v[kTokenRows << kLookahead]; };
 constexpr TokenTable build_token_table() {
   TokenTable t{};
@@ -142,7 +160,7 @@ constexpr TokenTable build_token_table() {
     // coefficients between the current one and the last; row 0 stands for nine and more
     const uint32_t room = row == 0 ? 15u : 9u - row;
     for (uint32_t s = 0; s < (1u << kLookahead); ++s) {
-      uint32_t ones = 0, passed = 0, used = 0, done = 0;
+      uint32_t ones = 0, passed = 0, used = 0, done = 0, checked = 0;
       for (;;) {
         if (passed > room) { done = 1; break; }             // the last coefficient has been dealt with
         if (used >= (uint32_t)kLookahead) break;
@@ -156,10 +174,12 @@ constexpr TokenTable build_token_table() {
         }
         if (!in_sight) break;
         ones |= 1u << (passed + z);
+        if (passed + z == room) checked = 1;
         used += 1 + z + (passed + z == room ? 0 : 1);       // no closing one at the last coefficient
         passed += z + 1;
       }
-      t.v[(row << kLookahead) + s] = ones | passed << 10 | done << 15 | used << 20 | (used == 0u ? 1u << 31 : 0u);
+      if (used == 0u) checked = 1;
+      t.v[(row << kLookahead) + s] = used | passed << 8 | done << 13 | ones << 16 | (checked ? kTokenChecked : 0u);
     }
   }
   return t;
@@ -221,27 +241,40 @@ ZC_DEV void forward_transform(const uint32_t (&x)[16], uint32_t& E, uint32_t (&u
   for (int c = 0; c < 16; ++c) u[c] = ((uint32_t)q[kOrder.v[c]] + 0xAAAAAAAAu) ^ 0xAAAAAAAAu;
 }
 
-// One plane of the embedded code.  pat: the plane's bit of each coefficient; n: how many
-// leading coefficients are significant; left: budget.  Appends to the window W.
-template <int NW>
-ZC_DEV void encode_plane(uint32_t pat, const uint32_t* expand, uint32_t (&W)[NW], uint32_t& n, uint32_t& left) {
-  // coefficients already significant: their bits as they are
-  const uint32_t vlen = umin(n, left);
-  zc::shift_in<NW>(W, pat, vlen);
-  left -= vlen;
-  // the rest: ends of the tokens, then their starts one bit after the previous end
-  const uint32_t rest = pat >> n;
-  const uint32_t lo = expand[rest & 0xFFu], hi = expand[rest >> 8];
-  const uint32_t ends = lo | hi << (8u + (uint32_t)__builtin_popcount(rest & 0xFFu));
-  const uint32_t last = 31u - count_leading_zeros(ends);      // wraps to -1 if there is none
-  const uint32_t starts = ((ends << 1) & ((1u << (last & 31u)) - 1u)) | umin(ends, 1u);
-  uint32_t len = last + 2u;              // up to the last end, and the closing group bit 0
-  if (pat >> 15) len -= 2u;              // the last coefficient needs neither its end nor a closing bit
-  if (n == 16u) len = 0u;                // (when n is 16 the bit tested above was not a new one)
-  const uint32_t glen = umin(len, left);
-  zc::shift_in<NW>(W, ends | starts, glen);
-  left -= glen;
-  n = umax(n, 32u - count_leading_zeros(pat));
+// One plane of the embedded code, appended to the window W as one code word: the bits of the
+// coefficients already significant, then the group tests.  pat: the plane's bit of each
+// coefficient; m = 32 + how many leading coefficients are significant (shift counts and field
+// widths use their low five bits, and the word's length falls out as m less a count of leading
+// zeros); known: all patterns so far; left: budget; last_reached (the same in every lane): whether
+// some lane's pattern has ever had the last coefficient.
+// The tokens' starts and ends come from two look-ups (see ExpandTable) without any case
+// distinction: the topmost bit of the expansion is the group bit after the last one, or the
+// plane's only one, and both are zeros in the code.  Only the last coefficient is different (no
+// end, no group bit after it; and no group test at all once it is significant), so that is
+// corrected where some lane of the wavefront has got there.  The length is at most 31.  (Before:
+// starts and ends formed separately, verbatim bits appended on their own, 33 instructions per
+// plane at rate 4 instead of 23; compress2d of 8192 x 32768 values at rate 8 0.283 -> 0.262 ms.)
+template <int NW, class AnyActive>
+ZC_DEV void encode_plane(uint32_t pat, const uint32_t* expand, uint32_t (&W)[NW], uint32_t& m, uint32_t& known,
+                         uint32_t& left, bool& last_reached, AnyActive any_lane_active) {
+  const uint32_t rest = pat >> (m & 31u);
+  const uint32_t lo = expand[rest & 0xFFu], hi = expand[256u + (rest >> 8)];
+  uint32_t tokens = (lo & kExpandBits) | hi << (lo >> kExpandShift);
+  const uint32_t c = count_leading_zeros_nonzero(tokens);
+  uint32_t len = m - c;
+  last_reached = last_reached || any_lane_active(pat >= 0x8000u);
+  if (last_reached) {
+    // (sixteen ones in a first plane: the expansion is one bit longer than the word)
+    if (pat >= 0x8000u) len -= tokens == 0xFFFFFFFFu ? 1u : 2u;
+    if (m == 48u) len = 16u;
+  }
+  tokens ^= 0x80000000u >> c;
+  const uint32_t code = (pat & ((1u << (m & 31u)) - 1u)) | tokens << (m & 31u);
+  const uint32_t take = umin(len, left);
+  zc::shift_in<NW>(W, code, take);
+  left -= take;
+  known |= pat;
+  m = 64u - count_leading_zeros_nonzero(known);
 }
 
 template <int RATE, class AnyActive>
@@ -261,7 +294,8 @@ ZC_DEV void encode_block(const uint32_t (&x)[16], const uint32_t* expand, uint32
   for (int c = 0; c < 16; ++c) u[c] <<= (lead & 31u);   // first non-empty plane to bit 31
 #pragma unroll
   for (int j = 0; j < NW; ++j) W[j] = 0;
-  uint32_t n = 0;
+  uint32_t m = 32u, known = 0u;
+  bool last_reached = false;
   uint32_t h[8];
 #pragma unroll
   for (int w = 0; w < 8; ++w) h[w] = (u[w] >> 16) | (u[w + 8] & 0xFFFF0000u);
@@ -270,7 +304,7 @@ ZC_DEV void encode_block(const uint32_t (&x)[16], const uint32_t* expand, uint32
   for (int t = 0; t < 16; ++t) {
     if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
     const int b = 15 - t;
-    encode_plane<NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, n, left);
+    encode_plane<NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, m, known, left, last_reached, any_lane_active);
   }
   if (kMaxPlanes > 16 && any_lane_active(left > 0)) {
 #pragma unroll
@@ -280,7 +314,7 @@ ZC_DEV void encode_block(const uint32_t (&x)[16], const uint32_t* expand, uint32
     for (int t = 16; t < 32; ++t) {
       if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
       const int b = 31 - t;
-      encode_plane<NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, n, left);
+      encode_plane<NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, m, known, left, last_reached, any_lane_active);
     }
   }
   zc::shift_right<NW>(W, (uint32_t)(32 * NW - Traits<RATE>::kBlockBits) + left);
@@ -321,70 +355,64 @@ ZC_DEV void accumulate_scaled(const int32_t (&q)[16], uint32_t E, float (&sum)[1
 // zero times anything finite added to the sum is the sum plus zero.
 ZC_DEV bool scaling_is_exact(uint32_t E) { return E - 28u <= 222u || E == 0u; }
 
-// One plane of the embedded code, read from the bottom of the window W.  Returns the
-// plane's bit of each coefficient.  n: how many leading coefficients are significant.
+// One plane of the embedded code, read from the bottom of the window W, whose bits past the
+// budget are zeros.  Returns the plane's bit of each coefficient.  n: how many leading
+// coefficients are significant; left: budget, which zeros read past its end make negative (a lane
+// that has run out reads zero bits and a closed group test, which is what unseen bits are).
 //
-// The group tests are read in steps that all lanes of the wavefront take together.  A step
-// looks the next bits up in the token table (see there for the state s and the rows); if in
-// every lane that still reads this plane the entry's tokens lie inside the budget, the step is
-// just the entry applied: lanes whose plane is closed read empty entries, lanes out of budget
-// apply nothing.  Otherwise (some lane's first token is longer than the look-ahead, or its
-// budget ends inside the entry's bits) the step takes the general form: per lane the entry if
-// it fits, else one token by count-trailing-zeros with the limits applied.  Budgets of the
-// lanes of a wavefront end within a few steps of each other, so the general form is needed
-// near a block's end only.  any_lane_active.lanes(p) is the set of lanes where p holds, taken
-// per comparison (a compare instruction's result is that set), and .some(set) whether a set
-// is non-empty.
+// The group tests are read in steps that all lanes of the wavefront take together.  A step looks
+// the next bits up in the token table (see there for the state s and the rows) and applies the
+// entry, also in lanes whose plane is closed (they read empty entries).  Only if some lane's entry
+// is marked as one that the budget matters to, and that lane's first token is longer than the
+// look-ahead or its budget ends inside the entry's bits, an entry for one token is made for it by
+// count-trailing-zeros with the limits applied.  The first step looks up behind the bits of the significant coefficients, without moving the window
+// past them on their own (16 + 9 bits are in its first word).
+// (With every entry checked against the budget, lanes out of budget masked and the significant
+// coefficients' bits shifted out apart, a plane took 12 instructions and a step 17 at rate 4, now 6
+// and 14: decompress2d of 8192 x 32768 values 0.262 -> 0.253 ms at rate 4, 0.308 -> 0.294 ms at
+// rate 8, the 2-way reduce 0.642 -> 0.623 and 0.850 -> 0.784 ms with the encoder's part.)
 template <int NW, class AnyActive>
-ZC_DEV uint32_t decode_plane(const uint32_t* token, uint32_t (&W)[NW], uint32_t& n, uint32_t& left,
+ZC_DEV uint32_t decode_plane(const uint32_t* token, uint32_t (&W)[NW], uint32_t& n, int32_t& left,
                              AnyActive any_lane_active) {
-  const uint32_t vlen = umin(n, left);
-  uint32_t pat = W[0] & ((1u << vlen) - 1u);
-  zc::shift_out<NW>(W, vlen);
-  left -= vlen;
-  uint32_t s = n;   // n = 16: nothing left to test, the plane counts as closed
-  for (;;) {
-    const bool open = s < kTokenIdleState, funded = left > 0u;
-    const auto reading = any_lane_active.lanes(open) & any_lane_active.lanes(funded);
-    if (!any_lane_active.some(reading)) break;
-    // byte offset of the entry: (clamped state - first row's state) rows, then the next bits;
-    // the constant rides on the masking of the bits (it has none of their positions set)
-    constexpr uint32_t kRowBytesLg = kLookahead + 2;
-    constexpr uint32_t kBias = 0u - (kTokenFirstRowState << kRowBytesLg);
-    const uint32_t clamped = umin(umax(s, kTokenFirstRowState), kTokenIdleState);
-    uint32_t bits = W[0] & ((1u << kLookahead) - 1u);
+  // byte offset of the entry: (clamped state - first row's state) rows, then the next bits;
+  // the constant rides on the masking of the bits (it has none of their positions set)
+  constexpr uint32_t kRowBytesLg = kLookahead + 2;
+  constexpr uint32_t kBias = 0u - (kTokenFirstRowState << kRowBytesLg);
+  auto look_up = [&](uint32_t state, uint32_t bits) {
+    const uint32_t clamped = umin(umax(state, kTokenFirstRowState), kTokenIdleState);
     zc::materialise(bits);   // (a bit-field extract, then shift-and-or with the constant, then shift-and-add:
     bits = bits << 2 | kBias;   //  otherwise the constant comes back as an addition of its own)
     zc::materialise(bits);
-    const uint32_t at = (clamped << kRowBytesLg) + bits;
-    const uint32_t e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(token) + at);
-    const bool unfit = (e >> 20) > left;
-    if (!any_lane_active.some(reading & any_lane_active.lanes(unfit))) {
-      const uint32_t a = funded ? e : 0u;
-      pat |= (a & 0x3FFu) << (s & 31u);
-      s += (a >> 10) & 0x3Fu;
-      const uint32_t used = (a >> 20) & 15u;
-      zc::shift_out<NW>(W, used);
-      left -= used;
-    } else if (open && funded) {
-      // one token with the limits applied where the entry does not fit (its group bit is a one,
-      // or the table would have served): zeros up to the one; the run ends at the last
-      // coefficient or at the budget.  (The entry is taken up afresh here, so that nothing of
-      // this rare form is computed ahead of the branch.)
-      uint32_t f = e;
-      zc::materialise(f);
-      const bool cut = (f >> 20) > left;
-      const uint32_t room = umin(15u - s, left - 1u);
-      const uint32_t z = umin(count_trailing_zeros(W[0] >> 1), room);
-      const uint32_t used = cut ? 1u + z + (z < room ? 1u : 0u) : (f >> 20) & 15u;
-      pat |= (cut ? 1u << z : f & 0x3FFu) << s;
-      s += cut ? z + 1u : (f >> 10) & 0x3Fu;
-      zc::shift_out<NW>(W, used);
-      left -= used;
+    return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(token) + ((clamped << kRowBytesLg) + bits));
+  };
+  uint32_t s = n;   // n = 16: nothing left to test, the plane counts as closed
+  uint32_t pat = W[0] & ((1u << n) - 1u);
+  uint32_t skip = n;   // bits of the window that are read but not yet shifted out (none after the first step)
+#pragma unroll 1
+  do {
+    uint32_t e = look_up(s, (W[0] >> skip) & ((1u << kLookahead) - 1u));
+    if (any_lane_active((int32_t)e < 0)) {
+      const uint32_t used = e & 0xFFu;
+      const int32_t budget = left - (int32_t)skip;
+      const bool cut = (int32_t)e < 0 && (used == 0u || (int32_t)used > budget);
+      if (any_lane_active(cut)) {
+        // in such a lane one token, as an entry made here: zeros up to the one; the run ends at the
+        // last coefficient or at the budget (of which some is left: the group bit is a one)
+        const uint32_t room = umin(15u - s, (uint32_t)budget - 1u);
+        const uint32_t z = umin(count_trailing_zeros(W[0] >> skip >> 1), room);
+        const uint32_t made = (0x10000u << (z & 31u)) | (z + 1u) << 8 | (1u + z + (z < room ? 1u : 0u));
+        e = cut ? made : e;
+      }
     }
-  }
+    pat |= (e >> 16) << (s & 31u);
+    s += (e >> 8) & 0xFFu;
+    const uint32_t used = skip + (e & 0xFFu);
+    zc::shift_out<NW>(W, used);
+    left -= (int32_t)used;
+    skip = 0u;
+  } while (any_lane_active(s < kTokenIdleState));
   n = s & 31u;
-  return pat;
+  return pat;   // (in its lower sixteen bits)
 }
 
 // Whole block up to the fixed-point values; returns the exponent byte.
@@ -408,14 +436,21 @@ ZC_DEV uint32_t decode_block_fixed(uint32_t (&W)[Traits<RATE>::kWords], const ui
     lead -= 8u;
   }
   lead = umin(lead, (uint32_t)kPayload);
-  uint32_t left = (uint32_t)kPayload - lead;
-  if (E == 0u || (kPayload > 32 && lead >= 32u)) left = 0u;
+  int32_t left = (int32_t)kPayload - (int32_t)lead;
   // past the header byte and the leading zeros: two shifts of less than 32 each (with 32 and
-  // more leading zeros nothing is read from the window, whatever it holds)
+  // more leading zeros there is nothing to read, as in a zero block, whatever its payload)
   zc::shift_out<NW>(W, 8u);
   zc::shift_out<NW>(W, lead & 31u);
+  const bool empty = E == 0u || lead >= 32u;
+  if (any_lane_active(empty)) {
+    if (empty) {
+      left = 0;
+#pragma unroll
+      for (int j = 0; j < NW; ++j) W[j] = 0u;
+    }
+  }
   // a lane whose planes start more than 16 below the top (and that has any to read)
-  const bool low_start = lead > 16u && left > 0u;
+  const bool low_start = lead > 16u && left > 0;
   uint32_t n = 0;
   uint32_t h[8], u[16];
 #pragma unroll
@@ -424,7 +459,8 @@ ZC_DEV uint32_t decode_block_fixed(uint32_t (&W)[Traits<RATE>::kWords], const ui
   for (int t = 0; t < 16; ++t) {
     if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
     const int b = 15 - t;
-    h[b & 7] |= decode_plane<NW>(token, W, n, left, any_lane_active) << (16 * (b >> 3));
+    const uint32_t pat = decode_plane<NW>(token, W, n, left, any_lane_active);
+    h[b & 7] |= (b >> 3) ? pat << 16 : pat & 0xFFFFu;
   }
   transpose_halves<true>(h);
 #pragma unroll
@@ -452,7 +488,8 @@ ZC_DEV uint32_t decode_block_fixed(uint32_t (&W)[Traits<RATE>::kWords], const ui
       for (int t = 16; t < 32; ++t) {
         if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
         const int b = 31 - t;
-        h[b & 7] |= decode_plane<NW>(token, W, n, left, any_lane_active) << (16 * (b >> 3));
+        const uint32_t pat = decode_plane<NW>(token, W, n, left, any_lane_active);
+    h[b & 7] |= (b >> 3) ? pat << 16 : pat & 0xFFFFu;
       }
       transpose_halves<true>(h);
 #pragma unroll

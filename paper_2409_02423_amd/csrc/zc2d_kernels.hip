@@ -204,8 +204,8 @@ __device__ __forceinline__ void store_words(uint8_t* p, const uint32_t (&W)[NW])
 template <int RATE, int DT>
 __global__ __launch_bounds__(kThreads) void compress2d_kernel(const void* __restrict__ in, Walk w,
                                                               uint8_t* __restrict__ out) {
-  __shared__ __attribute__((aligned(16))) uint32_t expand[256];
-  stage_table<256>(g_expand.v, expand);
+  __shared__ __attribute__((aligned(16))) uint32_t expand[zc2d::kExpandEntries];
+  stage_table<zc2d::kExpandEntries>(g_expand.v, expand);
   constexpr int NW = zc2d::Traits<RATE>::kWords;
   const size_t b0 = (size_t)blockIdx.x * kThreads + threadIdx.x;
   if (b0 >= w.blocks) return;
@@ -276,9 +276,9 @@ struct ChunkPointers2d {
 template <int RATE, bool LOCAL, bool RAW_OUT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RATE <= 4 && !LOCAL && !RAW_OUT ? 6 : 1)))
 void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, uint8_t* out, float* out_raw) {
-  __shared__ __attribute__((aligned(16))) uint32_t expand[256];
+  __shared__ __attribute__((aligned(16))) uint32_t expand[zc2d::kExpandEntries];
   __shared__ __attribute__((aligned(16))) uint32_t token[zc2d::kTokenRows << zc2d::kLookahead];
-  for (int i = threadIdx.x; i < 256 / 4; i += kThreads)
+  for (int i = threadIdx.x; i < zc2d::kExpandEntries / 4; i += kThreads)
     reinterpret_cast<uint4*>(expand)[i] = reinterpret_cast<const uint4*>(g_expand.v)[i];
   stage_table<(zc2d::kTokenRows << zc2d::kLookahead)>(g_token.v, token);   // (its barrier covers both tables)
   constexpr int NW = zc2d::Traits<RATE>::kWords;
@@ -289,20 +289,17 @@ void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, 
   for (;;) {
     const size_t at = cur.b * zc2d::Traits<RATE>::kBlockBytes;
     float sum[16];
-    {
-      uint32_t W[NW];
-      load_words<NW>(chunks.p[0] + at, W);
-      zc2d::decode_block<RATE>(W, token, sum, AnyLane());
-    }
 #pragma unroll 1
-    for (int j = 1; j < k; ++j) {
+    for (int j = 0; j < k; ++j) {   // (the first chunk in the same loop: the decoder is a few hundred instructions long, one copy of it is enough)
       uint32_t W[NW];
       int32_t q[16];
       load_words<NW>(chunks.p[j] + at, W);
       const uint32_t E = zc2d::decode_block_fixed<RATE>(W, token, q, AnyLane());
       // scale and add in one fused step, unless some lane's exponent byte is one where the
       // scaling may round or overflow (tiny or huge blocks, arbitrary bytes)
-      if (AnyLane()(!zc2d::scaling_is_exact(E))) {
+      if (j == 0) {
+        zc2d::scale_block(q, E, sum);
+      } else if (AnyLane()(!zc2d::scaling_is_exact(E))) {
         float y[16];
         zc2d::scale_block(q, E, y);
 #pragma unroll
