@@ -13,8 +13,10 @@
 //     16-bit rows each), so that each of the first 16 planes is one 16-bit pattern in a
 //     register; the lower halves are transposed only if some lane of the wavefront gets
 //     that far within its budget, which low rates rarely do;
-//   * the plane loop is unrolled, uniform over the wavefront, and ends when no lane has
-//     budget left;
+//   * the encoder's plane loop is unrolled, uniform over the wavefront, and ends when no
+//     lane has budget left; the decoder's lanes go through their planes on their own,
+//     one table look-up per step, and keep the patterns in LDS until they are
+//     transposed;
 //   * encoder: a plane is one code word, formed without a loop.  Past the coefficients
 //     already significant, a zero is one bit 0 and a newly significant coefficient two
 //     bits 1 (the end of its token and the next group bit), which two look-ups in a
@@ -24,10 +26,7 @@
 //     whole within those bits.  The window is zero past the budget, which decodes to
 //     what unseen bits are but for a run cut by the budget (its one goes to the lowest
 //     index still possible); entries where that can matter are marked, and where it
-//     does, one token is decoded by count-trailing-zeros with the limits applied.  A
-//     lane's progress through a plane is one state word that table entries are added to;
-//     lanes whose plane is closed read an all-zero row, so that a step needs no per-lane
-//     case distinction;
+//     does, one token is decoded by count-trailing-zeros with the limits applied;
 //   * after the planes, the usual case (at most 16 planes read, starting within the top
 //     16) turns each coefficient's 16-bit pattern into its word with one shift.
 #ifndef ZC2D_CODEC_H
@@ -129,30 +128,27 @@ constexpr ExpandTable build_expand_table() {
 }
 
 // Decoder: entry for the next kLookahead stream bits at the start of a group test, by how far
-// the last coefficient is.  The decoder keeps, per plane, a state s = (index of the first
-// coefficient not yet known to be significant) | (plane closed) << 5 and looks up row
-// clamp(s, 6, 16) - 6: row 0 serves the indices up to 6, from where the last coefficient
-// cannot be reached within the look-ahead; rows 1..9 are the indices 7..15 (8..0 coefficients
-// between the current one and the last); row 10, all zeros, is what a lane reads whose plane is
-// closed (a closing zero was read, or the last coefficient dealt with), so that it can step
-// along with the others and nothing happens.
+// the last coefficient is.  With n the index of the first coefficient not yet known to be
+// significant, the row is clamp(n, 6, 16) - 6: row 0 serves the indices up to 6, from where the
+// last coefficient cannot be reached within the look-ahead; rows 1..9 are the indices 7..15 (8..0
+// coefficients between the current one and the last); row 10 is that of a plane with nothing left
+// to test, which it closes without reading anything.
 // An entry holds all the tokens that lie whole within the look-ahead: group bit, zeros,
 // closing one; a run that reaches the last coefficient needs no closing one, and the plane is
 // closed after it; a group bit 0 closes the plane.
-// Byte 0: how many stream bits were used; byte 1, which is added to s: how many coefficients were
-// passed, bit 13: the plane is closed; upper half: the ones, as positions past the current
-// coefficient, nine at most, and in its top bit whether the budget matters to this entry.
+// Byte 0: how many stream bits were used; byte 1, which is added to n: how many coefficients were
+// passed, and kTokenClosed if the plane is closed; byte 2: the ones, as positions past the
+// current coefficient; byte 3: how many bits of budget the entry must find.
 // Bits past the budget are zeros in the decoder's window, and what they decode to there is right
 // everywhere but in one place: zeros after a group bit 1 would put the one on the last
-// coefficient, where a run cut by the budget has it at the lowest index still possible.  So an
-// entry has bit 31 set if it holds a run that reaches the last coefficient without a closing one,
-// or no whole token at all (no bits used), and only these are ever checked against the budget.
-// (Such a run's entry belongs to an index of 7 or more, which moves bit 31 past the sixteen bits of
-// a plane when it is applied as it is.)
+// coefficient, where a run cut by the budget has it at the lowest index still possible.  So
+// byte 3 is the bits used if the entry holds a run that reaches the last coefficient without a
+// closing one, kTokenNone (more than any budget) if it holds no whole token at all (or one whose
+// position byte 2 has no room for), and zero otherwise.
 constexpr int kLookahead = 9;
 constexpr int kTokenRows = 11;
-constexpr uint32_t kTokenFirstRowState = 6, kTokenIdleState = 16;
-constexpr uint32_t kTokenChecked = 1u << 31;
+constexpr uint32_t kTokenFirstRowIndex = 6, kTokenLastRowIndex = 16;
+constexpr uint32_t kTokenClosed = 32, kTokenNone = 255;
 struct TokenTable { uint32_t v[kTokenRows << kLookahead]; };
 constexpr TokenTable build_token_table() {
   TokenTable t{};
@@ -160,11 +156,11 @@ constexpr TokenTable build_token_table() {
     // coefficients between the current one and the last; row 0 stands for nine and more
     const uint32_t room = row == 0 ? 15u : 9u - row;
     for (uint32_t s = 0; s < (1u << kLookahead); ++s) {
-      uint32_t ones = 0, passed = 0, used = 0, done = 0, checked = 0;
+      uint32_t ones = 0, passed = 0, used = 0, closed = 0, to_last = 0;
       for (;;) {
-        if (passed > room) { done = 1; break; }             // the last coefficient has been dealt with
+        if (passed > room) { closed = kTokenClosed; break; }   // the last coefficient has been dealt with
         if (used >= (uint32_t)kLookahead) break;
-        if (((s >> used) & 1u) == 0u) { done = 1; ++used; break; }
+        if (((s >> used) & 1u) == 0u) { closed = kTokenClosed; ++used; break; }
         uint32_t z = 0;
         bool in_sight = true;
         while (passed + z < room) {
@@ -172,16 +168,17 @@ constexpr TokenTable build_token_table() {
           if ((s >> (used + 1 + z)) & 1u) break;
           ++z;
         }
-        if (!in_sight) break;
+        if (!in_sight || passed + z > 7u) break;
         ones |= 1u << (passed + z);
-        if (passed + z == room) checked = 1;
+        if (passed + z == room) to_last = 1;
         used += 1 + z + (passed + z == room ? 0 : 1);       // no closing one at the last coefficient
         passed += z + 1;
       }
-      if (used == 0u) checked = 1;
-      t.v[(row << kLookahead) + s] = used | passed << 8 | done << 13 | ones << 16 | (checked ? kTokenChecked : 0u);
+      const uint32_t need = used == 0u ? kTokenNone : (to_last ? used : 0u);
+      t.v[(row << kLookahead) + s] = used | (passed | closed) << 8 | ones << 16 | need << 24;
     }
   }
+  for (uint32_t s = 0; s < (1u << kLookahead); ++s) t.v[((kTokenRows - 1) << kLookahead) + s] = kTokenClosed << 8;
   return t;
 }
 
@@ -355,70 +352,102 @@ ZC_DEV void accumulate_scaled(const int32_t (&q)[16], uint32_t E, float (&sum)[1
 // zero times anything finite added to the sum is the sum plus zero.
 ZC_DEV bool scaling_is_exact(uint32_t E) { return E - 28u <= 222u || E == 0u; }
 
-// One plane of the embedded code, read from the bottom of the window W, whose bits past the
-// budget are zeros.  Returns the plane's bit of each coefficient.  n: how many leading
-// coefficients are significant; left: budget, which zeros read past its end make negative (a lane
-// that has run out reads zero bits and a closed group test, which is what unseen bits are).
+// Where a lane's decoded planes go: sixteen 16-bit patterns, in the order they are read, that
+// start as zeros.  A place is given in steps of kPlaneStep, which on the device is the distance, in
+// bytes, of two planes in the wavefront's LDS (64 lanes, two bytes each); this one is for the host.
+constexpr uint32_t kPlaneStep = 128, kPlaneEnd = 16 * kPlaneStep;
+struct LocalPlanes {
+  uint16_t v[16];
+  ZC_DEV void clear() { for (int t = 0; t < 16; ++t) v[t] = 0; }
+  ZC_DEV void put(uint32_t at, uint32_t pattern) { v[at / kPlaneStep] = (uint16_t)pattern; }
+  ZC_DEV uint32_t pair(int lower, int upper) const { return v[lower] | (uint32_t)v[upper] << 16; }
+};
+
+// A lane's progress through its block's planes.
+template <int NW>
+struct PlaneReader {
+  uint32_t (&W)[NW];   // the window: what is not yet read, zeros past the budget
+  int32_t left;        // budget, which zeros read past its end make negative
+  uint32_t n;          // how many leading coefficients are significant
+  uint32_t skip;       // bits of the window that belong to these, at the start of a plane (otherwise 0)
+  uint32_t pattern;    // the ones of the current plane found so far
+  uint32_t at;         // the current plane's place
+};
+
+// Reads planes, from the bottom of the window, until no lane has budget left or, in the plain
+// form, some lane has read sixteen, or, in the CAREFUL one, all lanes with budget left have (a lane
+// that has them then waits for the others, which the plain form does not provide for).
 //
-// The group tests are read in steps that all lanes of the wavefront take together.  A step looks
-// the next bits up in the token table (see there for the state s and the rows) and applies the
-// entry, also in lanes whose plane is closed (they read empty entries).  Only if some lane's entry
-// is marked as one that the budget matters to, and that lane's first token is longer than the
-// look-ahead or its budget ends inside the entry's bits, an entry for one token is made for it by
-// count-trailing-zeros with the limits applied.  The first step looks up behind the bits of the significant coefficients, without moving the window
-// past them on their own (16 + 9 bits are in its first word).
-// (With every entry checked against the budget, lanes out of budget masked and the significant
-// coefficients' bits shifted out apart, a plane took 12 instructions and a step 17 at rate 4, now 6
-// and 14: decompress2d of 8192 x 32768 values 0.262 -> 0.253 ms at rate 4, 0.308 -> 0.294 ms at
-// rate 8, the 2-way reduce 0.642 -> 0.623 and 0.850 -> 0.784 ms with the encoder's part.)
-template <int NW, class AnyActive>
-ZC_DEV uint32_t decode_plane(const uint32_t* token, uint32_t (&W)[NW], uint32_t& n, int32_t& left,
-                             AnyActive any_lane_active) {
-  // byte offset of the entry: (clamped state - first row's state) rows, then the next bits;
+// Lanes go through their planes on their own: a step is one look-up in the token table and, in
+// lanes that start a plane, the bits of the significant coefficients before it (16 + 9 bits are in
+// the window's first word).  A lane out of budget goes on reading empty planes.  The current
+// plane's pattern is put in its place in every step, whether it is whole or not: LDS writes are
+// what this kernel has to spare, and it takes no test.  Only if some lane's entry asks for more
+// budget than the lane has, an entry for one token is made for it by count-trailing-zeros with the
+// limits applied.
+// (What bounds the 4 x 4 kernels is their instruction count, and here the number of steps that
+// the wavefront's slowest lane needs.  Plane by plane in step, the patterns in registers, that was
+// 11.1 steps at rate 4 and 14.3 at rate 8 on the gradient matrix, as the sum over planes of the
+// slowest lane's; this way, the slowest lane's sum, it is 6.7 and 10.4: 578 -> 526 instructions
+// per block and 0.253 -> 0.233 ms for decompress2d of 8192 x 32768 values at rate 4, 0.623 -> 0.572 ms
+// for the 2-way reduce.)
+template <bool CAREFUL, int NW, class AnyActive, class Planes>
+ZC_DEV void read_planes(const uint32_t* token, PlaneReader<NW>& r, Planes& planes, AnyActive any_lane_active) {
+  // byte offset of the entry: (clamped index - first row's index) rows, then the next bits;
   // the constant rides on the masking of the bits (it has none of their positions set)
   constexpr uint32_t kRowBytesLg = kLookahead + 2;
-  constexpr uint32_t kBias = 0u - (kTokenFirstRowState << kRowBytesLg);
-  auto look_up = [&](uint32_t state, uint32_t bits) {
-    const uint32_t clamped = umin(umax(state, kTokenFirstRowState), kTokenIdleState);
-    zc::materialise(bits);   // (a bit-field extract, then shift-and-or with the constant, then shift-and-add:
-    bits = bits << 2 | kBias;   //  otherwise the constant comes back as an addition of its own)
-    zc::materialise(bits);
-    return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(token) + ((clamped << kRowBytesLg) + bits));
-  };
-  uint32_t s = n;   // n = 16: nothing left to test, the plane counts as closed
-  uint32_t pat = W[0] & ((1u << n) - 1u);
-  uint32_t skip = n;   // bits of the window that are read but not yet shifted out (none after the first step)
+  constexpr uint32_t kBias = 0u - (kTokenFirstRowIndex << kRowBytesLg);
 #pragma unroll 1
-  do {
-    uint32_t e = look_up(s, (W[0] >> skip) & ((1u << kLookahead) - 1u));
-    if (any_lane_active((int32_t)e < 0)) {
-      const uint32_t used = e & 0xFFu;
-      const int32_t budget = left - (int32_t)skip;
-      const bool cut = (int32_t)e < 0 && (used == 0u || (int32_t)used > budget);
-      if (any_lane_active(cut)) {
-        // in such a lane one token, as an entry made here: zeros up to the one; the run ends at the
-        // last coefficient or at the budget (of which some is left: the group bit is a one)
-        const uint32_t room = umin(15u - s, (uint32_t)budget - 1u);
-        const uint32_t z = umin(count_trailing_zeros(W[0] >> skip >> 1), room);
-        const uint32_t made = (0x10000u << (z & 31u)) | (z + 1u) << 8 | (1u + z + (z < room ? 1u : 0u));
-        e = cut ? made : e;
-      }
+  for (;;) {
+    const bool reading = !CAREFUL || r.at != kPlaneEnd;
+    uint32_t e = 0u, ones = 0u;
+    int32_t budget = 0;
+    bool cut = false;
+    if (reading) {
+      r.pattern |= r.W[0] & ((1u << r.skip) - 1u);
+      const uint32_t clamped = umin(umax(r.n, kTokenFirstRowIndex), kTokenLastRowIndex);
+      uint32_t bits = (r.W[0] >> r.skip) & ((1u << kLookahead) - 1u);
+      zc::materialise(bits);   // (a bit-field extract, then shift-and-or with the constant, then shift-and-add:
+      bits = bits << 2 | kBias;   //  otherwise the constant comes back as an addition of its own)
+      zc::materialise(bits);
+      e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(token) + ((clamped << kRowBytesLg) + bits));
+      budget = r.left - (int32_t)r.skip;
+      ones = (e >> 16) & 0xFFu;
+      cut = (e >> 24) > (uint32_t)budget;   // (no budget at all: the window is empty, and so is byte 3)
     }
-    pat |= (e >> 16) << (s & 31u);
-    s += (e >> 8) & 0xFFu;
-    const uint32_t used = skip + (e & 0xFFu);
-    zc::shift_out<NW>(W, used);
-    left -= (int32_t)used;
-    skip = 0u;
-  } while (any_lane_active(s < kTokenIdleState));
-  n = s & 31u;
-  return pat;   // (in its lower sixteen bits)
+    if (any_lane_active(cut)) {
+      // zeros up to the one; the run ends at the last coefficient or at the budget (of which some is
+      // left: the group bit is a one)
+      const uint32_t room = umin(15u - r.n, (uint32_t)budget - 1u);
+      const uint32_t z = umin(count_trailing_zeros(r.W[0] >> r.skip >> 1), room);
+      const uint32_t made = (z + 1u) << 8 | (1u + z + (z < room ? 1u : 0u));
+      e = cut ? made : e;
+      ones = cut ? 1u << (z & 31u) : ones;
+    }
+    if (reading) {
+      r.pattern |= ones << r.n;
+      const uint32_t s = r.n + ((e >> 8) & 0xFFu), used = e & 0xFFu;
+      zc::shift_out<NW>(r.W, r.skip + used);
+      r.left = budget - (int32_t)used;
+      planes.put(r.at, r.pattern);
+      const bool closed = s >= kTokenClosed;
+      r.n = s & 31u;
+      r.skip = closed ? r.n : 0u;
+      r.pattern = closed ? 0u : r.pattern;
+      r.at += closed ? kPlaneStep : 0u;
+    }
+    if (CAREFUL) {
+      if (!any_lane_active(r.left > 0 && r.at != kPlaneEnd)) break;
+    } else {
+      if (!any_lane_active(r.left > 0) || any_lane_active(r.at == kPlaneEnd)) break;
+    }
+  }
 }
 
 // Whole block up to the fixed-point values; returns the exponent byte.
-template <int RATE, class AnyActive>
+template <int RATE, class AnyActive, class Planes>
 ZC_DEV uint32_t decode_block_fixed(uint32_t (&W)[Traits<RATE>::kWords], const uint32_t* token, int32_t (&q)[16],
-                                   AnyActive any_lane_active) {
+                                   AnyActive any_lane_active, Planes& planes) {
   constexpr int NW = Traits<RATE>::kWords;
   constexpr int kPayload = Traits<RATE>::kPayloadBits;
   constexpr int kMaxPlanes = kPayload < 32 ? kPayload : 32;
@@ -451,21 +480,19 @@ ZC_DEV uint32_t decode_block_fixed(uint32_t (&W)[Traits<RATE>::kWords], const ui
   }
   // a lane whose planes start more than 16 below the top (and that has any to read)
   const bool low_start = lead > 16u && left > 0;
-  uint32_t n = 0;
+  PlaneReader<NW> r = {W, left, 0u, 0u, 0u, 0u};
+  planes.clear();
+  read_planes<false>(token, r, planes, any_lane_active);
+  if (any_lane_active(r.left > 0)) {   // some lane has read sixteen planes
+    if (any_lane_active(r.left > 0 && r.at != kPlaneEnd)) read_planes<true>(token, r, planes, any_lane_active);
+  }
   uint32_t h[8], u[16];
 #pragma unroll
-  for (int w = 0; w < 8; ++w) h[w] = 0u;
-#pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
-    const int b = 15 - t;
-    const uint32_t pat = decode_plane<NW>(token, W, n, left, any_lane_active);
-    h[b & 7] |= (b >> 3) ? pat << 16 : pat & 0xFFFFu;
-  }
+  for (int w = 0; w < 8; ++w) h[w] = planes.pair(15 - w, 7 - w);
   transpose_halves<true>(h);
 #pragma unroll
   for (int w = 0; w < 8; ++w) zc::materialise(h[w]);   // one transpose, not one per half
-  const bool deeper = kMaxPlanes > 16 && any_lane_active(left > 0);
+  const bool deeper = kMaxPlanes > 16 && any_lane_active(r.left > 0);
   if (!deeper && !any_lane_active(low_start)) {
     // the usual case: at most 16 planes were read and they start within the top 16, so each
     // coefficient is its 16-bit pattern moved up (a lane that read nothing has zero patterns)
@@ -482,15 +509,12 @@ ZC_DEV uint32_t decode_block_fixed(uint32_t (&W)[Traits<RATE>::kWords], const ui
       u[w + 8] = h[w] & 0xFFFF0000u;
     }
     if (deeper) {
+      r.at = 0u;
+      r.pattern = 0u;   // (a lane that ran out of budget within a plane has put it where it belongs)
+      planes.clear();
+      read_planes<true>(token, r, planes, any_lane_active);
 #pragma unroll
-      for (int w = 0; w < 8; ++w) h[w] = 0u;
-#pragma unroll
-      for (int t = 16; t < 32; ++t) {
-        if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
-        const int b = 31 - t;
-        const uint32_t pat = decode_plane<NW>(token, W, n, left, any_lane_active);
-    h[b & 7] |= (b >> 3) ? pat << 16 : pat & 0xFFFFu;
-      }
+      for (int w = 0; w < 8; ++w) h[w] = planes.pair(15 - w, 7 - w);
       transpose_halves<true>(h);
 #pragma unroll
       for (int w = 0; w < 8; ++w) {
@@ -506,12 +530,19 @@ ZC_DEV uint32_t decode_block_fixed(uint32_t (&W)[Traits<RATE>::kWords], const ui
   return E;
 }
 
+template <int RATE, class AnyActive, class Planes>
+ZC_DEV void decode_block(uint32_t (&W)[Traits<RATE>::kWords], const uint32_t* token, float (&out)[16],
+                         AnyActive any_lane_active, Planes& planes) {
+  int32_t q[16];
+  const uint32_t E = decode_block_fixed<RATE>(W, token, q, any_lane_active, planes);
+  scale_block(q, E, out);
+}
+
 template <int RATE, class AnyActive>
 ZC_DEV void decode_block(uint32_t (&W)[Traits<RATE>::kWords], const uint32_t* token, float (&out)[16],
                          AnyActive any_lane_active) {
-  int32_t q[16];
-  const uint32_t E = decode_block_fixed<RATE>(W, token, q, any_lane_active);
-  scale_block(q, E, out);
+  LocalPlanes planes;
+  decode_block<RATE>(W, token, out, any_lane_active, planes);
 }
 
 }  // namespace zc2d

@@ -17,6 +17,7 @@
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kDecodeThreads = 512;   // of the kernels that decode: more wavefronts share one copy of the 22 KiB token table (see below)
 
 __device__ __align__(16) const zc2d::ExpandTable g_expand = zc2d::build_expand_table();
 __device__ __align__(16) const zc2d::TokenTable g_token = zc2d::build_token_table();
@@ -25,11 +26,11 @@ __device__ __align__(16) const zc2d::TokenTable g_token = zc2d::build_token_tabl
 // its loads back to back and then writes (one wait for the whole table, not one per step).
 // In a last, partial step of several the lanes beyond the table's end copy its first entry
 // once more.
-template <int WORDS>
+template <int WORDS, int THREADS>
 __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, uint32_t* dst) {
   static_assert(WORDS % 4 == 0, "table size");
   constexpr int kVecs = WORDS / 4;
-  constexpr int kSteps = (kVecs + kThreads - 1) / kThreads;
+  constexpr int kSteps = (kVecs + THREADS - 1) / THREADS;
   if constexpr (kSteps == 1) {
     if (threadIdx.x < kVecs) reinterpret_cast<uint4*>(dst)[threadIdx.x] = reinterpret_cast<const uint4*>(src)[threadIdx.x];
   } else {
@@ -37,8 +38,8 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
     int idx[kSteps];
 #pragma unroll
     for (int i = 0; i < kSteps; ++i) {
-      idx[i] = threadIdx.x + i * kThreads;
-      if ((i + 1) * kThreads > kVecs && idx[i] >= kVecs) idx[i] = 0;
+      idx[i] = threadIdx.x + i * THREADS;
+      if ((i + 1) * THREADS > kVecs && idx[i] >= kVecs) idx[i] = 0;
       v[i] = reinterpret_cast<const uint4*>(src)[idx[i]];
     }
 #pragma unroll
@@ -48,9 +49,15 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
   }
   __syncthreads();
 }
-// Workgroups per CU in the grid (measured: the decoder-bound kernels like a few more than
-// the compress kernel).  Only a build with -DZC_TUNING_KNOBS lets ZC2D_WORKGROUPS_PER_CU override both; the shipped library reads no environment variable.
-constexpr int kCompressWorkgroupsPerCU = 16, kDecodeWorkgroupsPerCU = 48;
+// Workgroups per CU in the grid.  The kernels that decode have 512 lanes per workgroup: 22 KiB of
+// token table and 2 KiB per wavefront for its planes are 38 KiB, four of which fit a CU and fill it
+// (with 256 lanes, 30 KiB, five fit, 20 wavefronts of the 32 the registers allow: decompress2d of
+// 8192 x 32768 values at rate 4 0.270 against 0.248 ms, the 2-way reduce 0.613 against 0.583 ms;
+// 1024 lanes, whose 54 KiB fit twice: 0.599 ms for the reduce).  Their grid, swept from 4 to 48:
+// decompress2d at rate 8 0.296 ms at 4, 0.275 at 24, 0.280 at 48, but with rows that are aligned to
+// their elements only (6144 x 43690) 0.365 at 4, 0.313 at 24, 0.288 at 48: there neighbouring
+// wavefronts write to the same cache lines and gain from running at the same time.  Only a build with -DZC_TUNING_KNOBS lets ZC2D_WORKGROUPS_PER_CU override both; the shipped library reads no environment variable.
+constexpr int kCompressWorkgroupsPerCU = 16, kDecodeWorkgroupsPerCU = 24, kDecodeWorkgroupsPerCUUnaligned = 48;
 
 // The wavefront-wide votes of the codec: lanes(p) is the set of lanes where p holds (one
 // comparison each, so that the compare instruction's own mask is the set), some(set) whether
@@ -63,6 +70,42 @@ struct AnyLane {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// A lane's share of its wavefront's 2 KiB of LDS for the decoded planes of its block: plane t at
+// byte 128 * t + 2 * lane.  (LDS operations of one wavefront take effect in program order.)
+constexpr int kPlaneBytes = zc2d::kPlaneEnd;
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+struct WavePlanes {
+  char* wave;   // the wavefront's LDS
+  char* mine;   // the lane's first place
+  __device__ __forceinline__ explicit WavePlanes(char* lds) {
+    wave = lds + (threadIdx.x >> 6) * kPlaneBytes;
+    mine = wave + 2 * (threadIdx.x & 63);
+  }
+  __device__ __forceinline__ void clear() {
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+    if (__builtin_amdgcn_ballot_w64(true) == ~0ull) {
+      // all lanes are here: each clears 32 bytes of the wavefront's 2 KiB, whosever they are
+      u32x4* p = reinterpret_cast<u32x4*>(wave) + 2 * (threadIdx.x & 63);
+      p[0] = u32x4{0, 0, 0, 0};
+      p[1] = u32x4{0, 0, 0, 0};
+    } else {
+      // the last blocks of the matrix: a lane without one takes no part any more
+#pragma unroll
+      for (int t = 0; t < 16; ++t) put(zc2d::kPlaneStep * t, 0u);
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+  }
+  __device__ __forceinline__ void put(uint32_t at, uint32_t pattern) { *reinterpret_cast<uint16_t*>(mine + at) = (uint16_t)pattern; }
+  __device__ __forceinline__ uint32_t pair(int lower, int upper) const {
+    asm volatile("" ::: "memory");
+    const u16x2 v = {*reinterpret_cast<const uint16_t*>(mine + zc2d::kPlaneStep * lower),
+                     *reinterpret_cast<const uint16_t*>(mine + zc2d::kPlaneStep * upper)};
+    return __builtin_bit_cast(uint32_t, v);
+  }
+};
 
 // Shape of the matrix and of the walk over its blocks; the same for every lane.
 struct Walk {
@@ -205,7 +248,7 @@ template <int RATE, int DT>
 __global__ __launch_bounds__(kThreads) void compress2d_kernel(const void* __restrict__ in, Walk w,
                                                               uint8_t* __restrict__ out) {
   __shared__ __attribute__((aligned(16))) uint32_t expand[zc2d::kExpandEntries];
-  stage_table<zc2d::kExpandEntries>(g_expand.v, expand);
+  stage_table<zc2d::kExpandEntries, kThreads>(g_expand.v, expand);
   constexpr int NW = zc2d::Traits<RATE>::kWords;
   const size_t b0 = (size_t)blockIdx.x * kThreads + threadIdx.x;
   if (b0 >= w.blocks) return;
@@ -234,12 +277,14 @@ __global__ __launch_bounds__(kThreads) void compress2d_kernel(const void* __rest
 }
 
 template <int RATE, int DT>
-__global__ __launch_bounds__(kThreads) void decompress2d_kernel(const uint8_t* __restrict__ in, Walk w,
+__global__ __launch_bounds__(kDecodeThreads) void decompress2d_kernel(const uint8_t* __restrict__ in, Walk w,
                                                                 void* __restrict__ out) {
   __shared__ __attribute__((aligned(16))) uint32_t token[zc2d::kTokenRows << zc2d::kLookahead];
-  stage_table<(zc2d::kTokenRows << zc2d::kLookahead)>(g_token.v, token);
+  __shared__ __attribute__((aligned(16))) char plane_lds[kDecodeThreads / 64 * kPlaneBytes];
+  WavePlanes planes(plane_lds);
+  stage_table<(zc2d::kTokenRows << zc2d::kLookahead), kDecodeThreads>(g_token.v, token);
   constexpr int NW = zc2d::Traits<RATE>::kWords;
-  const size_t b0 = (size_t)blockIdx.x * kThreads + threadIdx.x;
+  const size_t b0 = (size_t)blockIdx.x * kDecodeThreads + threadIdx.x;
   if (b0 >= w.blocks) return;
   Cursor cur;
   cur.start(w, b0);
@@ -253,7 +298,7 @@ __global__ __launch_bounds__(kThreads) void decompress2d_kernel(const uint8_t* _
     uint32_t Wn[NW];
     if (more) load_words<NW>(in + next.b * zc2d::Traits<RATE>::kBlockBytes, Wn);   // the next block's stream, ahead of time
     float y[16];
-    zc2d::decode_block<RATE>(W, token, y, AnyLane());
+    zc2d::decode_block<RATE>(W, token, y, AnyLane(), planes);
     store_block<DT>(out, w, cur, y);
     if (!more) break;
 #pragma unroll
@@ -274,15 +319,17 @@ struct ChunkPointers2d {
 // (The plain form at the low rates is two registers away from a sixth wavefront per SIMD, which
 // it gains from: the compiler is told to stay within that; the other forms would spill.)
 template <int RATE, bool LOCAL, bool RAW_OUT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RATE <= 4 && !LOCAL && !RAW_OUT ? 6 : 1)))
+__global__ __launch_bounds__(kDecodeThreads) __attribute__((amdgpu_waves_per_eu(RATE <= 4 && !LOCAL && !RAW_OUT ? 6 : 1)))
 void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, uint8_t* out, float* out_raw) {
   __shared__ __attribute__((aligned(16))) uint32_t expand[zc2d::kExpandEntries];
   __shared__ __attribute__((aligned(16))) uint32_t token[zc2d::kTokenRows << zc2d::kLookahead];
-  for (int i = threadIdx.x; i < zc2d::kExpandEntries / 4; i += kThreads)
+  __shared__ __attribute__((aligned(16))) char plane_lds[kDecodeThreads / 64 * kPlaneBytes];
+  WavePlanes planes(plane_lds);
+  for (int i = threadIdx.x; i < zc2d::kExpandEntries / 4; i += kDecodeThreads)
     reinterpret_cast<uint4*>(expand)[i] = reinterpret_cast<const uint4*>(g_expand.v)[i];
-  stage_table<(zc2d::kTokenRows << zc2d::kLookahead)>(g_token.v, token);   // (its barrier covers both tables)
+  stage_table<(zc2d::kTokenRows << zc2d::kLookahead), kDecodeThreads>(g_token.v, token);   // (its barrier covers both tables)
   constexpr int NW = zc2d::Traits<RATE>::kWords;
-  const size_t b0 = (size_t)blockIdx.x * kThreads + threadIdx.x;
+  const size_t b0 = (size_t)blockIdx.x * kDecodeThreads + threadIdx.x;
   if (b0 >= w.blocks) return;
   Cursor cur;
   cur.start(w, b0);
@@ -294,7 +341,7 @@ void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, 
       uint32_t W[NW];
       int32_t q[16];
       load_words<NW>(chunks.p[j] + at, W);
-      const uint32_t E = zc2d::decode_block_fixed<RATE>(W, token, q, AnyLane());
+      const uint32_t E = zc2d::decode_block_fixed<RATE>(W, token, q, AnyLane(), planes);
       // scale and add in one fused step, unless some lane's exponent byte is one where the
       // scaling may round or overflow (tiny or huge blocks, arbitrary bytes)
       if (j == 0) {
@@ -371,13 +418,13 @@ int workgroups_per_cu(int preset) {
   return preset;
 }
 
-unsigned grid_for(size_t blocks, int preset) {
-  const size_t groups = (blocks + kThreads - 1) / kThreads;
+unsigned grid_for(size_t blocks, int preset, int threads) {
+  const size_t groups = (blocks + threads - 1) / threads;
   const size_t cap = (size_t)compute_units() * (size_t)workgroups_per_cu(preset);
   return (unsigned)(groups < cap ? groups : cap);
 }
 
-Walk walk_for(size_t rows, size_t cols, unsigned grid) {
+Walk walk_for(size_t rows, size_t cols, unsigned grid, int threads) {
   Walk w;
   w.rows = rows;
   w.cols = cols;
@@ -385,7 +432,7 @@ Walk walk_for(size_t rows, size_t cols, unsigned grid) {
   w.blocks = ((rows + 3) / 4) * w.bc;
   w.whole_br = rows / 4;
   w.whole_bc = cols / 4;
-  w.stride = (size_t)grid * kThreads;
+  w.stride = (size_t)grid * threads;
   w.step_bi = w.stride / w.bc;
   w.step_bj = w.stride % w.bc;
   return w;
@@ -417,8 +464,8 @@ int launch_compress2d(const void* d_in, size_t rows, size_t cols, int rate, void
   if (out_cap < zc2d_compressed_size(rows, cols, rate)) return ZC_ERR_CAPACITY;
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const unsigned grid = grid_for(blocks, kCompressWorkgroupsPerCU);
-  const Walk w = walk_for(rows, cols, grid);
+  const unsigned grid = grid_for(blocks, kCompressWorkgroupsPerCU, kThreads);
+  const Walk w = walk_for(rows, cols, grid, kThreads);
 #define CALL(R) hipLaunchKernelGGL((compress2d_kernel<R, DT>), dim3(grid), dim3(kThreads), 0, s, d_in, w, static_cast<uint8_t*>(d_out))
   ZC2D_DISPATCH_RATE(rate, CALL)
 #undef CALL
@@ -434,9 +481,9 @@ int launch_decompress2d(const void* d_in, size_t rows, size_t cols, int rate, vo
   if (rows > kMaxValues || cols > kMaxValues || rows > kMaxValues / cols) return ZC_ERR_SIZE;
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const unsigned grid = grid_for(blocks, kDecodeWorkgroupsPerCU);
-  const Walk w = walk_for(rows, cols, grid);
-#define CALL(R) hipLaunchKernelGGL((decompress2d_kernel<R, DT>), dim3(grid), dim3(kThreads), 0, s, static_cast<const uint8_t*>(d_in), w, d_out)
+  const unsigned grid = grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUUnaligned : kDecodeWorkgroupsPerCU, kDecodeThreads);
+  const Walk w = walk_for(rows, cols, grid, kDecodeThreads);
+#define CALL(R) hipLaunchKernelGGL((decompress2d_kernel<R, DT>), dim3(grid), dim3(kDecodeThreads), 0, s, static_cast<const uint8_t*>(d_in), w, d_out)
   ZC2D_DISPATCH_RATE(rate, CALL)
 #undef CALL
   return hipGetLastError() == hipSuccess ? ZC_OK : ZC_ERR_LAUNCH;
@@ -461,11 +508,11 @@ int launch_reduce2d(const void* const* d_in, int k, const float* d_local, size_t
   if (!raw_out && out_cap < zc2d_compressed_size(rows, cols, rate)) return ZC_ERR_CAPACITY;
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const unsigned grid = grid_for(blocks, kDecodeWorkgroupsPerCU);
-  const Walk w = walk_for(rows, cols, grid);
+  const unsigned grid = grid_for(blocks, kDecodeWorkgroupsPerCU, kDecodeThreads);
+  const Walk w = walk_for(rows, cols, grid, kDecodeThreads);
   uint8_t* out = static_cast<uint8_t*>(d_out);
 #define LAUNCH(R, LOCAL, RAW) \
-  hipLaunchKernelGGL((reduce2d_kernel<R, LOCAL, RAW>), dim3(grid), dim3(kThreads), 0, s, chunks, k, d_local, w, out, d_out_raw)
+  hipLaunchKernelGGL((reduce2d_kernel<R, LOCAL, RAW>), dim3(grid), dim3(kDecodeThreads), 0, s, chunks, k, d_local, w, out, d_out_raw)
 #define CALL(R)                                    \
   do {                                             \
     if (d_local && raw_out) LAUNCH(R, true, true); \

@@ -363,3 +363,25 @@ def test_rows_aligned_to_their_elements_only(gpu, ref, cols):
             # the narrowing is torch's: round to nearest even
             back = gpu.zc2d_decompress_half(c, rows, cols, rate, dtype)
             assert torch.equal(back.view(torch.int16), gpu.zc2d_decompress(c, rows, cols, rate).to(dtype).view(torch.int16))
+
+
+@pytest.mark.parametrize("blocks", (1, 63, 64, 65, 511, 513, 1100))
+def test_blocks_of_few_and_many_planes_side_by_side(gpu, ref, blocks):
+    """Lanes of one wavefront read their planes on their own: constant blocks (one coefficient, as many
+    planes as the budget holds, more than sixteen from rate 4 on), sparse, dense, zero and arbitrary
+    blocks next to each other, in full wavefronts and in a last one with few lanes."""
+    rng = np.random.default_rng(blocks)
+    for rate in RATES:
+        print("planes side by side", blocks, rate, flush=True)
+        x = np.zeros((blocks, 16), dtype=np.float32)
+        x[0::4] = (1.0 / 3.0 + rng.random((len(x[0::4]), 1))).astype(np.float32)
+        x[1::4] = rng.standard_normal((len(x[1::4]), 16)).astype(np.float32)
+        x[2::8, 15] = 1.7
+        m = np.ascontiguousarray(x.reshape(blocks, 4, 4).transpose(1, 0, 2).reshape(4, 4 * blocks))
+        _round_trip(gpu, ref, m, rate, "%d mixed blocks r%d" % (blocks, rate))
+        s = rng.integers(0, 256, size=(blocks, 2 * rate), dtype=np.uint8)
+        s[::2] &= rng.integers(0, 256, size=s[::2].shape, dtype=np.uint8) & rng.integers(0, 256, size=s[::2].shape, dtype=np.uint8)
+        s = s.reshape(-1)
+        with np.errstate(all="ignore"):
+            want = ref.decompress(s, 4, 4 * blocks, rate)
+        _same_floats(_host(gpu.zc2d_decompress(_dev(s), 4, 4 * blocks, rate)), want, "arbitrary bytes")
