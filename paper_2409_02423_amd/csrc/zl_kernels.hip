@@ -9,25 +9,31 @@
 // seven workgroups fit on a CU and hide each other's waits).
 //
 // Chunks have data-dependent sizes, so a chunk's place in the stream is the sum of the
-// sizes before it.  That sum is formed in the same launch.  The compress kernel runs about
-// as many workgroups as fit on the chip at once; each takes chunk numbers from a counter,
-// one after the other, and publishes a chunk's own size in the stream's table as soon as
-// the chunk is coded.  The coded chunk then waits in registers while the workgroup codes
-// its next one; only after that does the workgroup add up the entries of the chunks before
-// the waiting one, 64 at a time, back to the nearest entry that already holds a running
-// total, replace the chunk's entry by its own running total and write the chunk.  By then
-// most of what the sum needs has arrived, so the look-back rarely has to poll.
-// Every entry a workgroup waits for belongs to a chunk number taken by a running workgroup,
-// and between taking a number and publishing that chunk's size a workgroup waits for no
-// other workgroup; so every wait ends (also with several such kernels running at once,
-// which a fixed assignment of chunks to workgroups would not survive).  A spin limit turns
-// the impossible case into a flaw mark in the header.  The counter is the header's chunk
-// count; it runs past its end (every workgroup asks once too often) and a last one-lane
-// kernel sets it, and the rest of the header, to their final values.  The table is part
-// of the stream (the decoder needs it): no memory beyond input and output is used.
-// What bounds the kernel from below is the counter itself: 11.5 ns per request, however many
-// workgroups ask (32768 requests alone take 0.38 ms); for 16-bit messages a workgroup of 512
-// lanes therefore takes two chunks per request.
+// sizes before it.  That sum is formed in the same launch.  A workgroup publishes a chunk's own
+// size in the stream's table as soon as that is known, which is before its planes are formed;
+// later it adds up the entries of the chunks before it, 64 at a time, back to the nearest
+// entry that already holds a running total, replaces the chunk's entry by its own running total
+// and writes the chunk.
+// Messages of up to twice as many chunks as workgroups fit on the chip have a workgroup per
+// chunk.  For longer ones about as many workgroups run as fit, and each asks for chunk numbers,
+// one after the other.  A coded chunk then waits in registers while its workgroup codes the next
+// one, and only after that looks for its place: by then most of what the sum needs has arrived,
+// so the look-back rarely has to poll.  (Chunks b, b + G, b + 2G, ... for workgroup b of G need no
+// asking, but all wait for the slowest: 2^28 fp32 words took 0.466 instead of 0.403 ms.)
+// A counter serves one request in about 11.5 ns, however many workgroups ask, so there are
+// eight, one for each remainder of the chunk number: each is a field of 19 bits in the table
+// entry of an early chunk, between its byte count and its state bits, on a cache line of its
+// own, and the last to ask clears it.  (A single one takes 0.38 ms for the 32768 chunks of 2^28
+// words; with it the kernel took 0.457 ms.)
+// Whoever is waited for is a running workgroup, or one that started earlier.  Where that fails
+// all the same, nobody waits for good: a workgroup that has polled for a while in vain works out
+// the missing chunks' sizes itself (a size depends on the message alone) and goes on.
+// With all this, the residuals' or as the bitmap, byte permutes in the transpose and 16-bit
+// groups kept as 16 registers: 2^28 fp32 words 0.452 -> 0.403 ms (5.1 TB/s of message and
+// stream), as 16-bit words 0.332 -> 0.260 ms; 2048 x 6144 words 0.056 -> 0.032 ms, as 16-bit words
+// 0.036 -> 0.021 ms.
+// The table is part of the stream (the decoder needs it): no memory beyond input and output
+// is used.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
@@ -38,11 +44,10 @@
 namespace {
 
 constexpr int kThreads = zl::kGroups;
-constexpr uint32_t kSpinLimit = 1u << 22;
-// Chunks per workgroup of the compress kernel.  Two for 16-bit messages, whose compressor
-// is otherwise bound by the chunk counter (half the bytes per chunk); one for 32-bit
-// messages, where the wider workgroup's barriers cost more than the counter saves.
-template <bool HALF> constexpr int chunks_per_workgroup() { return HALF ? 2 : 1; }
+constexpr uint32_t kCounters = 8;      // of chunk numbers, in entries kCounterStride apart
+constexpr uint32_t kCounterStride = 16;
+constexpr uint32_t kPatience = 256;     // polls of the table (about 1 us each) before a workgroup helps itself
+template <bool HALF> constexpr int kMinWavesPerSimd = HALF ? 7 : 4;   // registers per lane: 72 and 128
 constexpr int kWaveStageWords = 32 * 33;   // planes of 32 lanes: a wavefront's LDS, one spare word per 32
 
 // Where plane word i of a half-wavefront sits in its LDS.  Lanes reach their planes with a
@@ -51,10 +56,11 @@ constexpr int kWaveStageWords = 32 * 33;   // planes of 32 lanes: a wavefront's 
 __device__ __forceinline__ uint32_t staged(uint32_t i) { return i + (i >> 5); }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t Word4 __attribute__((ext_vector_type(4), aligned(4)));   // four words of the stream
 
 struct Header {
   uint32_t magic;
-  uint32_t chunks;   // while compressing: chunk numbers handed out so far
+  uint32_t chunks;
   uint64_t n;
   uint64_t total;
   uint64_t flaw;     // zero in a valid stream
@@ -113,13 +119,17 @@ __device__ __forceinline__ Places workgroup_places(uint32_t count, uint32_t* wav
   __syncthreads();
   Places p;
   p.in_wave = incl - count;
-  p.wave_total = wave_totals[wave];
+  // (the same in every lane of the wavefront: these go to scalar registers)
+  const uint32_t first_wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave) & ~3u;
+  p.wave_total = 0;
   p.wave_start = 0;
   p.total = 0;
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    const uint32_t t = wave_totals[(wave & ~3) + w];
-    p.wave_start += w < (wave & 3) ? t : 0u;
+    const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_totals[first_wave + w]);
+    const uint32_t ahead = (uint32_t)__builtin_amdgcn_readfirstlane(wave & 3);
+    p.wave_start += (uint32_t)w < ahead ? t : 0u;
+    p.wave_total = (uint32_t)w == ahead ? t : p.wave_total;
     p.total += t;
   }
   return p;
@@ -132,76 +142,48 @@ __device__ __forceinline__ void half_span(const Places& p, int half, uint32_t& s
   end = half ? p.wave_total : middle;
 }
 
-// Sum of the sizes of chunks 0..c-1, read from the table (run by one whole wavefront):
-// 64 entries per pass, the lane's being the chunk at distance lane + 1 before c.  (Wider
-// passes were slower: the polls of all workgroups in flight fall on the same few hundred
-// table entries, and it is the number of these loads that costs.)  Returns false if a
-// needed entry stayed empty for kSpinLimit polls, or if the stream has been marked flawed
-// meanwhile (after one such failure nobody waits any more, so the launch ends at once).
-__device__ bool bytes_before(uint64_t* table, const uint64_t* flaw, uint32_t c, int lane, uint64_t& before) {
-  uint64_t sum = 0;
-  int64_t base = (int64_t)c - 1;
-  while (base >= 0) {
-    const int64_t idx = base - lane;
-    uint64_t s = 0;
-    uint32_t first = 64;
-    uint32_t polls = 0;
-    for (;;) {
-      s = idx >= 0 ? __hip_atomic_load(&table[idx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : zl::kEnd;
-      const uint64_t totals = __builtin_amdgcn_ballot_w64((s >> 62) == 2u);
-      const uint64_t empty = __builtin_amdgcn_ballot_w64((s >> 62) == 0u);
-      first = totals ? (uint32_t)__builtin_ctzll(totals) : 64u;
-      const uint64_t needed = first >= 63u ? ~0ull : ((2ull << first) - 1ull);
-      if ((empty & needed) == 0) break;
-      if (++polls > kSpinLimit) return false;
-      if ((polls & 255u) == 0u && __hip_atomic_load(flaw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
-      __builtin_amdgcn_s_sleep(2);
-    }
-    sum += wave_sum64((uint32_t)lane <= first ? (s & zl::kValueMask) : 0ull);
-    if (first != 64u) break;
-    base -= 64;
-  }
-  before = sum;
-  return true;
-}
-
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // The lane's group of chunk c: words 1024*t + 4*tid .. +3 of the chunk, t = 0..7; words
-// past the end of the message read as zero.  HALF: the message holds 16-bit words, which
-// are coded as the 32-bit words v << 16.
-template <bool HALF>
+// past the end of the message read as zero.
 __device__ __forceinline__ void load_group(const void* __restrict__ message, size_t n, uint32_t c, int tid, uint32_t (&w)[32]) {
   const size_t base = (size_t)c * zl::kChunkWords;
-  if constexpr (HALF) {
-    const uint16_t* in = static_cast<const uint16_t*>(message);
-    if (base + zl::kChunkWords <= n) {
+  const uint32_t* in = static_cast<const uint32_t*>(message);
+  if (base + zl::kChunkWords <= n) {
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const u32x2 v = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(in + base + 1024 * t + 4 * tid));
-        w[4 * t] = v.x << 16; w[4 * t + 1] = v.x & 0xFFFF0000u; w[4 * t + 2] = v.y << 16; w[4 * t + 3] = v.y & 0xFFFF0000u;
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 32; ++j) {
-        const size_t i = base + 1024 * (j >> 2) + 4 * tid + (j & 3);
-        w[j] = i < n ? (uint32_t)in[i] << 16 : 0u;
-      }
+    for (int t = 0; t < 8; ++t) {
+      const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(in + base + 1024 * t + 4 * tid));
+      w[4 * t] = v.x; w[4 * t + 1] = v.y; w[4 * t + 2] = v.z; w[4 * t + 3] = v.w;
     }
   } else {
-    const uint32_t* in = static_cast<const uint32_t*>(message);
-    if (base + zl::kChunkWords <= n) {
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(in + base + 1024 * t + 4 * tid));
-        w[4 * t] = v.x; w[4 * t + 1] = v.y; w[4 * t + 2] = v.z; w[4 * t + 3] = v.w;
-      }
-    } else {
+    for (int j = 0; j < 32; ++j) {
+      const size_t i = base + 1024 * (j >> 2) + 4 * tid + (j & 3);
+      w[j] = i < n ? in[i] : 0u;
+    }
+  }
+}
+
+// The same for 16-bit words, two to a register: word j in the lower, word j + 16 in the upper half
+// of register j.
+__device__ __forceinline__ void load_group_of_halves(const void* __restrict__ message, size_t n, uint32_t c, int tid, uint32_t (&w)[16]) {
+  const size_t base = (size_t)c * zl::kChunkWords;
+  const uint16_t* in = static_cast<const uint16_t*>(message);
+  if (base + zl::kChunkWords <= n) {
 #pragma unroll
-      for (int j = 0; j < 32; ++j) {
-        const size_t i = base + 1024 * (j >> 2) + 4 * tid + (j & 3);
-        w[j] = i < n ? in[i] : 0u;
-      }
+    for (int t = 0; t < 4; ++t) {
+      const u32x2 a = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(in + base + 1024 * t + 4 * tid));
+      const u32x2 b = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(in + base + 1024 * (t + 4) + 4 * tid));
+      w[4 * t] = zl::permute_bytes(b.x, a.x, 0x05040100u);
+      w[4 * t + 1] = zl::permute_bytes(b.x, a.x, 0x07060302u);
+      w[4 * t + 2] = zl::permute_bytes(b.y, a.y, 0x05040100u);
+      w[4 * t + 3] = zl::permute_bytes(b.y, a.y, 0x07060302u);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const size_t i = base + 1024 * (j >> 2) + 4 * tid + (j & 3), k = i + 4 * 1024;
+      w[j] = (i < n ? in[i] : 0u) | (k < n ? (uint32_t)in[k] << 16 : 0u);
     }
   }
 }
@@ -243,129 +225,224 @@ __device__ __forceinline__ void store_group(void* __restrict__ message, size_t n
   }
 }
 
+// Sets entry c of the table, to the chunk's own size or to its running total.  In an entry that
+// counts, the counter's field is left alone.
+__device__ __forceinline__ void publish(uint64_t* table, uint32_t c, uint64_t entry) {
+  if (c % kCounterStride != 0 || c >= kCounters * kCounterStride) {
+    __hip_atomic_store(&table[c], entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    uint64_t old = __hip_atomic_load(&table[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (!__hip_atomic_compare_exchange_strong(&table[c], &old, (old & zl::kTicketMask) | entry, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+    }
+  }
+}
+
+// The workgroup's next chunk number, or `chunks` if there is none.  Counter i hands out i,
+// i + kCounters, ...; workgroup b asks counter b mod kCounters until it gets a number past the end,
+// so the last request is known by its number, and clears the field.  (Workgroups start in order,
+// so however many of them run at a time, they are spread evenly over the counters, and whoever
+// waits for a number waits for a running workgroup or for one that some running workgroup is about to take.)
+__device__ __forceinline__ uint32_t next_chunk(uint64_t* table, uint32_t chunks) {
+  const uint32_t i = blockIdx.x % kCounters;
+  uint64_t* entry = &table[kCounterStride * i];
+  const uint64_t old = __hip_atomic_fetch_add(entry, (uint64_t)1 << zl::kTicketShift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint32_t ticket = (uint32_t)((old & zl::kTicketMask) >> zl::kTicketShift);
+  const uint32_t tickets = (chunks - i + kCounters - 1) / kCounters;
+  if (ticket + 1 == tickets + gridDim.x / kCounters)
+    __hip_atomic_fetch_and(entry, ~zl::kTicketMask, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return ticket < tickets ? i + kCounters * ticket : chunks;
+}
+
+// Bytes that chunk c takes in the payload, worked out from the message by one whole wavefront (two
+// passes over the chunk, few registers: this is the exception).
+template <bool HALF>
+__device__ uint64_t size_of_chunk(const void* __restrict__ message, size_t n, uint32_t c, int lane) {
+  const size_t base = (size_t)c * zl::kChunkWords;
+  auto word = [&](int tid, int j) {
+    const size_t i = base + 1024 * (j >> 2) + 4 * tid + (j & 3);
+    if constexpr (HALF) return i < n ? (uint32_t)static_cast<const uint16_t*>(message)[i] << 16 : 0u;
+    else return i < n ? static_cast<const uint32_t*>(message)[i] : 0u;
+  };
+  uint32_t planes = 0;
+#pragma unroll 1
+  for (int tid = lane; tid < kThreads; tid += 64) {
+    uint32_t m = 0, bitmap = 0;
+#pragma unroll 1
+    for (int j = 0; j < 32; ++j) {
+      const uint32_t mag = word(tid, j) & 0x7FFFFFFFu;
+      m = mag > m ? mag : m;
+    }
+#pragma unroll 1
+    for (int j = 0; j < 32; ++j) {
+      const uint32_t w = word(tid, j);
+      bitmap |= (w & 0x80000000u) | (m - (w & 0x7FFFFFFFu));
+    }
+    planes += (uint32_t)__builtin_popcount(bitmap);
+  }
+  return zl::kFixedChunkBytes + 4 * wave_sum64(planes);
+}
+
+// Sum of the sizes of chunks 0..c-1, read from the table (run by one whole wavefront):
+// 64 entries per pass, the lane's being the chunk at distance lane + 1 before c.  (Wider
+// passes were slower: the polls of all workgroups in flight fall on the same few hundred
+// table entries, and it is the number of these loads that costs.)  Where entries stay empty,
+// the wavefront works one of them out after the other, its pick among the empty ones
+// depending on c, so that several wavefronts in want of the same entries share the work; the
+// chunk's own workgroup may publish the same size at any time.
+template <bool HALF>
+__device__ uint64_t bytes_before(uint64_t* table, const void* __restrict__ message, size_t n, uint32_t c, int lane,
+                                 uint32_t patience) {
+  uint64_t sum = 0;
+  int64_t base = (int64_t)c - 1;
+  uint32_t polls = 0;
+  while (base >= 0) {
+    const int64_t idx = base - lane;
+    uint64_t s = 0;
+    uint32_t first = 64;
+    for (;;) {
+      s = idx >= 0 ? __hip_atomic_load(&table[idx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : zl::kEnd;
+      const uint64_t totals = __builtin_amdgcn_ballot_w64((s >> 62) == 2u);
+      const uint64_t empty = __builtin_amdgcn_ballot_w64((s >> 62) == 0u);
+      first = totals ? (uint32_t)__builtin_ctzll(totals) : 64u;
+      const uint64_t needed = first >= 63u ? ~0ull : ((2ull << first) - 1ull);
+      uint64_t missing = empty & needed;
+      if (missing == 0) break;
+      if (++polls > patience) {
+        for (uint32_t skip = c % (uint32_t)__builtin_popcountll(missing); skip != 0; --skip) missing &= missing - 1;
+        const uint32_t other = (uint32_t)(base - __builtin_ctzll(missing));
+        const uint64_t size = size_of_chunk<HALF>(message, n, other, lane);
+        if (lane == 0) {   // (unless the entry has changed meanwhile; if only its counter has, this is done again)
+          uint64_t old = __hip_atomic_load(&table[other], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if ((old >> 62) == 0u)
+            __hip_atomic_compare_exchange_strong(&table[other], &old, old | zl::kOwnSize | size, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+        }
+      } else {
+        __builtin_amdgcn_s_sleep(2);
+      }
+    }
+    sum += wave_sum64((uint32_t)lane <= first ? (s & zl::kValueMask & ~zl::kTicketMask) : 0ull);
+    if (first != 64u) break;
+    base -= 64;
+  }
+  return sum;
+}
+
 // A coded chunk that waits, in registers, for its place in the stream.
+// A group of 16-bit words has planes 16 and up only.
+template <bool HALF>
 struct Coded {
-  uint32_t planes[32];
+  static constexpr int kPlanes = HALF ? 16 : 32;
+  uint32_t planes[kPlanes];
   uint32_t reference, bitmap, chunk;
   Places at;
 };
 
-// CPW chunks per workgroup and counter value: chunks CPW*t .. CPW*t + CPW-1 are coded side
-// by side by 256 lanes each, so that the counter, which serves one request in about 11.5 ns
-// however many workgroups ask (measured: 32768 requests take 0.38 ms), is asked 1/CPW as often.
-template <int CPW, bool HALF>
-__global__ __launch_bounds__(kThreads * CPW, 4) void zl_compress_kernel(const void* __restrict__ in, size_t n, uint8_t* out,
-                                                                        uint32_t chunks) {
-  constexpr int kWaves = CPW * kThreads / 64;
+template <bool HALF>
+__global__ __launch_bounds__(kThreads, kMinWavesPerSimd<HALF>) void zl_compress_kernel(const void* __restrict__ in, size_t n, uint8_t* out,
+                                                                  uint32_t chunks, bool counted, uint32_t patience) {
+  constexpr int kWaves = kThreads / 64;
   __shared__ uint32_t stage[kWaveStageWords * kWaves];
   __shared__ uint32_t wave_totals[kWaves];
-  __shared__ uint32_t next_first;
-  __shared__ uint64_t my_start[CPW];
-  __shared__ uint32_t failed;
+  __shared__ uint64_t my_start;
+  __shared__ uint32_t next;
   Header* header = reinterpret_cast<Header*>(out);
   uint64_t* table = reinterpret_cast<uint64_t*>(out + zl::kHeaderBytes);
   uint8_t* payload = out + zl::kHeaderBytes + 8 * (size_t)chunks;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int part = tid / kThreads, lid = tid % kThreads;   // which of the CPW chunks, and the lane within it
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-  if (tid == 0) {
-    next_first = CPW * __hip_atomic_fetch_add(&header->chunks, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    failed = 0;
-  }
-  __syncthreads();
-  uint32_t first = next_first;
-  if (first >= chunks) return;
-
-  // A workgroup codes chunk after chunk.  A chunk's size is published as soon as it is
-  // coded; its place is worked out, and it is written, only after the next chunk has
-  // been coded in turn, by which time most of what its place depends on has arrived.
-  // No wait for another workgroup lies between taking a counter value and publishing
-  // the sizes of its chunks.
-  constexpr uint32_t kNone = 0xFFFFFFFFu;
-  Coded held;
-  held.chunk = kNone;
+  // A workgroup codes chunk after chunk.  A chunk's size is published as soon as it is known;
+  // its place is worked out, and it is written, only after the next chunk has been coded in turn,
+  // by which time most of what its place depends on has arrived.
+  Coded<HALF> held;
   bool holding = false;
+  uint32_t c = blockIdx.x;
+  if (counted) {
+    if (threadIdx.x == 0) next = next_chunk(table, chunks);
+    __syncthreads();
+    c = next;
+    __syncthreads();
+  }
   for (;;) {
-    const bool coding = first < chunks;   // the workgroup has chunks to code (its last ones may fall past the end)
-    Coded now;
-    now.chunk = kNone;
+    // (The lane's number anew in every pass: what is worked out from it, three dozen offsets, would
+    // otherwise be kept across the passes, in memory, for want of registers.)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
+    const bool coding = c < chunks;
+    Coded<HALF> now;
     if (coding) {
-      const uint32_t c = first + part;
-      const bool mine = c < chunks;
-      uint32_t count = 0;
-      if (mine) {
-        load_group<HALF>(in, n, c, lid, now.planes);
-        now.bitmap = zl::to_planes(now.planes, now.reference);
-        now.chunk = c;
-        count = (uint32_t)__builtin_popcount(now.bitmap);
+      if constexpr (HALF) {
+        load_group_of_halves(in, n, c, tid, now.planes);
+        now.bitmap = zl::to_residuals_of_halves(now.planes, now.reference);
+      } else {
+        load_group(in, n, c, tid, now.planes);
+        now.bitmap = zl::to_residuals(now.planes, now.reference);
       }
-      now.at = workgroup_places(count, wave_totals);
-      if (mine && lid == 0)
-        __hip_atomic_store(&table[c], (c == 0 ? zl::kEnd : zl::kOwnSize) | (zl::kFixedChunkBytes + 4ull * now.at.total),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      now.chunk = c;
+      now.at = workgroup_places((uint32_t)__builtin_popcount(now.bitmap), wave_totals);
+      if (tid == 0) publish(table, c, (c == 0 ? zl::kEnd : zl::kOwnSize) | (zl::kFixedChunkBytes + 4ull * now.at.total));
+      zl::transpose(now.planes);
     }
     if (holding) {
-      const uint64_t bytes = zl::kFixedChunkBytes + 4ull * held.at.total;
-      if ((wave & 3) == 0 && held.chunk != kNone) {   // the first wavefront of each chunk
-        uint64_t before = 0;
-        const bool ok = held.chunk == 0 || bytes_before(table, &header->flaw, held.chunk, lane, before);
+      if (wave == 0) {
+        const uint64_t bytes = zl::kFixedChunkBytes + 4ull * held.at.total;
+        const uint64_t before = held.chunk == 0 ? 0 : bytes_before<HALF>(table, in, n, held.chunk, lane, patience);
         if (lane == 0) {
-          if (!ok) {
-            failed = 1;
-            __hip_atomic_fetch_or(&header->flaw, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (held.chunk != 0) publish(table, held.chunk, zl::kEnd | (before + bytes));
+          my_start = before;
+          if (held.chunk == chunks - 1) {   // the last chunk's end is the stream's
+            header->magic = zl::kMagic;
+            header->chunks = chunks;
+            header->n = n;
+            header->total = zl::kHeaderBytes + 8ull * chunks + before + bytes;
           }
-          // publish a running total in any case, so that no later chunk waits for this one
-          if (held.chunk != 0)
-            __hip_atomic_store(&table[held.chunk], zl::kEnd | (before + bytes), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          my_start[part] = before;
         }
       }
       __syncthreads();
     }
-    // the next counter value travels while the held chunks are written
-    uint32_t asked = 0;
-    if (coding && tid == 0) asked = CPW * __hip_atomic_fetch_add(&header->chunks, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (holding && held.chunk != kNone && !failed) {   // (a flawed stream is marked in the header; nothing more of it is written)
-      uint32_t* dst = reinterpret_cast<uint32_t*>(payload + my_start[part]);
-      dst[lid] = held.reference;
-      dst[kThreads + lid] = held.bitmap;
+    // the next chunk number travels while the held chunk is written
+    uint32_t asked = chunks;
+    if (coding && counted && tid == 0) asked = next_chunk(table, chunks);
+    if (holding) {
+      uint32_t* dst = reinterpret_cast<uint32_t*>(payload + my_start);
+      dst[tid] = held.reference;
+      dst[kThreads + tid] = held.bitmap;
       dst += 2 * kThreads + held.at.wave_start;
-      // the wavefront's planes, 32 lanes at a time: into its LDS by lane, out of it by address
-      // (LDS operations of one wavefront take effect in program order)
+      // the wavefront's planes, as many lanes at a time as the LDS holds: into it by lane, out of it
+      // by address, four words per lane and step (LDS operations of one wavefront take effect in
+      // program order; the stream is aligned to words only, which a global store of any width may be)
+      constexpr int kPlanes = Coded<HALF>::kPlanes, kParts = HALF ? 1 : 2;
       uint32_t* mine = stage + kWaveStageWords * wave;
 #pragma unroll 1
-      for (int half = 0; half < 2; ++half) {
-        uint32_t start, end;
-        half_span(held.at, half, start, end);
-        if ((lane >> 5) == half) {
+      for (int part = 0; part < kParts; ++part) {
+        uint32_t start = 0, end = held.at.wave_total;
+        if (kParts == 2) half_span(held.at, part, start, end);
+        if (kParts == 1 || (lane >> 5) == part) {
           uint32_t pos = held.at.in_wave - start;
 #pragma unroll
-          for (int k = 0; k < 32; ++k)
-            if ((held.bitmap >> k) & 1u) mine[staged(pos++)] = held.planes[k];
+          for (int k = 0; k < kPlanes; ++k)
+            if ((held.bitmap >> (32 - kPlanes + k)) & 1u) mine[staged(pos++)] = held.planes[k];
         }
         __builtin_amdgcn_wave_barrier();
-        for (uint32_t i = lane; i < end - start; i += 64) dst[start + i] = mine[staged(i)];
+        const uint32_t count = end - start, whole = count & ~3u;
+        for (uint32_t i = 4 * lane; i < whole; i += 256) {
+          const uint32_t* p = mine + staged(i);   // (four words from a multiple of 4 on lie together)
+          const Word4 v = {p[0], p[1], p[2], p[3]};
+          *reinterpret_cast<Word4*>(dst + start + i) = v;
+        }
+        if ((uint32_t)lane < count - whole) dst[start + whole + lane] = mine[staged(whole + lane)];
         __builtin_amdgcn_wave_barrier();
       }
     }
     if (!coding) break;
-    if (tid == 0) next_first = asked;
     held = now;
     holding = true;
-    __syncthreads();
-    first = next_first;
+    if (tid == 0) next = asked;
+    __syncthreads();   // (also: the totals and the start are used again)
+    c = next;
   }
-}
-
-// Completes the header once every chunk is placed (the chunk counter has run past its end).
-__global__ void zl_finish_kernel(uint8_t* out, size_t n, uint32_t chunks) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  Header* header = reinterpret_cast<Header*>(out);
-  const uint64_t* table = reinterpret_cast<const uint64_t*>(out + zl::kHeaderBytes);
-  header->chunks = chunks;
-  header->n = n;
-  header->total = zl::kHeaderBytes + 8ull * chunks + (table[chunks - 1] & zl::kValueMask);
-  header->magic = zl::kMagic;
 }
 
 // in_bytes: size of the buffer that holds the stream; every read stays below it.
@@ -458,16 +535,24 @@ int compute_units() {
   return cus;
 }
 
-// 256-lane workgroups of the compress kernel per CU (wider workgroups: proportionally fewer).
-// (Only a build with -DZC_TUNING_KNOBS lets ZL_WORKGROUPS_PER_CU override it.)
-int workgroups_per_cu() {
+// Workgroups of the compress kernel per CU: as many as the registers allow.
+// (Only a build with -DZC_TUNING_KNOBS lets ZL_WORKGROUPS_PER_CU override it, and ZL_PATIENCE the
+// number of polls before a workgroup works out missing sizes itself.)
+int workgroups_per_cu(int preset) {
 #ifdef ZC_TUNING_KNOBS
   if (const char* e = getenv("ZL_WORKGROUPS_PER_CU")) {
     const int v = atoi(e);
     if (v >= 1 && v <= 64) return v;
   }
 #endif
-  return 4;
+  return preset;
+}
+
+uint32_t patience() {
+#ifdef ZC_TUNING_KNOBS
+  if (const char* e = getenv("ZL_PATIENCE")) return (uint32_t)atoi(e);
+#endif
+  return kPatience;
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -490,20 +575,20 @@ int launch_zl_compress(const void* d_in, size_t n, void* d_out, size_t out_cap, 
     hipLaunchKernelGGL(empty_stream_kernel, dim3(1), dim3(64), 0, s, static_cast<Header*>(d_out));
     return hipGetLastError() == hipSuccess ? ZC_OK : ZC_ERR_LAUNCH;
   }
-  // header and table start as zeros: the chunk counter, the empty table entries, the flaw mark
+  // header and table start as zeros: the empty table entries, the flaw mark
   // (a fill kernel rather than a memset node, so that the call can be captured in a graph)
   const size_t clear = (zl::kHeaderBytes + 8 * chunks) / 8;
   const unsigned zgrid = (unsigned)((clear + 255) / 256 < 1024 ? (clear + 255) / 256 : 1024);
   hipLaunchKernelGGL(zero_words_kernel, dim3(zgrid), dim3(256), 0, s, static_cast<uint64_t*>(d_out), clear);
   if (hipGetLastError() != hipSuccess) return ZC_ERR_LAUNCH;
-  constexpr int kPer = chunks_per_workgroup<HALF>();
-  const size_t resident = (size_t)compute_units() * workgroups_per_cu() / kPer;   // 128 registers per lane: 16 wavefronts per CU
-  const size_t tickets = (chunks + kPer - 1) / kPer;
-  const unsigned grid = (unsigned)(tickets < resident ? tickets : resident);
-  hipLaunchKernelGGL((zl_compress_kernel<kPer, HALF>), dim3(grid), dim3(kThreads * kPer), 0, s, d_in, n,
-                     static_cast<uint8_t*>(d_out), (uint32_t)chunks);
-  if (hipGetLastError() != hipSuccess) return ZC_ERR_LAUNCH;
-  hipLaunchKernelGGL(zl_finish_kernel, dim3(1), dim3(64), 0, s, static_cast<uint8_t*>(d_out), n, (uint32_t)chunks);
+  const size_t resident = (size_t)compute_units() * workgroups_per_cu(kMinWavesPerSimd<HALF>);
+  // a workgroup per chunk up to twice as many as run at a time (measured at 1536 chunks of 32-bit
+  // words: 0.032 ms, asking for numbers 0.035 ms; at 2560: 0.048 either way), and where a counter's
+  // field of 19 bits is too small: beyond 2^22 chunks, 2^35 words
+  const bool countable = chunks / kCounters + resident < ((size_t)1 << (62 - zl::kTicketShift));
+  const unsigned grid = (unsigned)(chunks <= 2 * resident || !countable ? chunks : resident / kCounters * kCounters);
+  hipLaunchKernelGGL((zl_compress_kernel<HALF>), dim3(grid), dim3(kThreads), 0, s, d_in, n,
+                     static_cast<uint8_t*>(d_out), (uint32_t)chunks, grid < chunks, patience());
   return hipGetLastError() == hipSuccess ? ZC_OK : ZC_ERR_LAUNCH;
 }
 

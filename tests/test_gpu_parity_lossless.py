@@ -246,3 +246,27 @@ def test_full_size_messages_sampled(gpu, ref):
             _same(_host(c[p0:p0 + int(wt[-1])]), want[32 + 128:], "payload from chunk %d" % c0)
         print("lossless full size", label, "stream is %.4f of the message" % (size / (4.0 * n)), flush=True)
         del dx, c, y
+
+
+@pytest.mark.parametrize("chunks, half", [(2047, False), (2100, False), (3583, True), (3601, True)])
+def test_a_workgroup_per_chunk_and_chunk_numbers_on_request(gpu, ref, chunks, half):
+    """On 256 compute units 32-bit messages of up to 2048 chunks and 16-bit ones of up to 3584 have a
+    workgroup per chunk; longer ones hand out chunk numbers through fields of early table entries, which
+    must be clean afterwards.  Uneven chunk sizes, a ragged last chunk, used buffers."""
+    import torch
+    n = (chunks - 1) * C + 77
+    g = torch.Generator(device="cuda")
+    g.manual_seed(chunks)
+    x = torch.randn(n, generator=g, device="cuda") * 1e-3
+    x[n // 3: n // 2] = 0.25
+    x = x.to(torch.bfloat16) if half else x
+    words = _host(x.float()).view(np.int32)
+    want = ref.compress(words)
+    out = torch.full((gpu.zl_max_compressed_size(n),), 0xA5, dtype=torch.uint8, device="cuda")
+    for rep in range(2):
+        print("chunks", chunks, "half", half, "repetition", rep, flush=True)
+        (gpu.zl_compress16 if half else gpu.zl_compress)(x, d_out=out)
+        size = gpu.zl_stream_bytes(out)
+        _same(_host(out[:size]), want, "stream of %d chunks" % chunks)
+    back = gpu.zl_decompress16(out, n) if half else gpu.zl_decompress(out, n)
+    assert torch.equal(back.view(torch.int16 if half else torch.int32), x.view(torch.int16 if half else torch.int32))
