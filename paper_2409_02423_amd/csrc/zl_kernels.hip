@@ -14,8 +14,8 @@
 // later it adds up the entries of the chunks before it, 64 at a time, back to the nearest
 // entry that already holds a running total, replaces the chunk's entry by its own running total
 // and writes the chunk.
-// Messages of up to twice as many chunks as workgroups fit on the chip have a workgroup per
-// chunk.  For longer ones about as many workgroups run as fit, and each asks for chunk numbers,
+// Messages of up to two and a half times as many chunks as workgroups fit on the chip have a
+// workgroup per chunk.  For longer ones about as many workgroups run as fit, and each asks for chunk numbers,
 // one after the other.  A coded chunk then waits in registers while its workgroup codes the next
 // one, and only after that looks for its place: by then most of what the sum needs has arrived,
 // so the look-back rarely has to poll.  (Chunks b, b + G, b + 2G, ... for workgroup b of G need no
@@ -25,9 +25,11 @@
 // entry of an early chunk, between its byte count and its state bits, on a cache line of its
 // own, and the last to ask clears it.  (A single one takes 0.38 ms for the 32768 chunks of 2^28
 // words; with it the kernel took 0.457 ms.)
-// Whoever is waited for is a running workgroup, or one that started earlier.  Where that fails
-// all the same, nobody waits for good: a workgroup that has polled for a while in vain works out
-// the missing chunks' sizes itself (a size depends on the message alone) and goes on.
+// A workgroup that is waited for may not run yet: its number may be one that no workgroup has asked
+// for, and a workgroup per chunk has to wait for its place on its die (with 24 of one die's 32 CUs
+// held by another kernel 2048 x 6144 words take 0.068 instead of 0.036 ms).  Nobody waits for good
+// all the same: a workgroup that has polled for a while in vain works out the missing chunks' sizes
+// itself (a size depends on the message alone) and goes on.
 // With all this, the residuals' or as the bitmap, byte permutes in the transpose and 16-bit
 // groups kept as 16 registers: 2^28 fp32 words 0.452 -> 0.403 ms (5.1 TB/s of message and
 // stream), as 16-bit words 0.332 -> 0.260 ms; 2048 x 6144 words 0.056 -> 0.032 ms, as 16-bit words
@@ -44,8 +46,8 @@
 namespace {
 
 constexpr int kThreads = zl::kGroups;
-constexpr uint32_t kCounters = 8;      // of chunk numbers, in entries kCounterStride apart
-constexpr uint32_t kCounterStride = 16;
+using zl::kCounters;
+using zl::kCounterStride;
 constexpr uint32_t kPatience = 256;     // polls of the table (about 1 us each) before a workgroup helps itself
 template <bool HALF> constexpr int kMinWavesPerSimd = HALF ? 7 : 4;   // registers per lane: 72 and 128
 constexpr int kWaveStageWords = 32 * 33;   // planes of 32 lanes: a wavefront's LDS, one spare word per 32
@@ -238,13 +240,11 @@ __device__ __forceinline__ void publish(uint64_t* table, uint32_t c, uint64_t en
   }
 }
 
-// The workgroup's next chunk number, or `chunks` if there is none.  Counter i hands out i,
-// i + kCounters, ...; workgroup b asks counter b mod kCounters until it gets a number past the end,
-// so the last request is known by its number, and clears the field.  (Workgroups start in order,
-// so however many of them run at a time, they are spread evenly over the counters, and whoever
-// waits for a number waits for a running workgroup or for one that some running workgroup is about to take.)
+// The workgroup's next chunk number, or `chunks` if there is none.  It asks its counter until it
+// gets a number past the end, so a counter's last request is known by its number, and clears the
+// field: the grid is a multiple of kCounters, and so as many workgroups ask each counter.
 __device__ __forceinline__ uint32_t next_chunk(uint64_t* table, uint32_t chunks) {
-  const uint32_t i = blockIdx.x % kCounters;
+  const uint32_t i = zl::counter_of(blockIdx.x);
   uint64_t* entry = &table[kCounterStride * i];
   const uint64_t old = __hip_atomic_fetch_add(entry, (uint64_t)1 << zl::kTicketShift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t ticket = (uint32_t)((old & zl::kTicketMask) >> zl::kTicketShift);
@@ -582,11 +582,12 @@ int launch_zl_compress(const void* d_in, size_t n, void* d_out, size_t out_cap, 
   hipLaunchKernelGGL(zero_words_kernel, dim3(zgrid), dim3(256), 0, s, static_cast<uint64_t*>(d_out), clear);
   if (hipGetLastError() != hipSuccess) return ZC_ERR_LAUNCH;
   const size_t resident = (size_t)compute_units() * workgroups_per_cu(kMinWavesPerSimd<HALF>);
-  // a workgroup per chunk up to twice as many as run at a time (measured at 1536 chunks of 32-bit
-  // words: 0.032 ms, asking for numbers 0.035 ms; at 2560: 0.048 either way), and where a counter's
-  // field of 19 bits is too small: beyond 2^22 chunks, 2^35 words
+  // a workgroup per chunk up to two and a half times as many as run at a time (us, a workgroup per
+  // chunk against asking for numbers: 2048 chunks of 32-bit words 37.7 and 41.6, 2320 44.6 and 46.7,
+  // 2930 51.9 and 51.2, 3418 61.9 and 56.8; of 16-bit words 3589 41.0 and 43.1, 4395 49.9 and 48.8),
+  // and where a counter's field of 19 bits is too small: beyond 2^22 chunks, 2^35 words
   const bool countable = chunks / kCounters + resident < ((size_t)1 << (62 - zl::kTicketShift));
-  const unsigned grid = (unsigned)(chunks <= 2 * resident || !countable ? chunks : resident / kCounters * kCounters);
+  const unsigned grid = (unsigned)(chunks <= 5 * resident / 2 || !countable ? chunks : resident / kCounters * kCounters);
   hipLaunchKernelGGL((zl_compress_kernel<HALF>), dim3(grid), dim3(kThreads), 0, s, d_in, n,
                      static_cast<uint8_t*>(d_out), (uint32_t)chunks, grid < chunks, patience());
   return hipGetLastError() == hipSuccess ? ZC_OK : ZC_ERR_LAUNCH;

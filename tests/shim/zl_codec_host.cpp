@@ -22,3 +22,6 @@ extern "C" void zl_host_from_planes(const uint32_t* planes, const uint32_t* refe
     std::memcpy(words + 32 * g, p, sizeof p);
   }
 }
+
+extern "C" uint32_t zl_host_counters() { return zl::kCounters; }
+extern "C" uint32_t zl_host_counter_of(uint32_t workgroup) { return zl::counter_of(workgroup); }

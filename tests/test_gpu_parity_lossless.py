@@ -248,9 +248,10 @@ def test_full_size_messages_sampled(gpu, ref):
         del dx, c, y
 
 
-@pytest.mark.parametrize("chunks, half", [(2047, False), (2100, False), (3583, True), (3601, True)])
+@pytest.mark.parametrize("chunks, half", [(2047, False), (2100, False), (3583, True), (3601, True),
+                                          (2560, False), (2561, False), (4480, True), (4481, True)])
 def test_a_workgroup_per_chunk_and_chunk_numbers_on_request(gpu, ref, chunks, half):
-    """On 256 compute units 32-bit messages of up to 2048 chunks and 16-bit ones of up to 3584 have a
+    """On 256 compute units 32-bit messages of up to 2560 chunks and 16-bit ones of up to 4480 have a
     workgroup per chunk; longer ones hand out chunk numbers through fields of early table entries, which
     must be clean afterwards.  Uneven chunk sizes, a ragged last chunk, used buffers."""
     import torch

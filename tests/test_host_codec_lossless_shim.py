@@ -54,3 +54,19 @@ def test_planes_and_words_match_reference(shim):
     shim.zl_host_from_planes(odd.ctypes.data, oref.ctypes.data, 200, back[:200].ctypes.data)
     for g in range(200):
         assert np.array_equal(back[g], zl_ref.words(int(oref[g]), zl_ref.unplanes(odd[g]))), g
+
+
+@pytest.mark.parametrize("grid", [1024, 1792, 128, 8])
+def test_chunk_counters_are_asked_evenly_whichever_dies_are_busy(shim, grid):
+    """Workgroup b runs on die b mod 8.  As many workgroups ask each counter as any other (the last
+    request is found by counting), with every die and with any one die held by another kernel, up
+    to the rounding of its share, and also in the first workgroup of each die alone."""
+    counters, dies = shim.zl_host_counters(), 8
+    asked = np.array([shim.zl_host_counter_of(b) for b in range(grid)])
+    die = np.arange(grid) % dies
+    assert asked.min() >= 0 and asked.max() < counters
+    assert (np.bincount(asked, minlength=counters) == grid // counters).all()
+    for busy in range(dies):
+        on_it = np.bincount(asked[die == busy], minlength=counters)
+        assert on_it.max() - on_it.min() <= 1, busy
+    assert sorted(asked[:dies]) == list(range(counters))
