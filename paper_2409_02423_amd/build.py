@@ -1,5 +1,6 @@
 """Compile the HIP library (csrc/zc_kernels.hip, csrc/zc2d_kernels.hip, csrc/zl_kernels.hip) for gfx950 into
-libzc.so next to this file.  hipcc cross-compiles without a GPU."""
+libzc.so next to this file, and the lossless kernels once more, with their tuning knobs, into
+libzl_knobs.so for the tests.  hipcc cross-compiles without a GPU."""
 import os
 import subprocess
 
@@ -9,6 +10,11 @@ DEPS = SOURCES + [os.path.join(HERE, "csrc", f) for f in ("zc_codec.h", "zc_half
                   os.path.join(HERE, "..", "include", "zc.h")]
 LIB = os.path.join(HERE, "libzc.so")
 STAMP = LIB + ".stamp"   # digest of what the library was built from (file times do not survive every copy)
+# The lossless calls alone, reading ZL_PATIENCE and ZL_WORKGROUPS_PER_CU from the environment: for tests
+# of what the shipped library does in rare conditions only.
+KNOBS_LIB = os.path.join(HERE, "libzl_knobs.so")
+KNOBS_SOURCES = SOURCES[2:]
+KNOBS_FLAGS = ("-DZC_TUNING_KNOBS",)
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -31,36 +37,43 @@ def deps_digest(extra_flags=()):
     return h.hexdigest()
 
 
-def is_stale():
+def is_stale(lib=None, extra_flags=()):
     """True if there is no built library or it was built from other sources than the present ones."""
-    if not os.path.exists(LIB) or not os.path.exists(STAMP):
+    stamp = (lib + ".stamp") if lib else STAMP
+    if not os.path.exists(lib or LIB) or not os.path.exists(stamp):
         return True
-    with open(STAMP) as f:
-        return f.read().strip() != deps_digest()
+    with open(stamp) as f:
+        return f.read().strip() != deps_digest(extra_flags)
 
 
-def build(extra_flags=(), out=None):
+def build(extra_flags=(), out=None, sources=None):
     """Compile every source (in parallel, one hipcc each) and link them into the library."""
     from concurrent.futures import ThreadPoolExecutor
     import tempfile
     out = out or LIB
+    sources = sources or SOURCES
     compile_flags = [f for f in FLAGS if f != "-shared"] + list(extra_flags)
     with tempfile.TemporaryDirectory(prefix="zc_build_") as work:
-        objects = [os.path.join(work, os.path.basename(src) + ".o") for src in SOURCES]
+        objects = [os.path.join(work, os.path.basename(src) + ".o") for src in sources]
 
         def compile_one(pair):
             src, obj = pair
             subprocess.check_call([HIPCC] + compile_flags + ["-c", src, "-o", obj])
 
-        with ThreadPoolExecutor(max_workers=len(SOURCES)) as pool:
-            list(pool.map(compile_one, zip(SOURCES, objects)))
+        with ThreadPoolExecutor(max_workers=len(sources)) as pool:
+            list(pool.map(compile_one, zip(sources, objects)))
         tmp = out + ".tmp.%d" % os.getpid()
         subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objects + ["-o", tmp])
     os.replace(tmp, out)
-    if out == LIB:
-        with open(STAMP, "w") as f:
+    if out in (LIB, KNOBS_LIB):
+        with open(out + ".stamp", "w") as f:
             f.write(deps_digest(extra_flags) + "\n")
     return out
+
+
+def build_knobs():
+    """The lossless kernels with their tuning knobs."""
+    return build(KNOBS_FLAGS, KNOBS_LIB, KNOBS_SOURCES)
 
 
 if __name__ == "__main__":

@@ -125,6 +125,24 @@ ZL_DEV uint32_t to_planes(uint32_t (&w)[32], uint32_t& reference) {
   return bitmap;
 }
 
+// How many planes of a group are not empty, from its words one at a time (word(j), j = 0..31): two
+// passes over them instead of 32 registers, for where a size is wanted without the group.
+template <class Word>
+ZL_DEV uint32_t planes_of_group(Word word) {
+  uint32_t m = 0, bitmap = 0;
+#pragma unroll 1
+  for (int j = 0; j < 32; ++j) {
+    const uint32_t mag = word(j) & 0x7FFFFFFFu;
+    m = mag > m ? mag : m;
+  }
+#pragma unroll 1
+  for (int j = 0; j < 32; ++j) {
+    const uint32_t w = word(j);
+    bitmap |= (w & 0x80000000u) | (m - (w & 0x7FFFFFFFu));
+  }
+  return (uint32_t)__builtin_popcount(bitmap);
+}
+
 // A group of 16-bit words v, coded as the 32-bit words v << 16: everything below bit 16 is zero, so
 // the group is kept as 16 registers, word j in the lower and word j + 16 in the upper half of
 // register j.  Reference and bitmap as the 32-bit form has them; after transpose<16> register k

@@ -240,6 +240,16 @@ __device__ __forceinline__ void publish(uint64_t* table, uint32_t c, uint64_t en
   }
 }
 
+// Whether workgroups publish the sizes of the chunks they code.  They do; only with the tuning knobs,
+// ZL_PATIENCE=0 keeps them from it, so that every size has to be worked out by those that wait for it.
+__device__ __forceinline__ bool sizes_are_published(uint32_t patience) {
+#ifdef ZC_TUNING_KNOBS
+  return patience != 0;
+#else
+  return true;
+#endif
+}
+
 // The workgroup's next chunk number, or `chunks` if there is none.  It asks its counter until it
 // gets a number past the end, so a counter's last request is known by its number, and clears the
 // field: the grid is a multiple of kCounters, and so as many workgroups ask each counter.
@@ -266,20 +276,7 @@ __device__ uint64_t size_of_chunk(const void* __restrict__ message, size_t n, ui
   };
   uint32_t planes = 0;
 #pragma unroll 1
-  for (int tid = lane; tid < kThreads; tid += 64) {
-    uint32_t m = 0, bitmap = 0;
-#pragma unroll 1
-    for (int j = 0; j < 32; ++j) {
-      const uint32_t mag = word(tid, j) & 0x7FFFFFFFu;
-      m = mag > m ? mag : m;
-    }
-#pragma unroll 1
-    for (int j = 0; j < 32; ++j) {
-      const uint32_t w = word(tid, j);
-      bitmap |= (w & 0x80000000u) | (m - (w & 0x7FFFFFFFu));
-    }
-    planes += (uint32_t)__builtin_popcount(bitmap);
-  }
+  for (int tid = lane; tid < kThreads; tid += 64) planes += zl::planes_of_group([&](int j) { return word(tid, j); });
   return zl::kFixedChunkBytes + 4 * wave_sum64(planes);
 }
 
@@ -382,7 +379,7 @@ __global__ __launch_bounds__(kThreads, kMinWavesPerSimd<HALF>) void zl_compress_
       }
       now.chunk = c;
       now.at = workgroup_places((uint32_t)__builtin_popcount(now.bitmap), wave_totals);
-      if (tid == 0) publish(table, c, (c == 0 ? zl::kEnd : zl::kOwnSize) | (zl::kFixedChunkBytes + 4ull * now.at.total));
+      if (tid == 0 && (c == 0 || sizes_are_published(patience))) publish(table, c, (c == 0 ? zl::kEnd : zl::kOwnSize) | (zl::kFixedChunkBytes + 4ull * now.at.total));
       zl::transpose(now.planes);
     }
     if (holding) {
@@ -537,7 +534,7 @@ int compute_units() {
 
 // Workgroups of the compress kernel per CU: as many as the registers allow.
 // (Only a build with -DZC_TUNING_KNOBS lets ZL_WORKGROUPS_PER_CU override it, and ZL_PATIENCE the
-// number of polls before a workgroup works out missing sizes itself.)
+// number of polls before a workgroup works out missing sizes itself; with 0, see sizes_are_published.)
 int workgroups_per_cu(int preset) {
 #ifdef ZC_TUNING_KNOBS
   if (const char* e = getenv("ZL_WORKGROUPS_PER_CU")) {

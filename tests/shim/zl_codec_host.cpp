@@ -23,5 +23,9 @@ extern "C" void zl_host_from_planes(const uint32_t* planes, const uint32_t* refe
   }
 }
 
+extern "C" void zl_host_planes_of_groups(const uint32_t* words, size_t groups, uint32_t* counts) {
+  for (size_t g = 0; g < groups; ++g) counts[g] = zl::planes_of_group([&](int j) { return words[32 * g + j]; });
+}
+
 extern "C" uint32_t zl_host_counters() { return zl::kCounters; }
 extern "C" uint32_t zl_host_counter_of(uint32_t workgroup) { return zl::counter_of(workgroup); }

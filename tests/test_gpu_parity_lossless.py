@@ -271,3 +271,38 @@ def test_a_workgroup_per_chunk_and_chunk_numbers_on_request(gpu, ref, chunks, ha
         _same(_host(out[:size]), want, "stream of %d chunks" % chunks)
     back = gpu.zl_decompress16(out, n) if half else gpu.zl_decompress(out, n)
     assert torch.equal(back.view(torch.int16 if half else torch.int32), x.view(torch.int16 if half else torch.int32))
+
+
+@pytest.mark.parametrize("chunks, per_cu, half", [(700, None, False), (700, None, True), (900, 1, False), (900, 1, True)])
+def test_sizes_worked_out_by_workgroups_that_wait(ref, monkeypatch, chunks, per_cu, half):
+    """A workgroup that waits in vain for the sizes of earlier chunks works them out itself (the shipped
+    library: after 256 polls, which only other work on the chip brings about).  Here no workgroup
+    publishes the sizes of its own chunks, so that every look-back past the nearest running total needs
+    sizes worked out by those that wait: with a workgroup per chunk, and with chunk numbers on request,
+    whose counters share entries with the sizes; uneven chunks, a ragged last one, a used buffer."""
+    import ctypes
+    import torch
+    from paper_2409_02423_amd import build
+    if build.is_stale(build.KNOBS_LIB, build.KNOBS_FLAGS):
+        build.build_knobs()
+    lib = ctypes.CDLL(build.KNOBS_LIB)
+    call = lib.zl_compress16 if half else lib.zl_compress
+    call.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+    lib.zl_max_compressed_size.argtypes, lib.zl_max_compressed_size.restype = [ctypes.c_size_t], ctypes.c_size_t
+    monkeypatch.setenv("ZL_PATIENCE", "0")
+    if per_cu:
+        monkeypatch.setenv("ZL_WORKGROUPS_PER_CU", str(per_cu))
+    n = (chunks - 1) * C + 77
+    g = torch.Generator(device="cuda")
+    g.manual_seed(chunks + half)
+    x = torch.randn(n, generator=g, device="cuda") * 1e-3
+    x[n // 3: n // 2] = 0.25
+    x[n // 2: n // 2 + 90 * C] *= torch.randint(0, 2, (90 * C,), generator=g, device="cuda")
+    x = x.to(torch.bfloat16) if half else x
+    want = ref.compress(_host(x.float()).view(np.int32))
+    out = torch.full((lib.zl_max_compressed_size(n),), 0xA5, dtype=torch.uint8, device="cuda")
+    for rep in range(4):
+        print("impatient: chunks", chunks, "per CU", per_cu, "half", half, "repetition", rep, flush=True)
+        assert call(x.data_ptr(), n, out.data_ptr(), out.numel(), torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        _same(_host(out[:want.size]), want, "stream of %d chunks" % chunks)

@@ -22,19 +22,35 @@ def shim():
         subprocess.check_call(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", SRC, "-o", LIB])
     L = ctypes.CDLL(LIB)
     L.zl_host_to_planes.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
+    L.zl_host_planes_of_groups.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     L.zl_host_from_planes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     return L
 
 
-def test_planes_and_words_match_reference(shim):
-    from oracle import zl_ref
+def _groups():
     rng = np.random.default_rng(11)
     parts = [workloads.edge_values(3).view(np.uint32), workloads.gradient_iid(4096).view(np.uint32),
              rng.integers(0, 1 << 32, size=4096, dtype=np.uint64).astype(np.uint32),
              (rng.integers(0, 1 << 32, size=2048, dtype=np.uint64).astype(np.uint32) & np.uint32(0xFFFF0000)),
              np.zeros(64, dtype=np.uint32), np.full(64, 0xC0490FDB, dtype=np.uint32)]
     w = np.concatenate(parts)
-    w = w[: w.size // 32 * 32].reshape(-1, 32).copy()
+    return w[: w.size // 32 * 32].reshape(-1, 32).copy()
+
+
+def test_plane_counts_match_reference(shim):
+    """The count from which a workgroup works out the size of a chunk that it has not coded."""
+    from oracle import zl_ref
+    w = _groups()
+    counts = np.zeros(len(w), dtype=np.uint32)
+    shim.zl_host_planes_of_groups(w.ctypes.data, len(w), counts.ctypes.data)
+    for g in range(len(w)):
+        assert counts[g] == sum(1 for p in zl_ref.planes(zl_ref.residuals(w[g])[1]) if p), g
+
+
+def test_planes_and_words_match_reference(shim):
+    from oracle import zl_ref
+    rng = np.random.default_rng(12)
+    w = _groups()
     groups = len(w)
     refs = np.zeros(groups, dtype=np.uint32)
     maps = np.zeros(groups, dtype=np.uint32)
