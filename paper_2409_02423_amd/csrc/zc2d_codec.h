@@ -81,7 +81,7 @@ ZC_DEV constexpr void transpose_halves(uint32_t (&a)[8]) {
   // bytes of each word change places)
 #pragma unroll
   for (int w = 0; w < 8; ++w) {
-    if (!WHOLE || __builtin_is_constant_evaluated())
+    if (!WHOLE)
       a[w] = (a[w] & 0xFF0000FFu) | ((a[w] & 0x0000FF00u) << 8) | ((a[w] >> 8) & 0x0000FF00u);
     else
       a[w] = zc::permute_bytes(a[w], a[w], 0x03010200u);

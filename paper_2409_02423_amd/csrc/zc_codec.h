@@ -70,10 +70,10 @@ ZC_DEV uint32_t alignbit(uint32_t hi, uint32_t lo, uint32_t s) {
 
 // Byte j of the result is byte sel[j] of the eight bytes {hi, lo} (0..3 = lo, 4..7 = hi);
 // a selector byte of 0x0c gives a zero byte.
-ZC_DEV uint32_t permute_bytes(uint32_t hi, uint32_t lo, uint32_t sel) {
+ZC_DEV constexpr uint32_t permute_bytes(uint32_t hi, uint32_t lo, uint32_t sel) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_perm(hi, lo, sel);
-#else
+  if (!__builtin_is_constant_evaluated()) return __builtin_amdgcn_perm(hi, lo, sel);
+#endif
   const uint64_t pool = ((uint64_t)hi << 32) | lo;
   uint32_t r = 0;
   for (int j = 0; j < 4; ++j) {
@@ -82,7 +82,6 @@ ZC_DEV uint32_t permute_bytes(uint32_t hi, uint32_t lo, uint32_t sel) {
     r |= b << (8 * j);
   }
   return r;
-#endif
 }
 
 ZC_DEV uint32_t count_leading_zeros(uint32_t x) { return x ? (uint32_t)__builtin_clz(x) : 32u; }

@@ -45,15 +45,14 @@ constexpr uint32_t kCounterStride = 16;
 ZL_DEV constexpr uint32_t counter_of(uint32_t workgroup) { return (workgroup + workgroup / kCounters) % kCounters; }
 
 // Byte j of the result is byte sel[j] of the eight bytes {hi, lo} (0..3 = lo, 4..7 = hi).
-ZL_DEV uint32_t permute_bytes(uint32_t hi, uint32_t lo, uint32_t sel) {
+ZL_DEV constexpr uint32_t permute_bytes(uint32_t hi, uint32_t lo, uint32_t sel) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_perm(hi, lo, sel);
-#else
+  if (!__builtin_is_constant_evaluated()) return __builtin_amdgcn_perm(hi, lo, sel);
+#endif
   const uint64_t pool = ((uint64_t)hi << 32) | lo;
   uint32_t r = 0;
   for (int j = 0; j < 4; ++j) r |= (uint32_t)((pool >> (8 * ((sel >> (8 * j)) & 7u))) & 0xFFu) << (8 * j);
   return r;
-#endif
 }
 
 // N = 32: the 32 x 32 bit transpose, out word k, bit j = in word j, bit k; its own inverse.
@@ -70,7 +69,7 @@ ZL_DEV constexpr void transpose(uint32_t (&a)[N]) {
     for (int i = 0; i < N; ++i)
       if ((i & s) == 0) {
         const uint32_t lo = a[i], hi = a[i + s];
-        if (s >= 8 && !__builtin_is_constant_evaluated()) {
+        if (s >= 8) {
           a[i] = permute_bytes(hi, lo, s == 16 ? 0x05040100u : 0x06020400u);
           a[i + s] = permute_bytes(hi, lo, s == 16 ? 0x07060302u : 0x07030501u);
         } else {
@@ -79,7 +78,6 @@ ZL_DEV constexpr void transpose(uint32_t (&a)[N]) {
         }
       }
 }
-ZL_DEV constexpr void transpose32(uint32_t (&a)[32]) { transpose<32>(a); }
 
 namespace selfcheck {
 template <int N>
@@ -100,7 +98,8 @@ static_assert(transpose_ok<32>() && transpose_ok<16>(), "bit transpose");
 
 // Words of a group -> its reference (largest magnitude as a bit pattern), and in place the
 // residuals sign | (reference - magnitude).  Returns the bitmap of the planes that are not empty,
-// which is the residuals or-ed together: it is known before the transpose.
+// which is the residuals or-ed together: it is known before the transpose, after which register k
+// is plane k.
 ZL_DEV uint32_t to_residuals(uint32_t (&w)[32], uint32_t& reference) {
   uint32_t m = 0;
 #pragma unroll
@@ -115,13 +114,6 @@ ZL_DEV uint32_t to_residuals(uint32_t (&w)[32], uint32_t& reference) {
     bitmap |= w[j];
   }
   reference = m;
-  return bitmap;
-}
-
-// The same, with the residuals' planes in place of the residuals.
-ZL_DEV uint32_t to_planes(uint32_t (&w)[32], uint32_t& reference) {
-  const uint32_t bitmap = to_residuals(w, reference);
-  transpose32(w);
   return bitmap;
 }
 
@@ -171,7 +163,7 @@ ZL_DEV uint32_t to_residuals_of_halves(uint32_t (&w)[16], uint32_t& reference) {
 // Planes (absent ones as zero) and reference -> the words, in place.  The distance wraps
 // within 31 bits, so residuals that no encoder produces still decode.
 ZL_DEV void from_planes(uint32_t (&p)[32], uint32_t reference) {
-  transpose32(p);
+  transpose(p);
 #pragma unroll
   for (int j = 0; j < 32; ++j) p[j] = (p[j] & 0x80000000u) | ((reference - (p[j] & 0x7FFFFFFFu)) & 0x7FFFFFFFu);
 }

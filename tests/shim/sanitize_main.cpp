@@ -32,6 +32,8 @@ int zc_host_decode_blocks(int rate, const uint8_t* in, size_t blocks, float* x);
 int zc2d_host_encode_blocks(int rate, const float* x, size_t blocks, uint8_t* out);
 int zc2d_host_decode_blocks(int rate, const uint8_t* in, size_t blocks, float* x);
 void zl_host_to_planes(const uint32_t* words, size_t groups, uint32_t* references, uint32_t* bitmaps, uint32_t* planes);
+void zl_host_halves_to_planes(const uint16_t* words, size_t groups, uint32_t* references, uint32_t* bitmaps, uint32_t* planes);
+void zl_host_planes_of_groups(const uint32_t* words, size_t groups, uint32_t* counts);
 void zl_host_from_planes(const uint32_t* planes, const uint32_t* references, size_t groups, uint32_t* words);
 }
 
@@ -151,6 +153,18 @@ int main() {
     zl_host_to_planes(w.data(), groups, refs.data(), maps.data(), planes.data());
     zl_host_from_planes(planes.data(), refs.data(), groups, back.data());
     CHECK(back == w, "lossless per-lane round trip");
+    std::vector<uint32_t> counts(groups);
+    zl_host_planes_of_groups(w.data(), groups, counts.data());
+    for (size_t g = 0; g < groups; ++g) CHECK((int)counts[g] == __builtin_popcount(maps[g]), "lossless plane count of group %zu", g);
+    // 16-bit words against the 32-bit words v << 16
+    std::vector<uint16_t> h(32 * groups);
+    for (size_t i = 0; i < h.size(); ++i) { h[i] = (uint16_t)(rnd() & (rnd() | 0xFF00u)); w[i] = (uint32_t)h[i] << 16; }
+    std::vector<uint32_t> hrefs(groups), hmaps(groups), hplanes(16 * groups);
+    zl_host_to_planes(w.data(), groups, refs.data(), maps.data(), planes.data());
+    zl_host_halves_to_planes(h.data(), groups, hrefs.data(), hmaps.data(), hplanes.data());
+    CHECK(hrefs == refs && hmaps == maps, "lossless 16-bit references or bitmaps");
+    for (size_t g = 0; g < groups; ++g)
+      CHECK(std::memcmp(&hplanes[16 * g], &planes[32 * g + 16], 64) == 0, "lossless 16-bit planes of group %zu", g);
   }
   if (g_failed) return 1;
   std::puts("sanitize driver: ok");

@@ -9,8 +9,21 @@ extern "C" void zl_host_to_planes(const uint32_t* words, size_t groups, uint32_t
   for (size_t g = 0; g < groups; ++g) {
     uint32_t w[32];
     std::memcpy(w, words + 32 * g, sizeof w);
-    bitmaps[g] = zl::to_planes(w, references[g]);
+    bitmaps[g] = zl::to_residuals(w, references[g]);
+    zl::transpose(w);
     std::memcpy(planes + 32 * g, w, sizeof w);
+  }
+}
+
+// Groups of 32 16-bit words, as the kernel for such messages has them; planes 16..31 of each.
+extern "C" void zl_host_halves_to_planes(const uint16_t* words, size_t groups, uint32_t* references, uint32_t* bitmaps,
+                                         uint32_t* planes) {
+  for (size_t g = 0; g < groups; ++g) {
+    uint32_t w[16];
+    for (int j = 0; j < 16; ++j) w[j] = words[32 * g + j] | (uint32_t)words[32 * g + j + 16] << 16;
+    bitmaps[g] = zl::to_residuals_of_halves(w, references[g]);
+    zl::transpose(w);
+    std::memcpy(planes + 16 * g, w, sizeof w);
   }
 }
 

@@ -22,6 +22,7 @@ def shim():
         subprocess.check_call(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", SRC, "-o", LIB])
     L = ctypes.CDLL(LIB)
     L.zl_host_to_planes.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
+    L.zl_host_halves_to_planes.argtypes = L.zl_host_to_planes.argtypes
     L.zl_host_planes_of_groups.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     L.zl_host_from_planes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     return L
@@ -35,6 +36,30 @@ def _groups():
              np.zeros(64, dtype=np.uint32), np.full(64, 0xC0490FDB, dtype=np.uint32)]
     w = np.concatenate(parts)
     return w[: w.size // 32 * 32].reshape(-1, 32).copy()
+
+
+def test_planes_of_16_bit_words_match_reference(shim):
+    """A group of 16-bit words v as two words to a register, against the reference on the words v << 16:
+    either sign, the largest patterns in either half, equal words, zeros."""
+    from oracle import zl_ref
+    rng = np.random.default_rng(13)
+    same = np.repeat(np.array([0x7FFF, 0xFFFF, 0x8000, 0x0000, 0xC049], dtype=np.uint16), 32)
+    parts = [(workloads.activation_gelu(4096).view(np.uint32) >> np.uint32(16)).astype(np.uint16), same,
+             rng.integers(0, 65536, size=4096).astype(np.uint16), rng.integers(0, 4, size=1024).astype(np.uint16)]
+    for at in (0, 15, 16, 31):     # one word that stands out, in each register half's first and last place
+        g = np.full(32, 0x3F80, dtype=np.uint16)
+        g[at] = 0xFFFF
+        parts.append(g)
+    h = np.concatenate(parts).reshape(-1, 32)
+    groups = len(h)
+    refs, maps = np.zeros(groups, dtype=np.uint32), np.zeros(groups, dtype=np.uint32)
+    planes = np.zeros((groups, 16), dtype=np.uint32)
+    shim.zl_host_halves_to_planes(h.ctypes.data, groups, refs.ctypes.data, maps.ctypes.data, planes.ctypes.data)
+    for g in range(groups):
+        m, r = zl_ref.residuals(h[g].astype(np.uint32) << np.uint32(16))
+        p = zl_ref.planes(r)
+        assert refs[g] == m and not any(p[:16]) and np.array_equal(planes[g], p[16:]), g
+        assert maps[g] == sum(1 << k for k in range(32) if p[k]), g
 
 
 def test_plane_counts_match_reference(shim):
