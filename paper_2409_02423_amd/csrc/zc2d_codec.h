@@ -451,6 +451,7 @@ ZC_DEV uint32_t decode_block_fixed(uint32_t (&W)[Traits<RATE>::kWords], const ui
   constexpr int NW = Traits<RATE>::kWords;
   constexpr int kPayload = Traits<RATE>::kPayloadBits;
   constexpr int kMaxPlanes = kPayload < 32 ? kPayload : 32;
+  static_assert(kPayload < (int)kTokenNone, "no budget lets an entry without a token pass (it would be read for ever)");
   const uint32_t E = W[0] & 0xFFu;
   uint32_t lead = 0;
   {
