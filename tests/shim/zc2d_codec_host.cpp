@@ -9,10 +9,8 @@
 #include "../../paper_2409_02423_amd/csrc/zc2d_codec.h"
 
 namespace {
-// one lane alone: the set of lanes where p holds is p itself
+// one lane alone: its own predicate is the vote
 struct Alone {
-  bool lanes(bool p) const { return p; }
-  bool some(bool set) const { return set; }
   bool operator()(bool p) const { return p; }
 };
 const Alone always;
@@ -65,11 +63,8 @@ template <int RATE>
 void wave(bool encode, const uint8_t* in, size_t blocks, uint8_t* out, int lanes) {
   constexpr int B = zc2d::Traits<RATE>::kBlockBytes;
   Ballot ballot(lanes);
-  // a thread's share of a set of lanes is its own predicate; the vote joins them
   struct Vote {
     Ballot* b;
-    bool lanes(bool p) const { return p; }
-    bool some(bool set) const { return b->vote(set); }
     bool operator()(bool p) const { return b->vote(p); }
   };
   const Vote vote{&ballot};
