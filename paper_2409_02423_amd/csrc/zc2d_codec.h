@@ -242,16 +242,19 @@ ZC_DEV void forward_transform(const uint32_t (&x)[16], uint32_t& E, uint32_t (&u
 // coefficients already significant, then the group tests.  pat: the plane's bit of each
 // coefficient; m = 32 + how many leading coefficients are significant (shift counts and field
 // widths use their low five bits, and the word's length falls out as m less a count of leading
-// zeros); known: all patterns so far; left: budget; last_reached (the same in every lane): whether
-// some lane's pattern has ever had the last coefficient.
+// zeros); known: all patterns so far; left: budget; last_reached (the same in every lane): with VOTES,
+// whether some lane's pattern has ever had the last coefficient.
 // The tokens' starts and ends come from two look-ups (see ExpandTable) without any case
 // distinction: the topmost bit of the expansion is the group bit after the last one, or the
 // plane's only one, and both are zeros in the code.  Only the last coefficient is different (no
-// end, no group bit after it; and no group test at all once it is significant), so that is
-// corrected where some lane of the wavefront has got there.  The length is at most 31.  (Before:
-// starts and ends formed separately, verbatim bits appended on their own, 33 instructions per
-// plane at rate 4 instead of 23; compress2d of 8192 x 32768 values at rate 8 0.283 -> 0.262 ms.)
-template <int NW, class AnyActive>
+// end, no group bit after it; and no group test at all once it is significant).  At the low rates
+// (VOTES) that is corrected where some lane of the wavefront has got there, which few do; from rate
+// 8 on in every plane, because a vote and a branch in each are what the few wavefronts of a small
+// matrix wait for.  The length is at most 31.  (Before: starts and ends formed separately, verbatim
+// bits appended on their own, 33 instructions per plane at rate 4 instead of 23.  us of compress2d
+// with those, with votes at every rate and as it is: 64 x 256 values at rate 16 4.44, 4.89, 4.36,
+// 8192 x 32768 at rate 16 493, 430, 425, at rate 8 293, 267, 268.)
+template <bool VOTES, int NW, class AnyActive>
 ZC_DEV void encode_plane(uint32_t pat, const uint32_t* expand, uint32_t (&W)[NW], uint32_t& m, uint32_t& known,
                          uint32_t& left, bool& last_reached, AnyActive any_lane_active) {
   const uint32_t rest = pat >> (m & 31u);
@@ -259,8 +262,8 @@ ZC_DEV void encode_plane(uint32_t pat, const uint32_t* expand, uint32_t (&W)[NW]
   uint32_t tokens = (lo & kExpandBits) | hi << (lo >> kExpandShift);
   const uint32_t c = count_leading_zeros_nonzero(tokens);
   uint32_t len = m - c;
-  last_reached = last_reached || any_lane_active(pat >= 0x8000u);
-  if (last_reached) {
+  if (VOTES) last_reached = last_reached || any_lane_active(pat >= 0x8000u);
+  if (!VOTES || last_reached) {
     // (sixteen ones in a first plane: the expansion is one bit longer than the word)
     if (pat >= 0x8000u) len -= tokens == 0xFFFFFFFFu ? 1u : 2u;
     if (m == 48u) len = 16u;
@@ -301,7 +304,7 @@ ZC_DEV void encode_block(const uint32_t (&x)[16], const uint32_t* expand, uint32
   for (int t = 0; t < 16; ++t) {
     if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
     const int b = 15 - t;
-    encode_plane<NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, m, known, left, last_reached, any_lane_active);
+    encode_plane<(RATE < 8), NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, m, known, left, last_reached, any_lane_active);
   }
   if (kMaxPlanes > 16 && any_lane_active(left > 0)) {
 #pragma unroll
@@ -311,7 +314,7 @@ ZC_DEV void encode_block(const uint32_t (&x)[16], const uint32_t* expand, uint32
     for (int t = 16; t < 32; ++t) {
       if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
       const int b = 31 - t;
-      encode_plane<NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, m, known, left, last_reached, any_lane_active);
+      encode_plane<(RATE < 8), NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, m, known, left, last_reached, any_lane_active);
     }
   }
   zc::shift_right<NW>(W, (uint32_t)(32 * NW - Traits<RATE>::kBlockBits) + left);
