@@ -17,7 +17,9 @@
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kDecodeThreads = 512;   // of the kernels that decode: more wavefronts share one copy of the 22 KiB token table (see below)
+// Of the kernels that decode (see below): more wavefronts share one copy of the 22 KiB token table,
+// but a small matrix occupies fewer CUs.
+constexpr int kDecodeThreads = 512, kDecodeThreadsSmall = 256;
 
 __device__ __align__(16) const zc2d::ExpandTable g_expand = zc2d::build_expand_table();
 __device__ __align__(16) const zc2d::TokenTable g_token = zc2d::build_token_table();
@@ -49,14 +51,18 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
   }
   __syncthreads();
 }
-// Workgroups per CU in the grid.  The kernels that decode have 512 lanes per workgroup: 22 KiB of
-// token table and 2 KiB per wavefront for its planes are 38 KiB, four of which fit a CU and fill it
-// (with 256 lanes, 30 KiB, five fit, 20 wavefronts of the 32 the registers allow: decompress2d of
-// 8192 x 32768 values at rate 4 0.270 against 0.248 ms, the 2-way reduce 0.613 against 0.583 ms;
-// 1024 lanes, whose 54 KiB fit twice: 0.599 ms for the reduce).  Their grid, swept from 4 to 48:
-// decompress2d at rate 8 0.296 ms at 4, 0.275 at 24, 0.280 at 48, but with rows that are aligned to
-// their elements only (6144 x 43690) 0.365 at 4, 0.313 at 24, 0.288 at 48: there neighbouring
-// wavefronts write to the same cache lines and gain from running at the same time.  Only a build with -DZC_TUNING_KNOBS lets ZC2D_WORKGROUPS_PER_CU override both; the shipped library reads no environment variable.
+// Workgroups per CU in the grid.  The kernels that decode have 512 lanes per workgroup (256 for small
+// matrices, see decode_threads): 22 KiB of token table and 2 KiB per wavefront for its planes are 38
+// KiB, 40 with the encoder's table, four of which fit a CU.  decompress2d up to rate 8 (54 to 61
+// registers) then fills it; at rate 16 (69) and in the reduces (71 to 80) the registers leave room for
+// three, in the one with local values and a stream as output at rate 16 (82) for two.  (With 256 lanes
+// five fit, 20 wavefronts: decompress2d of 8192 x 32768 values at rate 4, streams from memory, 0.270
+// against 0.248 ms, the 2-way reduce 0.613 against 0.583 ms; 1024 lanes, whose 54 KiB fit twice: 0.599
+// ms for the reduce.)  Their grid, swept from 4 to 48 on 8192 x 32768 values: decompress2d at rate 8
+// 0.296 ms at 4, 0.275 at 24, 0.280 at 48, but with rows that are aligned to their elements only (6144 x
+// 43690, fp32, rate 8) 0.365 at 4, 0.313 at 24, 0.288 at 48: there neighbouring wavefronts write to the
+// same cache lines and gain from running at the same time.  Only a build with -DZC_TUNING_KNOBS lets
+// ZC2D_WORKGROUPS_PER_CU override both; the shipped library reads no environment variable.
 constexpr int kCompressWorkgroupsPerCU = 16, kDecodeWorkgroupsPerCU = 24, kDecodeWorkgroupsPerCUUnaligned = 48;
 
 // The wavefront-wide vote of the codec: whether p holds in some lane.
@@ -272,15 +278,14 @@ __global__ __launch_bounds__(kThreads) void compress2d_kernel(const void* __rest
   }
 }
 
-template <int RATE, int DT>
-__global__ __launch_bounds__(kDecodeThreads) void decompress2d_kernel(const uint8_t* __restrict__ in, Walk w,
-                                                                void* __restrict__ out) {
+template <int RATE, int DT, int THREADS>
+__global__ __launch_bounds__(THREADS) void decompress2d_kernel(const uint8_t* __restrict__ in, Walk w, void* __restrict__ out) {
   __shared__ __attribute__((aligned(16))) uint32_t token[zc2d::kTokenRows << zc2d::kLookahead];
-  __shared__ __attribute__((aligned(16))) char plane_lds[kDecodeThreads / 64 * kPlaneBytes];
+  __shared__ __attribute__((aligned(16))) char plane_lds[THREADS / 64 * kPlaneBytes];
   WavePlanes planes(plane_lds);
-  stage_table<(zc2d::kTokenRows << zc2d::kLookahead), kDecodeThreads>(g_token.v, token);
+  stage_table<(zc2d::kTokenRows << zc2d::kLookahead), THREADS>(g_token.v, token);
   constexpr int NW = zc2d::Traits<RATE>::kWords;
-  const size_t b0 = (size_t)blockIdx.x * kDecodeThreads + threadIdx.x;
+  const size_t b0 = (size_t)blockIdx.x * THREADS + threadIdx.x;
   if (b0 >= w.blocks) return;
   Cursor cur;
   cur.start(w, b0);
@@ -314,18 +319,18 @@ struct ChunkPointers2d {
 // is stored as an fp32 matrix instead of being encoded (the last hop).
 // (The plain form at the low rates is two registers away from a sixth wavefront per SIMD, which
 // it gains from: the compiler is told to stay within that; the other forms would spill.)
-template <int RATE, bool LOCAL, bool RAW_OUT>
-__global__ __launch_bounds__(kDecodeThreads) __attribute__((amdgpu_waves_per_eu(RATE <= 4 && !LOCAL && !RAW_OUT ? 6 : 1)))
+template <int RATE, bool LOCAL, bool RAW_OUT, int THREADS>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(RATE <= 4 && !LOCAL && !RAW_OUT ? 6 : 1)))
 void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, uint8_t* out, float* out_raw) {
   __shared__ __attribute__((aligned(16))) uint32_t expand[zc2d::kExpandEntries];
   __shared__ __attribute__((aligned(16))) uint32_t token[zc2d::kTokenRows << zc2d::kLookahead];
-  __shared__ __attribute__((aligned(16))) char plane_lds[kDecodeThreads / 64 * kPlaneBytes];
+  __shared__ __attribute__((aligned(16))) char plane_lds[THREADS / 64 * kPlaneBytes];
   WavePlanes planes(plane_lds);
-  for (int i = threadIdx.x; i < zc2d::kExpandEntries / 4; i += kDecodeThreads)
+  for (int i = threadIdx.x; i < zc2d::kExpandEntries / 4; i += THREADS)
     reinterpret_cast<uint4*>(expand)[i] = reinterpret_cast<const uint4*>(g_expand.v)[i];
-  stage_table<(zc2d::kTokenRows << zc2d::kLookahead), kDecodeThreads>(g_token.v, token);   // (its barrier covers both tables)
+  stage_table<(zc2d::kTokenRows << zc2d::kLookahead), THREADS>(g_token.v, token);   // (its barrier covers both tables)
   constexpr int NW = zc2d::Traits<RATE>::kWords;
-  const size_t b0 = (size_t)blockIdx.x * kDecodeThreads + threadIdx.x;
+  const size_t b0 = (size_t)blockIdx.x * THREADS + threadIdx.x;
   if (b0 >= w.blocks) return;
   Cursor cur;
   cur.start(w, b0);
@@ -414,11 +419,18 @@ int workgroups_per_cu(int preset) {
   return preset;
 }
 
-unsigned grid_for(size_t blocks, int preset, int threads) {
+// preset: workgroups per CU of so many lanes.
+unsigned grid_for(size_t blocks, int preset, int threads, int cus) {
   const size_t groups = (blocks + threads - 1) / threads;
-  const size_t cap = (size_t)compute_units() * (size_t)workgroups_per_cu(preset);
+  const size_t cap = (size_t)cus * (size_t)workgroups_per_cu(preset);
   return (unsigned)(groups < cap ? groups : cap);
 }
+
+// Lanes per workgroup of a decoding kernel: the fewer where the wide ones would not be one per CU.
+// (us with 512 and 256 lanes, 2-way reduce at rates 4 and 16: 64 x 256 values 8.6 and 7.3, 16.7 and
+// 13.3; 512 x 1024 8.9 and 7.5, 17.0 and 14.0; 700 x 2500, just below the line, 9.1 and 8.9, 17.4
+// and 17.2; 1024 x 2048, on it, 9.1 both, 17.4 and 17.3; 2048 x 4096 23.1 and 24.1, 49.1 and 50.3.)
+int decode_threads(size_t blocks, int cus) { return blocks < (size_t)cus * kDecodeThreads ? kDecodeThreadsSmall : kDecodeThreads; }
 
 Walk walk_for(size_t rows, size_t cols, unsigned grid, int threads) {
   Walk w;
@@ -460,7 +472,7 @@ int launch_compress2d(const void* d_in, size_t rows, size_t cols, int rate, void
   if (out_cap < zc2d_compressed_size(rows, cols, rate)) return ZC_ERR_CAPACITY;
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const unsigned grid = grid_for(blocks, kCompressWorkgroupsPerCU, kThreads);
+  const unsigned grid = grid_for(blocks, kCompressWorkgroupsPerCU, kThreads, compute_units());
   const Walk w = walk_for(rows, cols, grid, kThreads);
 #define CALL(R) hipLaunchKernelGGL((compress2d_kernel<R, DT>), dim3(grid), dim3(kThreads), 0, s, d_in, w, static_cast<uint8_t*>(d_out))
   ZC2D_DISPATCH_RATE(rate, CALL)
@@ -477,11 +489,18 @@ int launch_decompress2d(const void* d_in, size_t rows, size_t cols, int rate, vo
   if (rows > kMaxValues || cols > kMaxValues || rows > kMaxValues / cols) return ZC_ERR_SIZE;
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const unsigned grid = grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUUnaligned : kDecodeWorkgroupsPerCU, kDecodeThreads);
-  const Walk w = walk_for(rows, cols, grid, kDecodeThreads);
-#define CALL(R) hipLaunchKernelGGL((decompress2d_kernel<R, DT>), dim3(grid), dim3(kDecodeThreads), 0, s, static_cast<const uint8_t*>(d_in), w, d_out)
+  const int cus = compute_units(), threads = decode_threads(blocks, cus);
+  const unsigned grid = grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUUnaligned : kDecodeWorkgroupsPerCU, threads, cus);
+  const Walk w = walk_for(rows, cols, grid, threads);
+#define LAUNCH(R, T) hipLaunchKernelGGL((decompress2d_kernel<R, DT, T>), dim3(grid), dim3(T), 0, s, static_cast<const uint8_t*>(d_in), w, d_out)
+#define CALL(R)                                                                \
+  do {                                                                         \
+    if (threads == kDecodeThreadsSmall) LAUNCH(R, kDecodeThreadsSmall);        \
+    else LAUNCH(R, kDecodeThreads);                                            \
+  } while (0)
   ZC2D_DISPATCH_RATE(rate, CALL)
 #undef CALL
+#undef LAUNCH
   return hipGetLastError() == hipSuccess ? ZC_OK : ZC_ERR_LAUNCH;
 }
 
@@ -504,20 +523,27 @@ int launch_reduce2d(const void* const* d_in, int k, const float* d_local, size_t
   if (!raw_out && out_cap < zc2d_compressed_size(rows, cols, rate)) return ZC_ERR_CAPACITY;
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const unsigned grid = grid_for(blocks, kDecodeWorkgroupsPerCU, kDecodeThreads);
-  const Walk w = walk_for(rows, cols, grid, kDecodeThreads);
+  const int cus = compute_units(), threads = decode_threads(blocks, cus);
+  const unsigned grid = grid_for(blocks, kDecodeWorkgroupsPerCU, threads, cus);
+  const Walk w = walk_for(rows, cols, grid, threads);
   uint8_t* out = static_cast<uint8_t*>(d_out);
-#define LAUNCH(R, LOCAL, RAW) \
-  hipLaunchKernelGGL((reduce2d_kernel<R, LOCAL, RAW>), dim3(grid), dim3(kDecodeThreads), 0, s, chunks, k, d_local, w, out, d_out_raw)
-#define CALL(R)                                    \
-  do {                                             \
-    if (d_local && raw_out) LAUNCH(R, true, true); \
-    else if (d_local) LAUNCH(R, true, false);      \
-    else if (raw_out) LAUNCH(R, false, true);      \
-    else LAUNCH(R, false, false);                  \
+#define LAUNCH(R, LOCAL, RAW, T) \
+  hipLaunchKernelGGL((reduce2d_kernel<R, LOCAL, RAW, T>), dim3(grid), dim3(T), 0, s, chunks, k, d_local, w, out, d_out_raw)
+#define FORMS(R, T)                                   \
+  do {                                                \
+    if (d_local && raw_out) LAUNCH(R, true, true, T); \
+    else if (d_local) LAUNCH(R, true, false, T);      \
+    else if (raw_out) LAUNCH(R, false, true, T);      \
+    else LAUNCH(R, false, false, T);                  \
+  } while (0)
+#define CALL(R)                                                        \
+  do {                                                                 \
+    if (threads == kDecodeThreadsSmall) FORMS(R, kDecodeThreadsSmall); \
+    else FORMS(R, kDecodeThreads);                                     \
   } while (0)
   ZC2D_DISPATCH_RATE(rate, CALL)
 #undef CALL
+#undef FORMS
 #undef LAUNCH
   return hipGetLastError() == hipSuccess ? ZC_OK : ZC_ERR_LAUNCH;
 }

@@ -385,3 +385,38 @@ def test_blocks_of_few_and_many_planes_side_by_side(gpu, ref, blocks):
         with np.errstate(all="ignore"):
             want = ref.decompress(s, 4, 4 * blocks, rate)
         _same_floats(_host(gpu.zc2d_decompress(_dev(s), 4, 4 * blocks, rate)), want, "arbitrary bytes")
+
+
+@pytest.mark.parametrize("rows, cols", [(1020, 2045), (1023, 2045), (1023, 2050)])
+def test_both_widths_of_the_decoding_kernels(gpu, ref, rows, cols):
+    """On 256 compute units matrices of fewer than 131072 blocks are decoded by workgroups of 256 lanes,
+    others by 512: just below that line, on it and past it with a last workgroup that is half empty.
+    Every decoding call at every rate, on streams of the encoder and on arbitrary bytes (values of any
+    size, lanes that read few and many planes side by side)."""
+    import torch
+    blocks = (rows + 3) // 4 * ((cols + 3) // 4)
+    x, y = _matrix(rows, cols, seed=1), _matrix(rows, cols, seed=2, kind="act")
+    rng = np.random.default_rng(cols)
+    for rate in RATES:
+        print("widths", rows, cols, rate, flush=True)
+        _round_trip(gpu, ref, x, rate, "%d blocks r%d" % (blocks, rate))
+        cx, cy = ref.compress(x, rate), ref.compress(y, rate)
+        got = gpu.zc2d_reduce_compressed([_dev(cx), _dev(cy)], rows, cols, rate)
+        _same_bytes(_host(got), ref.reduce_compressed([cx, cy], rows, cols, rate), rate, "reduce")
+        got = gpu.zc2d_reduce_mixed([_dev(cx)], _dev(y), rows, cols, rate)
+        _same_bytes(_host(got), ref.reduce_mixed([cx], y, rows, cols, rate), rate, "reduce_mixed")
+        got = gpu.zc2d_reduce_decompress([_dev(cx)], _dev(y), rows, cols, rate)
+        _same_floats(_host(got), ref.reduce_decompress([cx], y, rows, cols, rate), "reduce_decompress")
+        got = gpu.zc2d_reduce_decompress([_dev(cx), _dev(cy)], None, rows, cols, rate)
+        _same_floats(_host(got), ref.reduce_decompress([cx, cy], None, rows, cols, rate), "reduce_decompress of two")
+        s = rng.integers(0, 256, size=blocks * 2 * rate, dtype=np.uint8).reshape(blocks, 2 * rate)
+        s[::2, 1:] &= rng.integers(0, 256, size=s[::2, 1:].shape, dtype=np.uint8) & rng.integers(0, 256, size=s[::2, 1:].shape, dtype=np.uint8)
+        s = s.reshape(-1)
+        with np.errstate(all="ignore"):
+            want = ref.decompress(s, rows, cols, rate)
+        back = gpu.zc2d_decompress(_dev(s), rows, cols, rate)
+        _same_floats(_host(back), want, "arbitrary bytes")
+        for dtype in (torch.bfloat16, torch.float16):
+            # the narrowing is torch's: round to nearest even
+            half = gpu.zc2d_decompress_half(_dev(s), rows, cols, rate, dtype)
+            assert torch.equal(half.view(torch.int16), back.to(dtype).view(torch.int16)), dtype
