@@ -3,9 +3,9 @@
 // One lane per block of 4 x 4 values, blocks taken in row-major block order with a grid
 // stride, so that the 64 lanes of a wavefront read four contiguous 1 KiB spans (one per
 // matrix row of the block row) and write one contiguous span of 64 * 2*RATE stream bytes.
-// A block lives in registers from load to store; LDS holds only the coder's look-up table
-// (1 KiB for the encoder, 22 KiB for the decoder).  No matrix cores: nothing here is a
-// contraction.
+// A block lives in registers from load to store; LDS holds the coder's look-up tables (2 KiB
+// for the encoder, 22 KiB for the decoder) and, while a block is decoded, its planes (2 KiB per
+// wavefront).  No matrix cores: nothing here is a contraction.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
@@ -317,8 +317,9 @@ struct ChunkPointers2d {
 // block sticks out of the matrix its fill is taken from the sum's last valid row / column.
 // LOCAL: a raw fp32 matrix is added last (a ring hop's own contribution); RAW_OUT: the sum
 // is stored as an fp32 matrix instead of being encoded (the last hop).
-// (The plain form at the low rates is two registers away from a sixth wavefront per SIMD, which
-// it gains from: the compiler is told to stay within that; the other forms would spill.)
+// (All forms but one have six wavefronts per SIMD or seven.  That the plain form at the low rates is
+// told to stay within six changes a few instructions: 576 instead of 581 us for 8192 x 32768 values at
+// rate 4.)
 template <int RATE, bool LOCAL, bool RAW_OUT, int THREADS>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(RATE <= 4 && !LOCAL && !RAW_OUT ? 6 : 1)))
 void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, uint8_t* out, float* out_raw) {
