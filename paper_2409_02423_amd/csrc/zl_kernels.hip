@@ -259,8 +259,10 @@ __device__ __forceinline__ uint32_t next_chunk(uint64_t* table, uint32_t chunks)
   const uint64_t old = __hip_atomic_fetch_add(entry, (uint64_t)1 << zl::kTicketShift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t ticket = (uint32_t)((old & zl::kTicketMask) >> zl::kTicketShift);
   const uint32_t tickets = (chunks - i + kCounters - 1) / kCounters;
+  // (what was added is taken away again; a mask for the field, a constant of 64 bits, would be kept in
+  // memory throughout the 16-bit kernel for want of registers)
   if (ticket + 1 == tickets + gridDim.x / kCounters)
-    __hip_atomic_fetch_and(entry, ~zl::kTicketMask, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(entry, 0 - ((uint64_t)(ticket + 1) << zl::kTicketShift), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return ticket < tickets ? i + kCounters * ticket : chunks;
 }
 
