@@ -391,9 +391,11 @@ struct PlaneReader {
 // (What bounds the 4 x 4 kernels is their instruction count, and here the number of steps that
 // the wavefront's slowest lane needs.  Plane by plane in step, the patterns in registers, that was
 // 11.1 steps at rate 4 and 14.3 at rate 8 on the gradient matrix, as the sum over planes of the
-// slowest lane's; this way, the slowest lane's sum, it is 6.7 and 10.4: 578 -> 526 instructions
-// per block and 0.253 -> 0.233 ms for decompress2d of 8192 x 32768 values at rate 4, 0.623 -> 0.572 ms
-// for the 2-way reduce.)
+// slowest lane's; this way, the slowest lane's sum, it is 6.7 and 10.4: 578 -> 529 instructions
+// per block and 0.253 -> 0.233 ms for decompress2d of 8192 x 32768 values at rate 4 with the stream in
+// the last-level cache, 0.278 -> 0.248 ms with streams from memory and with what else changed in the
+// decoder, 0.623 -> 0.572 ms for the 2-way reduce.  At rate 16, where lanes differ least, it costs a
+// little: 118 -> 122 us for decompress2d of 8192 x 8192 values.)
 template <bool CAREFUL, int NW, class AnyActive, class Planes>
 ZC_DEV void read_planes(const uint32_t* token, PlaneReader<NW>& r, Planes& planes, AnyActive any_lane_active) {
   // byte offset of the entry: (clamped index - first row's index) rows, then the next bits;

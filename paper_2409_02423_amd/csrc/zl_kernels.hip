@@ -31,9 +31,9 @@
 // all the same: a workgroup that has polled for a while in vain works out the missing chunks' sizes
 // itself (a size depends on the message alone) and goes on.
 // With all this, the residuals' or as the bitmap, byte permutes in the transpose and 16-bit
-// groups kept as 16 registers: 2^28 fp32 words 0.452 -> 0.403 ms (5.1 TB/s of message and
-// stream), as 16-bit words 0.332 -> 0.260 ms; 2048 x 6144 words 0.056 -> 0.032 ms, as 16-bit words
-// 0.036 -> 0.021 ms.
+// groups kept as 16 registers: 2^28 fp32 words 0.452 -> 0.390 ms (5.2 TB/s of message and
+// stream), as 16-bit words 0.332 -> 0.253 ms; 2048 x 6144 words 0.056 -> 0.031 ms, as 16-bit words
+// 0.036 -> 0.020 ms.
 // The table is part of the stream (the decoder needs it): no memory beyond input and output
 // is used.
 #include <hip/hip_runtime.h>
@@ -49,7 +49,7 @@ constexpr int kThreads = zl::kGroups;
 using zl::kCounters;
 using zl::kCounterStride;
 constexpr uint32_t kPatience = 256;     // polls of the table (about 1 us each) before a workgroup helps itself
-template <bool HALF> constexpr int kMinWavesPerSimd = HALF ? 7 : 4;   // registers per lane: 72 and 128
+template <bool HALF> constexpr int kMinWavesPerSimd = HALF ? 7 : 4;   // registers per lane: 72 and 128, of which the kernels use 72 and 113
 constexpr int kWaveStageWords = 32 * 33;   // planes of 32 lanes: a wavefront's LDS, one spare word per 32
 
 // Where plane word i of a half-wavefront sits in its LDS.  Lanes reach their planes with a
@@ -65,7 +65,7 @@ struct Header {
   uint32_t chunks;
   uint64_t n;
   uint64_t total;
-  uint64_t flaw;     // zero in a valid stream
+  uint64_t reserved;   // zero
 };
 static_assert(sizeof(Header) == zl::kHeaderBytes, "header layout");
 
@@ -80,7 +80,7 @@ __global__ void empty_stream_kernel(Header* header) {
     header->chunks = 0;
     header->n = 0;
     header->total = zl::kHeaderBytes;
-    header->flaw = 0;
+    header->reserved = 0;
   }
 }
 
@@ -574,7 +574,7 @@ int launch_zl_compress(const void* d_in, size_t n, void* d_out, size_t out_cap, 
     hipLaunchKernelGGL(empty_stream_kernel, dim3(1), dim3(64), 0, s, static_cast<Header*>(d_out));
     return hipGetLastError() == hipSuccess ? ZC_OK : ZC_ERR_LAUNCH;
   }
-  // header and table start as zeros: the empty table entries, the flaw mark
+  // header and table start as zeros: the empty table entries, the reserved word
   // (a fill kernel rather than a memset node, so that the call can be captured in a graph)
   const size_t clear = (zl::kHeaderBytes + 8 * chunks) / 8;
   const unsigned zgrid = (unsigned)((clear + 255) / 256 < 1024 ? (clear + 255) / 256 : 1024);
@@ -627,7 +627,7 @@ int zl_stream_bytes(const void* d_stream, size_t* h_bytes, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (hipMemcpyAsync(&h, d_stream, sizeof h, hipMemcpyDeviceToHost, s) != hipSuccess) return ZC_ERR_LAUNCH;
   if (hipStreamSynchronize(s) != hipSuccess) return ZC_ERR_LAUNCH;
-  if (h.magic != zl::kMagic || h.flaw != 0) return ZC_ERR_STREAM;
+  if (h.magic != zl::kMagic || h.reserved != 0) return ZC_ERR_STREAM;
   *h_bytes = (size_t)h.total;
   return ZC_OK;
 }
