@@ -247,13 +247,13 @@ ZC_DEV void forward_transform(const uint32_t (&x)[16], uint32_t& E, uint32_t (&u
 // The tokens' starts and ends come from two look-ups (see ExpandTable) without any case
 // distinction: the topmost bit of the expansion is the group bit after the last one, or the
 // plane's only one, and both are zeros in the code.  Only the last coefficient is different (no
-// end, no group bit after it; and no group test at all once it is significant).  At the low rates
-// (VOTES) that is corrected where some lane of the wavefront has got there, which few do; from rate
-// 8 on in every plane, because a vote and a branch in each are what the few wavefronts of a small
-// matrix wait for.  The length is at most 31.  (Before: starts and ends formed separately, verbatim
-// bits appended on their own, 33 instructions per plane at rate 4 instead of 23.  us of compress2d
-// with those, with votes at every rate and as it is: 64 x 256 values at rate 16 4.44, 4.89, 4.36,
-// 8192 x 32768 at rate 16 493, 430, 425, at rate 8 293, 267, 268.)
+// end, no group bit after it; and no group test at all once it is significant), so with it reached
+// the length is counted instead.  At the low rates (VOTES) that is done where some lane of the
+// wavefront has got there, which few do; from rate 8 on in every plane, because a vote and a branch in
+// each are what the few wavefronts of a small matrix wait for.  The length is at most 31.  (Before:
+// starts and ends formed separately, verbatim bits appended on their own, 33 instructions per plane at
+// rate 4 instead of 23.  us of compress2d with those, with votes at every rate and as it is: 64 x 256
+// values at rate 16 4.50, 4.94, 4.35, 8192 x 32768 at rate 16 495, 429, 406, at rate 8 294, 267, 258.)
 template <bool VOTES, int NW, class AnyActive>
 ZC_DEV void encode_plane(uint32_t pat, const uint32_t* expand, uint32_t (&W)[NW], uint32_t& m, uint32_t& known,
                          uint32_t& left, bool& last_reached, AnyActive any_lane_active) {
@@ -262,18 +262,16 @@ ZC_DEV void encode_plane(uint32_t pat, const uint32_t* expand, uint32_t (&W)[NW]
   uint32_t tokens = (lo & kExpandBits) | hi << (lo >> kExpandShift);
   const uint32_t c = count_leading_zeros_nonzero(tokens);
   uint32_t len = m - c;
-  if (VOTES) last_reached = last_reached || any_lane_active(pat >= 0x8000u);
-  if (!VOTES || last_reached) {
-    // (sixteen ones in a first plane: the expansion is one bit longer than the word)
-    if (pat >= 0x8000u) len -= tokens == 0xFFFFFFFFu ? 1u : 2u;
-    if (m == 48u) len = 16u;
-  }
+  known |= pat;
+  if (VOTES) last_reached = last_reached || any_lane_active(known >= 0x8000u);
+  // a group bit or an end bit for each coefficient of the rest but the last one's, and one more for each
+  // that becomes significant; with all significant before, their sixteen bits (m >> 4 is 2 or 3)
+  if (!VOTES || last_reached) len = known >= 0x8000u ? 13u + (m >> 4) + (uint32_t)__builtin_popcount(rest) : len;
   tokens ^= 0x80000000u >> c;
   const uint32_t code = (pat & ((1u << (m & 31u)) - 1u)) | tokens << (m & 31u);
   const uint32_t take = umin(len, left);
   zc::shift_in<NW>(W, code, take);
   left -= take;
-  known |= pat;
   m = 64u - count_leading_zeros_nonzero(known);
 }
 
