@@ -61,7 +61,10 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
 // ms for the reduce.)  Their grid, swept from 4 to 48 on 8192 x 32768 values: decompress2d at rate 8
 // 0.296 ms at 4, 0.275 at 24, 0.280 at 48, but with rows that are aligned to their elements only (6144 x
 // 43690, fp32, rate 8) 0.365 at 4, 0.313 at 24, 0.288 at 48: there neighbouring wavefronts write to the
-// same cache lines and gain from running at the same time.  Only a build with -DZC_TUNING_KNOBS lets
+// same cache lines and gain from running at the same time (at rate 4 0.308 and 0.270 ms at 24 and 48, at
+// rate 16 0.455 both; as bf16 0.238 and 0.242 ms at rate 4, 0.285 and 0.287 at rate 8).  The reduces keep
+// 24; of theirs the one with local values and fp32 output writes such rows too (one chunk at rate 8: 0.516
+// and 0.466 ms), where the streams as output make no difference (0.742 and 0.740).  Only a build with -DZC_TUNING_KNOBS lets
 // ZC2D_WORKGROUPS_PER_CU override both; the shipped library reads no environment variable.
 constexpr int kCompressWorkgroupsPerCU = 16, kDecodeWorkgroupsPerCU = 24, kDecodeWorkgroupsPerCUUnaligned = 48;
 
