@@ -42,6 +42,7 @@ using zc::umax;
 using zc::count_leading_zeros;
 using zc::count_leading_zeros_nonzero;
 using zc::count_trailing_zeros;
+using zc::count_trailing_zeros_nonzero;
 
 constexpr int kFractionBits = 27;
 
@@ -68,6 +69,15 @@ constexpr Order build_order() {
   return o;
 }
 constexpr Order kOrder = build_order();
+
+// bits of a where mask is set, of b elsewhere (bit operations of three operands take the GPU half as
+// long as its bit-field insert)
+ZC_DEV constexpr uint32_t select_bits(uint32_t mask, uint32_t a, uint32_t b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if (!__builtin_is_constant_evaluated()) return __builtin_amdgcn_bitop3_b32(mask, a, b, 0xCA);
+#endif
+  return (a & mask) | (b & ~mask);
+}
 
 // ---- 16 x 16 bit transpose on eight words ----------------------------------------------
 // Row r of a 16 x 16 bit matrix sits in half r >> 3 of word r & 7 (half 0 = bits 0..15).
@@ -96,8 +106,8 @@ ZC_DEV constexpr void transpose_halves(uint32_t (&a)[8]) {
     for (int w = 0; w < 8; ++w)
       if ((w & j) == 0) {
         const uint32_t lo = a[w], hi = a[w + j];
-        a[w] = (lo & mask[m]) | ((hi << j) & ~mask[m]);
-        a[w + j] = ((lo >> j) & mask[m]) | (hi & ~mask[m]);
+        a[w] = select_bits(mask[m], lo, hi << j);
+        a[w + j] = select_bits(mask[m], lo >> j, hi);
       }
 }
 
@@ -353,15 +363,29 @@ ZC_DEV void accumulate_scaled(const int32_t (&q)[16], uint32_t E, float (&sum)[1
 // zero times anything finite added to the sum is the sum plus zero.
 ZC_DEV bool scaling_is_exact(uint32_t E) { return E - 28u <= 222u || E == 0u; }
 
+// Whether p or q holds in some lane (each comparison's own result is a set of lanes, and sets combine for
+// free on the device).
+template <class AnyActive>
+ZC_DEV bool any_of(AnyActive any_lane_active, bool p, bool q) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  (void)any_lane_active;
+  return (__builtin_amdgcn_ballot_w64(p) | __builtin_amdgcn_ballot_w64(q)) != 0;
+#else
+  return any_lane_active(p || q);
+#endif
+}
+
 // Where a lane's decoded planes go: sixteen 16-bit patterns, in the order they are read, that
-// start as zeros.  A place is given in steps of kPlaneStep, which on the device is the distance, in
-// bytes, of two planes in the wavefront's LDS (64 lanes, two bytes each); this one is for the host.
-constexpr uint32_t kPlaneStep = 128, kPlaneEnd = 16 * kPlaneStep;
+// start as zeros.  Places are kPlaneStep apart, from begin() to end(); word k is patterns 2k and, above
+// it, 2k + 1.  This one is for the host.
+constexpr uint32_t kPlaneStep = 2;
 struct LocalPlanes {
   uint16_t v[16];
   ZC_DEV void clear() { for (int t = 0; t < 16; ++t) v[t] = 0; }
+  ZC_DEV uint32_t begin() const { return 0u; }
+  ZC_DEV uint32_t end() const { return 16 * kPlaneStep; }
   ZC_DEV void put(uint32_t at, uint32_t pattern) { v[at / kPlaneStep] = (uint16_t)pattern; }
-  ZC_DEV uint32_t pair(int lower, int upper) const { return v[lower] | (uint32_t)v[upper] << 16; }
+  ZC_DEV uint32_t word(int k) const { return v[2 * k] | (uint32_t)v[2 * k + 1] << 16; }
 };
 
 // A lane's progress through its block's planes.
@@ -392,47 +416,51 @@ struct PlaneReader {
 // slowest lane's; this way, the slowest lane's sum, it is 6.7 and 10.4: 578 -> 529 instructions
 // per block and 0.253 -> 0.233 ms for decompress2d of 8192 x 32768 values at rate 4 with the stream in
 // the last-level cache, 0.278 -> 0.248 ms with streams from memory and with what else changed in the
-// decoder, 0.623 -> 0.572 ms for the 2-way reduce.  At rate 16, where lanes differ least, it costs a
-// little: 118 -> 122 us for decompress2d of 8192 x 8192 values.)
+// decoder, 0.623 -> 0.572 ms for the 2-way reduce.  A step of about 22 instructions instead of 28, without a vote on the places left and with a lane's
+// planes on end in LDS: decompress2d at rate 16 120 -> 112 us for 8192 x 8192 values, 2-way reduce 328 ->
+// 314 us, at rate 4 8192 x 32768 values 490 -> 469 us.)
 template <bool CAREFUL, int NW, class AnyActive, class Planes>
 ZC_DEV void read_planes(const uint32_t* token, PlaneReader<NW>& r, Planes& planes, AnyActive any_lane_active) {
   // byte offset of the entry: (clamped index - first row's index) rows, then the next bits;
   // the constant rides on the masking of the bits (it has none of their positions set)
   constexpr uint32_t kRowBytesLg = kLookahead + 2;
   constexpr uint32_t kBias = 0u - (kTokenFirstRowIndex << kRowBytesLg);
+  // Up to rate 8 (NW <= 4) few blocks take sixteen steps, and in as many no lane can pass its
+  // sixteenth place: the plain form counts them.  At rate 16 it asks whether some lane has got there.
+  constexpr bool kCounted = !CAREFUL && NW <= 4;
+  uint32_t steps = 16;
 #pragma unroll 1
   for (;;) {
-    const bool reading = !CAREFUL || r.at != kPlaneEnd;
-    uint32_t e = 0u, ones = 0u;
+    const bool reading = !CAREFUL || r.at != planes.end();
+    uint32_t e = 0u;
     int32_t budget = 0;
     bool cut = false;
     if (reading) {
-      r.pattern |= r.W[0] & ((1u << r.skip) - 1u);
       const uint32_t clamped = umin(umax(r.n, kTokenFirstRowIndex), kTokenLastRowIndex);
       uint32_t bits = (r.W[0] >> r.skip) & ((1u << kLookahead) - 1u);
       zc::materialise(bits);   // (a bit-field extract, then shift-and-or with the constant, then shift-and-add:
       bits = bits << 2 | kBias;   //  otherwise the constant comes back as an addition of its own)
       zc::materialise(bits);
       e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(token) + ((clamped << kRowBytesLg) + bits));
+      r.pattern |= r.W[0] & ((1u << r.skip) - 1u);
       budget = r.left - (int32_t)r.skip;
-      ones = (e >> 16) & 0xFFu;
       cut = (e >> 24) > (uint32_t)budget;   // (no budget at all: the window is empty, and so is byte 3)
     }
     if (any_lane_active(cut)) {
       // zeros up to the one; the run ends at the last coefficient or at the budget (of which some is
-      // left: the group bit is a one)
+      // left: the group bit is a one).  The one may be too far on for an entry.
       const uint32_t room = umin(15u - r.n, (uint32_t)budget - 1u);
       const uint32_t z = umin(count_trailing_zeros(r.W[0] >> r.skip >> 1), room);
       const uint32_t made = (z + 1u) << 8 | (1u + z + (z < room ? 1u : 0u));
       e = cut ? made : e;
-      ones = cut ? 1u << (z & 31u) : ones;
+      r.pattern |= cut ? 1u << ((r.n + z) & 31u) : 0u;
     }
     if (reading) {
-      r.pattern |= ones << r.n;
+      r.pattern |= ((e >> 16) & 0xFFu) << r.n;
       const uint32_t s = r.n + ((e >> 8) & 0xFFu), used = e & 0xFFu;
+      planes.put(r.at, r.pattern);
       zc::shift_out<NW>(r.W, r.skip + used);
       r.left = budget - (int32_t)used;
-      planes.put(r.at, r.pattern);
       const bool closed = s >= kTokenClosed;
       r.n = s & 31u;
       r.skip = closed ? r.n : 0u;
@@ -440,67 +468,101 @@ ZC_DEV void read_planes(const uint32_t* token, PlaneReader<NW>& r, Planes& plane
       r.at += closed ? kPlaneStep : 0u;
     }
     if (CAREFUL) {
-      if (!any_lane_active(r.left > 0 && r.at != kPlaneEnd)) break;
+      if (!any_lane_active(r.left > 0 && r.at != planes.end())) break;
+    } else if (kCounted) {
+      if (!any_lane_active(r.left > 0) || --steps == 0) break;
     } else {
-      if (!any_lane_active(r.left > 0) || any_lane_active(r.at == kPlaneEnd)) break;
+      if (!any_lane_active(r.left > 0) || any_lane_active(r.at == planes.end())) break;
     }
   }
 }
 
-// Whole block up to the fixed-point values; returns the exponent byte.
+// A block whose planes have been read: its exponent byte, the empty planes before the first one, and
+// where reading stopped.  An empty block (a zero exponent byte, or 32 and more empty planes) has
+// neither planes nor budget and counts as three empty planes under the exponent byte of 1.
+template <int NW>
+struct BlockReading {
+  uint32_t E, lead;
+  bool low_start;        // planes that start more than 16 below the top (and any to read)
+  PlaneReader<NW> r;
+};
+constexpr uint32_t kEmptyLead = 3u, kEmptyExponent = 127u;
+
+// Reads the first (up to sixteen) planes of the block in the window W.
 template <int RATE, class AnyActive, class Planes>
-ZC_DEV uint32_t decode_block_fixed(uint32_t (&W)[Traits<RATE>::kWords], const uint32_t* token, int32_t (&q)[16],
-                                   AnyActive any_lane_active, Planes& planes) {
+ZC_DEV BlockReading<Traits<RATE>::kWords> read_block(uint32_t (&W)[Traits<RATE>::kWords], const uint32_t* token,
+                                                     AnyActive any_lane_active, Planes& planes) {
   constexpr int NW = Traits<RATE>::kWords;
   constexpr int kPayload = Traits<RATE>::kPayloadBits;
-  constexpr int kMaxPlanes = kPayload < 32 ? kPayload : 32;
   static_assert(kPayload < (int)kTokenNone, "no budget lets an entry without a token pass (it would be read for ever)");
-  const uint32_t E = W[0] & 0xFFu;
-  uint32_t lead = 0;
-  {
+  uint32_t E = W[0] & 0xFFu;
+  // empty planes before the first one: zeros from bit 8 on, which seldom pass the first word
+  const uint32_t top = W[0] & 0xFFFFFF00u;
+  uint32_t lead = count_trailing_zeros_nonzero(top) - 8u;
+  bool empty = false;
+  if (any_of(any_lane_active, top == 0u, E == 0u)) {
+    lead = 0;
     bool found = false;
 #pragma unroll
     for (int j = 0; j < NW; ++j) {
-      const uint32_t w = j == 0 ? (W[0] & 0xFFFFFF00u) : W[j];
+      const uint32_t w = j == 0 ? top : W[j];
       const uint32_t z = count_trailing_zeros(w);
       lead = found ? lead : lead + z;
       found = found || (w != 0);
     }
-    lead -= 8u;
+    lead = umin(lead - 8u, (uint32_t)kPayload);
+    empty = E == 0u || lead >= 32u;
   }
-  lead = umin(lead, (uint32_t)kPayload);
   int32_t left = (int32_t)kPayload - (int32_t)lead;
   // past the header byte and the leading zeros: two shifts of less than 32 each (with 32 and
   // more leading zeros there is nothing to read, as in a zero block, whatever its payload)
   zc::shift_out<NW>(W, 8u);
   zc::shift_out<NW>(W, lead & 31u);
-  const bool empty = E == 0u || lead >= 32u;
   if (any_lane_active(empty)) {
     if (empty) {
       left = 0;
+      lead = kEmptyLead;
+      E = kEmptyExponent;
 #pragma unroll
       for (int j = 0; j < NW; ++j) W[j] = 0u;
     }
   }
-  // a lane whose planes start more than 16 below the top (and that has any to read)
-  const bool low_start = lead > 16u && left > 0;
-  PlaneReader<NW> r = {W, left, 0u, 0u, 0u, 0u};
+  BlockReading<NW> b = {E, lead, lead > 16u && left > 0, {W, left, 0u, 0u, 0u, planes.begin()}};
   planes.clear();
-  read_planes<false>(token, r, planes, any_lane_active);
-  if (any_lane_active(r.left > 0)) {   // some lane has read sixteen planes
-    if (any_lane_active(r.left > 0 && r.at != kPlaneEnd)) read_planes<true>(token, r, planes, any_lane_active);
+  read_planes<false>(token, b.r, planes, any_lane_active);
+  if (any_lane_active(b.r.left > 0)) {   // some lane may have read sixteen planes
+    if (any_lane_active(b.r.left > 0 && b.r.at != planes.end())) read_planes<true>(token, b.r, planes, any_lane_active);
   }
-  uint32_t h[8], u[16];
+  return b;
+}
+
+// Rows of the 16 x 16 transpose, the first plane the highest: plane 15 - w in the lower and 7 - w in the upper
+// half of word w.
+template <class Planes>
+ZC_DEV void load_planes(const Planes& planes, uint32_t (&h)[8]) {
+  uint32_t p[8];
 #pragma unroll
-  for (int w = 0; w < 8; ++w) h[w] = planes.pair(15 - w, 7 - w);
+  for (int k = 0; k < 8; ++k) p[k] = planes.word(k);
+#pragma unroll
+  for (int w = 0; w < 8; ++w) h[w] = zc::permute_bytes(p[(7 - w) >> 1], p[(15 - w) >> 1], w & 1 ? 0x05040100u : 0x07060302u);
+}
+
+// The rest of the way to the fixed-point values, for any block.
+template <int RATE, class AnyActive, class Planes>
+ZC_DEV void finish_block(BlockReading<Traits<RATE>::kWords>& b, const uint32_t* token, int32_t (&q)[16],
+                         AnyActive any_lane_active, Planes& planes) {
+  constexpr int kPayload = Traits<RATE>::kPayloadBits;
+  constexpr int kMaxPlanes = kPayload < 32 ? kPayload : 32;
+  uint32_t h[8], u[16];
+  load_planes(planes, h);
   transpose_halves<true>(h);
 #pragma unroll
   for (int w = 0; w < 8; ++w) zc::materialise(h[w]);   // one transpose, not one per half
-  const bool deeper = kMaxPlanes > 16 && any_lane_active(r.left > 0);
-  if (!deeper && !any_lane_active(low_start)) {
+  const bool deeper = kMaxPlanes > 16 && any_lane_active(b.r.left > 0);
+  if (!deeper && !any_lane_active(b.low_start)) {
     // the usual case: at most 16 planes were read and they start within the top 16, so each
     // coefficient is its 16-bit pattern moved up (a lane that read nothing has zero patterns)
-    const uint32_t up = (16u - lead) & 31u;
+    const uint32_t up = (16u - b.lead) & 31u;
 #pragma unroll
     for (int w = 0; w < 8; ++w) {
       u[w] = (h[w] & 0xFFFFu) << up;
@@ -513,12 +575,11 @@ ZC_DEV uint32_t decode_block_fixed(uint32_t (&W)[Traits<RATE>::kWords], const ui
       u[w + 8] = h[w] & 0xFFFF0000u;
     }
     if (deeper) {
-      r.at = 0u;
-      r.pattern = 0u;   // (a lane that ran out of budget within a plane has put it where it belongs)
+      b.r.at = planes.begin();
+      b.r.pattern = 0u;   // (a lane that ran out of budget within a plane has put it where it belongs)
       planes.clear();
-      read_planes<true>(token, r, planes, any_lane_active);
-#pragma unroll
-      for (int w = 0; w < 8; ++w) h[w] = planes.pair(15 - w, 7 - w);
+      read_planes<true>(token, b.r, planes, any_lane_active);
+      load_planes(planes, h);
       transpose_halves<true>(h);
 #pragma unroll
       for (int w = 0; w < 8; ++w) {
@@ -528,10 +589,115 @@ ZC_DEV uint32_t decode_block_fixed(uint32_t (&W)[Traits<RATE>::kWords], const ui
       }
     }
 #pragma unroll
-    for (int c = 0; c < 16; ++c) u[c] >>= (lead & 31u);   // nothing was decoded if lead >= 32
+    for (int c = 0; c < 16; ++c) u[c] >>= b.lead;
   }
   inverse_transform(u, q);
-  return E;
+}
+
+// Whole block up to the fixed-point values; returns the exponent byte.
+template <int RATE, class AnyActive, class Planes>
+ZC_DEV uint32_t decode_block_fixed(uint32_t (&W)[Traits<RATE>::kWords], const uint32_t* token, int32_t (&q)[16],
+                                   AnyActive any_lane_active, Planes& planes) {
+  auto b = read_block<RATE>(W, token, any_lane_active, planes);
+  finish_block<RATE>(b, token, q, any_lane_active, planes);
+  return b.E;
+}
+
+// ---- the inverse transform as a matrix ----------------------------------------------------
+// The inverse lifting halves with floors, but a halving that leaves no remainder is linear, and a
+// coefficient that ends six digits above the lowest leaves none in either pass (the passes divide by
+// 8 each in all).  Then the 16 values are a fixed 16 x 16 matrix times the coefficients, which the
+// matrix cores work out, exactly: the digits that have been read, in bytes, are small whole
+// numbers, and so are the sums.  What is needed for that to be the lifting's own result:
+//   * digits end six or more above bit 0: lead + digits <= 26 (digits = 8 or 15, see below);
+//   * no sum of the lifting wraps.  In the first pass a column's sums are at most 2.25 times its
+//     largest coefficient.  With lead >= 2 coefficients are within -715827882..357913941 and
+//     fit; with lead = 1 they are up to 1431655765 where the digit of bit 30 is set, and the
+//     largest sum, a + c/2 - b/8 - 5d/8, is 2^31 - 1 if one of the four has it (and 1 if none has);
+//     the block's first plane must then have a single one.  In the second pass every sum is a sum of
+//     the values that come out, with weights of up to 4 in all: no value of 2^29 or more is allowed,
+//     which is looked at afterwards, for lead <= 2 (from lead = 3 on coefficients are within
+//     -178956970..357913941, and 2.25 * 2.25 times that fits).  Blocks that an encoder made have
+//     values of about 2^27 at most;
+//   * the scaling by the exponent byte is exact and finite.
+constexpr int kInverse8[4][4] = {{8, 3, -4, -1}, {8, 1, 4, 5}, {8, -1, 4, -5}, {8, -3, -4, 1}};   // 8 x what inverse_lift does
+
+// 64 x the weight of coefficient c in value p (row-major).
+constexpr int inverse64(int p, int c) {
+  return kInverse8[p >> 2][kOrder.v[c] >> 2] * kInverse8[p & 3][kOrder.v[c] & 3];
+}
+
+namespace selfcheck {
+constexpr bool inverse64_ok() {
+  for (int c = 0; c < 16; ++c)
+    for (int sign = -1; sign <= 1; sign += 2) {
+      int32_t q[16] = {};
+      q[kOrder.v[c]] = sign * 64;
+      for (int i = 0; i < 4; ++i) zc::inverse_lift(q[i], q[4 + i], q[8 + i], q[12 + i]);
+      for (int i = 0; i < 4; ++i) zc::inverse_lift(q[4 * i], q[4 * i + 1], q[4 * i + 2], q[4 * i + 3]);
+      for (int p = 0; p < 16; ++p)
+        if (q[p] != sign * inverse64(p, c)) return false;
+    }
+  return true;
+}
+static_assert(inverse64_ok(), "the inverse transform as a matrix");
+}  // namespace selfcheck
+
+// Eight planes t = 0..7, plane 6 - 2w in the lower and 7 - 2w in the upper half of word w, to
+// eight digits of each coefficient, plane 0 the highest: byte b of word w = coefficient
+// digit_coefficient(w, b).
+ZC_DEV constexpr void planes_to_digits(uint32_t (&x)[4]) {
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {
+    const uint32_t lo = x[w], hi = x[w + 2];
+    x[w] = select_bits(0x0F0F0F0Fu, lo, hi << 4);
+    x[w + 2] = select_bits(0x0F0F0F0Fu, lo >> 4, hi);
+  }
+#pragma unroll
+  for (int w = 0; w < 4; w += 2) {
+    const uint32_t lo = x[w], hi = x[w + 1];
+    x[w] = select_bits(0x33333333u, lo, hi << 2);
+    x[w + 1] = select_bits(0x33333333u, lo >> 2, hi);
+  }
+#pragma unroll
+  for (int w = 0; w < 4; ++w)
+    x[w] = select_bits(0xAAAA0000u, x[w] << 17, select_bits(0x00005555u, x[w] >> 17, x[w]));
+}
+constexpr int digit_coefficient(int w, int b) { return 8 * (b & 1) + 2 * w + 1 - (b >> 1); }
+
+namespace selfcheck {
+constexpr bool digits_ok() {
+  uint32_t s = 0x1234567u, pattern[8] = {}, x[4] = {};
+  for (int t = 0; t < 8; ++t) { s = s * 1664525u + 1013904223u; pattern[t] = s >> 16; }
+  for (int w = 0; w < 4; ++w) x[w] = pattern[6 - 2 * w] | pattern[7 - 2 * w] << 16;
+  planes_to_digits(x);
+  for (int w = 0; w < 4; ++w)
+    for (int b = 0; b < 4; ++b)
+      for (int t = 0; t < 8; ++t)
+        if (((x[w] >> (8 * b + 7 - t)) & 1u) != ((pattern[t] >> digit_coefficient(w, b)) & 1u)) return false;
+  return true;
+}
+static_assert(digits_ok(), "digits of eight planes");
+}  // namespace selfcheck
+
+// A byte of digits d stands for (d ^ 0xAA) - 0xAA (negabinary, the lowest digit positive).
+constexpr uint32_t kDigitSigns = 0xAAAAAAAAu;
+constexpr int kDigitBias = 0xAA;
+
+// Whether the matrix covers a block, as far as that can be told from how it was read: first = the
+// pattern of its first plane, digits = 8 or 15 of them.
+ZC_DEV bool matrix_covers(uint32_t E, uint32_t lead, uint32_t first, uint32_t digits) {
+  const bool place = lead - 1u <= 25u - digits;                      // 1 .. 26 - digits
+  const bool crowded = lead < 2u && (first & (first - 1u)) != 0u;
+  return place && !crowded && E - 28u <= 221u;
+}
+// ... and by its values, which come out as value * 2^(lead - 33): 2^29 for lead <= 2.
+constexpr float kMatrixMost = 0.125f;
+
+// What these numbers are multiplied with: 2^(33 - lead), the sign of the lowest digit, and the block's
+// own scale, 2^(E - 154).
+ZC_DEV float matrix_scale(uint32_t E, uint32_t lead) {
+  return zc::bits_to_float(((E + 6u - lead) << 23) | lead << 31);
 }
 
 template <int RATE, class AnyActive, class Planes>

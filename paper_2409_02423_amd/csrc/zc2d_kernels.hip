@@ -4,8 +4,9 @@
 // stride, so that the 64 lanes of a wavefront read four contiguous 1 KiB spans (one per
 // matrix row of the block row) and write one contiguous span of 64 * 2*RATE stream bytes.
 // A block lives in registers from load to store; LDS holds the coder's look-up tables (2 KiB
-// for the encoder, 22 KiB for the decoder) and, while a block is decoded, its planes (2 KiB per
-// wavefront).  No matrix cores: nothing here is a contraction.
+// for the encoder, 22 KiB for the decoder) and, while a block is decoded, its planes (36 bytes per
+// lane).  The decoder's inverse transform is a matrix product where its halvings leave no remainder,
+// and then runs on the matrix cores (see "the decoder's values as a matrix product").
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
@@ -52,19 +53,17 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
   __syncthreads();
 }
 // Workgroups per CU in the grid.  The kernels that decode have 512 lanes per workgroup (256 for small
-// matrices, see decode_threads): 22 KiB of token table and 2 KiB per wavefront for its planes are 38
-// KiB, 40 with the encoder's table, four of which fit a CU.  decompress2d up to rate 8 (54 to 61
-// registers) then fills it; at rate 16 (69) and in the reduces (71 to 80) the registers leave room for
-// three, in the one with local values and a stream as output at rate 16 (82) for two.  (With 256 lanes
-// five fit, 20 wavefronts: decompress2d of 8192 x 32768 values at rate 4, streams from memory, 0.270
-// against 0.248 ms, the 2-way reduce 0.613 against 0.583 ms; 1024 lanes, whose 54 KiB fit twice: 0.599
-// ms for the reduce.)  Their grid, swept from 4 to 48 on 8192 x 32768 values: decompress2d at rate 8
+// matrices, see decode_threads): 22 KiB of token table, 18 KiB of planes, 1 KiB for the matrix product and 2
+// KiB for an encoder are 41 to 43 KiB, of which three fit a CU: six wavefronts per SIMD, for which 80 registers
+// are left.  The forms with the matrix product are held to that (without being told the reduces took 88,
+// four wavefronts: 0.530 against 0.496 ms for the 2-way reduce of 8192 x 32768 values at rate 4).  (256 lanes, as
+// the kernels were before: 0.270 against 0.248 ms for decompress2d, 0.613 against 0.583 ms for the reduce;
+// 1024: 0.599 ms.)  Their grid, swept from 4 to 48 on 8192 x 32768 values: decompress2d at rate 8
 // 0.296 ms at 4, 0.275 at 24, 0.280 at 48, but with rows that are aligned to their elements only (6144 x
 // 43690, fp32, rate 8) 0.365 at 4, 0.313 at 24, 0.288 at 48: there neighbouring wavefronts write to the
 // same cache lines and gain from running at the same time (at rate 4 0.308 and 0.270 ms at 24 and 48, at
 // rate 16 0.455 both; as bf16 0.238 and 0.242 ms at rate 4, 0.285 and 0.287 at rate 8).  The reduces keep
-// 24; of theirs the one with local values and fp32 output writes such rows too (one chunk at rate 8: 0.516
-// and 0.466 ms), where the streams as output make no difference (0.742 and 0.740).  Only a build with -DZC_TUNING_KNOBS lets
+// 24.  Only a build with -DZC_TUNING_KNOBS lets
 // ZC2D_WORKGROUPS_PER_CU override both; the shipped library reads no environment variable.
 constexpr int kCompressWorkgroupsPerCU = 16, kDecodeWorkgroupsPerCU = 24, kDecodeWorkgroupsPerCUUnaligned = 48;
 
@@ -76,39 +75,28 @@ struct AnyLane {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// A lane's share of its wavefront's 2 KiB of LDS for the decoded planes of its block: plane t at
-// byte 128 * t + 2 * lane.  (LDS operations of one wavefront take effect in program order.)
-constexpr int kPlaneBytes = zc2d::kPlaneEnd;
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+// A lane's sixteen decoded planes in LDS: 32 bytes on end, and a spare word between lanes so that lanes at
+// the same plane are on different banks.  Places are byte offsets within the workgroup's planes.
+constexpr int kPlaneBytes = 36;
 struct WavePlanes {
-  char* wave;   // the wavefront's LDS
-  char* mine;   // the lane's first place
-  __device__ __forceinline__ explicit WavePlanes(char* lds) {
-    wave = lds + (threadIdx.x >> 6) * kPlaneBytes;
-    mine = wave + 2 * (threadIdx.x & 63);
-  }
+  char* lds;
+  uint32_t mine;
+  __device__ __forceinline__ WavePlanes(char* planes, uint32_t tid) : lds(planes), mine(tid * kPlaneBytes) {}
+  __device__ __forceinline__ uint32_t begin() const { return mine; }
+  __device__ __forceinline__ uint32_t end() const { return mine + 16 * zc2d::kPlaneStep; }
   __device__ __forceinline__ void clear() {
-    __builtin_amdgcn_wave_barrier();
-    asm volatile("" ::: "memory");
-    if (__builtin_amdgcn_ballot_w64(true) == ~0ull) {
-      // all lanes are here: each clears 32 bytes of the wavefront's 2 KiB, whosever they are
-      u32x4* p = reinterpret_cast<u32x4*>(wave) + 2 * (threadIdx.x & 63);
-      p[0] = u32x4{0, 0, 0, 0};
-      p[1] = u32x4{0, 0, 0, 0};
-    } else {
-      // the last blocks of the matrix: a lane without one takes no part any more
+    uint32_t* p = reinterpret_cast<uint32_t*>(lds + mine);
 #pragma unroll
-      for (int t = 0; t < 16; ++t) put(zc2d::kPlaneStep * t, 0u);
-    }
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_wave_barrier();
+    for (int k = 0; k < 8; ++k) p[k] = 0u;
   }
-  __device__ __forceinline__ void put(uint32_t at, uint32_t pattern) { *reinterpret_cast<uint16_t*>(mine + at) = (uint16_t)pattern; }
-  __device__ __forceinline__ uint32_t pair(int lower, int upper) const {
+  __device__ __forceinline__ void put(uint32_t at, uint32_t pattern) {
+    asm volatile("" ::: "memory");   // (halves and words of the same memory)
+    *reinterpret_cast<uint16_t*>(lds + at) = (uint16_t)pattern;
     asm volatile("" ::: "memory");
-    const u16x2 v = {*reinterpret_cast<const uint16_t*>(mine + zc2d::kPlaneStep * lower),
-                     *reinterpret_cast<const uint16_t*>(mine + zc2d::kPlaneStep * upper)};
-    return __builtin_bit_cast(uint32_t, v);
+  }
+  __device__ __forceinline__ uint32_t word(int k) const {
+    asm volatile("" ::: "memory");   // (read where they are wanted, and not kept)
+    return *reinterpret_cast<const uint32_t*>(lds + mine + 4 * k);
   }
 };
 
@@ -281,33 +269,352 @@ __global__ __launch_bounds__(kThreads) void compress2d_kernel(const void* __rest
   }
 }
 
+// ---- the decoder's values as a matrix product ------------------------------------------
+// (See "the inverse transform as a matrix" in zc2d_codec.h.)  The wavefront's 64 blocks are four
+// groups of 16, and a group is one matrix instruction: 16 x 16 weights times 16 coefficients of 16
+// blocks.  Rows of lanes (lane / 16) and registers change places on the way in, so that lane 16*j + i
+// has the digits of four coefficients (word j of planes_to_digits) of block i of each group; of the
+// result it has row j of these blocks, four values that lie together in the matrix.  From there they
+// are stored as they are, or change places back to a block per lane.
+// (What bounds these kernels is their VALU cycles.  The lifting's way, transpose of 16 planes, xor,
+// shifts, lifting, conversions and scaling, takes about 250 instructions per block, this one about 100, 150
+// with more than eight planes.  With the loop and the planes' layout as they are now, us before and after:
+// 8192 x 32768 values, streams from memory, decompress2d at rate 4 244 and 220, at rate 8 275 and 242, 2-way
+// reduce 577 and 469, 737 and 643; 8192 x 6144 values to bf16 at rate 8 59.3 and 49.5.  For the few wavefronts of
+// a small matrix the product's latencies only add up: 1000 x 1003 values at rate 4 5.2 us to decompress
+// with it, 4.9 without, so the kernels of 256 lanes do without.)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+// What each lane puts into the product.  A byte of digits goes in as the half-precision number of the same
+// bits, digits * 2^-24 (the matrix instructions take subnormal halves as they are), and comes out
+// as value * 2^(lead - 33) with the weights 64 * weight * 2^9 for the upper eight digits of 16 and 64 *
+// weight * 2 for the lower eight.  bias: what takes the bytes' offset away, for the upper eight alone.
+struct MatrixOperands { uint32_t weight[64][4]; float bias[4][4]; };   // by lane, by lane / 16
+constexpr int kMatrixWords = sizeof(MatrixOperands) / 4;
+constexpr uint32_t half_of_weight(int w, int lg) {   // w * 2^lg, |w| <= 64
+  if (w == 0) return 0;
+  const uint32_t m = (uint32_t)(w < 0 ? -w : w);
+  int e = 0;
+  while ((m >> (e + 1)) != 0) ++e;
+  return (w < 0 ? 0x8000u : 0u) | (uint32_t)(15 + e + lg) << 10 | ((m << (10 - e)) & 0x3FFu);
+}
+constexpr MatrixOperands build_matrix_operands() {
+  MatrixOperands t{};
+  for (int l = 0; l < 64; ++l) {
+    for (int b = 0; b < 4; ++b) {
+      const int w = zc2d::inverse64(l & 15, zc2d::digit_coefficient(l >> 4, b));
+      t.weight[l][b >> 1] |= half_of_weight(w, 9) << (16 * (b & 1));
+      t.weight[l][2 + (b >> 1)] |= half_of_weight(w, 1) << (16 * (b & 1));
+    }
+  }
+  for (int p = 0; p < 16; ++p) {
+    int sum = 0;
+    for (int c = 0; c < 16; ++c) sum += zc2d::inverse64(p, c);
+    t.bias[p >> 2][p & 3] = -(float)(zc2d::kDigitBias * sum) / 32768.0f;
+  }
+  return t;
+}
+__device__ __align__(16) const MatrixOperands g_matrix = build_matrix_operands();
+
+
+// Rows of lanes and registers change places: what lane 16*j + i has in register g goes to lane 16*g + i,
+// register j.
+__device__ __forceinline__ void swap_rows(uint32_t& a0, uint32_t& a1, uint32_t& a2, uint32_t& a3) {
+  u32x2 r = __builtin_amdgcn_permlane32_swap(a0, a2, false, false);
+  a0 = r.x; a2 = r.y;
+  r = __builtin_amdgcn_permlane32_swap(a1, a3, false, false);
+  a1 = r.x; a3 = r.y;
+  r = __builtin_amdgcn_permlane16_swap(a0, a1, false, false);
+  a0 = r.x; a1 = r.y;
+  r = __builtin_amdgcn_permlane16_swap(a2, a3, false, false);
+  a2 = r.x; a3 = r.y;
+}
+
+// Values of a block per lane, row-major, from and to rows: rows[g] = row lane/16 of block lane%16 of
+// group g.
+__device__ __forceinline__ void blocks_to_rows(const float (&y)[16], f32x4 (&rows)[4]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint32_t a[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) a[r] = __float_as_uint(y[4 * r + q]);
+    swap_rows(a[0], a[1], a[2], a[3]);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) rows[g][q] = __uint_as_float(a[g]);
+  }
+}
+__device__ __forceinline__ void rows_to_blocks(const f32x4 (&rows)[4], float (&y)[16]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint32_t a[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) a[g] = __float_as_uint(rows[g][q]);
+    swap_rows(a[0], a[1], a[2], a[3]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[4 * r + q] = __uint_as_float(a[r]);
+  }
+}
+
+// The lane's number in the workgroup, anew in each pass of a loop: what is worked out from it, some dozen
+// offsets, would otherwise be kept across the passes for want of registers.
+__device__ __forceinline__ uint32_t fresh_tid() {
+  uint32_t tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  return tid;
+}
+
+// The wavefront's blocks as rows, unscaled, and each group's scale; false if some block is not covered.
+// All 64 lanes take part.
+__device__ __forceinline__ bool matrix_product(const WavePlanes& planes, uint32_t E, uint32_t lead, const uint32_t* matrix, uint32_t tid,
+                                               f32x4 (&d)[4], float (&scale)[4]) {
+  uint32_t x[4], lower[4];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    x[w] = planes.word(3 - w);
+    lower[w] = planes.word(7 - w);
+  }
+  const bool more = AnyLane()((lower[0] | lower[1] | lower[2] | lower[3]) != 0u);   // more than eight planes
+  // (the sixteenth would make the sums too long for a float)
+  if (AnyLane()(!zc2d::matrix_covers(E, lead, x[3] & 0xFFFFu, more ? 15u : 8u) || (lower[0] >> 16) != 0u)) return false;
+  zc2d::planes_to_digits(x);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) x[w] ^= zc2d::kDigitSigns;
+  swap_rows(x[0], x[1], x[2], x[3]);
+  f32x4 bias = *reinterpret_cast<const f32x4*>(matrix + 256 + ((tid & 48) >> 2));
+  if (!more) {
+    const f16x4 weight = __builtin_bit_cast(f16x4, *reinterpret_cast<const u32x2*>(matrix + 4 * (tid & 63)));
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const u32x2 v = {zc::permute_bytes(0u, x[g], 0x0c010c00u), zc::permute_bytes(0u, x[g], 0x0c030c02u)};
+      d[g] = __builtin_amdgcn_mfma_f32_16x16x16f16(weight, __builtin_bit_cast(f16x4, v), bias, 0, 0, 0);
+    }
+  } else {
+    zc2d::planes_to_digits(lower);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) lower[w] ^= zc2d::kDigitSigns;
+    swap_rows(lower[0], lower[1], lower[2], lower[3]);
+    const f16x8 weight = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(matrix + 4 * (tid & 63)));
+    bias *= 257.0f / 256.0f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const u32x4 v = {zc::permute_bytes(0u, x[g], 0x0c010c00u), zc::permute_bytes(0u, x[g], 0x0c030c02u),
+                       zc::permute_bytes(0u, lower[g], 0x0c010c00u), zc::permute_bytes(0u, lower[g], 0x0c030c02u)};
+      d[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(weight, __builtin_bit_cast(f16x8, v), bias, 0, 0, 0);
+    }
+  }
+  {
+    uint32_t s = __float_as_uint(zc2d::matrix_scale(E, lead));
+    u32x2 r = __builtin_amdgcn_permlane32_swap(s, s, false, false);
+    const u32x2 lo = __builtin_amdgcn_permlane16_swap(r.x, r.x, false, false);
+    const u32x2 hi = __builtin_amdgcn_permlane16_swap(r.y, r.y, false, false);
+    scale[0] = __uint_as_float(lo.x); scale[1] = __uint_as_float(lo.y);
+    scale[2] = __uint_as_float(hi.x); scale[3] = __uint_as_float(hi.y);
+  }
+  // values that the lifting's sums may not have room for, in blocks where they could be
+  const uint64_t early = __builtin_amdgcn_ballot_w64(lead <= 2u);
+  uint64_t bad = 0;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    float v;
+    asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(v) : "v"(d[g][0]), "v"(d[g][1]), "v"(d[g][2]));
+    asm("v_max_f32_e64 %0, %1, |%2|" : "=v"(v) : "v"(v), "v"(d[g][3]));
+    const uint64_t group = (early >> (16 * g)) & 0xFFFFu;
+    bad |= __builtin_amdgcn_ballot_w64(v >= zc2d::kMatrixMost) & (group | group << 16 | group << 32 | group << 48);
+  }
+  return bad == 0;
+}
+
+// ---- the kernels that decode ----------------------------------------------------------
+// A wavefront takes 64 consecutive blocks at a time, and all of its lanes stay together: lanes past the
+// last block decode an empty one and store nothing.
+// Whether a difference of two sizes is negative, from its upper half and on the scalar side (there are no
+// scalar comparisons of 64 bits, and the vector ones would draw the cursor into vector registers).
+__device__ __forceinline__ bool negative(size_t difference) {
+  return __builtin_amdgcn_readfirstlane((int)(difference >> 32)) < 0;
+}
+
+struct WaveCursor {
+  size_t b, bi, bj;   // the first of the 64 blocks, its block row and block column
+  size_t first;       // index of its first value
+  __device__ __forceinline__ void start(const Walk& w, size_t b0) {
+    const size_t row = b0 / w.bc;   // (worked out in vector registers)
+    b = b0;
+    bi = (size_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(row >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)row);
+    bj = b0 - bi * w.bc;
+    first = 4 * bi * w.cols + 4 * bj;
+  }
+  __device__ __forceinline__ void advance(const Walk& w) {
+    b += w.stride;
+    bi += w.step_bi;
+    bj += w.step_bj;
+    first += 4 * (w.step_bi * w.cols + w.step_bj);
+    const size_t past = bj - w.bc;
+    if (!negative(past)) {
+      bj = past;
+      bi += 1;
+      first += 4 * w.cols - 4 * w.bc;
+    }
+  }
+  // how many of the 64 there are
+  __device__ __forceinline__ uint32_t count(const Walk& w) const { return negative(w.blocks - b - 64) ? (uint32_t)(w.blocks - b) : 64u; }
+  __device__ __forceinline__ bool inside(const Walk& w) const { return negative(b - w.blocks); }
+  // all 64 in one block row and whole
+  __device__ __forceinline__ bool whole(const Walk& w) const { return negative(bi - w.whole_br) && !negative(w.whole_bc - bj - 64); }
+  // the lane's own block
+  __device__ __forceinline__ Cursor lane(const Walk& w, uint32_t tid) const {
+    Cursor c;
+    const size_t l = tid & 63;
+    c.b = b + l;
+    c.bi = bi;
+    c.bj = bj + l;
+    c.first = first + 4 * l;
+    while (c.bj >= w.bc) {
+      c.bj -= w.bc;
+      c.bi += 1;
+      c.first += 4 * w.cols - 4 * w.bc;
+    }
+    return c;
+  }
+  // where the lane's four values of group 0 are if the wavefront's blocks are whole; group g is 64*g values on
+  __device__ __forceinline__ size_t row(const Walk& w, uint32_t tid) const {
+    const size_t l = tid & 63;
+    return first + (l >> 4) * w.cols + 4 * (l & 15);
+  }
+};
+
+// The wavefront's first block (the same in all its lanes).
+template <int THREADS>
+__device__ __forceinline__ size_t first_block() {
+  return (size_t)blockIdx.x * THREADS + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u));
+}
+
+// The words of the lane's block, or of an empty one past the end.  (The wavefront's place is added up on the
+// scalar side, the lane's is an offset.)
+template <int RATE>
+__device__ __forceinline__ void load_block_words(const uint8_t* in, const WaveCursor& cur, const Walk& w, uint32_t tid,
+                                                 uint32_t (&W)[zc2d::Traits<RATE>::kWords]) {
+#pragma unroll
+  for (int i = 0; i < zc2d::Traits<RATE>::kWords; ++i) W[i] = 0u;
+  const uint8_t* p = in + cur.b * zc2d::Traits<RATE>::kBlockBytes;
+  const uint32_t lane = tid & 63u;
+  if (lane < cur.count(w)) load_words<zc2d::Traits<RATE>::kWords>(p + lane * zc2d::Traits<RATE>::kBlockBytes, W);
+}
+
+template <int DT>
+__device__ __forceinline__ void store_row(void* out, size_t at, const f32x4& y) {
+  if constexpr (DT == kF32) {
+    const Row32 v = {__float_as_uint(y[0]), __float_as_uint(y[1]), __float_as_uint(y[2]), __float_as_uint(y[3])};
+    __builtin_nontemporal_store(v, reinterpret_cast<Row32*>(static_cast<float*>(out) + at));
+  } else {
+    const Row16 v = {narrow_half<DT>(y[0]) | narrow_half<DT>(y[1]) << 16, narrow_half<DT>(y[2]) | narrow_half<DT>(y[3]) << 16};
+    __builtin_nontemporal_store(v, reinterpret_cast<Row16*>(static_cast<uint16_t*>(out) + at));
+  }
+}
+
+// Stores the wavefront's blocks, given as rows.  (fp32 rows aligned to their elements only go from a block
+// per lane, 1 KiB of a row at a time: four pieces of 256 bytes that share cache lines with their neighbours
+// took 0.312 instead of 0.281 ms, 6144 x 43690 values at rate 4; of half-precision rows the pieces are better, 40 against
+// 44 us for 8192 x 6145 values.)
+template <int DT>
+__device__ __forceinline__ void store_rows(void* out, const Walk& w, const WaveCursor& cur, uint32_t tid, const f32x4 (&rows)[4]) {
+  if (cur.whole(w) && (DT != kF32 || (w.cols & 3) == 0)) {
+    const size_t at = cur.row(w, tid);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) store_row<DT>(out, at + 64 * g, rows[g]);
+  } else {
+    float y[16];
+    rows_to_blocks(rows, y);
+    if ((tid & 63) < cur.count(w)) store_block<DT>(out, w, cur.lane(w, tid), y);
+  }
+}
+
+// sum += the wavefront's blocks, as rows, that the lanes' windows W hold (or = for the first).
+// Up to rate 8 nearly all blocks are covered by the matrix; at rate 16 they have too many planes, and
+// only the lifting's way is there.  Told by the rate and by the width of the workgroups (see as_matrix).
+template <int RATE>
+__device__ __forceinline__ void add_blocks(uint32_t (&W)[zc2d::Traits<RATE>::kWords], const uint32_t* token, WavePlanes& planes,
+                                           const uint32_t* matrix, uint32_t tid, bool first, f32x4 (&sum)[4]) {
+  auto b = zc2d::read_block<RATE>(W, token, AnyLane(), planes);
+  f32x4 d[4];
+  float scale[4];
+  if (AnyLane()(b.r.left > 0) || !matrix_product(planes, b.E, b.lead, matrix, tid, d, scale)) {
+    int32_t q[16];
+    float y[16];
+    zc2d::finish_block<RATE>(b, token, q, AnyLane(), planes);
+    zc2d::scale_block(q, b.E, y);
+    blocks_to_rows(y, d);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      scale[g] = 1.0f;
+      if (first) sum[g] = f32x4{-0.0f, -0.0f, -0.0f, -0.0f};   // (what keeps the sign of a zero)
+    }
+  }
+  // (onto + 0 the product of a zero and a negative scale is + 0, as the lifting has it)
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum[g][q] = __builtin_fmaf(d[g][q], scale[g], sum[g][q]);
+}
+constexpr bool as_matrix(int rate, int threads) { return rate <= 8 && threads == kDecodeThreads; }
+
 template <int RATE, int DT, int THREADS>
 __global__ __launch_bounds__(THREADS) void decompress2d_kernel(const uint8_t* __restrict__ in, Walk w, void* __restrict__ out) {
   __shared__ __attribute__((aligned(16))) uint32_t token[zc2d::kTokenRows << zc2d::kLookahead];
-  __shared__ __attribute__((aligned(16))) char plane_lds[THREADS / 64 * kPlaneBytes];
-  WavePlanes planes(plane_lds);
+  __shared__ __attribute__((aligned(16))) char plane_lds[THREADS * kPlaneBytes];
+  __shared__ __attribute__((aligned(16))) uint32_t matrix[as_matrix(RATE, THREADS) ? kMatrixWords : 4];
+  if (as_matrix(RATE, THREADS) && threadIdx.x < kMatrixWords / 4)
+    reinterpret_cast<uint4*>(matrix)[threadIdx.x] = reinterpret_cast<const uint4*>(&g_matrix)[threadIdx.x];
   stage_table<(zc2d::kTokenRows << zc2d::kLookahead), THREADS>(g_token.v, token);
   constexpr int NW = zc2d::Traits<RATE>::kWords;
-  const size_t b0 = (size_t)blockIdx.x * THREADS + threadIdx.x;
-  if (b0 >= w.blocks) return;
-  Cursor cur;
-  cur.start(w, b0);
-  uint32_t W[NW];
-  load_words<NW>(in + cur.b * zc2d::Traits<RATE>::kBlockBytes, W);
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), for the same reason as in the compress kernel
-  for (;;) {
-    Cursor next = cur;
-    next.advance(w);
-    const bool more = next.b < w.blocks;
-    uint32_t Wn[NW];
-    if (more) load_words<NW>(in + next.b * zc2d::Traits<RATE>::kBlockBytes, Wn);   // the next block's stream, ahead of time
-    float y[16];
-    zc2d::decode_block<RATE>(W, token, y, AnyLane(), planes);
-    store_block<DT>(out, w, cur, y);
-    if (!more) break;
+  if constexpr (as_matrix(RATE, THREADS)) {
+    const uint32_t tid = threadIdx.x;
+    WavePlanes planes(plane_lds, tid);
+    WaveCursor cur;
+    const size_t b0 = first_block<THREADS>();
+    if (b0 >= w.blocks) return;
+    cur.start(w, b0);
+    uint32_t W[NW];
+    load_block_words<RATE>(in, cur, w, tid, W);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), for the same reason as in the compress kernel
+    for (;;) {
+      WaveCursor next = cur;
+      next.advance(w);
+      const bool more = next.inside(w);
+      uint32_t Wn[NW];
+      if (more) load_block_words<RATE>(in, next, w, tid, Wn);   // the next blocks' stream, ahead of time
+      f32x4 y[4] = {};
+      add_blocks<RATE>(W, token, planes, matrix, tid, true, y);
+      store_rows<DT>(out, w, cur, tid, y);
+      if (!more) break;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) W[i] = Wn[i];
-    cur = next;
+      for (int i = 0; i < NW; ++i) W[i] = Wn[i];
+      cur = next;
+    }
+  } else {
+    const size_t b0 = (size_t)blockIdx.x * THREADS + threadIdx.x;
+    if (b0 >= w.blocks) return;
+    WavePlanes planes(plane_lds, threadIdx.x);
+    Cursor cur;
+    cur.start(w, b0);
+    uint32_t W[NW];
+    load_words<NW>(in + cur.b * zc2d::Traits<RATE>::kBlockBytes, W);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), for the same reason as in the compress kernel
+    for (;;) {
+      Cursor next = cur;
+      next.advance(w);
+      const bool more = next.b < w.blocks;
+      uint32_t Wn[NW];
+      if (more) load_words<NW>(in + next.b * zc2d::Traits<RATE>::kBlockBytes, Wn);   // the next block's stream, ahead of time
+      float y[16];
+      zc2d::decode_block<RATE>(W, token, y, AnyLane(), planes);
+      store_block<DT>(out, w, cur, y);
+      if (!more) break;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) W[i] = Wn[i];
+      cur = next;
+    }
   }
 }
 
@@ -315,94 +622,141 @@ struct ChunkPointers2d {
   const uint8_t* p[16];
 };
 
+// What is encoded of a lane's block: where it sticks out of the matrix its fill is taken from the sum's
+// last valid row / column.
+__device__ __forceinline__ void fill_block(const Walk& w, const Cursor& cur, const float (&sum)[16], uint32_t (&x)[16]) {
+  if (cur.whole(w)) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = __float_as_uint(sum[i]);
+  } else {
+    const uint32_t rv = (uint32_t)(w.rows - 4 * cur.bi < 4 ? w.rows - 4 * cur.bi : 4);
+    const uint32_t cv = (uint32_t)(w.cols - 4 * cur.bj < 4 ? w.cols - 4 * cur.bj : 4);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        // value at (min(r, rv-1), min(q, cv-1)), picked without indexing registers by a variable
+        float v = sum[0];
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+          for (int qq = 0; qq < 4; ++qq) {
+            const bool pick = (uint32_t)rr == ((uint32_t)r < rv ? (uint32_t)r : rv - 1) &&
+                              (uint32_t)qq == ((uint32_t)q < cv ? (uint32_t)q : cv - 1);
+            v = pick ? sum[4 * rr + qq] : v;
+          }
+        x[4 * r + q] = __float_as_uint(v);
+      }
+  }
+}
+
 // The reduce-scatter step on matrix-shaped messages: block b of the k chunks is decoded,
 // the 16 values are added in registers in chunk order, and the sum is encoded; where the
 // block sticks out of the matrix its fill is taken from the sum's last valid row / column.
 // LOCAL: a raw fp32 matrix is added last (a ring hop's own contribution); RAW_OUT: the sum
 // is stored as an fp32 matrix instead of being encoded (the last hop).
-// (All forms but one have six wavefronts per SIMD or seven.  That the plain form at the low rates is
-// told to stay within six changes a few instructions: 576 instead of 581 us for 8192 x 32768 values at
-// rate 4.)
+// (Where local values are added the lifting's way is kept: a block per lane is what they are added to, and
+// the matrix product, the rows' way back and the local values together took 88 registers and four
+// wavefronts per SIMD: 23.8 against 22.4 us for one chunk and fp32 output, 2048 x 6144 values at rate 4.)
 template <int RATE, bool LOCAL, bool RAW_OUT, int THREADS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(RATE <= 4 && !LOCAL && !RAW_OUT ? 6 : 1)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(as_matrix(RATE, THREADS) && !LOCAL ? 6 : 1)))
 void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, uint8_t* out, float* out_raw) {
+  constexpr bool kMatrix = as_matrix(RATE, THREADS) && !LOCAL;
   __shared__ __attribute__((aligned(16))) uint32_t expand[zc2d::kExpandEntries];
   __shared__ __attribute__((aligned(16))) uint32_t token[zc2d::kTokenRows << zc2d::kLookahead];
-  __shared__ __attribute__((aligned(16))) char plane_lds[THREADS / 64 * kPlaneBytes];
-  WavePlanes planes(plane_lds);
+  __shared__ __attribute__((aligned(16))) char plane_lds[THREADS * kPlaneBytes];
+  __shared__ __attribute__((aligned(16))) uint32_t matrix[kMatrix ? kMatrixWords : 4];
+  if (kMatrix && threadIdx.x < kMatrixWords / 4)
+    reinterpret_cast<uint4*>(matrix)[threadIdx.x] = reinterpret_cast<const uint4*>(&g_matrix)[threadIdx.x];
   for (int i = threadIdx.x; i < zc2d::kExpandEntries / 4; i += THREADS)
     reinterpret_cast<uint4*>(expand)[i] = reinterpret_cast<const uint4*>(g_expand.v)[i];
-  stage_table<(zc2d::kTokenRows << zc2d::kLookahead), THREADS>(g_token.v, token);   // (its barrier covers both tables)
+  stage_table<(zc2d::kTokenRows << zc2d::kLookahead), THREADS>(g_token.v, token);   // (its barrier covers all tables)
   constexpr int NW = zc2d::Traits<RATE>::kWords;
-  const size_t b0 = (size_t)blockIdx.x * THREADS + threadIdx.x;
-  if (b0 >= w.blocks) return;
-  Cursor cur;
-  cur.start(w, b0);
-  for (;;) {
-    const size_t at = cur.b * zc2d::Traits<RATE>::kBlockBytes;
-    float sum[16];
+  if constexpr (kMatrix) {
+    WaveCursor cur;
+    const size_t b0 = first_block<THREADS>();
+    if (b0 >= w.blocks) return;
+    cur.start(w, b0);
+    for (;;) {
+      f32x4 rows[4] = {};
 #pragma unroll 1
-    for (int j = 0; j < k; ++j) {   // (the first chunk in the same loop: the decoder is a few hundred instructions long, one copy of it is enough)
-      uint32_t W[NW];
-      int32_t q[16];
-      load_words<NW>(chunks.p[j] + at, W);
-      const uint32_t E = zc2d::decode_block_fixed<RATE>(W, token, q, AnyLane(), planes);
-      // scale and add in one fused step, unless some lane's exponent byte is one where the
-      // scaling may round or overflow (tiny or huge blocks, arbitrary bytes)
-      if (j == 0) {
-        zc2d::scale_block(q, E, sum);
-      } else if (AnyLane()(!zc2d::scaling_is_exact(E))) {
-        float y[16];
-        zc2d::scale_block(q, E, y);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sum[i] += y[i];
-      } else {
-        zc2d::accumulate_scaled(q, E, sum);
+      for (int j = 0; j < k; ++j) {   // (one copy of the decoder, a few hundred instructions, is enough)
+        const uint32_t tid = fresh_tid();
+        WavePlanes planes(plane_lds, tid);
+        uint32_t W[NW];
+        load_block_words<RATE>(chunks.p[j], cur, w, tid, W);
+        add_blocks<RATE>(W, token, planes, matrix, tid, j == 0, rows);
       }
-    }
-    if constexpr (LOCAL) {
-      // (where the block sticks out of the matrix the clamped loads add copies of edge values;
-      // those positions are refilled from the sum or dropped below)
-      uint32_t mine[16];
-      load_block<kF32>(local, w, cur, mine);
+      const uint32_t tid = fresh_tid();
+      if constexpr (RAW_OUT) {
+        store_rows<kF32>(out_raw, w, cur, tid, rows);
+      } else {
+        float sum[16];
+        rows_to_blocks(rows, sum);
+        uint32_t x[16], W[NW];
+        if (cur.whole(w)) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sum[i] += __uint_as_float(mine[i]);
+          for (int i = 0; i < 16; ++i) x[i] = __float_as_uint(sum[i]);
+        } else {
+          fill_block(w, cur.lane(w, tid), sum, x);
+        }
+        zc2d::encode_block<RATE>(x, expand, W, AnyLane());
+        uint8_t* p = out + cur.b * zc2d::Traits<RATE>::kBlockBytes;
+        if ((tid & 63u) < cur.count(w)) store_words<NW>(p + (tid & 63u) * zc2d::Traits<RATE>::kBlockBytes, W);
+      }
+      cur.advance(w);
+      if (!cur.inside(w)) break;
     }
-    if constexpr (RAW_OUT) {
-      store_block<kF32>(out_raw, w, cur, sum);
+  } else {
+    WavePlanes planes(plane_lds, threadIdx.x);
+    const size_t b0 = (size_t)blockIdx.x * THREADS + threadIdx.x;
+    if (b0 >= w.blocks) return;
+    Cursor cur;
+    cur.start(w, b0);
+    for (;;) {
+      const size_t at = cur.b * zc2d::Traits<RATE>::kBlockBytes;
+      float sum[16];
+#pragma unroll 1
+      for (int j = 0; j < k; ++j) {   // (the first chunk in the same loop: the decoder is a few hundred instructions long, one copy of it is enough)
+        uint32_t W[NW];
+        int32_t q[16];
+        load_words<NW>(chunks.p[j] + at, W);
+        const uint32_t E = zc2d::decode_block_fixed<RATE>(W, token, q, AnyLane(), planes);
+        // scale and add in one fused step, unless some lane's exponent byte is one where the
+        // scaling may round or overflow (tiny or huge blocks, arbitrary bytes)
+        if (j == 0) {
+          zc2d::scale_block(q, E, sum);
+        } else if (AnyLane()(!zc2d::scaling_is_exact(E))) {
+          float y[16];
+          zc2d::scale_block(q, E, y);
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sum[i] += y[i];
+        } else {
+          zc2d::accumulate_scaled(q, E, sum);
+        }
+      }
+      if constexpr (LOCAL) {
+        // (where the block sticks out of the matrix the clamped loads add copies of edge values;
+        // those positions are refilled from the sum or dropped below)
+        uint32_t mine[16];
+        load_block<kF32>(local, w, cur, mine);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum[i] += __uint_as_float(mine[i]);
+      }
+      if constexpr (RAW_OUT) {
+        store_block<kF32>(out_raw, w, cur, sum);
+        cur.advance(w);
+        if (cur.b >= w.blocks) break;
+        continue;
+      }
+      uint32_t x[16];
+      fill_block(w, cur, sum, x);
+      uint32_t W[NW];
+      zc2d::encode_block<RATE>(x, expand, W, AnyLane());
+      store_words<NW>(out + at, W);
       cur.advance(w);
       if (cur.b >= w.blocks) break;
-      continue;
     }
-    uint32_t x[16];
-    if (cur.whole(w)) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) x[i] = __float_as_uint(sum[i]);
-    } else {
-      const uint32_t rv = (uint32_t)(w.rows - 4 * cur.bi < 4 ? w.rows - 4 * cur.bi : 4);
-      const uint32_t cv = (uint32_t)(w.cols - 4 * cur.bj < 4 ? w.cols - 4 * cur.bj : 4);
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          // value at (min(r, rv-1), min(q, cv-1)), picked without indexing registers by a variable
-          float v = sum[0];
-#pragma unroll
-          for (int rr = 0; rr < 4; ++rr)
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-              const bool pick = (uint32_t)rr == ((uint32_t)r < rv ? (uint32_t)r : rv - 1) &&
-                                (uint32_t)qq == ((uint32_t)q < cv ? (uint32_t)q : cv - 1);
-              v = pick ? sum[4 * rr + qq] : v;
-            }
-          x[4 * r + q] = __float_as_uint(v);
-        }
-    }
-    uint32_t W[NW];
-    zc2d::encode_block<RATE>(x, expand, W, AnyLane());
-    store_words<NW>(out + at, W);
-    cur.advance(w);
-    if (cur.b >= w.blocks) break;
   }
 }
 

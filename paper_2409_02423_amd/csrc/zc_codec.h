@@ -97,6 +97,16 @@ ZC_DEV uint32_t count_leading_zeros_nonzero(uint32_t x) {
 #endif
 }
 ZC_DEV uint32_t count_trailing_zeros(uint32_t x) { return x ? (uint32_t)__builtin_ctz(x) : 32u; }
+// The same for x != 0; for x = 0 some value.
+ZC_DEV uint32_t count_trailing_zeros_nonzero(uint32_t x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  uint32_t r;
+  asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(x));
+  return r;
+#else
+  return x ? (uint32_t)__builtin_ctz(x) : 0xFFFFFFFFu;
+#endif
+}
 ZC_DEV uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
 ZC_DEV uint32_t umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
 ZC_DEV float bits_to_float(uint32_t b) { return __builtin_bit_cast(float, b); }

@@ -106,6 +106,54 @@ extern "C" int zc2d_host_wave(int rate, int encode, const void* in, size_t block
   return 0;
 }
 
+// The matrix form of the decoder on one block, its products summed in whole numbers: false if the block
+// is not covered.
+namespace {
+template <int RATE>
+bool dec_matrix(const uint8_t* in, float* x) {
+  uint32_t W[zc2d::Traits<RATE>::kWords];
+  std::memcpy(W, in, zc2d::Traits<RATE>::kBlockBytes);
+  zc2d::LocalPlanes planes;
+  auto b = zc2d::read_block<RATE>(W, kToken.v, always, planes);
+  uint32_t upper[4], lower[4];
+  for (int w = 0; w < 4; ++w) {
+    upper[w] = planes.word(3 - w);
+    lower[w] = planes.word(7 - w);
+  }
+  const bool more = (lower[0] | lower[1] | lower[2] | lower[3]) != 0;
+  if (b.r.left > 0 || (lower[0] >> 16) != 0) return false;
+  if (!zc2d::matrix_covers(b.E, b.lead, upper[3] & 0xFFFFu, more ? 15u : 8u)) return false;
+  zc2d::planes_to_digits(upper);
+  zc2d::planes_to_digits(lower);
+  int64_t n[16];
+  for (int w = 0; w < 4; ++w)
+    for (int c = 0; c < 4; ++c) {
+      auto digits = [&](uint32_t word) { return (int64_t)(((word ^ zc2d::kDigitSigns) >> (8 * c)) & 0xFFu) - zc2d::kDigitBias; };
+      n[zc2d::digit_coefficient(w, c)] = 256 * digits(upper[w]) + digits(lower[w]);
+    }
+  const float scale = zc2d::matrix_scale(b.E, b.lead);
+  for (int p = 0; p < 16; ++p) {
+    int64_t sum = 0;
+    for (int c = 0; c < 16; ++c) sum += zc2d::inverse64(p, c) * n[c];
+    const float v = (float)sum / 8388608.0f;
+    if (sum != (int64_t)(v * 8388608.0f)) return false;   // (a sum that a float does not hold)
+    if (b.lead <= 2u && (v < 0 ? -v : v) >= zc2d::kMatrixMost) return false;
+    x[p] = __builtin_fmaf(v, scale, 0.0f);
+  }
+  return true;
+}
+}  // namespace
+
+extern "C" int zc2d_host_decode_by_matrix(int rate, const uint8_t* in, size_t blocks, float* x, uint8_t* covered) {
+  for (size_t j = 0; j < blocks; ++j) switch (rate) {
+      case 2: covered[j] = dec_matrix<2>(in + j * 4, x + 16 * j); break;
+      case 4: covered[j] = dec_matrix<4>(in + j * 8, x + 16 * j); break;
+      case 8: covered[j] = dec_matrix<8>(in + j * 16, x + 16 * j); break;
+      default: return -2;
+    }
+  return 0;
+}
+
 extern "C" int zc2d_host_encode_blocks(int rate, const float* x, size_t blocks, uint8_t* out) {
   for (size_t j = 0; j < blocks; ++j) switch (rate) {
       case 2: enc<2>(x + 16 * j, out + j * 4); break;

@@ -420,3 +420,43 @@ def test_both_widths_of_the_decoding_kernels(gpu, ref, rows, cols):
             # the narrowing is torch's: round to nearest even
             half = gpu.zc2d_decompress_half(_dev(s), rows, cols, rate, dtype)
             assert torch.equal(half.view(torch.int16), back.to(dtype).view(torch.int16)), dtype
+
+
+@pytest.mark.parametrize("rate", (2, 4, 8))
+@pytest.mark.parametrize("cols", (2052, 2050))
+def test_matrix_and_lifting_forms_of_the_decoder(gpu, ref, rate, cols):
+    """Matrices of 131328 blocks, whose wavefronts decode by a matrix product or, where a block is not
+    covered by it, by lifting: wavefronts of arbitrary blocks with at least 0, 1, 2 and 3 empty planes
+    (where sums wrap or not), with few and many planes (8, 15, 16 and more), sparse and dense, with
+    exponent bytes inside and outside the product's range, and zero blocks among them."""
+    rng = np.random.default_rng(rate + cols)
+    rows = 1024
+    blocks = (rows // 4) * ((cols + 3) // 4)
+    streams = []
+    for part in range(2):
+        wave = np.arange(blocks) // 64
+        least = rng.integers(0, 8, size=wave.max() + 1)[wave]
+        lead = np.minimum(least, 3) + rng.geometric(0.4, size=blocks) - 1
+        many = rng.random(blocks) < 0.02 * (rng.random(wave.max() + 1) < 0.2)[wave]
+        lead = np.where(many, rng.integers(3, 16 * rate, size=blocks), lead)
+        bits = rng.integers(0, 2, size=(blocks, 16 * rate - 8), dtype=np.uint8)
+        for thinned in (rng.random(wave.max() + 1)[wave] < 0.8, rng.random(blocks) < 0.7, rng.random(blocks) < 0.4):
+            bits[thinned] &= rng.integers(0, 2, size=(int(thinned.sum()), bits.shape[1]), dtype=np.uint8)
+        at = np.arange(bits.shape[1])[None, :]
+        bits[at < lead[:, None]] = 0
+        bits[at == lead[:, None]] = 1
+        s = np.zeros((blocks, 2 * rate), dtype=np.uint8)
+        s[:, 1:] = np.packbits(bits, axis=1, bitorder="little")
+        odd = (rng.random(wave.max() + 1) < 0.2)[wave] & (rng.random(blocks) < 0.05)
+        s[:, 0] = np.where(odd, rng.choice([0, 1, 27, 28, 249, 250], size=blocks), rng.integers(100, 130, size=blocks))
+        s[rng.random(blocks) < 0.01] = 0
+        streams.append(s.reshape(-1))
+    print("matrix and lifting", rate, cols, flush=True)
+    with np.errstate(all="ignore"):
+        want = ref.decompress(streams[0], rows, cols, rate)
+        both = ref.reduce_decompress(streams, None, rows, cols, rate)
+        coded = ref.reduce_compressed(streams, rows, cols, rate)
+    a, b = _dev(streams[0]), _dev(streams[1])
+    _same_floats(_host(gpu.zc2d_decompress(a, rows, cols, rate)), want, "decompress")
+    _same_floats(_host(gpu.zc2d_reduce_decompress([a, b], None, rows, cols, rate)), both, "reduce_decompress")
+    _same_bytes(_host(gpu.zc2d_reduce_compressed([a, b], rows, cols, rate)), coded, rate, "reduce")

@@ -96,3 +96,55 @@ def test_lockstep_lanes_match_reference(o2, shim, rate):
             assert shim.zc2d_host_wave(rate, 0, stream.ctypes.data, len(stream), gotd.ctypes.data, lanes) == 0
             bad = np.flatnonzero((gotd.view(np.uint32) != expect.view(np.uint32)).any(axis=1))
             assert bad.size == 0, (rate, lanes, bad[:5])
+
+
+def _blocks_with_lead(rng, rate, blocks, lead):
+    """Arbitrary blocks of `lead` empty planes, dense and sparse ones (which have more planes), under exponent
+    bytes of every kind."""
+    bits = rng.integers(0, 2, size=(blocks, 16 * rate - 8), dtype=np.uint8)
+    for k in range(3):
+        bits[k::4] &= rng.integers(0, 2, size=bits[k::4].shape, dtype=np.uint8)
+        bits[:blocks // 2] &= rng.integers(0, 2, size=bits[:blocks // 2].shape, dtype=np.uint8)
+    bits[:, :lead] = 0
+    bits[:, lead] = 1
+    s = np.zeros((blocks, 2 * rate), dtype=np.uint8)
+    s[:, 1:] = np.packbits(bits, axis=1, bitorder="little")
+    s[:, 0] = np.where(rng.random(blocks) < 0.1, rng.choice([0, 1, 27, 28, 249, 250, 251, 255], size=blocks),
+                       rng.integers(28, 250, size=blocks))
+    return s
+
+
+@pytest.mark.parametrize("rate", (2, 4, 8))
+def test_matrix_form_matches_reference_where_it_covers(o2, shim, rate):
+    """The decoder's inverse transform as a matrix product, against the reference decoder, on every block
+    that it says it covers: the encoder's own blocks (of which it covers nearly all) and arbitrary ones
+    by the number of empty planes, where sums of the lifting may wrap (few empty planes) or halve with a
+    remainder (many)."""
+    shim.zc2d_host_decode_by_matrix.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_void_p]
+    rng = np.random.default_rng(rate)
+
+    def covered(s, what):
+        n = len(s)
+        rows = np.ascontiguousarray(s)
+        got, mask = np.zeros((n, 16), dtype=np.float32), np.zeros(n, dtype=np.uint8)
+        assert shim.zc2d_host_decode_by_matrix(rate, rows.ctypes.data, n, got.ctypes.data, mask.ctypes.data) == 0
+        with np.errstate(all="ignore"):
+            want = o2.decompress(rows.reshape(-1), 4, 4 * n, rate).reshape(4, n, 4).transpose(1, 0, 2).reshape(n, 16)
+        bad = np.flatnonzero((got.view(np.uint32) != want.view(np.uint32)).any(axis=1) & (mask != 0))
+        assert bad.size == 0, (what, bad[:5], rows[bad[:1]], got[bad[:1]], want[bad[:1]])
+        return mask.mean()
+
+    x = _blocks()
+    covered(np.stack([o2.encode_block(b, rate) for b in x]), "encoder's blocks")
+    smooth = workloads.gradient_lowrank(256, 1024).reshape(256, 1024)
+    for name, m in (("lowrank", smooth), ("iid", workloads.gradient_iid(256 * 1024).reshape(256, 1024))):
+        share = covered(o2.compress(m, rate).reshape(-1, 2 * rate), name)
+        assert share > (0.995 if rate > 2 else 0.98), (name, share)
+    # the matrix ends where its rule says: shares of arbitrary blocks covered, by empty planes
+    shares = {}
+    for lead in range(24):
+        s = _blocks_with_lead(rng, rate, 4000, lead)
+        covered(s, lead)
+        shares[lead] = covered(s[s[:, 0] != 0], lead)
+    assert shares[0] == 0 and 0 < shares[1] < shares[3] and shares[3] > 0.8, shares
+    assert all(shares[lead] == 0 for lead in shares if lead > 18), shares
