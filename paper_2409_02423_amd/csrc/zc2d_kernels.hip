@@ -58,14 +58,20 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
 // are left.  The forms with the matrix product are held to that (without being told the reduces took 88,
 // four wavefronts: 0.530 against 0.496 ms for the 2-way reduce of 8192 x 32768 values at rate 4).  (256 lanes, as
 // the kernels were before: 0.270 against 0.248 ms for decompress2d, 0.613 against 0.583 ms for the reduce;
-// 1024: 0.599 ms.)  Their grid, swept from 4 to 48 on 8192 x 32768 values: decompress2d at rate 8
-// 0.296 ms at 4, 0.275 at 24, 0.280 at 48, but with rows that are aligned to their elements only (6144 x
-// 43690, fp32, rate 8) 0.365 at 4, 0.313 at 24, 0.288 at 48: there neighbouring wavefronts write to the
-// same cache lines and gain from running at the same time (at rate 4 0.308 and 0.270 ms at 24 and 48, at
-// rate 16 0.455 both; as bf16 0.238 and 0.242 ms at rate 4, 0.285 and 0.287 at rate 8).  The reduces keep
-// 24.  Only a build with -DZC_TUNING_KNOBS lets
-// ZC2D_WORKGROUPS_PER_CU override both; the shipped library reads no environment variable.
-constexpr int kCompressWorkgroupsPerCU = 16, kDecodeWorkgroupsPerCU = 24, kDecodeWorkgroupsPerCUUnaligned = 48;
+// 1024: 0.599 ms.)
+// Their grid, us of 8192 x 32768 values at rate 4: decompress2d 234, 222 and 222 at 16, 24 and 32, the 2-way reduce
+// with fp32 output 384, 357, 362 and 386 at 24, 48, 64 and 96.  With rows that are aligned to their
+// elements only, decompress2d gains from more: neighbouring wavefronts write to the same cache lines and
+// should do so at the same time (6144 x 43690 values at rate 4: 279 at 48, 250 at 64; at rate 8 274 and 277).  The
+// reduce with local values and fp32 output is like it (522 at 24, 457 at 64).  The reduces that write streams
+// keep 24: 469 at 16, 24 and 32.
+// The compress kernel has 16, and 64 where that leaves a lane four blocks or more: with one block per lane a
+// workgroup stages its table and asks for its values for nothing else (8192 x 32768 values at rate 4: 238 at 16, 224 at
+// 64, 229 at 128; 8192 x 8192 at rate 2: 48.9 at 16, four blocks per lane, 55.8 at 64, one block; 6144 x 43690 at rate 8
+// 296 and 265).
+// Only a build with -DZC_TUNING_KNOBS lets ZC2D_WORKGROUPS_PER_CU override these; the shipped library reads
+// no environment variable.
+constexpr int kCompressWorkgroupsPerCU = 16, kCompressWorkgroupsPerCUMost = 64, kDecodeWorkgroupsPerCU = 24, kDecodeWorkgroupsPerCUWide = 64;
 
 // The wavefront-wide vote of the codec: whether p holds in some lane.
 struct AnyLane {
@@ -830,7 +836,10 @@ int launch_compress2d(const void* d_in, size_t rows, size_t cols, int rate, void
   if (out_cap < zc2d_compressed_size(rows, cols, rate)) return ZC_ERR_CAPACITY;
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const unsigned grid = grid_for(blocks, kCompressWorkgroupsPerCU, kThreads, compute_units());
+  const int cus = compute_units();
+  const unsigned few = grid_for(blocks, kCompressWorkgroupsPerCU, kThreads, cus);
+  const unsigned many = grid_for(blocks / 4, kCompressWorkgroupsPerCUMost, kThreads, cus);   // four blocks per lane
+  const unsigned grid = few > many ? few : many;
   const Walk w = walk_for(rows, cols, grid, kThreads);
 #define CALL(R) hipLaunchKernelGGL((compress2d_kernel<R, DT>), dim3(grid), dim3(kThreads), 0, s, d_in, w, static_cast<uint8_t*>(d_out))
   ZC2D_DISPATCH_RATE(rate, CALL)
@@ -848,7 +857,7 @@ int launch_decompress2d(const void* d_in, size_t rows, size_t cols, int rate, vo
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int cus = compute_units(), threads = decode_threads(blocks, cus);
-  const unsigned grid = grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUUnaligned : kDecodeWorkgroupsPerCU, threads, cus);
+  const unsigned grid = grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
   const Walk w = walk_for(rows, cols, grid, threads);
 #define LAUNCH(R, T) hipLaunchKernelGGL((decompress2d_kernel<R, DT, T>), dim3(grid), dim3(T), 0, s, static_cast<const uint8_t*>(d_in), w, d_out)
 #define CALL(R)                                                                \
@@ -882,7 +891,7 @@ int launch_reduce2d(const void* const* d_in, int k, const float* d_local, size_t
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int cus = compute_units(), threads = decode_threads(blocks, cus);
-  const unsigned grid = grid_for(blocks, kDecodeWorkgroupsPerCU, threads, cus);
+  const unsigned grid = grid_for(blocks, raw_out ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
   const Walk w = walk_for(rows, cols, grid, threads);
   uint8_t* out = static_cast<uint8_t*>(d_out);
 #define LAUNCH(R, LOCAL, RAW, T) \
