@@ -713,6 +713,95 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(ChunkPointers chunks, 
   }
 }
 
+// ---- small messages -------------------------------------------------------------------
+// One block per lane, in as many workgroups as that takes, and what a lane reads is asked for before the
+// tables are staged.  A small message leaves CUs without a tile of the kernels above, and what it waits for
+// is one lane's chain: tables, barrier, values, then two or four blocks one after the other.  (Which messages are
+// small, and what both forms take: see small_half_groups_per_cu.)
+template <int RATE, int DT>
+__global__ __launch_bounds__(kThreads) void compress_small_kernel(const void* __restrict__ in, size_t n, uint8_t* __restrict__ out) {
+  __shared__ __align__(16) uint32_t enc[encoder_table_words<RATE>()];
+  const size_t j = (size_t)blockIdx.x * kThreads + threadIdx.x, whole = n / 4, blocks = whole + ((n & 3) != 0 ? 1 : 0);
+  uint32_t x[4] = {0u, 0u, 0u, 0u}, W[zc::Traits<RATE>::kWords];
+  if (j < whole) load_values<DT>(in, j, x);
+  else if (j < blocks) load_values_ragged<DT>(in, n, x);
+  stage_encoder_table<RATE>(enc);
+  __syncthreads();
+  if (j >= blocks) return;
+  zc::encode_block<RATE>(x, zc::Tables{enc, nullptr, nullptr}, W, AnyLane());
+  store_stream<RATE, true>(out, j, W);
+}
+
+template <int RATE, int DT>
+__global__ __launch_bounds__(kThreads) void decompress_small_kernel(const uint8_t* __restrict__ in, size_t n, void* __restrict__ out) {
+  __shared__ __align__(16) uint32_t dec[decoder_table_words<RATE>()];
+  const size_t j = (size_t)blockIdx.x * kThreads + threadIdx.x, whole = n / 4, blocks = whole + ((n & 3) != 0 ? 1 : 0);
+  uint32_t W[zc::Traits<RATE>::kWords];
+  float y[4];
+  if (j < blocks) load_stream<RATE>(in, j, W);
+  const zc::Tables tab = stage_decoder_table<RATE>(dec, nullptr);
+  __syncthreads();
+  if (j >= blocks) return;
+  zc::decode_block<RATE>(W, tab, y, AnyLane());
+  if (j < whole) store_values<DT>(out, j, y);
+  else store_values_ragged<DT>(out, n, y);
+}
+
+// (A chunk's stream is asked for two chunks ahead.)
+template <int RATE, bool LOCAL, bool RAW_OUT>
+__global__ __launch_bounds__(kThreads) void reduce_small_kernel(ChunkPointers chunks, int k, const float* local, size_t n,
+                                                                uint8_t* out, float* out_raw) {
+  __shared__ __align__(16) uint32_t dec[decoder_table_words<RATE>()];
+  __shared__ __align__(16) uint32_t dec_half[RATE == 4 ? kDec4HalfWords : 4];
+  __shared__ __align__(16) uint32_t enc[RAW_OUT ? 4 : encoder_table_words<RATE>()];
+  constexpr int NW = zc::Traits<RATE>::kWords;
+  const size_t j = (size_t)blockIdx.x * kThreads + threadIdx.x, whole = n / 4, blocks = whole + ((n & 3) != 0 ? 1 : 0);
+  uint32_t P[2][NW] = {}, x[4] = {0u, 0u, 0u, 0u};
+  if (j < blocks) {
+    load_stream<RATE>(chunks.p[0], j, P[0]);
+    if (k > 1) load_stream<RATE>(chunks.p[1], j, P[1]);
+    if constexpr (LOCAL) {
+      if (j < whole) load_values<kF32>(local, j, x);
+      else load_values_ragged<kF32>(local, n, x);
+    }
+  }
+  const zc::Tables tab = stage_reduce_tables<RATE, !RAW_OUT>(dec, dec_half, enc);
+  __syncthreads();
+  if (j >= blocks) return;
+  float s[4];
+#pragma unroll 1
+  for (int c = 0; c < k; ++c) {
+    uint32_t W[NW];
+    float y[4];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      W[i] = P[0][i];
+      P[0][i] = P[1][i];
+    }
+    if (c + 2 < k) load_stream<RATE>(chunks.p[c + 2], j, P[1]);
+    zc::decode_block<RATE>(W, tab, y, AnyLane());
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[i] = c ? s[i] + y[i] : y[i];
+  }
+  if constexpr (LOCAL) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[i] += __uint_as_float(x[i]);
+  }
+  if constexpr (RAW_OUT) {
+    if (j < whole) store_values<kF32>(out_raw, j, s);
+    else store_values_ragged<kF32>(out_raw, n, s);
+  } else {
+    // the pad of a ragged last block repeats the last valid sum
+    const int valid = j < whole ? 4 : (int)(n & 3);
+    const float pad = valid == 1 ? s[0] : (valid == 2 ? s[1] : s[2]);
+    uint32_t W[NW];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = __float_as_uint(i < valid ? s[i] : pad);
+    zc::encode_block<RATE>(x, tab, W, AnyLane());
+    store_stream<RATE>(out, j, W);
+  }
+}
+
 // ---- host side ----------------------------------------------------------------------
 
 int compute_units() {
@@ -766,6 +855,28 @@ unsigned grid_for(size_t n, Kernel kernel, int rate, int blocks_per_lane) {
   if (groups == 0) groups = 1;
   const size_t cap = (size_t)compute_units() * (size_t)workgroups_per_cu(kernel, rate);
   return (unsigned)(groups < cap ? groups : cap);
+}
+
+// Workgroups of a small message's kernel (one block per lane), or 0 if the message is not small.
+// The line is where the two forms meet, in workgroups of one block per lane and CU.  (us with tiles and with
+// one block per lane, as one of 30 launches in a graph: compress at rate 8 2^18 values, one such workgroup per CU,
+// 4.3 and 2.5, 2^20 5.0 and 3.6, 2^21 5.9 and 4.9, 2^22 7.5 and 7.7; decompress 5.1 and 3.2, 5.4 and 3.8, 6.0 and
+// 5.0, 7.2 and 8.4; 2-way reduce 6.0 and 4.6, 6.6 and 5.8, 8.3 and 8.0, 12.3 and 13.0, at rate 24 18.8 and 11.5 for 300001 values
+// but 11.3 and 11.6 for 2^21; with raw output 4.0 and 3.4, 5.0 and 4.5, 5.9 and 6.1, for 1500001 values 6.9 and 5.5.  At rate 4,
+// whose wide kernels take 512 blocks per wavefront: compress 2^18 3.2 and 2.4, 2^20 3.4 and 2.9, 2^22 4.9 and 6.4;
+// decompress 2.3 and 2.1, 2^19 2.38 and 2.36, 2^20 2.5 and 2.6; reduces 2^18 2.9 and 2.6, 2^20 3.0 and 3.1, of two chunks
+// to a stream 2^17 2.44 and 2.42, 2^18 2.44 and 2.49.)
+size_t small_half_groups_per_cu(Kernel kernel, int rate, bool two_chunks) {
+  switch (kernel) {
+    case kCompress: return rate == 4 ? 8 : 16;
+    case kDecompress: return rate == 4 ? 4 : 16;
+    case kReduceRaw: return rate == 4 ? 8 : 12;
+    default: return rate == 4 ? (two_chunks ? 1 : 4) : (rate <= 16 ? 16 : 12);
+  }
+}
+unsigned small_grid(size_t n, Kernel kernel, int rate, bool two_chunks = false) {
+  const size_t groups = ((n + 3) / 4 + kThreads - 1) / kThreads;
+  return 2 * groups <= small_half_groups_per_cu(kernel, rate, two_chunks) * (size_t)compute_units() ? (unsigned)groups : 0u;
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -846,7 +957,8 @@ static int launch_compress(const void* d_in, int dtype, size_t n, int rate, void
   if (out_cap < zc_compressed_size(n, rate)) return ZC_ERR_CAPACITY;
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint8_t* out = static_cast<uint8_t*>(d_out);
-  if (rate == 4 && n / 4 >= kWideBlocks) {
+  const unsigned small = small_grid(n, kCompress, rate);
+  if (small == 0 && rate == 4 && n / 4 >= kWideBlocks) {
     // whole runs of 512 blocks per wavefront go through the wide kernel, the rest through the general one
     const size_t wave_tiles = (n / 4) / kWideBlocks;
     const size_t groups = (wave_tiles + kThreads / 64 - 1) / (kThreads / 64);
@@ -862,8 +974,11 @@ static int launch_compress(const void* d_in, int dtype, size_t n, int rate, void
     if (n == 0) return finish_launch();
   }
 #define LAUNCH(R, DT)                                                                                            \
-  hipLaunchKernelGGL((compress_kernel<R, compress_unroll<R>(), DT>), dim3(grid_for(n, kCompress, R, compress_unroll<R>())), \
-                     dim3(kThreads), 0, s, d_in, n, out)
+  do {                                                                                                           \
+    if (small) hipLaunchKernelGGL((compress_small_kernel<R, DT>), dim3(small), dim3(kThreads), 0, s, d_in, n, out); \
+    else hipLaunchKernelGGL((compress_kernel<R, compress_unroll<R>(), DT>), dim3(grid_for(n, kCompress, R, compress_unroll<R>())), \
+                            dim3(kThreads), 0, s, d_in, n, out);                                                 \
+  } while (0)
 #define CALL(R)                                   \
   do {                                            \
     if (dtype == ZC_F32) LAUNCH(R, kF32);         \
@@ -885,7 +1000,8 @@ static int launch_decompress(const void* d_in, size_t n, int rate, int dtype, vo
   if (n > kMaxValues) return ZC_ERR_SIZE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const uint8_t* in = static_cast<const uint8_t*>(d_in);
-  if (rate == 4 && n / 4 >= kWideBlocks) {
+  const unsigned small = small_grid(n, kDecompress, rate);
+  if (small == 0 && rate == 4 && n / 4 >= kWideBlocks) {
     const size_t wave_tiles = (n / 4) / kWideBlocks;
     const size_t groups = (wave_tiles + kThreads / 64 - 1) / (kThreads / 64);
     const size_t cap = (size_t)compute_units() * (size_t)workgroups_per_cu(kDecompress, 4);
@@ -900,8 +1016,11 @@ static int launch_decompress(const void* d_in, size_t n, int rate, int dtype, vo
     if (n == 0) return finish_launch();
   }
 #define LAUNCH(R, DT)                                                                                            \
-  hipLaunchKernelGGL((decompress_kernel<R, decompress_unroll<R>(), DT>), dim3(grid_for(n, kDecompress, R, decompress_unroll<R>())), \
-                     dim3(kThreads), 0, s, in, n, d_out)
+  do {                                                                                                           \
+    if (small) hipLaunchKernelGGL((decompress_small_kernel<R, DT>), dim3(small), dim3(kThreads), 0, s, in, n, d_out); \
+    else hipLaunchKernelGGL((decompress_kernel<R, decompress_unroll<R>(), DT>), dim3(grid_for(n, kDecompress, R, decompress_unroll<R>())), \
+                            dim3(kThreads), 0, s, in, n, d_out);                                                 \
+  } while (0)
 #define CALL(R)                                   \
   do {                                            \
     if (dtype == ZC_F32) LAUNCH(R, kF32);         \
@@ -951,12 +1070,15 @@ static int launch_reduce(const void* const* d_in, int k, const float* d_local, s
   if (!raw_out && out_cap < zc_compressed_size(n, rate)) return ZC_ERR_CAPACITY;
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint8_t* out = static_cast<uint8_t*>(d_out);
+  const unsigned small = small_grid(n, raw_out ? kReduceRaw : kReduce, rate, k == 2 && !d_local && !raw_out);
 #define LAUNCH_K(R, LOCAL, RAW, K)                                                                            \
   hipLaunchKernelGGL((reduce_kernel<R, reduce_unroll<R>(), LOCAL, RAW, K>), dim3(grid_for(n, RAW ? kReduceRaw : kReduce, R, reduce_unroll<R>())),    \
                      dim3(kThreads), 0, s, chunks, k, d_local, n, out, d_out_raw)
 #define LAUNCH(R, LOCAL, RAW)                 \
   do {                                        \
-    if (k == 2) LAUNCH_K(R, LOCAL, RAW, 2);   \
+    if (small)                                \
+      hipLaunchKernelGGL((reduce_small_kernel<R, LOCAL, RAW>), dim3(small), dim3(kThreads), 0, s, chunks, k, d_local, n, out, d_out_raw); \
+    else if (k == 2) LAUNCH_K(R, LOCAL, RAW, 2);   \
     else LAUNCH_K(R, LOCAL, RAW, 0);          \
   } while (0)
 #define CALL(R)                                   \

@@ -392,3 +392,37 @@ def test_full_size_ring_share_sampled(gpu, oracle):
                             oracle.reduce_mixed(comp[:2], peers[7][sl], 4 * length, rate), bb, "mixed from %d" % b0)
         _assert_floats_equal(_host(to_raw[sl]), oracle.reduce_decompress(comp[:2], peers[7][sl], 4 * length, rate),
                              "to-raw from %d" % b0)
+
+
+@pytest.mark.parametrize("rate, per_cu", [(4, 0.5), (4, 2), (4, 4), (8, 6), (8, 8), (16, 8), (24, 6), (24, 8)])
+def test_both_sides_of_the_line_for_small_messages(gpu, oracle, rate, per_cu):
+    """Small messages go one block per lane, larger ones in tiles: the lines lie at 0.5 to 8 workgroups of
+    256 blocks per CU, by call and rate.  Every call on the last message below such a line and on one past it,
+    with a ragged end, on values and on arbitrary bytes."""
+    import torch
+    edge = int(per_cu * torch.cuda.get_device_properties(0).multi_processor_count) * 1024
+    rng = np.random.default_rng(rate)
+    for n in (edge - 1, edge + 6):
+        print("line", rate, per_cu, n, flush=True)
+        x = workloads.gradient_iid(n)
+        y = workloads.activation_gelu(n).astype(np.float32)
+        s = rng.integers(0, 256, size=oracle.compressed_size(n, rate), dtype=np.uint8)
+        s[: s.size // 2] &= rng.integers(0, 256, size=s.size // 2, dtype=np.uint8)
+        s[:: rate // 2] = rng.integers(90, 140, size=s[:: rate // 2].size, dtype=np.uint8)   # (sums stay finite)
+        s[: 64 * (rate // 2)] = 0
+        c = oracle.compress(x, rate)
+        _assert_bytes_equal(_host(gpu.zc_compress(_dev(x), rate)), c, rate // 2, "compress")
+        for stream in (c, s):
+            back = gpu.zc_decompress(_dev(stream), n, rate)
+            _assert_floats_equal(_host(back), oracle.decompress(stream, n, rate), "decompress")
+            half = gpu.zc_decompress_half(_dev(stream), n, rate, torch.bfloat16)
+            assert torch.equal(half.view(torch.int16), back.to(torch.bfloat16).view(torch.int16))
+        h = _dev(y).to(torch.bfloat16)
+        _assert_bytes_equal(_host(gpu.zc_compress_half(h, rate)), oracle.compress(_host(h.float()), rate), rate // 2, "compress_half")
+        dc, ds = _dev(c), _dev(s)
+        for streams, given in (([c, s], [dc, ds]), ([c, s, c], [dc, ds, dc])):
+            want = oracle.reduce_compressed(streams, n, rate)
+            _assert_bytes_equal(_host(gpu.zc_reduce_compressed(given, n, rate)), want, rate // 2, "reduce of %d" % len(given))
+        _assert_bytes_equal(_host(gpu.zc_reduce_mixed([ds], _dev(y), n, rate)), oracle.reduce_mixed([s], y, n, rate), rate // 2, "mixed")
+        _assert_floats_equal(_host(gpu.zc_reduce_decompress([ds], _dev(y), n, rate)), oracle.reduce_decompress([s], y, n, rate), "last hop")
+        _assert_floats_equal(_host(gpu.zc_reduce_decompress([dc, ds], None, n, rate)), oracle.reduce_decompress([c, s], None, n, rate), "raw sum")
