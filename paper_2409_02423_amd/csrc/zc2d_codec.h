@@ -147,14 +147,14 @@ constexpr ExpandTable build_expand_table() {
 // closing one; a run that reaches the last coefficient needs no closing one, and the plane is
 // closed after it; a group bit 0 closes the plane.
 // Byte 0: how many stream bits were used; byte 1, which is added to n: how many coefficients were
-// passed, and kTokenClosed if the plane is closed; byte 2: the ones, as positions past the
-// current coefficient; byte 3: how many bits of budget the entry must find.
+// passed, and kTokenClosed if the plane is closed; byte 2: how many bits of budget the entry must
+// find; byte 3: the ones, as positions past the current coefficient.
 // Bits past the budget are zeros in the decoder's window, and what they decode to there is right
 // everywhere but in one place: zeros after a group bit 1 would put the one on the last
 // coefficient, where a run cut by the budget has it at the lowest index still possible.  So
-// byte 3 is the bits used if the entry holds a run that reaches the last coefficient without a
+// byte 2 is the bits used if the entry holds a run that reaches the last coefficient without a
 // closing one, kTokenNone (more than any budget) if it holds no whole token at all (or one whose
-// position byte 2 has no room for), and zero otherwise.
+// position byte 3 has no room for), and zero otherwise.
 constexpr int kLookahead = 9;
 constexpr int kTokenRows = 11;
 constexpr uint32_t kTokenFirstRowIndex = 6, kTokenLastRowIndex = 16;
@@ -185,7 +185,7 @@ constexpr TokenTable build_token_table() {
         passed += z + 1;
       }
       const uint32_t need = used == 0u ? kTokenNone : (to_last ? used : 0u);
-      t.v[(row << kLookahead) + s] = used | (passed | closed) << 8 | ones << 16 | need << 24;
+      t.v[(row << kLookahead) + s] = used | (passed | closed) << 8 | need << 16 | ones << 24;
     }
   }
   for (uint32_t s = 0; s < (1u << kLookahead); ++s) t.v[((kTokenRows - 1) << kLookahead) + s] = kTokenClosed << 8;
@@ -376,11 +376,11 @@ ZC_DEV bool any_of(AnyActive any_lane_active, bool p, bool q) {
 }
 
 // Where a lane's decoded planes go: sixteen 16-bit patterns, in the order they are read, that
-// start as zeros.  Places are kPlaneStep apart, from begin() to end(); word k is patterns 2k and, above
-// it, 2k + 1.  This one is for the host.
+// start as zeros.  Places are kPlaneStep apart, from begin() to end(), where a pattern may be put as
+// well; word k is patterns 2k and, above it, 2k + 1.  This one is for the host.
 constexpr uint32_t kPlaneStep = 2;
 struct LocalPlanes {
-  uint16_t v[16];
+  uint16_t v[17];
   ZC_DEV void clear() { for (int t = 0; t < 16; ++t) v[t] = 0; }
   ZC_DEV uint32_t begin() const { return 0u; }
   ZC_DEV uint32_t end() const { return 16 * kPlaneStep; }
@@ -388,13 +388,21 @@ struct LocalPlanes {
   ZC_DEV uint32_t word(int k) const { return v[2 * k] | (uint32_t)v[2 * k + 1] << 16; }
 };
 
+// `width` bits of v from bit `offset` on (offset below 32, width below 32; none for width 0).
+ZC_DEV uint32_t bit_field(uint32_t v, uint32_t offset, uint32_t width) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_ubfe(v, offset, width);
+#else
+  return (v >> offset) & ((1u << width) - 1u);
+#endif
+}
+
 // A lane's progress through its block's planes.
 template <int NW>
 struct PlaneReader {
-  uint32_t (&W)[NW];   // the window: what is not yet read, zeros past the budget
+  uint32_t (&W)[NW];   // the window: what is not yet read, from bit 2 on, zeros past the budget
   int32_t left;        // budget, which zeros read past its end make negative
   uint32_t n;          // how many leading coefficients are significant
-  uint32_t skip;       // bits of the window that belong to these, at the start of a plane (otherwise 0)
   uint32_t pattern;    // the ones of the current plane found so far
   uint32_t at;         // the current plane's place
 };
@@ -404,10 +412,11 @@ struct PlaneReader {
 // that has them then waits for the others, which the plain form does not provide for).
 //
 // Lanes go through their planes on their own: a step is one look-up in the token table and, in
-// lanes that start a plane, the bits of the significant coefficients before it (16 + 9 bits are in
+// lanes that close a plane, the bits of the significant coefficients of the next one (9 + 16 bits are in
 // the window's first word).  A lane out of budget goes on reading empty planes.  The current
 // plane's pattern is put in its place in every step, whether it is whole or not: LDS writes are
-// what this kernel has to spare, and it takes no test.  Only if some lane's entry asks for more
+// what this kernel has to spare, and it takes no test.  (What a lane has at the end of a plane begun by its last step
+// is left to the caller.)  Only if some lane's entry asks for more
 // budget than the lane has, an entry for one token is made for it by count-trailing-zeros with the
 // limits applied.
 // (What bounds the 4 x 4 kernels is their instruction count, and here the number of steps that
@@ -418,13 +427,15 @@ struct PlaneReader {
 // the last-level cache, 0.278 -> 0.248 ms with streams from memory and with what else changed in the
 // decoder, 0.623 -> 0.572 ms for the 2-way reduce.  A step of about 22 instructions instead of 28, without a vote on the places left and with a lane's
 // planes on end in LDS: decompress2d at rate 16 120 -> 112 us for 8192 x 8192 values, 2-way reduce 328 ->
-// 314 us, at rate 4 8192 x 32768 values 490 -> 469 us.)
+// 314 us, at rate 4 8192 x 32768 values 490 -> 469 us.  With the significant coefficients' bits taken when a plane closes
+// and not when the next one starts, so that the look-up's bits are where the table wants them, a step is about
+// 66 cycles instead of 87: 469 -> 457 us, at rate 8 641 -> 623, decompress2d of 8192 x 8192 values at rate 16 112 ->
+// 108, the reduce of one chunk and local values there 222 -> 207.)
 template <bool CAREFUL, int NW, class AnyActive, class Planes>
 ZC_DEV void read_planes(const uint32_t* token, PlaneReader<NW>& r, Planes& planes, AnyActive any_lane_active) {
-  // byte offset of the entry: (clamped index - first row's index) rows, then the next bits;
-  // the constant rides on the masking of the bits (it has none of their positions set)
+  // byte offset of the entry: (clamped index - first row's index) rows, then the next bits
   constexpr uint32_t kRowBytesLg = kLookahead + 2;
-  constexpr uint32_t kBias = 0u - (kTokenFirstRowIndex << kRowBytesLg);
+  constexpr uint32_t kBitsMask = ((1u << kLookahead) - 1u) << 2;
   // Up to rate 8 (NW <= 4) few blocks take sixteen steps, and in as many no lane can pass its
   // sixteenth place: the plain form counts them.  At rate 16 it asks whether some lane has got there.
   constexpr bool kCounted = !CAREFUL && NW <= 4;
@@ -433,39 +444,36 @@ ZC_DEV void read_planes(const uint32_t* token, PlaneReader<NW>& r, Planes& plane
   for (;;) {
     const bool reading = !CAREFUL || r.at != planes.end();
     uint32_t e = 0u;
-    int32_t budget = 0;
     bool cut = false;
     if (reading) {
       const uint32_t clamped = umin(umax(r.n, kTokenFirstRowIndex), kTokenLastRowIndex);
-      uint32_t bits = (r.W[0] >> r.skip) & ((1u << kLookahead) - 1u);
-      zc::materialise(bits);   // (a bit-field extract, then shift-and-or with the constant, then shift-and-add:
-      bits = bits << 2 | kBias;   //  otherwise the constant comes back as an addition of its own)
-      zc::materialise(bits);
-      e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(token) + ((clamped << kRowBytesLg) + bits));
-      r.pattern |= r.W[0] & ((1u << r.skip) - 1u);
-      budget = r.left - (int32_t)r.skip;
-      cut = (e >> 24) > (uint32_t)budget;   // (no budget at all: the window is empty, and so is byte 3)
+      uint32_t bits = r.W[0] & kBitsMask;
+      zc::materialise(bits);   // (so that the row is shifted and added to it in one instruction)
+      const uint32_t offset = (clamped << kRowBytesLg) + bits - (kTokenFirstRowIndex << kRowBytesLg);
+      e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(token) + offset);
+      cut = ((e >> 16) & 0xFFu) > (uint32_t)r.left;   // (no budget at all: the window is empty, and so is byte 2)
     }
     if (any_lane_active(cut)) {
       // zeros up to the one; the run ends at the last coefficient or at the budget (of which some is
       // left: the group bit is a one).  The one may be too far on for an entry.
-      const uint32_t room = umin(15u - r.n, (uint32_t)budget - 1u);
-      const uint32_t z = umin(count_trailing_zeros(r.W[0] >> r.skip >> 1), room);
+      const uint32_t room = umin(15u - r.n, (uint32_t)r.left - 1u);
+      const uint32_t z = umin(count_trailing_zeros(r.W[0] >> 3), room);
       const uint32_t made = (z + 1u) << 8 | (1u + z + (z < room ? 1u : 0u));
       e = cut ? made : e;
       r.pattern |= cut ? 1u << ((r.n + z) & 31u) : 0u;
     }
     if (reading) {
-      r.pattern |= ((e >> 16) & 0xFFu) << r.n;
+      r.pattern |= (e >> 24) << r.n;
       const uint32_t s = r.n + ((e >> 8) & 0xFFu), used = e & 0xFFu;
       planes.put(r.at, r.pattern);
-      zc::shift_out<NW>(r.W, r.skip + used);
-      r.left = budget - (int32_t)used;
       const bool closed = s >= kTokenClosed;
       r.n = s & 31u;
-      r.skip = closed ? r.n : 0u;
-      r.pattern = closed ? 0u : r.pattern;
+      // a closed plane: the next one's bits of the significant coefficients
+      const uint32_t verbatim = closed ? r.n : 0u;
+      r.pattern = closed ? bit_field(r.W[0], used + 2u, verbatim) : r.pattern;
       r.at += closed ? kPlaneStep : 0u;
+      zc::shift_out<NW>(r.W, used + verbatim);
+      r.left -= (int32_t)(used + verbatim);
     }
     if (CAREFUL) {
       if (!any_lane_active(r.left > 0 && r.at != planes.end())) break;
@@ -487,6 +495,15 @@ struct BlockReading {
   PlaneReader<NW> r;
 };
 constexpr uint32_t kEmptyLead = 3u, kEmptyExponent = 127u;
+
+// After read_planes: a lane whose budget ended within the bits of significant coefficients has these in a
+// plane that no step has put in its place.  If that is a seventeenth, it is marked as budget left.
+template <int NW, class AnyActive, class Planes>
+ZC_DEV void put_begun_plane(PlaneReader<NW>& r, Planes& planes, AnyActive any_lane_active) {
+  planes.put(r.at, r.pattern);
+  if (any_lane_active(r.at == planes.end()))
+    r.left = r.at == planes.end() && r.pattern != 0u && r.left <= 0 ? 1 : r.left;
+}
 
 // Reads the first (up to sixteen) planes of the block in the window W.
 template <int RATE, class AnyActive, class Planes>
@@ -514,9 +531,9 @@ ZC_DEV BlockReading<Traits<RATE>::kWords> read_block(uint32_t (&W)[Traits<RATE>:
     empty = E == 0u || lead >= 32u;
   }
   int32_t left = (int32_t)kPayload - (int32_t)lead;
-  // past the header byte and the leading zeros: two shifts of less than 32 each (with 32 and
+  // past the header byte and the leading zeros but for two bits: two shifts of less than 32 each (with 32 and
   // more leading zeros there is nothing to read, as in a zero block, whatever its payload)
-  zc::shift_out<NW>(W, 8u);
+  zc::shift_out<NW>(W, 6u);
   zc::shift_out<NW>(W, lead & 31u);
   if (any_lane_active(empty)) {
     if (empty) {
@@ -527,12 +544,13 @@ ZC_DEV BlockReading<Traits<RATE>::kWords> read_block(uint32_t (&W)[Traits<RATE>:
       for (int j = 0; j < NW; ++j) W[j] = 0u;
     }
   }
-  BlockReading<NW> b = {E, lead, lead > 16u && left > 0, {W, left, 0u, 0u, 0u, planes.begin()}};
+  BlockReading<NW> b = {E, lead, lead > 16u && left > 0, {W, left, 0u, 0u, planes.begin()}};
   planes.clear();
   read_planes<false>(token, b.r, planes, any_lane_active);
   if (any_lane_active(b.r.left > 0)) {   // some lane may have read sixteen planes
     if (any_lane_active(b.r.left > 0 && b.r.at != planes.end())) read_planes<true>(token, b.r, planes, any_lane_active);
   }
+  put_begun_plane(b.r, planes, any_lane_active);
   return b;
 }
 
@@ -576,9 +594,10 @@ ZC_DEV void finish_block(BlockReading<Traits<RATE>::kWords>& b, const uint32_t* 
     }
     if (deeper) {
       b.r.at = planes.begin();
-      b.r.pattern = 0u;   // (a lane that ran out of budget within a plane has put it where it belongs)
+      b.r.pattern = b.r.left > 0 ? b.r.pattern : 0u;   // (a lane that ran out of budget within a plane has put it where it belongs)
       planes.clear();
       read_planes<true>(token, b.r, planes, any_lane_active);
+      put_begun_plane(b.r, planes, any_lane_active);
       load_planes(planes, h);
       transpose_halves<true>(h);
 #pragma unroll
