@@ -565,11 +565,28 @@ __device__ __forceinline__ void add_blocks(uint32_t (&W)[zc2d::Traits<RATE>::kWo
 }
 constexpr bool as_matrix(int rate, int threads) { return rate <= 8 && threads == kDecodeThreads; }
 
+// LDS of a kernel that decodes.  The planes come first, so that a lane's are at its number times a constant, and the
+// token table late enough for its place and what is taken off a row's index to make an offset that an instruction
+// can have (in the decompress kernels of 256 lanes the room for that, 3 KiB, costs more than it gives: 64 x 256 values at rate
+// 8 4.14 and 4.19 us; the reduce of 512 x 1024 values at rate 16 13.0 and 12.9).  us with the tables first and as it is: 2-way
+// reduce of 8192 x 32768 values at rate 4 457 and 450, at rate 8 623 and 617, 8192 x 8192 at rate 16 303 and 298.
+template <int THREADS, bool MATRIX, bool ENCODER>
+struct DecodeLds {
+  static constexpr int kExpand = ENCODER ? zc2d::kExpandEntries : 4;
+  static constexpr int kBefore = THREADS * kPlaneBytes + 4 * kExpand;
+  static constexpr int kTokenBias = (int)(zc2d::kTokenFirstRowIndex << (zc2d::kLookahead + 2));
+  char planes[THREADS * kPlaneBytes];
+  uint32_t expand[kExpand];
+  char unused[ENCODER && kBefore < kTokenBias ? kTokenBias - kBefore : 16];
+  uint32_t token[zc2d::kTokenRows << zc2d::kLookahead];
+  uint32_t matrix[MATRIX ? kMatrixWords : 4];
+};
+
 template <int RATE, int DT, int THREADS>
 __global__ __launch_bounds__(THREADS) void decompress2d_kernel(const uint8_t* __restrict__ in, Walk w, void* __restrict__ out) {
-  __shared__ __attribute__((aligned(16))) uint32_t token[zc2d::kTokenRows << zc2d::kLookahead];
-  __shared__ __attribute__((aligned(16))) char plane_lds[THREADS * kPlaneBytes];
-  __shared__ __attribute__((aligned(16))) uint32_t matrix[as_matrix(RATE, THREADS) ? kMatrixWords : 4];
+  __shared__ __attribute__((aligned(16))) DecodeLds<THREADS, as_matrix(RATE, THREADS), false> lds;
+  char* const plane_lds = lds.planes;
+  uint32_t *const token = lds.token, *const matrix = lds.matrix;
   if (as_matrix(RATE, THREADS) && threadIdx.x < kMatrixWords / 4)
     reinterpret_cast<uint4*>(matrix)[threadIdx.x] = reinterpret_cast<const uint4*>(&g_matrix)[threadIdx.x];
   stage_table<(zc2d::kTokenRows << zc2d::kLookahead), THREADS>(g_token.v, token);
@@ -668,14 +685,15 @@ template <int RATE, bool LOCAL, bool RAW_OUT, int THREADS>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(as_matrix(RATE, THREADS) && !LOCAL ? 6 : 1)))
 void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, uint8_t* out, float* out_raw) {
   constexpr bool kMatrix = as_matrix(RATE, THREADS) && !LOCAL;
-  __shared__ __attribute__((aligned(16))) uint32_t expand[zc2d::kExpandEntries];
-  __shared__ __attribute__((aligned(16))) uint32_t token[zc2d::kTokenRows << zc2d::kLookahead];
-  __shared__ __attribute__((aligned(16))) char plane_lds[THREADS * kPlaneBytes];
-  __shared__ __attribute__((aligned(16))) uint32_t matrix[kMatrix ? kMatrixWords : 4];
+  __shared__ __attribute__((aligned(16))) DecodeLds<THREADS, kMatrix, !RAW_OUT> lds;
+  char* const plane_lds = lds.planes;
+  uint32_t *const token = lds.token, *const matrix = lds.matrix, *const expand = lds.expand;
   if (kMatrix && threadIdx.x < kMatrixWords / 4)
     reinterpret_cast<uint4*>(matrix)[threadIdx.x] = reinterpret_cast<const uint4*>(&g_matrix)[threadIdx.x];
-  for (int i = threadIdx.x; i < zc2d::kExpandEntries / 4; i += THREADS)
-    reinterpret_cast<uint4*>(expand)[i] = reinterpret_cast<const uint4*>(g_expand.v)[i];
+  if constexpr (!RAW_OUT) {
+    for (int i = threadIdx.x; i < zc2d::kExpandEntries / 4; i += THREADS)
+      reinterpret_cast<uint4*>(expand)[i] = reinterpret_cast<const uint4*>(g_expand.v)[i];
+  }
   stage_table<(zc2d::kTokenRows << zc2d::kLookahead), THREADS>(g_token.v, token);   // (its barrier covers all tables)
   constexpr int NW = zc2d::Traits<RATE>::kWords;
   if constexpr (kMatrix) {
@@ -685,14 +703,15 @@ void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, 
     cur.start(w, b0);
     for (;;) {
       f32x4 rows[4] = {};
+      int j = 0;
 #pragma unroll 1
-      for (int j = 0; j < k; ++j) {   // (one copy of the decoder, a few hundred instructions, is enough)
+      do {   // (one copy of the decoder, a few hundred instructions, is enough)
         const uint32_t tid = fresh_tid();
         WavePlanes planes(plane_lds, tid);
         uint32_t W[NW];
         load_block_words<RATE>(chunks.p[j], cur, w, tid, W);
         add_blocks<RATE>(W, token, planes, matrix, tid, j == 0, rows);
-      }
+      } while (++j < k);
       const uint32_t tid = fresh_tid();
       if constexpr (RAW_OUT) {
         store_rows<kF32>(out_raw, w, cur, tid, rows);
