@@ -221,7 +221,8 @@ ZC_DEV void lift_forward(int32_t& a, int32_t& b, int32_t& c, int32_t& d) {
 
 // x: the block row-major as fp32 bit patterns.  Returns E and the negabinary words in
 // coefficient order.
-ZC_DEV void forward_transform(const uint32_t (&x)[16], uint32_t& E, uint32_t (&u)[16]) {
+template <class AnyActive>
+ZC_DEV void forward_transform(const uint32_t (&x)[16], uint32_t& E, uint32_t (&u)[16], AnyActive any_lane_active) {
   // largest magnitude as a bit pattern (on the device a float maximum with |x| operands, as in
   // the 1-D codec: the same pattern for finite values, a third of the instructions)
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -236,10 +237,19 @@ ZC_DEV void forward_transform(const uint32_t (&x)[16], uint32_t& E, uint32_t (&u
   for (int i = 0; i < 16; ++i) m = umax(m, x[i] & 0x7FFFFFFFu);
 #endif
   E = (m >> 23) + (m != 0u ? 1u : 0u);
-  const int scale = 127 + kFractionBits - (int)E;
   int32_t q[16];
+  if (any_lane_active(E - 1u < 26u)) {
+    const int scale = 127 + kFractionBits - (int)E;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) q[i] = (int32_t)__builtin_ldexpf(zc::bits_to_float(x[i]), scale);
+    for (int i = 0; i < 16; ++i) q[i] = (int32_t)__builtin_ldexpf(zc::bits_to_float(x[i]), scale);
+  } else {
+    // the power of two is a float (for a zero block anything finite does), and a multiplication takes the GPU half
+    // as long as its ldexp (us before and after: 2-way reduce of 8192 x 32768 values at rate 8 604.8 and 598, compress2d of
+    // 8192 x 6144 bf16 values 53.9 and 52.1)
+    const float scale = zc::bits_to_float((254u + kFractionBits - umax(E, 27u)) << 23);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) q[i] = (int32_t)(zc::bits_to_float(x[i]) * scale);
+  }
 #pragma unroll
   for (int r = 0; r < 4; ++r) lift_forward(q[4 * r], q[4 * r + 1], q[4 * r + 2], q[4 * r + 3]);
 #pragma unroll
@@ -258,9 +268,10 @@ ZC_DEV void forward_transform(const uint32_t (&x)[16], uint32_t& E, uint32_t (&u
 // distinction: the topmost bit of the expansion is the group bit after the last one, or the
 // plane's only one, and both are zeros in the code.  Only the last coefficient is different (no
 // end, no group bit after it; and no group test at all once it is significant), so with it reached
-// the length is counted instead.  At the low rates (VOTES) that is done where some lane of the
-// wavefront has got there, which few do; from rate 8 on in every plane, because a vote and a branch in
-// each are what the few wavefronts of a small matrix wait for.  The length is at most 31.  (Before:
+// the length is counted instead.  At rate 2 (VOTES) that is done where some lane of the
+// wavefront has got there, which few do; from rate 4 on in every plane, because most wavefronts get there and a vote and
+// a branch in each are what the few wavefronts of a small matrix wait for (rate 4 with votes and without: 64 x 256
+// values 3.16 and 2.95, 8192 x 6145 bf16 values 44.2 and 43.5, 2-way reduce of 8192 x 32768 445 and 443).  The length is at most 31.  (Before:
 // starts and ends formed separately, verbatim bits appended on their own, 33 instructions per plane at
 // rate 4 instead of 23.  us of compress2d with those, with votes at every rate and as it is: 64 x 256
 // values at rate 16 4.50, 4.94, 4.35, 8192 x 32768 at rate 16 495, 429, 406, at rate 8 294, 267, 258.)
@@ -291,7 +302,7 @@ ZC_DEV void encode_block(const uint32_t (&x)[16], const uint32_t* expand, uint32
   constexpr int NW = Traits<RATE>::kWords;
   constexpr int kMaxPlanes = Traits<RATE>::kPayloadBits < 32 ? Traits<RATE>::kPayloadBits : 32;
   uint32_t E, u[16];
-  forward_transform(x, E, u);
+  forward_transform(x, E, u, any_lane_active);
   uint32_t any = 0;
 #pragma unroll
   for (int c = 0; c < 16; ++c) any |= u[c];
@@ -312,7 +323,7 @@ ZC_DEV void encode_block(const uint32_t (&x)[16], const uint32_t* expand, uint32
   for (int t = 0; t < 16; ++t) {
     if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
     const int b = 15 - t;
-    encode_plane<(RATE < 8), NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, m, known, left, last_reached, any_lane_active);
+    encode_plane<(RATE < 4), NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, m, known, left, last_reached, any_lane_active);
   }
   if (kMaxPlanes > 16 && any_lane_active(left > 0)) {
 #pragma unroll
@@ -322,7 +333,7 @@ ZC_DEV void encode_block(const uint32_t (&x)[16], const uint32_t* expand, uint32
     for (int t = 16; t < 32; ++t) {
       if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
       const int b = 31 - t;
-      encode_plane<(RATE < 8), NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, m, known, left, last_reached, any_lane_active);
+      encode_plane<(RATE < 4), NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, m, known, left, last_reached, any_lane_active);
     }
   }
   zc::shift_right<NW>(W, (uint32_t)(32 * NW - Traits<RATE>::kBlockBits) + left);

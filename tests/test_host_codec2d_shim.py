@@ -98,6 +98,25 @@ def test_lockstep_lanes_match_reference(o2, shim, rate):
             assert bad.size == 0, (rate, lanes, bad[:5])
 
 
+@pytest.mark.parametrize("rate", RATES)
+def test_blocks_either_side_of_the_scale_that_is_a_float(o2, shim, rate):
+    """Blocks scale by 2^(154 - E), which is a float from E = 27 on: exponents about there and at both ends
+    of the range, alone (one path) and side by side in one wavefront (the other)."""
+    rng = np.random.default_rng(4100 + rate)
+    exponents = (-148, -126, -110, -102, -101, -100, 0, 126)   # of the largest value: E = 1, 2, 18, 26, 27, 28, 128, 254
+    x = np.concatenate([np.ldexp(rng.uniform(-1, 1, size=(32, 16)).astype(np.float32), e + 1) for e in exponents] +
+                       [np.zeros((8, 16), np.float32)]).astype(np.float32)
+    want = np.stack([o2.encode_block(b, rate) for b in x])
+    got = np.zeros_like(want)
+    assert shim.zc2d_host_encode_blocks(rate, x.ctypes.data, len(x), got.ctypes.data) == 0
+    assert np.array_equal(got, want), rate
+    for order in (np.arange(len(x)), rng.permutation(len(x))):
+        rows, ref = np.ascontiguousarray(x[order]), want[order]
+        got = np.zeros_like(ref)
+        assert shim.zc2d_host_wave(rate, 1, rows.ctypes.data, len(rows), got.ctypes.data, 16) == 0
+        assert np.array_equal(got, ref), rate
+
+
 def _blocks_with_lead(rng, rate, blocks, lead):
     """Arbitrary blocks of `lead` empty planes, dense and sparse ones (which have more planes), under exponent
     bytes of every kind."""
