@@ -79,6 +79,14 @@ ZC_DEV constexpr uint32_t select_bits(uint32_t mask, uint32_t a, uint32_t b) {
   return (a & mask) | (b & ~mask);
 }
 
+// the same of a and ~b
+ZC_DEV constexpr uint32_t select_bits_not(uint32_t mask, uint32_t a, uint32_t b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if (!__builtin_is_constant_evaluated()) return __builtin_amdgcn_bitop3_b32(mask, a, b, 0xC5);
+#endif
+  return (a & mask) | (~b & ~mask);
+}
+
 // ---- 16 x 16 bit transpose on eight words ----------------------------------------------
 // Row r of a 16 x 16 bit matrix sits in half r >> 3 of word r & 7 (half 0 = bits 0..15).
 // The transpose leaves the matrix in the same arrangement, so it is its own inverse.
@@ -675,7 +683,9 @@ static_assert(inverse64_ok(), "the inverse transform as a matrix");
 
 // Eight planes t = 0..7, plane 6 - 2w in the lower and 7 - 2w in the upper half of word w, to
 // eight digits of each coefficient, plane 0 the highest: byte b of word w = coefficient
-// digit_coefficient(w, b).
+// digit_coefficient(w, b).  SIGNED: bytes 0 and 1 xor 0xAA, bytes 2 and 3 xor 0x55 (see kDigitSigns), which rides
+// on the last step's operations.
+template <bool SIGNED = false>
 ZC_DEV constexpr void planes_to_digits(uint32_t (&x)[4]) {
 #pragma unroll
   for (int w = 0; w < 2; ++w) {
@@ -691,7 +701,7 @@ ZC_DEV constexpr void planes_to_digits(uint32_t (&x)[4]) {
   }
 #pragma unroll
   for (int w = 0; w < 4; ++w)
-    x[w] = select_bits(0xAAAA0000u, x[w] << 17, select_bits(0x00005555u, x[w] >> 17, x[w]));
+    x[w] = select_bits(0xAAAA0000u, x[w] << 17, SIGNED ? select_bits_not(0x00005555u, x[w] >> 17, x[w]) : select_bits(0x00005555u, x[w] >> 17, x[w]));
 }
 constexpr int digit_coefficient(int w, int b) { return 8 * (b & 1) + 2 * w + 1 - (b >> 1); }
 
@@ -700,11 +710,15 @@ constexpr bool digits_ok() {
   uint32_t s = 0x1234567u, pattern[8] = {}, x[4] = {};
   for (int t = 0; t < 8; ++t) { s = s * 1664525u + 1013904223u; pattern[t] = s >> 16; }
   for (int w = 0; w < 4; ++w) x[w] = pattern[6 - 2 * w] | pattern[7 - 2 * w] << 16;
+  uint32_t y[4] = {x[0], x[1], x[2], x[3]};
   planes_to_digits(x);
+  planes_to_digits<true>(y);
   for (int w = 0; w < 4; ++w)
     for (int b = 0; b < 4; ++b)
       for (int t = 0; t < 8; ++t)
         if (((x[w] >> (8 * b + 7 - t)) & 1u) != ((pattern[t] >> digit_coefficient(w, b)) & 1u)) return false;
+  for (int w = 0; w < 4; ++w)
+    if (y[w] != (x[w] ^ 0x5555AAAAu)) return false;
   return true;
 }
 static_assert(digits_ok(), "digits of eight planes");
@@ -713,6 +727,9 @@ static_assert(digits_ok(), "digits of eight planes");
 // A byte of digits d stands for (d ^ 0xAA) - 0xAA (negabinary, the lowest digit positive).
 constexpr uint32_t kDigitSigns = 0xAAAAAAAAu;
 constexpr int kDigitBias = 0xAA;
+// That is y - 0xAA for y = d ^ 0xAA and 0x55 - y for y = d ^ 0x55: what the SIGNED bytes stand for.
+constexpr int signed_digit_sign(int b) { return b < 2 ? 1 : -1; }
+constexpr int signed_digit_bias(int b) { return b < 2 ? 0xAA : -0x55; }
 
 // Whether the matrix covers a block, as far as that can be told from how it was read: first = the
 // pattern of its first plane, digits = 8 or 15 of them.
