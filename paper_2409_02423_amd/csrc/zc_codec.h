@@ -643,16 +643,33 @@ ZC_DEV int32_t negabinary_to_int(uint32_t u) {
 #endif
 }
 
-ZC_DEV void inverse_transform(const uint32_t (&u)[4], uint32_t E, float (&out)[4]) {
+ZC_DEV void inverse_transform(const uint32_t (&u)[4], int32_t (&q)[4]) {
   int32_t a = negabinary_to_int(u[0]), b = negabinary_to_int(u[1]), c = negabinary_to_int(u[2]), d = negabinary_to_int(u[3]);
   inverse_lift(a, b, c, d);
-  const int ex = (int)E - 127 - kFractionBits;
-  // int -> fp32 rounds to nearest even; the scaling is exact and rounds once more only
-  // for subnormal results.  A zero block arrives here with all words zero: +0.
-  out[0] = __builtin_ldexpf((float)a, ex);
-  out[1] = __builtin_ldexpf((float)b, ex);
-  out[2] = __builtin_ldexpf((float)c, ex);
-  out[3] = __builtin_ldexpf((float)d, ex);
+  q[0] = a; q[1] = b; q[2] = c; q[3] = d;
+}
+
+// Fixed-point values -> fp32, stored (FIRST) or added to the sum: int -> fp32 rounds to nearest even; the scaling is
+// exact and rounds once more only for subnormal results.  A zero block arrives here with all words
+// zero: +0.  Where all exponent bytes of the wavefront are common ones, the power of two is a float and its product with a value of
+// magnitude 1 .. 2^31 is exact and finite: a multiplication is then the ldexp (and takes the GPU half
+// as long), and a fused multiply-add rounds the sum once, as the addition would.
+ZC_DEV bool common_exponent(uint32_t E) { return E - 29u <= 222u; }
+
+template <bool FIRST>
+ZC_DEV void scale_values(const int32_t (&q)[4], uint32_t E, bool all_common, float (&sum)[4]) {
+  if (all_common) {
+    const float scale = bits_to_float((E - (uint32_t)kFractionBits) << 23);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum[i] = FIRST ? (float)q[i] * scale : __builtin_fmaf((float)q[i], scale, sum[i]);
+  } else {
+    const int ex = (int)E - 127 - kFractionBits;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float y = __builtin_ldexpf((float)q[i], ex);
+      sum[i] = FIRST ? y : sum[i] + y;
+    }
+  }
 }
 
 // W holds the block (bits beyond 4*RATE zero).
@@ -666,9 +683,17 @@ ZC_DEV void inverse_transform(const uint32_t (&u)[4], uint32_t E, float (&out)[4
 // past the budget are zeros in the window and decode as the zeros that unseen bits are; so
 // the rest of the window is taken as it stands, eight planes per 32 bits through the pair
 // table, with no loop, no budget and no state, and joined to the planes of phase 1.
-template <int RATE, class AnyActive>
-ZC_DEV void decode_block(uint32_t (&W)[Traits<RATE>::kWords], const Tables& tab, float (&out)[4],
-                         AnyActive any_lane_active) {
+//
+// FIRST: the values are stored in `out`, otherwise added to it.
+// BRANCHES: what few wavefronts need (a zero block, an empty first word, an uncommon exponent byte) is branched around.
+// Without, it is worked out always: what the few wavefronts of a small message wait for is the chain of a block's
+// instructions and branches, not their number.  (us without and with, on large messages: 2-way reduce at rate 8 2^25 values
+// 70.9 and 68.6, at rate 16 1.5e8 322 and 307, at rate 24 2^25 97.5 and 92.8, 8-way at rate 8 194 and 186, one chunk and local
+// values at rate 8 58.1 and 55.1, decompress at rate 24 5e7 bf16 values 57.0 and 54.3; on small ones: 2^17 values at rate 16
+// 2-way reduce 4.49 and 4.65, decompress 3.11 and 3.17.)
+template <int RATE, bool FIRST, bool BRANCHES, class AnyActive>
+ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& tab, float (&out)[4],
+                            AnyActive any_lane_active) {
   constexpr int NW = Traits<RATE>::kWords;
   constexpr int kPayload = Traits<RATE>::kPayloadBits;
   const uint32_t E = W[0] & 0xFFu;
@@ -678,24 +703,37 @@ ZC_DEV void decode_block(uint32_t (&W)[Traits<RATE>::kWords], const Tables& tab,
     const float* q = tab.dec4 + 4u * (E ? W[0] >> 8 : 0u);
     const int ex = (int)E - 127 - kFractionBits + 22;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) out[i] = __builtin_ldexpf(q[i], ex);
+    for (int i = 0; i < 4; ++i) {
+      const float y = __builtin_ldexpf(q[i], ex);
+      out[i] = FIRST ? y : out[i] + y;
+    }
   } else {
     // literal words of phase 2: at least one bit is gone after phase 1, and at most 31 planes remain
     constexpr int kLiteral = (kPayload - 1 + 31) / 32 < 4 ? (kPayload - 1 + 31) / 32 : 4;
-    // leading empty planes = zero bits at the start of the payload
-    uint32_t lead = 0;
-    {
-      bool found = false;
+    // leading empty planes = zero bits at the start of the payload, which seldom pass the first word
+    const uint32_t top = W[0] & 0xFFFFFF00u;
+    uint32_t lead = count_trailing_zeros_nonzero(top) - 8u;
+    if constexpr (NW == 1) lead = umin(lead, (uint32_t)kPayload);   // (for an empty payload too)
+    bool none = false;   // nothing to decode
+    const auto uncommon = any_lane_active.lanes(!common_exponent(E));
+    auto look_closer = uncommon;
+    if constexpr (NW > 1) look_closer = look_closer | any_lane_active.lanes(top == 0u);
+    if (!BRANCHES || any_lane_active.some(look_closer)) {
+      if constexpr (NW > 1) {
+        lead = 0;
+        bool found = false;
 #pragma unroll
-      for (int j = 0; j < NW; ++j) {
-        const uint32_t w = j == 0 ? (W[0] & 0xFFFFFF00u) : W[j];
-        const uint32_t z = count_trailing_zeros(w);
-        lead = found ? lead : lead + z;
-        found = found || (w != 0);
+        for (int j = 0; j < NW; ++j) {
+          const uint32_t w = j == 0 ? top : W[j];
+          const uint32_t z = count_trailing_zeros(w);
+          lead = found ? lead : lead + z;
+          found = found || (w != 0);
+        }
+        lead = umin(lead - 8u, (uint32_t)kPayload);   // (the header byte)
       }
-      lead -= 8u;  // the header byte
+      // a zero block ignores its payload; after 32 empty planes nothing is left to decode
+      none = E == 0u || (kPayload > 32 && lead >= 32u);
     }
-    lead = umin(lead, (uint32_t)kPayload);
     uint32_t left = (uint32_t)kPayload - lead;
     // keep the next stream bit at bit 2 of the window: bits 10..2 index the look-ahead table directly.
     // Two shifts of less than 32 each (a block with 32 and more leading empty planes has its
@@ -703,13 +741,14 @@ ZC_DEV void decode_block(uint32_t (&W)[Traits<RATE>::kWords], const Tables& tab,
     shift_out<NW>(W, 6u);
     shift_out<NW>(W, lead & 31u);
     uint32_t state = 0;
-    // a zero block ignores its payload; after 32 empty planes nothing is left to decode
-    if (E == 0u || (kPayload > 32 && lead >= 32u)) {
-      left = 0u;
-      lead = 0u;
-      state = kDecIdle;
+    if (!BRANCHES || any_lane_active.some(look_closer)) {
+      if (none) {
+        left = 0u;
+        lead = 0u;
+        state = kDecIdle;
 #pragma unroll
-      for (int j = 0; j < NW; ++j) W[j] = 0u;
+        for (int j = 0; j < NW; ++j) W[j] = 0u;
+      }
     }
     // phase 1.  A[i] collects the planes of coefficient i, the latest in bit 0; m counts them
     // (per lane: a step reads one or two planes, or none in a lane that is idle).
@@ -796,8 +835,19 @@ ZC_DEV void decode_block(uint32_t (&W)[Traits<RATE>::kWords], const Tables& tab,
         for (int i = 0; i < 4; ++i) u[i] = alignbit(A[i], u[i], down);
       }
     }
-    inverse_transform(u, E, out);
+    int32_t q[4];
+    inverse_transform(u, q);
+    scale_values<FIRST>(q, E, BRANCHES && !any_lane_active.some(uncommon), out);
   }
+}
+
+template <int RATE, bool BRANCHES = true, class AnyActive>
+ZC_DEV void decode_block(uint32_t (&W)[Traits<RATE>::kWords], const Tables& tab, float (&out)[4], AnyActive any_lane_active) {
+  decode_block_to<RATE, true, BRANCHES>(W, tab, out, any_lane_active);
+}
+template <int RATE, bool BRANCHES = true, class AnyActive>
+ZC_DEV void decode_block_add(uint32_t (&W)[Traits<RATE>::kWords], const Tables& tab, float (&sum)[4], AnyActive any_lane_active) {
+  decode_block_to<RATE, false, BRANCHES>(W, tab, sum, any_lane_active);
 }
 
 // Rate 4 in the fused reduce: sum = (FIRST) or sum += (otherwise) the decoded block, with one

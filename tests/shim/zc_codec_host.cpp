@@ -118,6 +118,32 @@ extern "C" int zc_host_encode_blocks(int rate, const float* x, size_t blocks, ui
   return 0;
 }
 
+// sum += the decoded blocks, as the reduces do it, with the rare cases branched around or not
+template <int RATE>
+static void add(bool branches, const uint8_t* in, float* sum) {
+  uint32_t W[zc::Traits<RATE>::kWords] = {};
+  std::memcpy(W, in, zc::Traits<RATE>::kBlockBytes);
+  float s[4];
+  std::memcpy(s, sum, 16);
+  if (branches) zc::decode_block_add<RATE, true>(W, kTables, s, always);
+  else zc::decode_block_add<RATE, false>(W, kTables, s, always);
+  std::memcpy(sum, s, 16);
+}
+extern "C" int zc_host_add_blocks(int rate, int branches, const uint8_t* in, size_t blocks, float* sum) {
+  for (size_t j = 0; j < blocks; ++j) switch (rate) {
+      case 4: add<4>(branches != 0, in + 2 * j, sum + 4 * j); break;
+      case 8: add<8>(branches != 0, in + 4 * j, sum + 4 * j); break;
+      case 12: add<12>(branches != 0, in + 6 * j, sum + 4 * j); break;
+      case 16: add<16>(branches != 0, in + 8 * j, sum + 4 * j); break;
+      case 20: add<20>(branches != 0, in + 10 * j, sum + 4 * j); break;
+      case 24: add<24>(branches != 0, in + 12 * j, sum + 4 * j); break;
+      case 28: add<28>(branches != 0, in + 14 * j, sum + 4 * j); break;
+      case 32: add<32>(branches != 0, in + 16 * j, sum + 4 * j); break;
+      default: return -2;
+    }
+  return 0;
+}
+
 extern "C" int zc_host_decode_blocks(int rate, const uint8_t* in, size_t blocks, float* x) {
   for (size_t j = 0; j < blocks; ++j) switch (rate) {
 #define F(R) case R: dec<R>(in + j * (R / 2), x + 4 * j); break;

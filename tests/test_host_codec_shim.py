@@ -27,6 +27,7 @@ def shim():
     L = ctypes.CDLL(LIB)
     L.zc_host_encode_blocks.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     L.zc_host_decode_blocks.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+    L.zc_host_add_blocks.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     L.zc_host_encode_wave.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_int]
     L.zc_host_decode_wave.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_int]
     L.zc_host_region_order.argtypes = [ctypes.c_size_t, ctypes.c_size_t, ctypes.c_int]
@@ -172,3 +173,28 @@ def test_rate4_accumulate_forms_on_every_block(oracle, shim):
                     assert same[~expect_flag].all()
                     plain_differs += int((~same[expect_flag]).any())
     assert plain_differs > 0
+
+
+@pytest.mark.parametrize("rate", RATES)
+@pytest.mark.parametrize("branches", (0, 1))
+def test_decoded_blocks_are_added_with_one_rounding(oracle, shim, rate, branches):
+    """The decoder that adds to a sum, with its rare cases branched around and not, against the reference's decoded
+    values added in fp32: exponent bytes where the scaling's form changes (28 and 29, 251 and 252), zero blocks, empty
+    first words and arbitrary bytes, onto ordinary sums, zeros of both signs and subnormals."""
+    rng = np.random.default_rng(50 * rate + branches)
+    n = 6000
+    s = rng.integers(0, 256, size=(n, rate // 2), dtype=np.uint8)
+    s[:, 0] = np.where(rng.random(n) < 0.7, rng.choice([0, 1, 2, 27, 28, 29, 30, 127, 250, 251, 252, 253, 255], size=n), s[:, 0])
+    s[::5, 1:4] = 0
+    s[::7, 1:] = 0
+    s[1::7, 1:] &= rng.integers(0, 256, size=s[1::7, 1:].shape, dtype=np.uint8) & rng.integers(0, 256, size=s[1::7, 1:].shape, dtype=np.uint8)
+    with np.errstate(all="ignore"):
+        y = np.concatenate([oracle.decode_block(b, rate) for b in s])
+        start = (rng.standard_normal(4 * n) * np.ldexp(1.0, rng.integers(-140, 120, size=4 * n))).astype(np.float32)
+        start[::9], start[4::9] = 0.0, -0.0
+        start[1::3] = (y[1::3] * rng.uniform(-2, 2, size=y[1::3].size)).astype(np.float32)
+        want = start + y
+    got = start.copy()
+    assert shim.zc_host_add_blocks(rate, branches, s.ctypes.data, n, got.ctypes.data) == 0
+    ok = (got.view(np.uint32) == want.view(np.uint32)) | (np.isnan(got) & np.isnan(want))
+    assert ok.all(), (rate, branches, np.flatnonzero(~ok)[:5])
