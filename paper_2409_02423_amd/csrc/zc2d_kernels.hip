@@ -71,7 +71,8 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
 // 296 and 265).
 // Only a build with -DZC_TUNING_KNOBS lets ZC2D_WORKGROUPS_PER_CU override these; the shipped library reads
 // no environment variable.
-constexpr int kCompressWorkgroupsPerCU = 16, kCompressWorkgroupsPerCUMost = 64, kDecodeWorkgroupsPerCU = 24, kDecodeWorkgroupsPerCUWide = 64;
+constexpr int kCompressWorkgroupsPerCU = 16, kCompressWorkgroupsPerCUMost = 64, kDecodeWorkgroupsPerCU = 24, kDecodeWorkgroupsPerCUWide = 64,
+              kDecodeWorkgroupsPerCULeast = 12;
 
 // The wavefront-wide vote of the codec: whether p holds in some lane.
 struct AnyLane {
@@ -825,6 +826,19 @@ unsigned grid_for(size_t blocks, int preset, int threads, int cus) {
   return (unsigned)(groups < cap ? groups : cap);
 }
 
+// The same for the decoding kernels, whose workgroups stage 22 KiB of token table for 8 to 32 KiB of values per block and
+// lane: from 12 per CU on a lane has two blocks or more.  (us at 24 per CU, one block per lane, and at 12: decompress2d of 8192 x
+// 6144 bf16 values at rate 8 46.8 and 43.9, at rate 16 86.4 and 84.3; 8192 x 8192 fp32 values, one or two at 24 and two or three at 12, at
+// rate 4 47.7 and 45.5, 2-way reduce 115.8 and 113.2; one chunk and local values of 8192 x 6144 at rate 8 99.0 and 94.1.  decompress2d with fp32 rows
+// aligned to their elements only keeps one: 5000 x 10003 values at rate 4 41.0 and 52.4.)
+unsigned decode_grid_for(size_t blocks, int preset, int threads, int cus) {
+  const size_t groups = (blocks + threads - 1) / threads, least = (size_t)cus * kDecodeWorkgroupsPerCULeast;
+  const unsigned most = grid_for(blocks, preset, threads, cus);
+  if (groups <= least) return most;
+  const size_t two = groups / 2 > least ? groups / 2 : least;
+  return (unsigned)(two < most ? two : most);
+}
+
 // Lanes per workgroup of a decoding kernel: the fewer where the wide ones would not be one per CU.
 // (us with 512 and 256 lanes, 2-way reduce at rates 4 and 16: 64 x 256 values 8.6 and 7.3, 16.7 and
 // 13.3; 512 x 1024 8.9 and 7.5, 17.0 and 14.0; 700 x 2500, just below the line, 9.1 and 8.9, 17.4
@@ -892,7 +906,8 @@ int launch_decompress2d(const void* d_in, size_t rows, size_t cols, int rate, vo
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int cus = compute_units(), threads = decode_threads(blocks, cus);
-  const unsigned grid = grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
+  const unsigned grid = (cols & 3) && DT == kF32 ? grid_for(blocks, kDecodeWorkgroupsPerCUWide, threads, cus)
+                        : decode_grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
   const Walk w = walk_for(rows, cols, grid, threads);
 #define LAUNCH(R, T) hipLaunchKernelGGL((decompress2d_kernel<R, DT, T>), dim3(grid), dim3(T), 0, s, static_cast<const uint8_t*>(d_in), w, d_out)
 #define CALL(R)                                                                \
@@ -926,7 +941,7 @@ int launch_reduce2d(const void* const* d_in, int k, const float* d_local, size_t
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int cus = compute_units(), threads = decode_threads(blocks, cus);
-  const unsigned grid = grid_for(blocks, raw_out ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
+  const unsigned grid = decode_grid_for(blocks, raw_out ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
   const Walk w = walk_for(rows, cols, grid, threads);
   uint8_t* out = static_cast<uint8_t*>(d_out);
 #define LAUNCH(R, LOCAL, RAW, T) \

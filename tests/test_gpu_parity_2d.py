@@ -460,3 +460,38 @@ def test_matrix_and_lifting_forms_of_the_decoder(gpu, ref, rate, cols):
     _same_floats(_host(gpu.zc2d_decompress(a, rows, cols, rate)), want, "decompress")
     _same_floats(_host(gpu.zc2d_reduce_decompress([a, b], None, rows, cols, rate)), both, "reduce_decompress")
     _same_bytes(_host(gpu.zc2d_reduce_compressed([a, b], rows, cols, rate)), coded, rate, "reduce")
+
+
+@pytest.mark.parametrize("rate", (4, 8, 16))
+@pytest.mark.parametrize("cols", (6148, 6145))
+def test_lanes_that_take_several_blocks(gpu, rate, cols):
+    """8192 rows: more blocks than the decoding kernels have lanes, so that a lane goes on to its next block, whose
+    words it has asked for ahead, and the last pass is partly empty.  Each call on the whole matrix equals the
+    calls on slices of 64 block rows, which are matrices of their own that take one block per lane."""
+    import torch
+    rows, slice_rows = 8192, 256
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rate + cols)
+    x = torch.randn((rows, cols), generator=g, device="cuda") * torch.randint(-8, 9, (rows, 1), generator=g, device="cuda").float().exp2()
+    x[1000:1100] = 0.0
+    y = torch.randn((rows, cols), generator=g, device="cuda")
+    bc = (cols + 3) // 4
+    part = slice_rows // 4 * bc * 2 * rate
+    print("several blocks", rate, cols, flush=True)
+    cx, cy = gpu.zc2d_compress(x, rate), gpu.zc2d_compress(y, rate)
+    calls = {
+        "decompress": lambda a, b, v, r: gpu.zc2d_decompress(a, r, cols, rate),
+        "to bf16": lambda a, b, v, r: gpu.zc2d_decompress_half(a, r, cols, rate, torch.bfloat16),
+        "reduce": lambda a, b, v, r: gpu.zc2d_reduce_compressed([a, b], r, cols, rate),
+        "three": lambda a, b, v, r: gpu.zc2d_reduce_compressed([a, b, a], r, cols, rate),
+        "mixed": lambda a, b, v, r: gpu.zc2d_reduce_mixed([a], v, r, cols, rate),
+        "to fp32": lambda a, b, v, r: gpu.zc2d_reduce_decompress([a, b], None, r, cols, rate),
+        "last": lambda a, b, v, r: gpu.zc2d_reduce_decompress([a], v, r, cols, rate),
+    }
+    for name, call in calls.items():
+        got = call(cx, cy, y, rows).view(torch.uint8).reshape(-1)
+        want = torch.cat([call(cx[i * part:(i + 1) * part].clone(), cy[i * part:(i + 1) * part].clone(),
+                               y[i * slice_rows:(i + 1) * slice_rows].clone(), slice_rows).view(torch.uint8).reshape(-1)
+                          for i in range(rows // slice_rows)])
+        assert torch.equal(got, want), (name, rate, cols)
+    assert torch.equal(cx, torch.cat([gpu.zc2d_compress(x[i:i + slice_rows].clone(), rate) for i in range(0, rows, slice_rows)]))
