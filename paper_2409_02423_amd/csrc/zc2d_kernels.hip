@@ -54,7 +54,7 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
 }
 // Workgroups per CU in the grid.  The kernels that decode have 512 lanes per workgroup (256 for small
 // matrices, see decode_threads): 22 KiB of token table, 18 KiB of planes, 1 KiB for the matrix product and 2
-// KiB for an encoder are 41 to 43 KiB, of which three fit a CU: six wavefronts per SIMD, for which 80 registers
+// KiB for an encoder are 42 to 44 KiB, of which three fit a CU: six wavefronts per SIMD, for which 80 registers
 // are left.  The forms with the matrix product are held to that (without being told the reduces took 88,
 // four wavefronts: 0.530 against 0.496 ms for the 2-way reduce of 8192 x 32768 values at rate 4).  (256 lanes, as
 // the kernels were before: 0.270 against 0.248 ms for decompress2d, 0.613 against 0.583 ms for the reduce;
