@@ -547,18 +547,27 @@ __device__ __forceinline__ void store_rows(void* out, const Walk& w, const WaveC
 // sum += the wavefront's blocks, as rows, that the lanes' windows W hold (or = for the first).
 // Up to rate 8 nearly all blocks are covered by the matrix; at rate 16 they have too many planes, and
 // only the lifting's way is there.  Told by the rate and by the width of the workgroups (see as_matrix).
+// Returns kLiftedFirst if the first went the lifting's way, kByMatrix if they went the matrix's, otherwise 0.
+//
+// The sign of a sum that is zero: where all of a block's parts went the lifting's way it is as added here (tiny
+// values round to - 0, and the sum of - 0 and - 0 is - 0).  From the matrix no value is - 0, but its zero times a negative scale
+// is, and added to a sum of - 0, which only the lifting's first part leaves, that stays; added as + 0 it would not.
+// So with both kinds among the parts no sum may be - 0, and + 0 added at the end sees to it.  (A stream has no sign for a zero.)
+constexpr uint32_t kByMatrix = 1u, kLiftedFirst = 2u;
 template <int RATE>
-__device__ __forceinline__ void add_blocks(uint32_t (&W)[zc2d::Traits<RATE>::kWords], const uint32_t* token, WavePlanes& planes,
+__device__ __forceinline__ uint32_t add_blocks(uint32_t (&W)[zc2d::Traits<RATE>::kWords], const uint32_t* token, WavePlanes& planes,
                                            const uint32_t* matrix, uint32_t tid, bool first, f32x4 (&sum)[4]) {
   auto b = zc2d::read_block<RATE>(W, token, AnyLane(), planes);
   f32x4 d[4];
   float scale[4];
+  uint32_t how = kByMatrix;
   if (AnyLane()(b.r.left > 0) || !matrix_product(planes, b.E, b.lead, matrix, tid, d, scale)) {
     int32_t q[16];
     float y[16];
     zc2d::finish_block<RATE>(b, token, q, AnyLane(), planes);
     zc2d::scale_block(q, b.E, y);
     blocks_to_rows(y, d);
+    how = first ? kLiftedFirst : 0u;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       scale[g] = 1.0f;
@@ -570,6 +579,7 @@ __device__ __forceinline__ void add_blocks(uint32_t (&W)[zc2d::Traits<RATE>::kWo
   for (int g = 0; g < 4; ++g)
 #pragma unroll
     for (int q = 0; q < 4; ++q) sum[g][q] = __builtin_fmaf(d[g][q], scale[g], sum[g][q]);
+  return how;
 }
 constexpr bool as_matrix(int rate, int threads) { return rate <= 8 && threads == kDecodeThreads; }
 
@@ -717,6 +727,7 @@ void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, 
       WaveCursor next = cur;
       next.advance(w);
       f32x4 rows[4] = {};
+      uint32_t how = 0u;
       int j = 0;
 #pragma unroll 1
       do {   // (one copy of the decoder, a few hundred instructions, is enough)
@@ -727,10 +738,14 @@ void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, 
         for (int i = 0; i < NW; ++i) W[i] = Wn[i];
         if (j + 1 < k) load_block_words<RATE>(chunks.p[j + 1], cur, w, tid, Wn);
         else if (next.inside(w)) load_block_words<RATE>(chunks.p[0], next, w, tid, Wn);
-        add_blocks<RATE>(W, token, planes, matrix, tid, j == 0, rows);
+        how |= add_blocks<RATE>(W, token, planes, matrix, tid, j == 0, rows);
       } while (++j < k);
       const uint32_t tid = fresh_tid();
       if constexpr (RAW_OUT) {
+        if (how == (kByMatrix | kLiftedFirst)) {
+#pragma unroll
+          for (int g = 0; g < 4; ++g) rows[g] += 0.0f;
+        }
         store_rows<kF32>(out_raw, w, cur, tid, rows);
       } else {
         float sum[16];

@@ -495,3 +495,35 @@ def test_lanes_that_take_several_blocks(gpu, rate, cols):
                           for i in range(rows // slice_rows)])
         assert torch.equal(got, want), (name, rate, cols)
     assert torch.equal(cx, torch.cat([gpu.zc2d_compress(x[i:i + slice_rows].clone(), rate) for i in range(0, rows, slice_rows)]))
+
+
+@pytest.mark.parametrize("rate", (2, 4, 8))
+@pytest.mark.parametrize("cols", (2052, 2050))
+def test_sign_of_zero_sums(gpu, ref, rate, cols):
+    """Blocks so small that their values round to zero decode to zeros of either sign, and take the lifting's way;
+    a zero block, and others with an odd and an even number of empty planes, take the matrix's.  A sum of zeros
+    is - 0 only where every part is, whichever way each was decoded and in whichever order."""
+    rng = np.random.default_rng(rate + cols)
+    rows = 1024
+    bc = (cols + 3) // 4
+    blocks = (rows // 4) * bc
+    tiny = np.ldexp(rng.standard_normal((rows, cols)), rng.integers(-151, -146, size=(rows, 1))).astype(np.float32)
+    tiny = ref.compress(tiny, rate).reshape(blocks, 2 * rate)
+    few = np.zeros((blocks, 16 * rate - 8), dtype=np.uint8)          # 2 to 5 empty planes, then few ones
+    few[:, 2:] = rng.random((blocks, few.shape[1] - 2)) < 0.2
+    few[np.arange(blocks), rng.integers(2, 6, size=blocks)] = 1
+    few = np.packbits(few, axis=1, bitorder="little")
+    other = np.concatenate([rng.integers(100, 130, size=(blocks, 1), dtype=np.uint8), few], axis=1)
+    other[rng.random(blocks) < 0.7] = 0
+    zero = np.zeros_like(other)
+    wave = np.arange(blocks) // 64
+    mixed = np.where((rng.random(wave.max() + 1) < 0.5)[wave][:, None], tiny, other)
+    negative = np.count_nonzero(ref.decompress(tiny.reshape(-1), rows, cols, rate).view(np.uint32) == 0x80000000)
+    assert negative > 10000 if rate > 2 else negative == 0   # (24 payload bits do not reach values so small)
+    parts = {"t": tiny, "o": other, "z": zero, "m": mixed}
+    dev = {name: _dev(p.reshape(-1)) for name, p in parts.items()}
+    for order in ("tz", "zt", "to", "tm", "mt", "mz", "ttz", "tzt", "tom", "zzt", "tmtt"):
+        print("sign of zero", rate, cols, order, flush=True)
+        want = ref.reduce_decompress([parts[c].reshape(-1) for c in order], None, rows, cols, rate)
+        got = gpu.zc2d_reduce_decompress([dev[c] for c in order], None, rows, cols, rate)
+        _same_floats(_host(got), want, "reduce_decompress of " + order)
