@@ -431,9 +431,10 @@ __device__ __forceinline__ bool matrix_product(const WavePlanes& planes, uint32_
   uint64_t bad = 0;
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
-    float v;
-    asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(v) : "v"(d[g][0]), "v"(d[g][1]), "v"(d[g][2]));
-    asm("v_max_f32_e64 %0, %1, |%2|" : "=v"(v) : "v"(v), "v"(d[g][3]));
+    // (not as inline assembly: how long an instruction has to wait for a matrix instruction's result, the compiler
+    // sees to for those that it knows.  These are two v_maximum3_f32.)
+    const float v = __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_fabsf(d[g][0]), __builtin_fabsf(d[g][1])),
+                                                  __builtin_elementwise_maximum(__builtin_fabsf(d[g][2]), __builtin_fabsf(d[g][3])));
     const uint64_t group = (early >> (16 * g)) & 0xFFFFu;
     bad |= __builtin_amdgcn_ballot_w64(v >= zc2d::kMatrixMost) & (group | group << 16 | group << 32 | group << 48);
   }
