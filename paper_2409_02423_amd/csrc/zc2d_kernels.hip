@@ -114,7 +114,10 @@ struct Walk {
   size_t whole_br, whole_bc;   // block rows and block columns that lie inside the matrix
   size_t stride;            // lanes in the grid: a lane's next block is `stride` blocks on
   size_t step_bi, step_bj;  // stride / bc, stride % bc
+  uint32_t narrow;          // 2^16 / bc, rounded up, if bc is less than 64, otherwise 0 (see WaveCursor::lane)
+  uint32_t pieces;          // how values that come as rows are stored (see store_rows)
 };
+constexpr uint32_t kPieces = 1, kNarrowPieces = 2;
 
 // A lane's place in the walk.  Advancing costs additions only: no division per block.
 struct Cursor {
@@ -480,15 +483,23 @@ struct WaveCursor {
   // the lane's own block
   __device__ __forceinline__ Cursor lane(const Walk& w, uint32_t tid) const {
     Cursor c;
-    const size_t l = tid & 63;
+    const uint32_t l = tid & 63;
     c.b = b + l;
-    c.bi = bi;
-    c.bj = bj + l;
-    c.first = first + 4 * l;
-    while (c.bj >= w.bc) {
-      c.bj -= w.bc;
-      c.bi += 1;
-      c.first += 4 * w.cols - 4 * w.bc;
+    if (w.narrow) {
+      // many block rows: on = (bj + l) / bc, of numbers below 128 and 64, is the product's upper half, since (bj + l) *
+      // (bc * narrow - 2^16) < 128 * 64 stays below 2^16.  (Subtracted in a loop: 2097152 x 4 values to bf16 at rate 4 15.4
+      // instead of 12.9 us, 2-way reduce to a stream 23.5 and 19.3.)
+      const uint32_t at = (uint32_t)bj + l, bc = (uint32_t)w.bc, on = at * w.narrow >> 16;
+      c.bi = bi + on;
+      c.bj = at - on * bc;
+      c.first = first + (4 * l + on * (4 * (uint32_t)w.cols - 4 * bc));
+    } else {
+      // at most the end of one
+      const uint32_t here = negative(w.bc - bj - 64) ? (uint32_t)(w.bc - bj) : 64u;
+      const bool on = l >= here;
+      c.bi = bi + (on ? 1 : 0);
+      c.bj = (on ? bj - w.bc : bj) + l;
+      c.first = (on ? first + 4 * w.cols - 4 * w.bc : first) + 4 * l;
     }
     return c;
   }
@@ -517,27 +528,57 @@ __device__ __forceinline__ void load_block_words(const uint8_t* in, const WaveCu
   if (lane < cur.count(w)) load_words<zc2d::Traits<RATE>::kWords>(p + lane * zc2d::Traits<RATE>::kBlockBytes, W);
 }
 
-template <int DT>
+template <int DT, bool PLAIN = false>
 __device__ __forceinline__ void store_row(void* out, size_t at, const f32x4& y) {
   if constexpr (DT == kF32) {
     const Row32 v = {__float_as_uint(y[0]), __float_as_uint(y[1]), __float_as_uint(y[2]), __float_as_uint(y[3])};
-    __builtin_nontemporal_store(v, reinterpret_cast<Row32*>(static_cast<float*>(out) + at));
+    Row32* p = reinterpret_cast<Row32*>(static_cast<float*>(out) + at);
+    if constexpr (PLAIN) *p = v;
+    else __builtin_nontemporal_store(v, p);
   } else {
     const Row16 v = {narrow_half<DT>(y[0]) | narrow_half<DT>(y[1]) << 16, narrow_half<DT>(y[2]) | narrow_half<DT>(y[3]) << 16};
-    __builtin_nontemporal_store(v, reinterpret_cast<Row16*>(static_cast<uint16_t*>(out) + at));
+    Row16* p = reinterpret_cast<Row16*>(static_cast<uint16_t*>(out) + at);
+    if constexpr (PLAIN) *p = v;
+    else __builtin_nontemporal_store(v, p);
   }
 }
 
-// Stores the wavefront's blocks, given as rows.  (fp32 rows aligned to their elements only go from a block
-// per lane, 1 KiB of a row at a time: four pieces of 256 bytes that share cache lines with their neighbours
-// took 0.312 instead of 0.281 ms, 6144 x 43690 values at rate 4; of half-precision rows the pieces are better, 40 against
-// 44 us for 8192 x 6145 values.)
+// Stores the wavefront's blocks, given as rows: as they are, four pieces of 256 bytes (kPieces), or from a block per lane, 1
+// KiB of a row at a time, or, where a block row is a few blocks long (kNarrowPieces), as they are with a place worked out for
+// each.  Which, the host says (see store_form).
 template <int DT>
 __device__ __forceinline__ void store_rows(void* out, const Walk& w, const WaveCursor& cur, uint32_t tid, const f32x4 (&rows)[4]) {
-  if (cur.whole(w) && (DT != kF32 || (w.cols & 3) == 0)) {
+  if (cur.whole(w) && (w.pieces & kPieces)) {
     const size_t at = cur.row(w, tid);
 #pragma unroll
     for (int g = 0; g < 4; ++g) store_row<DT>(out, at + 64 * g, rows[g]);
+  } else if (w.pieces & kNarrowPieces) {
+    // (as in WaveCursor::lane; the offsets are below 2^16, and blocks past the last one are past the last row)
+    const uint32_t bc = (uint32_t)w.bc, cols = (uint32_t)w.cols, bj = (uint32_t)cur.bj, r = (tid >> 4) & 3;
+    const uint32_t left = negative(w.rows - 4 * cur.bi - 256) ? (uint32_t)(w.rows - 4 * cur.bi) : 256u;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const uint32_t l = 16 * g + (tid & 15), on = (bj + l) * w.narrow >> 16, col = 4 * (bj + l - on * bc);
+      const size_t at = cur.first + (4 * l + on * (4 * cols - 4 * bc) + r * cols);
+      if (4 * on + r < left) {
+        if (col + 4 <= cols) {
+          if (cols & 3) {
+            asm volatile("" ::: "memory");   // (either side: otherwise the two become one, a plain one)
+            store_row<DT, true>(out, at, rows[g]);
+            asm volatile("" ::: "memory");
+          } else {
+            store_row<DT>(out, at, rows[g]);
+          }
+        } else {
+#pragma unroll
+          for (uint32_t q = 0; q < 3; ++q)
+            if (col + q < cols) {
+              if constexpr (DT == kF32) static_cast<float*>(out)[at + q] = rows[g][q];
+              else static_cast<uint16_t*>(out)[at + q] = (uint16_t)narrow_half<DT>(rows[g][q]);
+            }
+        }
+      }
+    }
   } else {
     float y[16];
     rows_to_blocks(rows, y);
@@ -861,7 +902,21 @@ unsigned decode_grid_for(size_t blocks, int preset, int threads, int cus) {
 // and 17.2; 1024 x 2048, on it, 9.1 both, 17.4 and 17.3; 2048 x 4096 23.1 and 24.1, 49.1 and 50.3.)
 int decode_threads(size_t blocks, int cus) { return blocks < (size_t)cus * kDecodeThreads ? kDecodeThreadsSmall : kDecodeThreads; }
 
-Walk walk_for(size_t rows, size_t cols, unsigned grid, int threads) {
+// How the wide decoding kernels store values that come as rows.  fp32 rows aligned to their elements only go from a
+// block per lane: four pieces of 256 bytes that share cache lines with their neighbours took 0.312 instead of 0.281 ms, 6144 x
+// 43690 values at rate 4; of half-precision rows the pieces are better, 40 against 44 us for 8192 x 6145 values.
+// With few blocks per block row, a wavefront's 64 blocks span many of these, and a row at a time would write a quarter of each
+// cache line, four times: 16 blocks at a time fill whole lines but for both ends (us, decompress2d at rate 4 from a block per lane and
+// in pieces: 2097152 x 4 values 43.8 and 10.2, to bf16 15.4 and 10.0, 2-way reduce to fp32 42.7 and 14.9; 400000 x 13 13.6 and
+// 11.7, 400001 x 23 18.6 and 17.0; 300001 x 31 16.1 and 15.2; but 262144 x 32 9.4 and 9.8, 65536 x 100 9.4 and 14.1).  Of rows aligned to their
+// elements only the ends then meet in the second-level cache (plain stores; without, 400001 x 26 21.6 instead of 16.1; of
+// others with them, 1048576 x 8 at rate 8 13.0 instead of 11.6).
+uint32_t store_form(size_t cols, bool half) {
+  const size_t bc = (cols + 3) / 4;
+  return (half || (cols & 3) == 0 ? kPieces : 0u) | (bc <= 5 || (bc <= 8 && (cols & 3) != 0) ? kNarrowPieces : 0u);
+}
+
+Walk walk_for(size_t rows, size_t cols, unsigned grid, int threads, uint32_t pieces = 0) {
   Walk w;
   w.rows = rows;
   w.cols = cols;
@@ -872,6 +927,8 @@ Walk walk_for(size_t rows, size_t cols, unsigned grid, int threads) {
   w.stride = (size_t)grid * threads;
   w.step_bi = w.stride / w.bc;
   w.step_bj = w.stride % w.bc;
+  w.pieces = pieces;
+  w.narrow = w.bc < 64 ? (uint32_t)((65535 + w.bc) / w.bc) : 0u;
   return w;
 }
 
@@ -924,7 +981,7 @@ int launch_decompress2d(const void* d_in, size_t rows, size_t cols, int rate, vo
   const int cus = compute_units(), threads = decode_threads(blocks, cus);
   const unsigned grid = (cols & 3) && DT == kF32 ? grid_for(blocks, kDecodeWorkgroupsPerCUWide, threads, cus)
                         : decode_grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
-  const Walk w = walk_for(rows, cols, grid, threads);
+  const Walk w = walk_for(rows, cols, grid, threads, store_form(cols, DT != kF32));
 #define LAUNCH(R, T) hipLaunchKernelGGL((decompress2d_kernel<R, DT, T>), dim3(grid), dim3(T), 0, s, static_cast<const uint8_t*>(d_in), w, d_out)
 #define CALL(R)                                                                \
   do {                                                                         \
@@ -958,7 +1015,7 @@ int launch_reduce2d(const void* const* d_in, int k, const float* d_local, size_t
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int cus = compute_units(), threads = decode_threads(blocks, cus);
   const unsigned grid = decode_grid_for(blocks, raw_out ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
-  const Walk w = walk_for(rows, cols, grid, threads);
+  const Walk w = walk_for(rows, cols, grid, threads, store_form(cols, false));
   uint8_t* out = static_cast<uint8_t*>(d_out);
 #define LAUNCH(R, LOCAL, RAW, T) \
   hipLaunchKernelGGL((reduce2d_kernel<R, LOCAL, RAW, T>), dim3(grid), dim3(T), 0, s, chunks, k, d_local, w, out, d_out_raw)

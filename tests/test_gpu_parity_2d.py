@@ -527,3 +527,36 @@ def test_sign_of_zero_sums(gpu, ref, rate, cols):
         want = ref.reduce_decompress([parts[c].reshape(-1) for c in order], None, rows, cols, rate)
         got = gpu.zc2d_reduce_decompress([dev[c] for c in order], None, rows, cols, rate)
         _same_floats(_host(got), want, "reduce_decompress of " + order)
+
+
+@pytest.mark.parametrize("cols", (1, 3, 4, 7, 8, 12, 13, 20, 23, 24, 31, 33, 100, 250, 252, 254, 260))
+def test_many_rows_of_few_blocks(gpu, ref, cols):
+    """At least 131072 blocks of 1 to 65 per block row: a wavefront of the wide decoding kernels spans up to 64 block
+    rows, several times over, and stores whole and partial rows of each; nothing is written past the matrix."""
+    import torch
+    bc = (cols + 3) // 4
+    rows = (131072 + bc - 1) // bc * 4 + 4 * 37 + cols % 3
+    n = rows * cols
+    rng = np.random.default_rng(cols)
+    x = (rng.standard_normal((rows, cols)) * np.exp2(rng.integers(-6, 7, size=(rows, 1)))).astype(np.float32)
+    y = rng.standard_normal((rows, cols)).astype(np.float32)
+    for rate in (2, 4, 8):
+        print("few blocks per row", rows, cols, rate, flush=True)
+        cx, cy = ref.compress(x, rate), ref.compress(y, rate)
+        dx, dy = gpu.zc2d_compress(_dev(x), rate), _dev(cy)
+        _same_bytes(_host(dx), cx, rate, "compress")
+        want = ref.decompress(cx, rows, cols, rate)
+        out = torch.full((n + 512,), 12345.0, device="cuda")
+        gpu.zc2d_decompress(dx, rows, cols, rate, d_out=out)
+        _same_floats(_host(out[:n]).reshape(rows, cols), want, "decompress")
+        assert bool((out[n:] == 12345.0).all()), "written past the end"
+        half = torch.full((n + 512,), 12345.0, device="cuda", dtype=torch.bfloat16)
+        gpu.zc2d_decompress_half(dx, rows, cols, rate, d_out=half)
+        assert torch.equal(half[:n].view(torch.int16), out[:n].to(torch.bfloat16).view(torch.int16)), "to bf16"
+        assert bool((half[n:] == torch.tensor(12345.0, dtype=torch.bfloat16)).all()), "written past the end"
+        got = gpu.zc2d_reduce_compressed([dx, dy], rows, cols, rate)
+        _same_bytes(_host(got), ref.reduce_compressed([cx, cy], rows, cols, rate), rate, "reduce")
+        out.fill_(12345.0)
+        gpu.zc2d_reduce_decompress([dx, dy], None, rows, cols, rate, d_out=out)
+        _same_floats(_host(out[:n]).reshape(rows, cols), ref.reduce_decompress([cx, cy], None, rows, cols, rate), "reduce_decompress")
+        assert bool((out[n:] == 12345.0).all()), "written past the end"
