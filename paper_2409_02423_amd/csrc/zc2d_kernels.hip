@@ -60,9 +60,10 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
 // the kernels were before: 0.270 against 0.248 ms for decompress2d, 0.613 against 0.583 ms for the reduce;
 // 1024: 0.599 ms.)
 // Their grid, us of 8192 x 32768 values at rate 4: decompress2d 234, 222 and 222 at 16, 24 and 32, the 2-way reduce
-// with fp32 output 384, 357, 362 and 386 at 24, 48, 64 and 96.  With rows that are aligned to their
-// elements only, decompress2d gains from more: neighbouring wavefronts write to the same cache lines and
-// should do so at the same time (6144 x 43690 values at rate 4: 279 at 48, 250 at 64; at rate 8 274 and 277).  The
+// with fp32 output 384, 357, 362 and 386 at 24, 48, 64 and 96.  With fp32 rows that do not start at
+// 64 bytes, decompress2d gains from more: neighbouring wavefronts write to the same cache lines and
+// should do so at the same time (6144 x 43690 values at rate 4: 279 at 48, 250 at 64; at rate 8 274 and 277; 6144 x 43688 at rate 4
+// 309 at 24, 255 at 64, at rate 8 298 and 240).  The
 // reduce with local values and fp32 output is like it (522 at 24, 457 at 64).  The reduces that write streams
 // keep 24: 469 at 16, 24 and 32.
 // The compress kernel has 16, and 64 where that leaves a lane four blocks or more: with one block per lane a
@@ -887,7 +888,7 @@ unsigned grid_for(size_t blocks, int preset, int threads, int cus) {
 // lane: from 12 per CU on a lane has two blocks or more.  (us at 24 per CU, one block per lane, and at 12: decompress2d of 8192 x
 // 6144 bf16 values at rate 8 46.8 and 43.9, at rate 16 86.4 and 84.3; 8192 x 8192 fp32 values, one or two at 24 and two or three at 12, at
 // rate 4 47.7 and 45.5, 2-way reduce 115.8 and 113.2; one chunk and local values of 8192 x 6144 at rate 8 99.0 and 94.1.  decompress2d with fp32 rows
-// aligned to their elements only keeps one: 5000 x 10003 values at rate 4 41.0 and 52.4.)
+// that do not start at 64 bytes keeps one: 5000 x 10003 values at rate 4 41.0 and 52.4, 5000 x 10004 41.2 and 56.0.)
 unsigned decode_grid_for(size_t blocks, int preset, int threads, int cus) {
   const size_t groups = (blocks + threads - 1) / threads, least = (size_t)cus * kDecodeWorkgroupsPerCULeast;
   const unsigned most = grid_for(blocks, preset, threads, cus);
@@ -904,16 +905,19 @@ int decode_threads(size_t blocks, int cus) { return blocks < (size_t)cus * kDeco
 
 // How the wide decoding kernels store values that come as rows.  fp32 rows aligned to their elements only go from a
 // block per lane: four pieces of 256 bytes that share cache lines with their neighbours took 0.312 instead of 0.281 ms, 6144 x
-// 43690 values at rate 4; of half-precision rows the pieces are better, 40 against 44 us for 8192 x 6145 values.
+// 43690 values at rate 4; of half-precision rows the pieces are better, 40 against 44 us for 8192 x 6145 values.  So it is with rows of
+// `per_piece` values' alignment: decompress2d at rates 2 and 4, which wait for memory most, wants the pieces' ends on 64 bytes (us in
+// pieces and from a block per lane, the grid being kDecodeWorkgroupsPerCUWide: 5000 x 10004 values 53.5 and 41.2 at rate 2, 52.0 and
+// 41.4 at rate 4, but 46.5 and 50.6 at rate 8; 2-way reduce to fp32 at rate 4 59.5 and 63.5).
 // With few blocks per block row, a wavefront's 64 blocks span many of these, and a row at a time would write a quarter of each
 // cache line, four times: 16 blocks at a time fill whole lines but for both ends (us, decompress2d at rate 4 from a block per lane and
 // in pieces: 2097152 x 4 values 43.8 and 10.2, to bf16 15.4 and 10.0, 2-way reduce to fp32 42.7 and 14.9; 400000 x 13 13.6 and
 // 11.7, 400001 x 23 18.6 and 17.0; 300001 x 31 16.1 and 15.2; but 262144 x 32 9.4 and 9.8, 65536 x 100 9.4 and 14.1).  Of rows aligned to their
 // elements only the ends then meet in the second-level cache (plain stores; without, 400001 x 26 21.6 instead of 16.1; of
 // others with them, 1048576 x 8 at rate 8 13.0 instead of 11.6).
-uint32_t store_form(size_t cols, bool half) {
+uint32_t store_form(size_t cols, bool half, size_t per_piece) {
   const size_t bc = (cols + 3) / 4;
-  return (half || (cols & 3) == 0 ? kPieces : 0u) | (bc <= 5 || (bc <= 8 && (cols & 3) != 0) ? kNarrowPieces : 0u);
+  return (half || cols % per_piece == 0 ? kPieces : 0u) | (bc <= 5 || (bc <= 8 && (cols & 3) != 0) ? kNarrowPieces : 0u);
 }
 
 Walk walk_for(size_t rows, size_t cols, unsigned grid, int threads, uint32_t pieces = 0) {
@@ -979,9 +983,9 @@ int launch_decompress2d(const void* d_in, size_t rows, size_t cols, int rate, vo
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int cus = compute_units(), threads = decode_threads(blocks, cus);
-  const unsigned grid = (cols & 3) && DT == kF32 ? grid_for(blocks, kDecodeWorkgroupsPerCUWide, threads, cus)
+  const unsigned grid = (cols & 15) && DT == kF32 ? grid_for(blocks, kDecodeWorkgroupsPerCUWide, threads, cus)
                         : decode_grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
-  const Walk w = walk_for(rows, cols, grid, threads, store_form(cols, DT != kF32));
+  const Walk w = walk_for(rows, cols, grid, threads, store_form(cols, DT != kF32, rate <= 4 ? 16 : 4));
 #define LAUNCH(R, T) hipLaunchKernelGGL((decompress2d_kernel<R, DT, T>), dim3(grid), dim3(T), 0, s, static_cast<const uint8_t*>(d_in), w, d_out)
 #define CALL(R)                                                                \
   do {                                                                         \
@@ -1015,7 +1019,7 @@ int launch_reduce2d(const void* const* d_in, int k, const float* d_local, size_t
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int cus = compute_units(), threads = decode_threads(blocks, cus);
   const unsigned grid = decode_grid_for(blocks, raw_out ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
-  const Walk w = walk_for(rows, cols, grid, threads, store_form(cols, false));
+  const Walk w = walk_for(rows, cols, grid, threads, store_form(cols, false, 4));
   uint8_t* out = static_cast<uint8_t*>(d_out);
 #define LAUNCH(R, LOCAL, RAW, T) \
   hipLaunchKernelGGL((reduce2d_kernel<R, LOCAL, RAW, T>), dim3(grid), dim3(T), 0, s, chunks, k, d_local, w, out, d_out_raw)
