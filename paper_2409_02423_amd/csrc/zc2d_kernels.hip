@@ -63,7 +63,9 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
 // with fp32 output 384, 357, 362 and 386 at 24, 48, 64 and 96.  With fp32 rows that do not start at
 // 64 bytes, decompress2d gains from more: neighbouring wavefronts write to the same cache lines and
 // should do so at the same time (6144 x 43690 values at rate 4: 279 at 48, 250 at 64; at rate 8 274 and 277; 6144 x 43688 at rate 4
-// 309 at 24, 255 at 64, at rate 8 298 and 240).  The
+// 309 at 24, 255 at 64, at rate 8 298 and 240).  Half-precision rows, half as long, do so at rate 2 where the matrix is larger
+// than the last-level cache (8192 x 24580 values 141 and 134, 8192 x 28676 201 and 152, but 12288 x 12292 97 and 107; at rate 4 132 and
+// 139, 155 and 159, 98 and 109).  The
 // reduce with local values and fp32 output is like it (522 at 24, 457 at 64).  The reduces that write streams
 // keep 24: 469 at 16, 24 and 32.
 // The compress kernel has 16, and 64 where that leaves a lane four blocks or more: with one block per lane a
@@ -74,6 +76,7 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
 // no environment variable.
 constexpr int kCompressWorkgroupsPerCU = 16, kCompressWorkgroupsPerCUMost = 64, kDecodeWorkgroupsPerCU = 24, kDecodeWorkgroupsPerCUWide = 64,
               kDecodeWorkgroupsPerCULeast = 12;
+constexpr size_t kDecodeBlocksLarge = (size_t)12 << 20;   // 384 MiB of half-precision values
 
 // The wavefront-wide vote of the codec: whether p holds in some lane.
 struct AnyLane {
@@ -983,7 +986,8 @@ int launch_decompress2d(const void* d_in, size_t rows, size_t cols, int rate, vo
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int cus = compute_units(), threads = decode_threads(blocks, cus);
-  const unsigned grid = (cols & 15) && DT == kF32 ? grid_for(blocks, kDecodeWorkgroupsPerCUWide, threads, cus)
+  const bool wide = DT == kF32 ? (cols & 15) != 0 : rate == 2 && (cols & 31) != 0 && blocks >= kDecodeBlocksLarge;
+  const unsigned grid = wide ? grid_for(blocks, kDecodeWorkgroupsPerCUWide, threads, cus)
                         : decode_grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
   const Walk w = walk_for(rows, cols, grid, threads, store_form(cols, DT != kF32, rate <= 4 ? 16 : 4));
 #define LAUNCH(R, T) hipLaunchKernelGGL((decompress2d_kernel<R, DT, T>), dim3(grid), dim3(T), 0, s, static_cast<const uint8_t*>(d_in), w, d_out)
