@@ -560,3 +560,23 @@ def test_many_rows_of_few_blocks(gpu, ref, cols):
         gpu.zc2d_reduce_decompress([dx, dy], None, rows, cols, rate, d_out=out)
         _same_floats(_host(out[:n]).reshape(rows, cols), ref.reduce_decompress([cx, cy], None, rows, cols, rate), "reduce_decompress")
         assert bool((out[n:] == 12345.0).all()), "written past the end"
+
+
+@pytest.mark.parametrize("rate", (2, 4))
+@pytest.mark.parametrize("rows, cols", [(1152, 6148), (1153, 6147), (2048, 6144)])
+def test_last_hop_of_few_passes(gpu, rate, rows, cols):
+    """3.4 to 6 workgroups of blocks per CU: the reduce of one chunk with local values and fp32 output takes them in two workgroups
+    per CU of several passes.  It equals its calls on slices of 32 block rows, which are of one pass."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rate + cols)
+    x = torch.randn((rows, cols), generator=g, device="cuda") * torch.randint(-8, 9, (rows, 1), generator=g, device="cuda").float().exp2()
+    y = torch.randn((rows, cols), generator=g, device="cuda")
+    part, step = 32 * ((cols + 3) // 4) * 2 * rate, 128
+    print("last hop", rows, cols, rate, flush=True)
+    cx = gpu.zc2d_compress(x, rate)
+    got = gpu.zc2d_reduce_decompress([cx], y, rows, cols, rate)
+    for i, r in enumerate(range(0, rows, step)):
+        s, v = cx[i * part:(i + 1) * part].clone(), y[r:r + step].clone()
+        want = gpu.zc2d_reduce_decompress([s], v, v.shape[0], cols, rate)
+        assert torch.equal(got[r:r + step].view(torch.int32), want.view(torch.int32)), (rate, r)
