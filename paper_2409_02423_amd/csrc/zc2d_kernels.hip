@@ -903,8 +903,13 @@ unsigned decode_grid_for(size_t blocks, int preset, int threads, int cus) {
 // Lanes per workgroup of a decoding kernel: the fewer where the wide ones would not be one per CU.
 // (us with 512 and 256 lanes, 2-way reduce at rates 4 and 16: 64 x 256 values 8.6 and 7.3, 16.7 and
 // 13.3; 512 x 1024 8.9 and 7.5, 17.0 and 14.0; 700 x 2500, just below the line, 9.1 and 8.9, 17.4
-// and 17.2; 1024 x 2048, on it, 9.1 both, 17.4 and 17.3; 2048 x 4096 23.1 and 24.1, 49.1 and 50.3.)
-int decode_threads(size_t blocks, int cus) { return blocks < (size_t)cus * kDecodeThreads ? kDecodeThreadsSmall : kDecodeThreads; }
+// and 17.2; 1024 x 2048, on it, 9.1 both, 17.4 and 17.3; 2048 x 4096 23.1 and 24.1, 49.1 and 50.3.  On the line at rate 2, where the
+// wide form's product gives least, 1024 x 2048 values 5.1 and 4.6 to decompress, 10.5 and 10.0 to reduce three chunks, but with local
+// values 5.9 and 6.3.)
+int decode_threads(size_t blocks, int rate, bool local, int cus) {
+  const size_t line = (size_t)cus * kDecodeThreads;
+  return blocks < line || (rate == 2 && !local && blocks == line) ? kDecodeThreadsSmall : kDecodeThreads;
+}
 
 // How the wide decoding kernels store values that come as rows.  fp32 rows aligned to their elements only go from a
 // block per lane: four pieces of 256 bytes that share cache lines with their neighbours took 0.312 instead of 0.281 ms, 6144 x
@@ -985,7 +990,7 @@ int launch_decompress2d(const void* d_in, size_t rows, size_t cols, int rate, vo
   if (rows > kMaxValues || cols > kMaxValues || rows > kMaxValues / cols) return ZC_ERR_SIZE;
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int cus = compute_units(), threads = decode_threads(blocks, cus);
+  const int cus = compute_units(), threads = decode_threads(blocks, rate, false, cus);
   const bool wide = DT == kF32 ? (cols & 15) != 0 : rate == 2 && (cols & 31) != 0 && blocks >= kDecodeBlocksLarge;
   const unsigned grid = wide ? grid_for(blocks, kDecodeWorkgroupsPerCUWide, threads, cus)
                         : decode_grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
@@ -1021,7 +1026,7 @@ int launch_reduce2d(const void* const* d_in, int k, const float* d_local, size_t
   if (!raw_out && out_cap < zc2d_compressed_size(rows, cols, rate)) return ZC_ERR_CAPACITY;
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int cus = compute_units(), threads = decode_threads(blocks, cus);
+  const int cus = compute_units(), threads = decode_threads(blocks, rate, d_local != nullptr, cus);
   // One chunk, local values and fp32 output at rates 2 and 4 wait for memory, and workgroups of one pass of each lane, of which three fit a CU,
   // leave the last ones by themselves: up to six per CU, all that there are take several passes (us with a workgroup per 512
   // blocks and with two per CU, at rate 4: 1100 x 6144 values, 3.2 per CU, 14.6 and 13.5, 1536 x 6144 17.3 and 15.6, 2048 x

@@ -580,3 +580,21 @@ def test_last_hop_of_few_passes(gpu, rate, rows, cols):
         s, v = cx[i * part:(i + 1) * part].clone(), y[r:r + step].clone()
         want = gpu.zc2d_reduce_decompress([s], v, v.shape[0], cols, rate)
         assert torch.equal(got[r:r + step].view(torch.int32), want.view(torch.int32)), (rate, r)
+
+
+@pytest.mark.parametrize("rate", (2, 4))
+@pytest.mark.parametrize("more", (-4, 0, 4))
+def test_at_the_line_between_the_widths(gpu, ref, rate, more):
+    """As many blocks as 512 lanes per CU, and a block row less and more: where the decoding kernels of 512 lanes start,
+    which at rate 2 and without local values is just past it."""
+    import torch
+    rows, cols = 4 * torch.cuda.get_device_properties(0).multi_processor_count + more, 2048
+    x, y = _matrix(rows, cols, seed=1), _matrix(rows, cols, seed=2, kind="act")
+    print("line", rows, rate, flush=True)
+    cx, cy = ref.compress(x, rate), ref.compress(y, rate)
+    dx, dy = _dev(cx), _dev(cy)
+    _same_floats(_host(gpu.zc2d_decompress(dx, rows, cols, rate)), ref.decompress(cx, rows, cols, rate), "decompress")
+    _same_bytes(_host(gpu.zc2d_reduce_compressed([dx, dy], rows, cols, rate)), ref.reduce_compressed([cx, cy], rows, cols, rate), rate, "reduce")
+    _same_bytes(_host(gpu.zc2d_reduce_mixed([dx], _dev(y), rows, cols, rate)), ref.reduce_mixed([cx], y, rows, cols, rate), rate, "mixed")
+    _same_floats(_host(gpu.zc2d_reduce_decompress([dx, dy], None, rows, cols, rate)), ref.reduce_decompress([cx, cy], None, rows, cols, rate), "two")
+    _same_floats(_host(gpu.zc2d_reduce_decompress([dx], _dev(y), rows, cols, rate)), ref.reduce_decompress([cx], y, rows, cols, rate), "last")
