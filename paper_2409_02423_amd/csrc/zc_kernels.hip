@@ -123,19 +123,19 @@ __device__ __forceinline__ zc::Tables stage_decoder_table(uint32_t* lds, const u
   return decoder_tables<RATE>(lds, enc);
 }
 
-// All tables of the fused reduce: the decoder's (at rate 4 also its half-precision copy) and,
+// All tables of the fused reduce: the decoder's (HALF: also its half-precision copy) and,
 // unless the sum is stored as fp32, the encoder's.
-template <int RATE, bool ENCODER>
+template <int RATE, bool ENCODER, bool HALF>
 __device__ __forceinline__ zc::Tables stage_reduce_tables(uint32_t* dec, uint32_t* dec_half, uint32_t* enc) {
   using Dec = TableCopy<decoder_table_words<RATE>()>;
-  using Half = TableCopy<RATE == 4 ? kDec4HalfWords : 4>;
+  using Half = TableCopy<HALF ? kDec4HalfWords : 4>;
   using Enc = TableCopy<ENCODER ? encoder_table_words<RATE>() : 4>;
-  constexpr int kSteps = Dec::kSteps + (RATE == 4 ? Half::kSteps : 0) + (ENCODER ? Enc::kSteps : 0);
+  constexpr int kSteps = Dec::kSteps + (HALF ? Half::kSteps : 0) + (ENCODER ? Enc::kSteps : 0);
   const Dec d(decoder_table<RATE>());
-  const Half h(RATE == 4 ? reinterpret_cast<const uint32_t*>(g_dec4_half_table.v) : decoder_table<RATE>());
+  const Half h(HALF ? reinterpret_cast<const uint32_t*>(g_dec4_half_table.v) : decoder_table<RATE>());
   const Enc e(ENCODER ? encoder_table<RATE>() : decoder_table<RATE>());
   d.put(dec);
-  if constexpr (RATE == 4) h.put(dec_half);
+  if constexpr (HALF) h.put(dec_half);
   if constexpr (ENCODER) e.put(enc);
   __builtin_amdgcn_sched_group_barrier(0x020, kSteps, 0);   // (for the instruction scheduler: the loads first,
   __builtin_amdgcn_sched_group_barrier(0x200, kSteps, 0);   // then the LDS writes)
@@ -511,7 +511,7 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(ChunkPointers chunks, 
   __shared__ __align__(16) uint32_t dec[decoder_table_words<RATE>()];
   __shared__ __align__(16) uint32_t dec_half[RATE == 4 ? kDec4HalfWords : 4];
   __shared__ __align__(16) uint32_t enc[RAW_OUT ? 4 : encoder_table_words<RATE>()];
-  const zc::Tables tab = stage_reduce_tables<RATE, !RAW_OUT>(dec, dec_half, enc);
+  const zc::Tables tab = stage_reduce_tables<RATE, !RAW_OUT, (RATE == 4)>(dec, dec_half, enc);
   __syncthreads();
   constexpr int NW = zc::Traits<RATE>::kWords;
   constexpr size_t kTile = (size_t)U * kThreads;
@@ -751,7 +751,6 @@ template <int RATE, bool LOCAL, bool RAW_OUT>
 __global__ __launch_bounds__(kThreads) void reduce_small_kernel(ChunkPointers chunks, int k, const float* local, size_t n,
                                                                 uint8_t* out, float* out_raw) {
   __shared__ __align__(16) uint32_t dec[decoder_table_words<RATE>()];
-  __shared__ __align__(16) uint32_t dec_half[RATE == 4 ? kDec4HalfWords : 4];
   __shared__ __align__(16) uint32_t enc[RAW_OUT ? 4 : encoder_table_words<RATE>()];
   constexpr int NW = zc::Traits<RATE>::kWords;
   const size_t j = (size_t)blockIdx.x * kThreads + threadIdx.x, whole = n / 4, blocks = whole + ((n & 3) != 0 ? 1 : 0);
@@ -764,7 +763,7 @@ __global__ __launch_bounds__(kThreads) void reduce_small_kernel(ChunkPointers ch
       else load_values_ragged<kF32>(local, n, x);
     }
   }
-  const zc::Tables tab = stage_reduce_tables<RATE, !RAW_OUT>(dec, dec_half, enc);
+  const zc::Tables tab = stage_reduce_tables<RATE, !RAW_OUT, false>(dec, nullptr, enc);
   __syncthreads();
   if (j >= blocks) return;
   float s[4] = {-0.0f, -0.0f, -0.0f, -0.0f};
