@@ -696,7 +696,7 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
                             AnyActive any_lane_active) {
   constexpr int NW = Traits<RATE>::kWords;
   constexpr int kPayload = Traits<RATE>::kPayloadBits;
-  const uint32_t E = W[0] & 0xFFu;
+  uint32_t E = W[0] & 0xFFu;
   if constexpr (RATE == 4) {
     // one lookup for the whole payload byte (entry 0 is the zero block, which ignores
     // its payload), then only the scaling by 2^(E - 155) is left
@@ -714,12 +714,17 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
     const uint32_t top = W[0] & 0xFFFFFF00u;
     uint32_t lead = count_trailing_zeros_nonzero(top) - 8u;
     if constexpr (NW == 1) lead = umin(lead, (uint32_t)kPayload);   // (for an empty payload too)
+    constexpr bool kZeroApart = BRANCHES && NW > 1;
     bool none = false;   // nothing to decode
-    const auto uncommon = any_lane_active.lanes(!common_exponent(E));
+    auto uncommon = any_lane_active.lanes(!common_exponent(E));
     auto look_closer = uncommon;
     if constexpr (NW > 1) look_closer = look_closer | any_lane_active.lanes(top == 0u);
     if (!BRANCHES || any_lane_active.some(look_closer)) {
-      if constexpr (NW > 1) {
+      // most often for zero blocks, whose scale does not matter and whose planes are not looked at.  (us of 98 % zeros
+      // without and with this: 2-way reduce of 2^25 values at rate 12 73.2 and 71.1, at rate 16 96.5 and 94.1, decompress of 5e6 at
+      // rate 20 8.42 and 8.14; at rate 8, where there is little to save, 58.6 and 59.3)
+      if constexpr (kZeroApart) uncommon = any_lane_active.lanes(E != 0u && !common_exponent(E));
+      if (NW > 1 && (!kZeroApart || any_lane_active(E != 0u && top == 0u))) {
         lead = 0;
         bool found = false;
 #pragma unroll
@@ -746,6 +751,7 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
         left = 0u;
         lead = 0u;
         state = kDecIdle;
+        if constexpr (kZeroApart) E = 127u;   // (the scale of a zero: any positive one)
 #pragma unroll
         for (int j = 0; j < NW; ++j) W[j] = 0u;
       }

@@ -198,3 +198,27 @@ def test_decoded_blocks_are_added_with_one_rounding(oracle, shim, rate, branches
     assert shim.zc_host_add_blocks(rate, branches, s.ctypes.data, n, got.ctypes.data) == 0
     ok = (got.view(np.uint32) == want.view(np.uint32)) | (np.isnan(got) & np.isnan(want))
     assert ok.all(), (rate, branches, np.flatnonzero(~ok)[:5])
+
+
+@pytest.mark.parametrize("rate", RATES)
+@pytest.mark.parametrize("share", (0.5, 0.95, 1.0))
+def test_zero_blocks_side_by_side_with_others(oracle, shim, rate, share):
+    """Lockstep lanes most of which hold zero blocks, with and without a payload (which is ignored), beside blocks with
+    common and uncommon exponent bytes, an empty first word and no payload at all."""
+    rng = np.random.default_rng(60 * rate + int(100 * share))
+    n = 1600
+    s = rng.integers(0, 256, size=(n, rate // 2), dtype=np.uint8)
+    s[:, 0] = np.where((rng.random(n // 80) < 0.4).repeat(80), rng.choice([1, 28, 29, 251, 252, 255], size=n), rng.integers(100, 140, size=n))
+    s[::5, 1:4] = 0
+    s[::11, 1:] = 0
+    zero = rng.random(n) < share
+    s[zero, 0] = 0
+    s[zero & (rng.random(n) < 0.5), 1:] = 0
+    s = np.ascontiguousarray(s.reshape(-1))
+    with np.errstate(all="ignore"):
+        want = oracle.decompress(s, 4 * n, rate)
+    for lanes in (16, 5):
+        got = np.zeros(4 * n, dtype=np.float32)
+        assert shim.zc_host_decode_wave(rate, s.ctypes.data, n, got.ctypes.data, lanes) == 0
+        bad = np.flatnonzero((got.view(np.uint32) != want.view(np.uint32)).reshape(-1, 4).any(axis=1))
+        assert bad.size == 0, (rate, share, lanes, bad[:5])
