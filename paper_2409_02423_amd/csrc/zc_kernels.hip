@@ -860,12 +860,12 @@ unsigned grid_for(size_t n, Kernel kernel, int rate, int blocks_per_lane) {
 // but 11.3 and 11.6 for 2^21; with raw output 4.0 and 3.4, 5.0 and 4.5, 5.9 and 6.1, for 1500001 values 6.9 and 5.5.  At rate 4,
 // whose wide kernels take 512 blocks per wavefront: compress 2^18 3.2 and 2.4, 2^20 3.4 and 2.9, 2^22 4.9 and 6.4;
 // decompress 2.3 and 2.1, 2^19 2.38 and 2.36, 2^20 2.5 and 2.6; reduces 2^18 2.9 and 2.6, 2^20 3.0 and 3.1, of two chunks
-// to a stream 2^17 2.44 and 2.42, 2^18 2.44 and 2.49.)
+// to a stream 2^17 2.44 and 2.42, 2^18 2.44 and 2.49, to fp32 700001 values 2.76 and 2.55 but 2^20 2.65 and 2.78.)
 size_t small_half_groups_per_cu(Kernel kernel, int rate, bool two_chunks) {
   switch (kernel) {
     case kCompress: return rate == 4 ? 8 : 16;
     case kDecompress: return rate == 4 ? 4 : 16;
-    case kReduceRaw: return rate == 4 ? 8 : 12;
+    case kReduceRaw: return rate == 4 ? (two_chunks ? 7 : 8) : 12;
     default: return rate == 4 ? (two_chunks ? 1 : 4) : (rate <= 16 ? 16 : 12);
   }
 }
@@ -1065,7 +1065,7 @@ static int launch_reduce(const void* const* d_in, int k, const float* d_local, s
   if (!raw_out && out_cap < zc_compressed_size(n, rate)) return ZC_ERR_CAPACITY;
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint8_t* out = static_cast<uint8_t*>(d_out);
-  const unsigned small = small_grid(n, raw_out ? kReduceRaw : kReduce, rate, k == 2 && !d_local && !raw_out);
+  const unsigned small = small_grid(n, raw_out ? kReduceRaw : kReduce, rate, k == 2 && !d_local);
 #define LAUNCH_K(R, LOCAL, RAW, K)                                                                            \
   hipLaunchKernelGGL((reduce_kernel<R, reduce_unroll<R>(), LOCAL, RAW, K>), dim3(grid_for(n, RAW ? kReduceRaw : kReduce, R, reduce_unroll<R>())),    \
                      dim3(kThreads), 0, s, chunks, k, d_local, n, out, d_out_raw)

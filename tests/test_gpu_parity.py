@@ -426,3 +426,8 @@ def test_both_sides_of_the_line_for_small_messages(gpu, oracle, rate, per_cu):
         _assert_bytes_equal(_host(gpu.zc_reduce_mixed([ds], _dev(y), n, rate)), oracle.reduce_mixed([s], y, n, rate), rate // 2, "mixed")
         _assert_floats_equal(_host(gpu.zc_reduce_decompress([ds], _dev(y), n, rate)), oracle.reduce_decompress([s], y, n, rate), "last hop")
         _assert_floats_equal(_host(gpu.zc_reduce_decompress([dc, ds], None, n, rate)), oracle.reduce_decompress([c, s], None, n, rate), "raw sum")
+
+
+def test_both_sides_of_the_line_for_two_raw_chunks(gpu, oracle):
+    """Two chunks without local values to fp32 at rate 4: the line lies at 3.5 workgroups of 256 blocks per CU."""
+    test_both_sides_of_the_line_for_small_messages(gpu, oracle, 4, 3.5)
