@@ -178,3 +178,27 @@ def test_no_fallback_when_the_library_is_missing(monkeypatch, tmp_path):
         zc.zc_version()
     with pytest.raises(RuntimeError):
         zc.zc_compressed_size(16, 4)
+
+
+@pytest.mark.parametrize("missing", ("_raw_stream_of", "_current_device"))
+def test_stream_of_a_torch_without_the_short_way(monkeypatch, missing):
+    """The binding asks torch's private functions for the current stream where there are any, and otherwise
+    torch.cuda.current_stream()."""
+    class Stream:
+        cuda_stream = 0x5150
+
+    monkeypatch.setattr(zc.torch.cuda, "current_stream", Stream)
+    monkeypatch.setattr(zc, missing, None)
+    assert zc._stream_handle(None) == 0x5150
+    assert zc._stream_handle(Stream()) == 0x5150
+
+
+@pytest.mark.gpu
+def test_current_stream_both_ways(monkeypatch):
+    import torch
+    for stream in (torch.cuda.default_stream(), torch.cuda.Stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(stream):
+            assert zc._stream_handle(None) == stream.cuda_stream == zc._stream_handle(stream)
+            with monkeypatch.context() as m:
+                m.setattr(zc, "_raw_stream_of", None)
+                assert zc._stream_handle(None) == stream.cuda_stream
