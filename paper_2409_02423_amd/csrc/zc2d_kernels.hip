@@ -301,46 +301,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-// What each lane puts into the product.  A byte of digits goes in as the half-precision number of the same
-// bits, digits * 2^-24 (the matrix instructions take subnormal halves as they are), and comes out
-// as value * 2^(lead - 33) with the weights 64 * weight * 2^9 for the upper eight digits of 16 and 64 *
-// weight * 2 for the lower eight.  The upper digits' bytes are SIGNED ones, the lower digits' all xor 0xAA, so that their
-// lowest bit, of a sixteenth plane, is zero (with all of them xor 0xAA by operations of their own: 2-way reduce of 8192 x
-// 32768 values at rate 8 612 instead of 598 us, with fp32 output 434 instead of 425).  bias: what takes the bytes' offset away, for the upper eight alone
-// and for all.
-struct MatrixOperands { uint32_t weight[64][4]; float bias[2][4][4]; };   // by lane, by lane / 16
-constexpr int kMatrixWords = sizeof(MatrixOperands) / 4;
-constexpr uint32_t half_of_weight(int w, int lg) {   // w * 2^lg, |w| <= 64
-  if (w == 0) return 0;
-  const uint32_t m = (uint32_t)(w < 0 ? -w : w);
-  int e = 0;
-  while ((m >> (e + 1)) != 0) ++e;
-  return (w < 0 ? 0x8000u : 0u) | (uint32_t)(15 + e + lg) << 10 | ((m << (10 - e)) & 0x3FFu);
-}
-constexpr MatrixOperands build_matrix_operands() {
-  MatrixOperands t{};
-  for (int l = 0; l < 64; ++l) {
-    for (int b = 0; b < 4; ++b) {
-      const int w = zc2d::inverse64(l & 15, zc2d::digit_coefficient(l >> 4, b));
-      t.weight[l][b >> 1] |= half_of_weight(zc2d::signed_digit_sign(b) * w, 9) << (16 * (b & 1));
-      t.weight[l][2 + (b >> 1)] |= half_of_weight(w, 1) << (16 * (b & 1));
-    }
-  }
-  for (int p = 0; p < 16; ++p) {
-    int upper = 0, lower = 0;
-    for (int w = 0; w < 4; ++w)
-      for (int b = 0; b < 4; ++b) {
-        const int weight = zc2d::inverse64(p, zc2d::digit_coefficient(w, b));
-        upper += zc2d::signed_digit_bias(b) * weight;
-        lower += zc2d::kDigitBias * weight;
-      }
-    t.bias[0][p >> 2][p & 3] = -(float)upper / 32768.0f;
-    t.bias[1][p >> 2][p & 3] = -(float)(256 * upper + lower) / 8388608.0f;
-  }
-  return t;
-}
-__device__ __align__(16) const MatrixOperands g_matrix = build_matrix_operands();
-
+__device__ __align__(16) const zc2d::MatrixOperands g_matrix = zc2d::build_matrix_operands();
+constexpr int kMatrixWords = sizeof(zc2d::MatrixOperands) / 4;
 
 // Rows of lanes and registers change places: what lane 16*j + i has in register g goes to lane 16*g + i,
 // register j.

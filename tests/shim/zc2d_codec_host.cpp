@@ -106,9 +106,18 @@ extern "C" int zc2d_host_wave(int rate, int encode, const void* in, size_t block
   return 0;
 }
 
-// The matrix form of the decoder on one block, its products summed in whole numbers: false if the block
-// is not covered.
+// The matrix form of the decoder on one block: the bytes, weights and biases that the kernels put into their matrix
+// instructions, multiplied and summed in fp32 from either end, which has to give the same (every sum is exact).  False
+// if the block is not covered.
 namespace {
+constexpr zc2d::MatrixOperands kMatrix = zc2d::build_matrix_operands();
+
+float half_to_float(uint32_t h) {   // (exact; no infinities here)
+  const int e = (int)((h >> 10) & 31u);
+  const float m = e ? __builtin_ldexpf((float)(1024u + (h & 1023u)), e - 25) : __builtin_ldexpf((float)(h & 1023u), -24);
+  return (h & 0x8000u) ? -m : m;
+}
+
 template <int RATE>
 bool dec_matrix(const uint8_t* in, float* x) {
   uint32_t W[zc2d::Traits<RATE>::kWords];
@@ -123,20 +132,27 @@ bool dec_matrix(const uint8_t* in, float* x) {
   const bool more = (lower[0] | lower[1] | lower[2] | lower[3]) != 0;
   if (b.r.left > 0 || (lower[0] >> 16) != 0) return false;
   if (!zc2d::matrix_covers(b.E, b.lead, upper[3] & 0xFFFFu, more ? 15u : 8u)) return false;
-  zc2d::planes_to_digits(upper);
+  zc2d::planes_to_digits<true>(upper);
   zc2d::planes_to_digits(lower);
-  int64_t n[16];
-  for (int w = 0; w < 4; ++w)
-    for (int c = 0; c < 4; ++c) {
-      auto digits = [&](uint32_t word) { return (int64_t)(((word ^ zc2d::kDigitSigns) >> (8 * c)) & 0xFFu) - zc2d::kDigitBias; };
-      n[zc2d::digit_coefficient(w, c)] = 256 * digits(upper[w]) + digits(lower[w]);
-    }
+  for (int w = 0; w < 4; ++w) lower[w] ^= zc2d::kDigitSigns;
   const float scale = zc2d::matrix_scale(b.E, b.lead);
   for (int p = 0; p < 16; ++p) {
-    int64_t sum = 0;
-    for (int c = 0; c < 16; ++c) sum += zc2d::inverse64(p, c) * n[c];
-    const float v = (float)sum / 8388608.0f;
-    if (sum != (int64_t)(v * 8388608.0f)) return false;   // (a sum that a float does not hold)
+    float term[32];
+    int n = 0;
+    for (int w = 0; w < 4; ++w)
+      for (int c = 0; c < 4; ++c) {
+        const uint32_t* weight = kMatrix.weight[16 * w + p];   // what lane 16 w + p has
+        term[n++] = half_to_float((upper[w] >> (8 * c)) & 0xFFu) * half_to_float((weight[c >> 1] >> (16 * (c & 1))) & 0xFFFFu);
+        if (more) term[n++] = half_to_float((lower[w] >> (8 * c)) & 0xFFu) * half_to_float((weight[2 + (c >> 1)] >> (16 * (c & 1))) & 0xFFFFu);
+      }
+    float v = kMatrix.bias[more][p >> 2][p & 3], back = 0.0f;
+    for (int i = 0; i < n; ++i) v += term[i];
+    for (int i = n; i-- > 0;) back += term[i];
+    back += kMatrix.bias[more][p >> 2][p & 3];
+    if (v != back) {
+      for (int i = 0; i < 16; ++i) x[i] = -1e30f;   // (no block's values: the caller sees a difference)
+      return true;
+    }
     if (b.lead <= 2u && (v < 0 ? -v : v) >= zc2d::kMatrixMost) return false;
     x[p] = __builtin_fmaf(v, scale, 0.0f);
   }
