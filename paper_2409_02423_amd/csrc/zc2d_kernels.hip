@@ -66,8 +66,8 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
 // 309 at 24, 255 at 64, at rate 8 298 and 240).  Half-precision rows, half as long, do so at rate 2 where the matrix is larger
 // than the last-level cache (8192 x 24580 values 141 and 134, 8192 x 28676 201 and 152, but 12288 x 12292 97 and 107; at rate 4 132 and
 // 139, 155 and 159, 98 and 109).  The
-// reduce with local values and fp32 output is like it (522 at 24, 457 at 64).  The reduces that write streams
-// keep 24: 469 at 16, 24 and 32.
+// reduce with local values and fp32 output is like it (522 at 24, 457 at 64).  The reduces that write streams have
+// 24: 469 at 16, 24 and 32.  Matrices of fewer than twice these many workgroups' blocks get fewer (see decode_grid_for).
 // The compress kernel has 16, and 64 where that leaves a lane four blocks or more: with one block per lane a
 // workgroup stages its table and asks for its values for nothing else (8192 x 32768 values at rate 4: 238 at 16, 224 at
 // 64, 229 at 128; 8192 x 8192 at rate 2: 48.9 at 16, four blocks per lane, 55.8 at 64, one block; 6144 x 43690 at rate 8
@@ -850,7 +850,8 @@ unsigned grid_for(size_t blocks, int preset, int threads, int cus) {
 }
 
 // The same for the decoding kernels, whose workgroups stage 22 KiB of token table for 8 to 32 KiB of values per block and
-// lane: from 12 per CU on a lane has two blocks or more.  (us at 24 per CU, one block per lane, and at 12: decompress2d of 8192 x
+// lane: one workgroup per 512 blocks up to 12 per CU, 12 per CU while that leaves a lane at most two blocks (up to 24 per CU), then
+// two blocks per lane up to the preset.  (us at 24 per CU, one block per lane, and at 12: decompress2d of 8192 x
 // 6144 bf16 values at rate 8 46.8 and 43.9, at rate 16 86.4 and 84.3; 8192 x 8192 fp32 values, one or two at 24 and two or three at 12, at
 // rate 4 47.7 and 45.5, 2-way reduce 115.8 and 113.2; one chunk and local values of 8192 x 6144 at rate 8 99.0 and 94.1.  decompress2d with fp32 rows
 // that do not start at 64 bytes keeps one: 5000 x 10003 values at rate 4 41.0 and 52.4, 5000 x 10004 41.2 and 56.0.)

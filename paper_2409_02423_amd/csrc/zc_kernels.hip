@@ -1,11 +1,12 @@
 // zc_kernels.hip -- gfx950 kernels and the C ABI of libzc (see include/zc.h).
 //
-// Three streaming kernels, one lane per block of 4 values, grid-stride over the
-// buffer.  All are specialised per rate.  Each lane reads 16 contiguous bytes of
-// fp32 (compress) or RATE/2 contiguous bytes of stream (decompress, reduce), so a
-// wavefront touches one contiguous span per access; the code tables are staged in
-// LDS once per workgroup; the next block is fetched before the current one is
-// coded.  No matrix cores: nothing here is a contraction.
+// Three calls (compress, decompress, reduce), each with a streaming kernel, one lane per block of 4 values
+// and a grid stride over the buffer, in which the next block is fetched before the current one is coded; at
+// rate 4 with a wide form of the first two for whole runs of 512 blocks per wavefront; and with a kernel for small
+// messages of one block per lane, which asks for its block before it stages its tables (see "small messages").
+// All are specialised per rate.  Each lane reads 16 contiguous bytes of fp32 (compress) or RATE/2 contiguous
+// bytes of stream (decompress, reduce), so a wavefront touches one contiguous span per access; the code
+// tables are staged in LDS once per workgroup.  No matrix cores: nothing here is a contraction.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
