@@ -60,12 +60,13 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
 // the kernels were before: 0.270 against 0.248 ms for decompress2d, 0.613 against 0.583 ms for the reduce;
 // 1024: 0.599 ms.)
 // Their grid, us of 8192 x 32768 values at rate 4: decompress2d 234, 222 and 222 at 16, 24 and 32, the 2-way reduce
-// with fp32 output 384, 357, 362 and 386 at 24, 48, 64 and 96.  With fp32 rows that do not start at
-// 64 bytes, decompress2d gains from more: neighbouring wavefronts write to the same cache lines and
-// should do so at the same time (6144 x 43690 values at rate 4: 279 at 48, 250 at 64; at rate 8 274 and 277; 6144 x 43688 at rate 4
-// 309 at 24, 255 at 64, at rate 8 298 and 240).  Half-precision rows, half as long, do so at rate 2 where the matrix is larger
-// than the last-level cache (8192 x 24580 values 141 and 134, 8192 x 28676 201 and 152, but 12288 x 12292 97 and 107; at rate 4 132 and
-// 139, 155 and 159, 98 and 109).  The
+// with fp32 output 384, 357, 362 and 386 at 24, 48, 64 and 96.  With fp32 rows that are aligned to
+// their elements only, at rates 2 and 4 also with those that do not start at 64 bytes, decompress2d gains from more:
+// neighbouring wavefronts write to the same cache lines and should do so at the same time (6144 x 43690 values at rate 4: 279
+// at 48, 250 at 64; at rate 8 274 and 277; 6144 x 43688 at rate 4 309 at 24, 255 at 64).  Where memory is waited for less it does
+// so from where the output is larger than the last-level cache: at rate 8 rows that do not start at 64 bytes (8192 x 12292 values 91 at
+// 24, 96 at 64; 10000 x 12292 136 and 113; 6144 x 43688 298 and 240), at rate 2 half-precision ones that do not start at cache lines
+// (12288 x 12292 97 and 107, 8192 x 24580 141 and 134, 8192 x 28676 201 and 152; at rate 4 98 and 109, 132 and 139, 155 and 159).  The
 // reduce with local values and fp32 output is like it (522 at 24, 457 at 64).  The reduces that write streams have
 // 24: 469 at 16, 24 and 32.  Matrices of fewer than twice these many workgroups' blocks get fewer (see decode_grid_for).
 // The compress kernel has 16, and 64 where that leaves a lane four blocks or more: with one block per lane a
@@ -76,7 +77,7 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
 // no environment variable.
 constexpr int kCompressWorkgroupsPerCU = 16, kCompressWorkgroupsPerCUMost = 64, kDecodeWorkgroupsPerCU = 24, kDecodeWorkgroupsPerCUWide = 64,
               kDecodeWorkgroupsPerCULeast = 12;
-constexpr size_t kDecodeBlocksLarge = (size_t)12 << 20;   // 384 MiB of half-precision values
+constexpr size_t kDecodeBytesLarge = (size_t)448 << 20;   // of output
 
 // The wavefront-wide vote of the codec: whether p holds in some lane.
 struct AnyLane {
@@ -854,7 +855,7 @@ unsigned grid_for(size_t blocks, int preset, int threads, int cus) {
 // two blocks per lane up to the preset.  (us at 24 per CU, one block per lane, and at 12: decompress2d of 8192 x
 // 6144 bf16 values at rate 8 46.8 and 43.9, at rate 16 86.4 and 84.3; 8192 x 8192 fp32 values, one or two at 24 and two or three at 12, at
 // rate 4 47.7 and 45.5, 2-way reduce 115.8 and 113.2; one chunk and local values of 8192 x 6144 at rate 8 99.0 and 94.1.  decompress2d with fp32 rows
-// that do not start at 64 bytes keeps one: 5000 x 10003 values at rate 4 41.0 and 52.4, 5000 x 10004 41.2 and 56.0.)
+// that take the wide grid keeps one: 5000 x 10003 values at rate 4 41.0 and 52.4, 5000 x 10004 41.2 and 56.0.)
 unsigned decode_grid_for(size_t blocks, int preset, int threads, int cus) {
   const size_t groups = (blocks + threads - 1) / threads, least = (size_t)cus * kDecodeWorkgroupsPerCULeast;
   const unsigned most = grid_for(blocks, preset, threads, cus);
@@ -954,7 +955,9 @@ int launch_decompress2d(const void* d_in, size_t rows, size_t cols, int rate, vo
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int cus = compute_units(), threads = decode_threads(blocks, rate, false, cus);
-  const bool wide = DT == kF32 ? (cols & 15) != 0 : rate == 2 && (cols & 31) != 0 && blocks >= kDecodeBlocksLarge;
+  const bool large = blocks * 16 * (DT == kF32 ? 4 : 2) >= kDecodeBytesLarge;
+  const bool wide = DT == kF32 ? (cols & 3) != 0 || ((cols & 15) != 0 && (rate <= 4 || (rate == 8 && large)))
+                               : rate == 2 && (cols & 31) != 0 && large;
   const unsigned grid = wide ? grid_for(blocks, kDecodeWorkgroupsPerCUWide, threads, cus)
                         : decode_grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
   const Walk w = walk_for(rows, cols, grid, threads, store_form(cols, DT != kF32, rate <= 4 ? 16 : 4));
