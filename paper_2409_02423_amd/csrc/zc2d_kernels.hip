@@ -993,14 +993,15 @@ int launch_reduce2d(const void* const* d_in, int k, const float* d_local, size_t
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int cus = compute_units(), threads = decode_threads(blocks, rate, d_local != nullptr, cus);
-  // One chunk, local values and fp32 output at rates 2 and 4 wait for memory, and workgroups of one pass of each lane, of which three fit a CU,
-  // leave the last ones by themselves: up to six per CU, all that there are take several passes (us with a workgroup per 512
-  // blocks and with two per CU, at rate 4: 1100 x 6144 values, 3.2 per CU, 14.6 and 13.5, 1536 x 6144 17.3 and 15.6, 2048 x
-  // 6144 21.0 and 20.0, but 2600 x 6144, 7.6 per CU, 25.7 and 26.2, 5000 x 5003, 12 per CU, 42.2 and 42.9, 1024 x 6144, 3 per CU, 11.5 and 11.6, and three
-  // chunks of 2048 x 6144 35.4 and 40.1).
+  // One chunk, local values and fp32 output at rates 2 and 4 wait for memory, and workgroups of one pass of each lane, of which three
+  // fit a CU, leave the last ones by themselves: up to six per CU, those that fit take several passes (us with a workgroup per 512
+  // blocks and with three per CU, at rate 4: 1100 x 6144 values, 3.2 per CU, 14.8 and 12.8, 1536 x 6144 17.5 and 16.4, 2048 x 6144 20.9 and
+  // 19.6, constant values 27.9 and 28.2, with two per CU 31.2; but 3072 x 6144, 9 per CU, 29.6 and 31.0, three chunks of 2048 x 6144 35.4 and
+  // 40.1 with two per CU, 2097152 x 4 33.6 and 35.5, 2000 x 5003 19.7 and 20.0).
   const size_t groups = (blocks + threads - 1) / threads;
-  const bool few = k == 1 && d_local && raw_out && rate <= 4 && groups > (size_t)cus * 3 && groups <= (size_t)cus * 6;
-  const unsigned grid = few ? grid_for(blocks, 2, threads, cus)
+  const bool few = k == 1 && d_local && raw_out && rate <= 4 && (cols & 3) == 0 && cols >= 32 &&
+                   groups > (size_t)cus * 3 && groups <= (size_t)cus * 6;
+  const unsigned grid = few ? grid_for(blocks, 3, threads, cus)
                             : decode_grid_for(blocks, raw_out ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
   const Walk w = walk_for(rows, cols, grid, threads, store_form(cols, false, 4));
   uint8_t* out = static_cast<uint8_t*>(d_out);
