@@ -565,8 +565,8 @@ def test_many_rows_of_few_blocks(gpu, ref, cols):
 @pytest.mark.parametrize("rate", (2, 4))
 @pytest.mark.parametrize("rows, cols", [(1152, 6148), (1153, 6147), (2048, 6144)])
 def test_last_hop_of_few_passes(gpu, rate, rows, cols):
-    """3.4 to 6 workgroups of blocks per CU: the reduce of one chunk with local values and fp32 output takes them in two workgroups
-    per CU of several passes.  It equals its calls on slices of 32 block rows, which are of one pass."""
+    """3.4 to 6 workgroups of blocks per CU: the reduce of one chunk with local values and fp32 output takes them in three workgroups
+    per CU of several passes where rows are aligned.  It equals its calls on slices of 32 block rows, which are of one pass."""
     import torch
     g = torch.Generator(device="cuda")
     g.manual_seed(rate + cols)
