@@ -19,8 +19,8 @@
 //     transposed;
 //   * encoder: a plane is one code word, formed without a loop.  Past the coefficients
 //     already significant, a zero is one bit 0 and a newly significant coefficient two
-//     bits 1 (the end of its token and the next group bit), which two look-ups in a
-//     256-entry table per byte write down; the topmost of these bits is a group bit 0;
+//     bits 1 (the end of its token and the next group bit), which two look-ups, one per
+//     byte of the plane, write down in place; the topmost of these bits is a group bit 0;
 //   * decoder: a table indexed by the next 9 stream bits and by how far the last
 //     coefficient is (whose token has no closing one) decodes all the tokens that lie
 //     whole within those bits.  The window is zero past the budget, which decodes to
@@ -71,7 +71,7 @@ constexpr Order build_order() {
 constexpr Order kOrder = build_order();
 
 // bits of a where mask is set, of b elsewhere (bit operations of three operands take the GPU half as
-// long as its bit-field insert)
+// long as its bit-field insert, as long as all three are in vector registers)
 ZC_DEV constexpr uint32_t select_bits(uint32_t mask, uint32_t a, uint32_t b) {
 #if defined(__HIP_DEVICE_COMPILE__)
   if (!__builtin_is_constant_evaluated()) return __builtin_amdgcn_bitop3_b32(mask, a, b, 0xCA);
@@ -90,43 +90,97 @@ ZC_DEV constexpr uint32_t select_bits_not(uint32_t mask, uint32_t a, uint32_t b)
 // ---- 16 x 16 bit transpose on eight words ----------------------------------------------
 // Row r of a 16 x 16 bit matrix sits in half r >> 3 of word r & 7 (half 0 = bits 0..15).
 // The transpose leaves the matrix in the same arrangement, so it is its own inverse.
-// WHOLE: all eight results are needed (the decoder), so the byte swap is one permute per word;
-// otherwise plain bit operations throughout, which lets the compiler compute only what the
-// planes actually coded ask for (the encoder, which at low rates codes few of the 16).
-template <bool WHOLE>
-ZC_DEV constexpr void transpose_halves(uint32_t (&a)[8]) {
-  // swap the 8 x 8 quadrants: bits 8..15 of row r with bits 0..7 of row r + 8 (the two middle
-  // bytes of each word change places)
-#pragma unroll
-  for (int w = 0; w < 8; ++w) {
-    if (!WHOLE)
-      a[w] = (a[w] & 0xFF0000FFu) | ((a[w] & 0x0000FF00u) << 8) | ((a[w] >> 8) & 0x0000FF00u);
-    else
-      a[w] = zc::permute_bytes(a[w], a[w], 0x03010200u);
+// The encoder makes its words with the 8 x 8 quadrants in their places already (swap_quadrants),
+// which is then one permute per word in all.
+// (Cycles of the GPU: 38 for each of the three steps, one shift to the left for two words at a time, masks in
+// vector registers.  A shift per word and masks in scalar registers took 67, the encoder's bit operations
+// for the quadrants 50 in all.)
+
+// Masks that operations of three operands take from vector registers: from scalar ones such an operation takes the
+// GPU 4.2 cycles instead of 2.5.
+struct SwapMasks { uint32_t v[3]; };
+ZC_DEV constexpr SwapMasks swap_masks() {
+  SwapMasks m = {{0x0F0F0F0Fu, 0x33333333u, 0x55555555u}};
+  if (!__builtin_is_constant_evaluated())
+    for (int i = 0; i < 3; ++i) zc::materialise(m.v[i]);
+  return m;
+}
+
+// a and b shifted to the left by LG, the bits that a loses at b's lower end (one instruction, as long as one for a
+// single word); with LG = 1 each by itself, as an addition.
+template <int LG>
+ZC_DEV void shift_left_two_here(uint32_t& a, uint32_t& b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (LG == 1) {
+    asm("v_add_u32 %0, %1, %1" : "=v"(a) : "v"(a));
+    asm("v_add_u32 %0, %1, %1" : "=v"(b) : "v"(b));
+  } else {
+    uint64_t both = (uint64_t)b << 32 | a;
+    asm("v_lshlrev_b64 %0, %1, %2" : "=v"(both) : "n"(LG), "v"(both));
+    a = (uint32_t)both;
+    b = (uint32_t)(both >> 32);
   }
-  // then 4 x 4, 2 x 2 and 1 x 1 blocks between words j apart; each mask's complement is the
-  // mask shifted up by j, so a result is one shift and one bit-field insert
-  constexpr uint32_t mask[3] = {0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
-  int m = 0;
+#else
+  b = b << LG | (LG == 1 ? 0u : a >> (32 - LG));
+  a <<= LG;
+#endif
+}
+template <int LG>
+ZC_DEV constexpr void shift_left_two(uint32_t& a, uint32_t& b) {
+  if (!__builtin_is_constant_evaluated()) {
+    shift_left_two_here<LG>(a, b);
+  } else {
+    b = b << LG | (LG == 1 ? 0u : a >> (32 - LG));
+    a <<= LG;
+  }
+}
+
+ZC_DEV constexpr void swap_quadrants(uint32_t (&a)[8]) {
+  // bits 8..15 of row r with bits 0..7 of row r + 8 (the two middle bytes of each word change places)
 #pragma unroll
-  for (int j = 4; j >= 1; j >>= 1, ++m)
+  for (int w = 0; w < 8; ++w) a[w] = zc::permute_bytes(a[w], a[w], 0x03010200u);
+}
+
+// JLG = 2, 1, 0: the 4 x 4, 2 x 2 and 1 x 1 blocks between words j = 2^JLG apart; each mask's complement is the
+// mask shifted up by j, and so is what the words of a pair leave at each other's lower end.
+template <int JLG>
+ZC_DEV constexpr void swap_blocks(uint32_t (&a)[8], const SwapMasks& masks) {
+  constexpr int j = 1 << JLG;
+  const uint32_t mask = masks.v[2 - JLG];
 #pragma unroll
-    for (int w = 0; w < 8; ++w)
-      if ((w & j) == 0) {
-        const uint32_t lo = a[w], hi = a[w + j];
-        a[w] = select_bits(mask[m], lo, hi << j);
-        a[w + j] = select_bits(mask[m], lo >> j, hi);
-      }
+  for (int w = 0; w < 8; ++w)
+    if ((w & j) == 0 && (JLG == 0 ? (w & 2) == 0 : (w & 1) == 0)) {
+      const int v = w + (JLG == 0 ? 2 : 1);   // two words at a time, w and v
+      const uint32_t lo0 = a[w], lo1 = a[v], hi0 = a[w + j], hi1 = a[v + j];
+      uint32_t up0 = hi0, up1 = hi1;
+      shift_left_two<j>(up0, up1);
+      a[w] = select_bits(mask, lo0, up0);
+      a[v] = select_bits(mask, lo1, up1);
+      a[w + j] = select_bits(mask, lo0 >> j, hi0);
+      a[v + j] = select_bits(mask, lo1 >> j, hi1);
+    }
+}
+ZC_DEV constexpr void swap_all_blocks(uint32_t (&a)[8]) {
+  const SwapMasks masks = swap_masks();
+  swap_blocks<2>(a, masks);
+  swap_blocks<1>(a, masks);
+  swap_blocks<0>(a, masks);
+}
+ZC_DEV constexpr void transpose_halves(uint32_t (&a)[8]) {
+  swap_quadrants(a);
+  swap_all_blocks(a);
 }
 
 // ---- tables --------------------------------------------------------------------------
 // Encoder.  Behind a plane's first group bit, a coefficient that is still zero is one bit 0 and
-// one that becomes significant is two bits 1: the end of its token and the next group bit.  Both
-// tables hold that expansion X(c) of eight coefficients c, for the two bytes of what a plane has
-// past the coefficients already significant.  v[c], the lower byte: bit 0 the first group bit (a
-// one), X(c) from bit 1 up (17 bits in all), and in the upper half how far the upper byte's
-// expansion moves up to follow it, 1 + 8 + (ones of c), from bit 20 up.  v[256 + c], the upper
-// byte: X(c).
+// one that becomes significant is two bits 1: the end of its token and the next group bit; the last
+// coefficient has neither, and is one bit 1 here, which only marks where the code ends.  Both tables hold
+// that expansion X(c) of eight coefficients c, for the two bytes of a plane without the coefficients
+// already significant.  These are zeros in it, one bit each, which is the room that their own bits take
+// before the group bit: so a byte's place does not depend on how many they are.  v[c], the lower byte: X(c) from
+// bit 1 up (the group bit lies below the first coefficient that is not yet significant), and in the
+// upper half how far the upper byte's expansion moves up to follow it, 8 + (ones of c), from bit 20 up.
+// v[256 + c], the upper byte: X(c) from bit 1 up.
 constexpr int kExpandEntries = 512;
 constexpr uint32_t kExpandBits = 0x1FFFFu;
 constexpr int kExpandShift = 20;
@@ -139,8 +193,8 @@ constexpr ExpandTable build_expand_table() {
       if ((c >> p) & 1) e |= 3u << at++;
       ++at;
     }
-    t.v[c] = 1u | e << 1 | (at + 1) << kExpandShift;
-    t.v[256 + c] = e;
+    t.v[c] = e << 1 | at << kExpandShift;
+    t.v[256 + c] = (c & 0x80 ? e ^ 1u << (at - 1) : e) << 1;   // (the last coefficient's second bit)
   }
   return t;
 }
@@ -201,7 +255,6 @@ constexpr TokenTable build_token_table() {
 }
 
 namespace selfcheck {
-template <bool WHOLE>
 constexpr bool transpose_ok() {
   uint32_t a[8] = {}, ref[8] = {};
   uint32_t s = 0x9E3779B9u;
@@ -209,12 +262,12 @@ constexpr bool transpose_ok() {
   for (int r = 0; r < 16; ++r)
     for (int b = 0; b < 16; ++b)
       ref[b & 7] |= ((a[r & 7] >> (16 * (r >> 3) + b)) & 1u) << (16 * (b >> 3) + r);
-  transpose_halves<WHOLE>(a);
+  transpose_halves(a);
   for (int w = 0; w < 8; ++w)
     if (a[w] != ref[w]) return false;
   return true;
 }
-static_assert(transpose_ok<true>() && transpose_ok<false>(), "16 x 16 bit transpose");
+static_assert(transpose_ok(), "16 x 16 bit transpose");
 }  // namespace selfcheck
 
 // ---- forward ---------------------------------------------------------------------------
@@ -228,9 +281,10 @@ ZC_DEV void lift_forward(int32_t& a, int32_t& b, int32_t& c, int32_t& d) {
 }
 
 // x: the block row-major as fp32 bit patterns.  Returns E and the negabinary words in
-// coefficient order.
+// coefficient order.  E is the exponent field of the largest magnitude plus one, also where that is zero.
+// The result says whether some block of the wavefront is a tiny one, whose largest magnitude is below 2^-101 and not zero.
 template <class AnyActive>
-ZC_DEV void forward_transform(const uint32_t (&x)[16], uint32_t& E, uint32_t (&u)[16], AnyActive any_lane_active) {
+ZC_DEV bool forward_transform(const uint32_t (&x)[16], uint32_t& E, uint32_t (&u)[16], AnyActive any_lane_active) {
   // largest magnitude as a bit pattern (on the device a float maximum with |x| operands, as in
   // the 1-D codec: the same pattern for finite values, a third of the instructions)
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -244,17 +298,18 @@ ZC_DEV void forward_transform(const uint32_t (&x)[16], uint32_t& E, uint32_t (&u
 #pragma unroll
   for (int i = 0; i < 16; ++i) m = umax(m, x[i] & 0x7FFFFFFFu);
 #endif
-  E = (m >> 23) + (m != 0u ? 1u : 0u);
+  E = (m >> 23) + 1u;
   int32_t q[16];
-  if (any_lane_active(E - 1u < 26u)) {
+  const bool tiny = any_lane_active(m - 1u < (26u << 23) - 1u);
+  if (tiny) {
     const int scale = 127 + kFractionBits - (int)E;
 #pragma unroll
     for (int i = 0; i < 16; ++i) q[i] = (int32_t)__builtin_ldexpf(zc::bits_to_float(x[i]), scale);
   } else {
-    // the power of two is a float (for a zero block anything finite does), and a multiplication takes the GPU half
+    // the power of two is a float (for a zero block some finite number), and a multiplication takes the GPU half
     // as long as its ldexp (us before and after: 2-way reduce of 8192 x 32768 values at rate 8 604.8 and 598, compress2d of
     // 8192 x 6144 bf16 values 53.9 and 52.1)
-    const float scale = zc::bits_to_float((254u + kFractionBits - umax(E, 27u)) << 23);
+    const float scale = zc::bits_to_float(((253u + kFractionBits) << 23) - (m & 0x7F800000u));
 #pragma unroll
     for (int i = 0; i < 16; ++i) q[i] = (int32_t)(zc::bits_to_float(x[i]) * scale);
   }
@@ -264,87 +319,116 @@ ZC_DEV void forward_transform(const uint32_t (&x)[16], uint32_t& E, uint32_t (&u
   for (int c = 0; c < 4; ++c) lift_forward(q[c], q[4 + c], q[8 + c], q[12 + c]);
 #pragma unroll
   for (int c = 0; c < 16; ++c) u[c] = ((uint32_t)q[kOrder.v[c]] + 0xAAAAAAAAu) ^ 0xAAAAAAAAu;
+  return tiny;
+}
+
+// Constants of encode_plane that are wanted in vector registers (see SwapMasks).
+struct PlaneConstants { uint32_t expand_bits, top, ones; };
+ZC_DEV PlaneConstants plane_constants() {
+  PlaneConstants k = {kExpandBits, 0x80000000u, 0xFFFFFFFFu};
+  zc::materialise(k.expand_bits);
+  zc::materialise(k.top);
+  zc::materialise(k.ones);
+  return k;
 }
 
 // One plane of the embedded code, appended to the window W as one code word: the bits of the
-// coefficients already significant, then the group tests.  pat: the plane's bit of each
-// coefficient; m = 32 + how many leading coefficients are significant (shift counts and field
-// widths use their low five bits, and the word's length falls out as m less a count of leading
-// zeros); known: all patterns so far; left: budget; last_reached (the same in every lane): with VOTES,
-// whether some lane's pattern has ever had the last coefficient.
+// coefficients already significant, then the group tests.  plane: the plane's bit of each
+// coefficient, in its lower half or (UPPER) in its upper half; sig: ones for the leading coefficients that are significant;
+// left: budget.
 // The tokens' starts and ends come from two look-ups (see ExpandTable) without any case
 // distinction: the topmost bit of the expansion is the group bit after the last one, or the
-// plane's only one, and both are zeros in the code.  Only the last coefficient is different (no
-// end, no group bit after it; and no group test at all once it is significant), so with it reached
-// the length is counted instead.  At rate 2 (VOTES) that is done where some lane of the
-// wavefront has got there, which few do; from rate 4 on in every plane, because most wavefronts get there and a vote and
-// a branch in each are what the few wavefronts of a small matrix wait for (rate 4 with votes and without: 64 x 256
-// values 3.16 and 2.95, 8192 x 6145 bf16 values 44.2 and 43.5, 2-way reduce of 8192 x 32768 445 and 443).  The length is at most 31.  (Before:
-// starts and ends formed separately, verbatim bits appended on their own, 33 instructions per plane at
-// rate 4 instead of 23.  us of compress2d with those, with votes at every rate and as it is: 64 x 256
-// values at rate 16 4.50, 4.94, 4.35, 8192 x 32768 at rate 16 495, 429, 406, at rate 8 294, 267, 258.)
-template <bool VOTES, int NW, class AnyActive>
-ZC_DEV void encode_plane(uint32_t pat, const uint32_t* expand, uint32_t (&W)[NW], uint32_t& m, uint32_t& known,
-                         uint32_t& left, bool& last_reached, AnyActive any_lane_active) {
-  const uint32_t rest = pat >> (m & 31u);
+// plane's only one, and both are zeros in the code, which is as long as that bit's place tells.  With the last coefficient
+// significant (its bit of sig, before or by this plane) that bit is no part of the code.  The length is at most 31.
+// (Cycles of the GPU per plane at rate 4, at 2.3 for additions, shifts to the right, bit operations and 16-bit
+// operations and 4.3 for anything else and whatever has an operand in a scalar register: 68.  With the pattern moved down by the
+// significant coefficients and the code word up again, and the length counted where the last coefficient is
+// reached, it was 93.  us before and after, with the transpose and the alignment as they are now: compress2d of 8192 x 32768
+// values at rate 4 218 and 205, at rate 8 267 and 234, at rate 16 424 and 345, 8192 x 6144 bf16 values at rate 8 53.5 and 48.2, 64 x 256
+// values at rate 16 4.25 and 3.65; 2-way reduce of 8192 x 32768 values at rate 4 430 and 414, at rate 8 593 and 562, at rate 16 1138 and
+// 1050.)
+template <bool UPPER, int NW>
+ZC_DEV void encode_plane(uint32_t plane, const uint32_t* expand, const PlaneConstants& k, uint32_t (&W)[NW], uint32_t& sig, uint32_t& left) {
+  const uint32_t pat = UPPER ? plane >> 16 : plane;
+  const uint32_t rest = UPPER ? pat & ~sig : pat & ~sig & 0xFFFFu;
   const uint32_t lo = expand[rest & 0xFFu], hi = expand[256u + (rest >> 8)];
-  uint32_t tokens = (lo & kExpandBits) | hi << (lo >> kExpandShift);
+  const uint32_t tokens = zc::and_or(lo, k.expand_bits, sig + 1u) | hi << (lo >> kExpandShift);
   const uint32_t c = count_leading_zeros_nonzero(tokens);
-  uint32_t len = m - c;
-  known |= pat;
-  if (VOTES) last_reached = last_reached || any_lane_active(known >= 0x8000u);
-  // a group bit or an end bit for each coefficient of the rest but the last one's, and one more for each
-  // that becomes significant; with all significant before, their sixteen bits (m >> 4 is 2 or 3)
-  if (!VOTES || last_reached) len = known >= 0x8000u ? 13u + (m >> 4) + (uint32_t)__builtin_popcount(rest) : len;
-  tokens ^= 0x80000000u >> c;
-  const uint32_t code = (pat & ((1u << (m & 31u)) - 1u)) | tokens << (m & 31u);
-  const uint32_t take = umin(len, left);
+  const uint32_t code = zc::and_or(pat, sig, tokens ^ (k.top >> c));
+  sig = k.ones >> (count_leading_zeros_nonzero(sig | rest) & 31u);
+  const uint32_t take = zc::umin16(32u - c - (sig >> 15), left);
   zc::shift_in<NW>(W, code, take);
   left -= take;
-  m = 64u - count_leading_zeros_nonzero(known);
 }
 
 template <int RATE, class AnyActive>
 ZC_DEV void encode_block(const uint32_t (&x)[16], const uint32_t* expand, uint32_t (&W)[Traits<RATE>::kWords],
                          AnyActive any_lane_active) {
   constexpr int NW = Traits<RATE>::kWords;
-  constexpr int kMaxPlanes = Traits<RATE>::kPayloadBits < 32 ? Traits<RATE>::kPayloadBits : 32;
+  constexpr int kPayload = Traits<RATE>::kPayloadBits;
+  constexpr int kMaxPlanes = kPayload < 32 ? kPayload : 32;
+  // in the first so many planes hardly a block of ordinary values spends its budget (on gradients, activations and parameters the first
+  // of 64 blocks does in plane 3, 7 and 15 at rates 4, 8 and 16, the last in 6, 10 and 18), so it is asked from there on
+  // (and at first, for wavefronts of zero blocks)
+  constexpr int kUnasked = kPayload / 20;
   uint32_t E, u[16];
-  forward_transform(x, E, u, any_lane_active);
-  uint32_t any = 0;
+  const bool tiny = forward_transform(x, E, u, any_lane_active);
+  uint32_t any = zc::or3(u[0], u[1], u[2]);
 #pragma unroll
-  for (int c = 0; c < 16; ++c) any |= u[c];
-  const uint32_t lead = count_leading_zeros(any);   // empty planes: one zero bit each
-  const int32_t avail = Traits<RATE>::kPayloadBits - (int32_t)lead;
-  uint32_t left = avail > 0 ? (uint32_t)avail : 0u;
-#pragma unroll
-  for (int c = 0; c < 16; ++c) u[c] <<= (lead & 31u);   // first non-empty plane to bit 31
+  for (int c = 3; c < 15; c += 2) any = zc::or3(any, u[c], u[c + 1]);
+  const uint32_t raw = count_leading_zeros_nonzero(any | u[15]);
+  E &= ~(uint32_t)((int32_t)raw >> 31);             // (the zero block)
+  uint32_t lead = zc::umin16(raw, (uint32_t)kPayload);   // empty planes: one zero bit each
+  uint32_t left = (uint32_t)kPayload - lead;
 #pragma unroll
   for (int j = 0; j < NW; ++j) W[j] = 0;
-  uint32_t m = 32u, known = 0u;
-  bool last_reached = false;
-  uint32_t h[8];
+  if (any_lane_active(left > 0)) {
+    uint32_t h[8], sig = 0u;
+    // the first non-empty plane to bit 31, or, where mostly sixteen planes or less are coded, to bit 15: shifts to the right take the
+    // GPU half as long, and but for tiny blocks (and zero ones) lead is 13 at most: the largest of the 16 numbers is 2^26 or
+    // more, and coefficients below 2^16 would make them 2^19 at most
+    constexpr bool kDown = RATE <= 8;
+    if constexpr (kDown) {
+      if (tiny) {
 #pragma unroll
-  for (int w = 0; w < 8; ++w) h[w] = (u[w] >> 16) | (u[w + 8] & 0xFFFF0000u);
-  transpose_halves<false>(h);
+        for (int c = 0; c < 16; ++c) u[c] <<= umax(lead & 31u, 16u) - 16u;
+        lead = umin(lead, 16u);
+      }
+      const uint32_t down = 16u - lead;
 #pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
-    const int b = 15 - t;
-    encode_plane<(RATE < 4), NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, m, known, left, last_reached, any_lane_active);
-  }
-  if (kMaxPlanes > 16 && any_lane_active(left > 0)) {
+      for (int w = 0; w < 8; ++w) h[w] = zc::permute_bytes(u[w + 8] >> (down & 31u), u[w] >> (down & 31u), 0x05010400u);
+    } else {
 #pragma unroll
-    for (int w = 0; w < 8; ++w) h[w] = (u[w] & 0xFFFFu) | (u[w + 8] << 16);
-    transpose_halves<false>(h);
+      for (int c = 0; c < 16; ++c) u[c] <<= (lead & 31u);
 #pragma unroll
-    for (int t = 16; t < 32; ++t) {
-      if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
-      const int b = 31 - t;
-      encode_plane<(RATE < 4), NW>((b >> 3) ? h[b & 7] >> 16 : h[b & 7] & 0xFFFFu, expand, W, m, known, left, last_reached, any_lane_active);
+      for (int w = 0; w < 8; ++w) h[w] = zc::permute_bytes(u[w + 8], u[w], 0x07030602u);
+    }
+    const PlaneConstants k = plane_constants();
+    swap_all_blocks(h);
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      if (t >= kMaxPlanes || (t >= kUnasked && !any_lane_active(left > 0))) break;
+      if (t < 8) encode_plane<true, NW>(h[7 - t], expand, k, W, sig, left);
+      else encode_plane<false, NW>(h[15 - t], expand, k, W, sig, left);
+    }
+    if (kMaxPlanes > 16 && any_lane_active(left > 0)) {
+      if constexpr (kDown) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) u[c] <<= (lead & 31u);
+      }
+#pragma unroll
+      for (int w = 0; w < 8; ++w) h[w] = zc::permute_bytes(u[w + 8], u[w], 0x05010400u);
+      swap_all_blocks(h);
+#pragma unroll
+      for (int t = 16; t < 32; ++t) {
+        if (t >= kMaxPlanes || !any_lane_active(left > 0)) break;
+        if (t < 24) encode_plane<true, NW>(h[23 - t], expand, k, W, sig, left);
+        else encode_plane<false, NW>(h[31 - t], expand, k, W, sig, left);
+      }
+      static_assert(32 * NW == Traits<RATE>::kBlockBits, "the window is the block");
+      if (any_lane_active(left > 0)) zc::shift_right<NW>(W, left);
     }
   }
-  zc::shift_right<NW>(W, (uint32_t)(32 * NW - Traits<RATE>::kBlockBits) + left);
   W[0] |= E;
 }
 
@@ -592,7 +676,7 @@ ZC_DEV void finish_block(BlockReading<Traits<RATE>::kWords>& b, const uint32_t* 
   constexpr int kMaxPlanes = kPayload < 32 ? kPayload : 32;
   uint32_t h[8], u[16];
   load_planes(planes, h);
-  transpose_halves<true>(h);
+  transpose_halves(h);
 #pragma unroll
   for (int w = 0; w < 8; ++w) zc::materialise(h[w]);   // one transpose, not one per half
   const bool deeper = kMaxPlanes > 16 && any_lane_active(b.r.left > 0);
@@ -618,7 +702,7 @@ ZC_DEV void finish_block(BlockReading<Traits<RATE>::kWords>& b, const uint32_t* 
       read_planes<true>(token, b.r, planes, any_lane_active);
       put_begun_plane(b.r, planes, any_lane_active);
       load_planes(planes, h);
-      transpose_halves<true>(h);
+      transpose_halves(h);
 #pragma unroll
       for (int w = 0; w < 8; ++w) {
         zc::materialise(h[w]);

@@ -117,6 +117,32 @@ def test_blocks_either_side_of_the_scale_that_is_a_float(o2, shim, rate):
         assert np.array_equal(got, ref), rate
 
 
+@pytest.mark.parametrize("rate", RATES)
+def test_encoder_on_every_kind_of_plane(o2, shim, rate):
+    """Blocks whose planes are arbitrary, sparse and dense (what arbitrary streams decode to, so that the last coefficient
+    becomes significant early, late, alone and with its neighbours), and tiny ones with up to 27 empty planes, whose
+    words are aligned the other way, alone and beside ordinary ones."""
+    rng = np.random.default_rng(5200 + rate)
+    s = rng.integers(0, 256, size=(2500, 2 * rate), dtype=np.uint8)
+    for k in range(3):
+        s[k::4] &= rng.integers(0, 256, size=s[k::4].shape, dtype=np.uint8)
+    s[:, 0] = rng.integers(60, 200, size=len(s))
+    planes = np.stack([o2.decode_block(b, rate) for b in s])
+    tiny = np.concatenate([np.ldexp(rng.integers(-1, 2, size=(24, 16)).astype(np.float32), e) for e in range(-149, -99, 3)])
+    x = np.concatenate([planes, tiny]).astype(np.float32)
+    want = np.stack([o2.encode_block(b, rate) for b in x])
+    got = np.zeros_like(want)
+    assert shim.zc2d_host_encode_blocks(rate, x.ctypes.data, len(x), got.ctypes.data) == 0
+    bad = np.flatnonzero((got != want).any(axis=1))
+    assert bad.size == 0, (rate, bad[:5], x[bad[:1]])
+    order = np.concatenate([np.arange(len(planes), len(x)), rng.permutation(len(planes))[:len(tiny)]])
+    rows = np.ascontiguousarray(x[rng.permutation(order)])
+    ref = np.stack([o2.encode_block(b, rate) for b in rows])
+    got = np.zeros_like(ref)
+    assert shim.zc2d_host_wave(rate, 1, rows.ctypes.data, len(rows), got.ctypes.data, 16) == 0
+    assert np.array_equal(got, ref), rate
+
+
 def _blocks_with_lead(rng, rate, blocks, lead):
     """Arbitrary blocks of `lead` empty planes, dense and sparse ones (which have more planes), under exponent
     bytes of every kind."""
