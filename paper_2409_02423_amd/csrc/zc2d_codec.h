@@ -208,19 +208,20 @@ constexpr ExpandTable build_expand_table() {
 // An entry holds all the tokens that lie whole within the look-ahead: group bit, zeros,
 // closing one; a run that reaches the last coefficient needs no closing one, and the plane is
 // closed after it; a group bit 0 closes the plane.
-// Byte 0: how many stream bits were used; byte 1, which is added to n: how many coefficients were
-// passed, and kTokenClosed if the plane is closed; byte 2: how many bits of budget the entry must
-// find; byte 3: the ones, as positions past the current coefficient.
+// Byte 0: how many bits of budget the entry must find; from bit kIndexShift on, where n is kept: how many coefficients were
+// passed; byte 2: the ones, as positions past the current coefficient; byte 3: how many stream bits were used, and
+// bit 31 if the plane is closed (bits 29 and 30 are zeros).
 // Bits past the budget are zeros in the decoder's window, and what they decode to there is right
 // everywhere but in one place: zeros after a group bit 1 would put the one on the last
 // coefficient, where a run cut by the budget has it at the lowest index still possible.  So
-// byte 2 is the bits used if the entry holds a run that reaches the last coefficient without a
+// byte 0 is the bits used if the entry holds a run that reaches the last coefficient without a
 // closing one, kTokenNone (more than any budget) if it holds no whole token at all (or one whose
-// position byte 3 has no room for), and zero otherwise.
+// position byte 2 has no room for), and zero otherwise.
 constexpr int kLookahead = 9;
 constexpr int kTokenRows = 11;
-constexpr uint32_t kTokenFirstRowIndex = 6, kTokenLastRowIndex = 16;
-constexpr uint32_t kTokenClosed = 32, kTokenNone = 255;
+constexpr uint32_t kTokenFirstRowIndex = 6;
+constexpr uint32_t kTokenClosed = 0x80000000u, kTokenNone = 255;
+constexpr int kIndexShift = kLookahead + 2;   // n, times the bytes of a row
 struct TokenTable { uint32_t v[kTokenRows << kLookahead]; };
 constexpr TokenTable build_token_table() {
   TokenTable t{};
@@ -247,10 +248,10 @@ constexpr TokenTable build_token_table() {
         passed += z + 1;
       }
       const uint32_t need = used == 0u ? kTokenNone : (to_last ? used : 0u);
-      t.v[(row << kLookahead) + s] = used | (passed | closed) << 8 | need << 16 | ones << 24;
+      t.v[(row << kLookahead) + s] = need | passed << kIndexShift | ones << 16 | used << 24 | closed;
     }
   }
-  for (uint32_t s = 0; s < (1u << kLookahead); ++s) t.v[((kTokenRows - 1) << kLookahead) + s] = kTokenClosed << 8;
+  for (uint32_t s = 0; s < (1u << kLookahead); ++s) t.v[((kTokenRows - 1) << kLookahead) + s] = kTokenClosed;
   return t;
 }
 
@@ -481,7 +482,7 @@ ZC_DEV bool any_of(AnyActive any_lane_active, bool p, bool q) {
 // Where a lane's decoded planes go: sixteen 16-bit patterns, in the order they are read, that
 // start as zeros.  Places are kPlaneStep apart, from begin() to end(), where a pattern may be put as
 // well; word k is patterns 2k and, above it, 2k + 1.  This one is for the host.
-constexpr uint32_t kPlaneStep = 2;
+constexpr uint32_t kPlaneStep = 2;   // (a closed token's two top bits)
 struct LocalPlanes {
   uint16_t v[17];
   ZC_DEV void clear() { for (int t = 0; t < 16; ++t) v[t] = 0; }
@@ -496,7 +497,39 @@ ZC_DEV uint32_t bit_field(uint32_t v, uint32_t offset, uint32_t width) {
 #if defined(__HIP_DEVICE_COMPILE__)
   return __builtin_amdgcn_ubfe(v, offset, width);
 #else
-  return (v >> offset) & ((1u << width) - 1u);
+  return (v >> (offset & 31u)) & ((1u << (width & 31u)) - 1u);
+#endif
+}
+
+// Byte 2 of e, moved up by n.
+ZC_DEV uint32_t shifted_byte2(uint32_t e, uint32_t n) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  uint32_t r;
+  asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(r) : "v"(n), "v"(e));
+  return r;
+#else
+  return ((e >> 16) & 0xFFu) << n;
+#endif
+}
+
+// Drops `len` bits (its lower six bits, below 32) at the bottom of the window; the two top words by one shift of 64
+// bits, which takes the GPU as long as the one that joins two words.  (In the 1-D decoder it does not pay: 2-way reduce of 2^27
+// values at rate 16 282 and 287 us.)
+template <int NW>
+ZC_DEV void drop_bits(uint32_t (&W)[NW], uint32_t len) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+  for (int j = 0; j < NW - 2; ++j) W[j] = alignbit(W[j + 1], W[j], len);
+  if constexpr (NW == 1) {
+    W[0] >>= len & 31u;
+  } else {
+    uint64_t top = (uint64_t)W[NW - 1] << 32 | W[NW - 2];
+    asm("v_lshrrev_b64 %0, %1, %0" : "+v"(top) : "v"(len));   // (the compiler makes the lower word once more)
+    W[NW - 2] = (uint32_t)top;
+    W[NW - 1] = (uint32_t)(top >> 32);
+  }
+#else
+  zc::shift_out<NW>(W, len & 31u);
 #endif
 }
 
@@ -505,7 +538,7 @@ template <int NW>
 struct PlaneReader {
   uint32_t (&W)[NW];   // the window: what is not yet read, from bit 2 on, zeros past the budget
   int32_t left;        // budget, which zeros read past its end make negative
-  uint32_t n;          // how many leading coefficients are significant
+  uint32_t n;          // how many leading coefficients are significant, from bit kIndexShift on (16 bits; what lies below has no meaning)
   uint32_t pattern;    // the ones of the current plane found so far
   uint32_t at;         // the current plane's place
 };
@@ -533,57 +566,71 @@ struct PlaneReader {
 // 314 us, at rate 4 8192 x 32768 values 490 -> 469 us.  With the significant coefficients' bits taken when a plane closes
 // and not when the next one starts, so that the look-up's bits are where the table wants them, a step is about
 // 66 cycles instead of 87: 469 -> 457 us, at rate 8 641 -> 623, decompress2d of 8192 x 8192 values at rate 16 112 ->
-// 108, the reduce of one chunk and local values there 222 -> 207.)
+// 108, the reduce of one chunk and local values there 222 -> 207.  With n kept where the row's offset has it, a mask in the place
+// of comparisons and selections, 16-bit operations and the last two words moved by one shift, so that
+// fewer of a step's instructions are slow ones, 58 cycles, and with no vote in the first steps: 2-way reduce of 8192 x 32768 values at
+// rate 4 414 -> 400 us, at rate 8 561 -> 538, at rate 16 1050 -> 1003, decompress2d of 8192 x 6144 bf16 values at rate 8 46.1 -> 43.9,
+// at rate 16 fp32 87.6 -> 82.7.)
 template <bool CAREFUL, int NW, class AnyActive, class Planes>
 ZC_DEV void read_planes(const uint32_t* token, PlaneReader<NW>& r, Planes& planes, AnyActive any_lane_active) {
   // byte offset of the entry: (clamped index - first row's index) rows, then the next bits
-  constexpr uint32_t kRowBytesLg = kLookahead + 2;
-  constexpr uint32_t kBitsMask = ((1u << kLookahead) - 1u) << 2;
+  uint32_t bits_mask = ((1u << kLookahead) - 1u) << 2;
+  zc::materialise(bits_mask);   // (in a vector register, see SwapMasks)
   // Up to rate 8 (NW <= 4) few blocks take sixteen steps, and in as many no lane can pass its
   // sixteenth place: the plain form counts them.  At rate 16 it asks whether some lane has got there.
   constexpr bool kCounted = !CAREFUL && NW <= 4;
-  uint32_t steps = 16;
-#pragma unroll 1
-  for (;;) {
+  // a step takes 25 bits at most and half as many mostly, so the first ones leave most lanes some: these are not asked
+  constexpr uint32_t kUnasked = NW == 8 ? 9u : (NW == 4 ? 5u : (NW == 2 ? 3u : 1u));
+  uint32_t n = r.n >> kIndexShift;
+  auto step = [&]() {
     const bool reading = !CAREFUL || r.at != planes.end();
     uint32_t e = 0u;
     bool cut = false;
     if (reading) {
-      const uint32_t clamped = umin(umax(r.n, kTokenFirstRowIndex), kTokenLastRowIndex);
-      uint32_t bits = r.W[0] & kBitsMask;
-      zc::materialise(bits);   // (so that the row is shifted and added to it in one instruction)
-      const uint32_t offset = (clamped << kRowBytesLg) + bits - (kTokenFirstRowIndex << kRowBytesLg);
+      const uint32_t row = zc::umax16<kTokenFirstRowIndex << kIndexShift>(r.n) & (0xFFFFu << kIndexShift);
+      const uint32_t offset = select_bits(bits_mask, r.W[0], row) - (kTokenFirstRowIndex << kIndexShift);
       e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(token) + offset);
-      cut = ((e >> 16) & 0xFFu) > (uint32_t)r.left;   // (no budget at all: the window is empty, and so is byte 2)
+      cut = (e & 0xFFu) > (uint32_t)r.left;   // (no budget at all: the window is empty, and so is byte 0)
     }
     if (any_lane_active(cut)) {
       // zeros up to the one; the run ends at the last coefficient or at the budget (of which some is
       // left: the group bit is a one).  The one may be too far on for an entry.
-      const uint32_t room = umin(15u - r.n, (uint32_t)r.left - 1u);
+      const uint32_t room = umin(15u - n, (uint32_t)r.left - 1u);
       const uint32_t z = umin(count_trailing_zeros(r.W[0] >> 3), room);
-      const uint32_t made = (z + 1u) << 8 | (1u + z + (z < room ? 1u : 0u));
+      const uint32_t made = (z + 1u) << kIndexShift | (1u + z + (z < room ? 1u : 0u)) << 24;
       e = cut ? made : e;
-      r.pattern |= cut ? 1u << ((r.n + z) & 31u) : 0u;
+      r.pattern |= cut ? 1u << ((n + z) & 31u) : 0u;
     }
     if (reading) {
-      r.pattern |= (e >> 24) << r.n;
-      const uint32_t s = r.n + ((e >> 8) & 0xFFu), used = e & 0xFFu;
+      r.pattern |= shifted_byte2(e, n);
       planes.put(r.at, r.pattern);
-      const bool closed = s >= kTokenClosed;
-      r.n = s & 31u;
+      r.n = zc::add16(r.n, e);
+      n = r.n >> kIndexShift;
       // a closed plane: the next one's bits of the significant coefficients
-      const uint32_t verbatim = closed ? r.n : 0u;
-      r.pattern = closed ? bit_field(r.W[0], used + 2u, verbatim) : r.pattern;
-      r.at += closed ? kPlaneStep : 0u;
-      zc::shift_out<NW>(r.W, used + verbatim);
-      r.left -= (int32_t)(used + verbatim);
+      const uint32_t closed = (uint32_t)((int32_t)e >> 31), verbatim = n & closed;
+      uint32_t used = e >> 24;   // (shifts and fields look at its lower five bits)
+      zc::materialise(used);     // (a shift and two additions are faster than two additions of a byte)
+      r.pattern = select_bits(closed, bit_field(r.W[0], used + 2u, n), r.pattern);
+      zc::materialise(r.pattern);   // (before the window moves)
+      r.at += e >> 30;
+      const uint32_t taken = used + verbatim;
+      drop_bits<NW>(r.W, taken);
+      r.left -= (int32_t)(taken & 31u);
     }
-    if (CAREFUL) {
-      if (!any_lane_active(r.left > 0 && r.at != planes.end())) break;
-    } else if (kCounted) {
-      if (!any_lane_active(r.left > 0) || --steps == 0) break;
+  };
+  if (CAREFUL) {
+#pragma unroll 1
+    do step(); while (any_lane_active(r.left > 0 && r.at != planes.end()));
+  } else {
+#pragma unroll 1
+    for (uint32_t steps = 0; steps < kUnasked; ++steps) step();
+    uint32_t steps = 16u - kUnasked;
+    if (kCounted) {
+#pragma unroll 1
+      do step(); while (any_lane_active(r.left > 0) && --steps != 0u);
     } else {
-      if (!any_lane_active(r.left > 0) || any_lane_active(r.at == planes.end())) break;
+#pragma unroll 1
+      do step(); while (any_lane_active(r.left > 0) && !any_lane_active(r.at == planes.end()));
     }
   }
 }
@@ -649,7 +696,7 @@ ZC_DEV BlockReading<Traits<RATE>::kWords> read_block(uint32_t (&W)[Traits<RATE>:
   }
   BlockReading<NW> b = {E, lead, lead > 16u && left > 0, {W, left, 0u, 0u, planes.begin()}};
   planes.clear();
-  read_planes<false>(token, b.r, planes, any_lane_active);
+  if (any_lane_active(left > 0)) read_planes<false>(token, b.r, planes, any_lane_active);   // (none in wavefronts of zero blocks)
   if (any_lane_active(b.r.left > 0)) {   // some lane may have read sixteen planes
     if (any_lane_active(b.r.left > 0 && b.r.at != planes.end())) read_planes<true>(token, b.r, planes, any_lane_active);
   }

@@ -601,7 +601,7 @@ template <int THREADS, bool MATRIX, bool ENCODER>
 struct DecodeLds {
   static constexpr int kExpand = ENCODER ? zc2d::kExpandEntries : 4;
   static constexpr int kBefore = THREADS * kPlaneBytes + 4 * kExpand;
-  static constexpr int kTokenBias = (int)(zc2d::kTokenFirstRowIndex << (zc2d::kLookahead + 2));
+  static constexpr int kTokenBias = (int)(zc2d::kTokenFirstRowIndex << zc2d::kIndexShift);
   char planes[THREADS * kPlaneBytes];
   uint32_t expand[kExpand];
   char unused[ENCODER && kBefore < kTokenBias ? kTokenBias - kBefore : 16];

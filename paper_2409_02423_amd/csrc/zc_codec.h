@@ -122,6 +122,26 @@ ZC_DEV uint32_t umin16(uint32_t a, uint32_t b) {
   return umin(a & 0xFFFFu, b & 0xFFFFu);
 #endif
 }
+// (the larger of a's and a number, and the sum)
+template <uint32_t B>
+ZC_DEV uint32_t umax16(uint32_t a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  uint32_t r;
+  asm("v_max_u16 %0, %2, %1" : "=v"(r) : "v"(a), "n"(B));
+  return r;
+#else
+  return umax(a & 0xFFFFu, B);
+#endif
+}
+ZC_DEV uint32_t add16(uint32_t a, uint32_t b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  uint32_t r;
+  asm("v_add_u16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+#else
+  return (a + b) & 0xFFFFu;
+#endif
+}
 // (a & b) | c and a | b | c
 ZC_DEV uint32_t and_or(uint32_t a, uint32_t b, uint32_t c) {
 #if defined(__HIP_DEVICE_COMPILE__)
