@@ -818,21 +818,33 @@ static_assert(inverse64_ok(), "the inverse transform as a matrix");
 // on the last step's operations.
 template <bool SIGNED = false>
 ZC_DEV constexpr void planes_to_digits(uint32_t (&x)[4]) {
+  uint32_t mask[4] = {0x0F0F0F0Fu, 0x33333333u, 0xAAAA0000u, 0x00005555u};   // (in vector registers, see SwapMasks)
+  if (!__builtin_is_constant_evaluated())
+    for (int i = 0; i < 4; ++i) zc::materialise(mask[i]);
+  uint32_t up[4] = {0, 0, x[2], x[3]};
+  shift_left_two<4>(up[2], up[3]);
 #pragma unroll
   for (int w = 0; w < 2; ++w) {
     const uint32_t lo = x[w], hi = x[w + 2];
-    x[w] = select_bits(0x0F0F0F0Fu, lo, hi << 4);
-    x[w + 2] = select_bits(0x0F0F0F0Fu, lo >> 4, hi);
+    x[w] = select_bits(mask[0], lo, up[w + 2]);
+    x[w + 2] = select_bits(mask[0], lo >> 4, hi);
   }
+  up[1] = x[1];
+  up[3] = x[3];
+  shift_left_two<2>(up[1], up[3]);
 #pragma unroll
   for (int w = 0; w < 4; w += 2) {
     const uint32_t lo = x[w], hi = x[w + 1];
-    x[w] = select_bits(0x33333333u, lo, hi << 2);
-    x[w + 1] = select_bits(0x33333333u, lo >> 2, hi);
+    x[w] = select_bits(mask[1], lo, up[w + 1]);
+    x[w + 1] = select_bits(mask[1], lo >> 2, hi);
   }
 #pragma unroll
+  for (int w = 0; w < 4; ++w) up[w] = x[w];
+  shift_left_two<17>(up[0], up[1]);
+  shift_left_two<17>(up[2], up[3]);
+#pragma unroll
   for (int w = 0; w < 4; ++w)
-    x[w] = select_bits(0xAAAA0000u, x[w] << 17, SIGNED ? select_bits_not(0x00005555u, x[w] >> 17, x[w]) : select_bits(0x00005555u, x[w] >> 17, x[w]));
+    x[w] = select_bits(mask[2], up[w], SIGNED ? select_bits_not(mask[3], x[w] >> 17, x[w]) : select_bits(mask[3], x[w] >> 17, x[w]));
 }
 constexpr int digit_coefficient(int w, int b) { return 8 * (b & 1) + 2 * w + 1 - (b >> 1); }
 

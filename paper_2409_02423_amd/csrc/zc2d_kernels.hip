@@ -53,8 +53,8 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
   __syncthreads();
 }
 // Workgroups per CU in the grid.  The kernels that decode have 512 lanes per workgroup (256 for small
-// matrices, see decode_threads): 22 KiB of token table, 18 KiB of planes, 1 KiB for the matrix product and 2
-// KiB for an encoder are 42 to 44 KiB, of which three fit a CU: six wavefronts per SIMD, for which 80 registers
+// matrices, see decode_threads): 22 KiB of token table, 18 KiB of planes, 9 KiB for the matrix product and 2
+// KiB for an encoder are 49 to 51 KiB, of which three fit a CU: six wavefronts per SIMD, for which 80 registers
 // are left.  The forms with the matrix product are held to that (without being told the reduces took 88,
 // four wavefronts: 0.530 against 0.496 ms for the 2-way reduce of 8192 x 32768 values at rate 4).  (256 lanes, as
 // the kernels were before: 0.270 against 0.248 ms for decompress2d, 0.613 against 0.583 ms for the reduce;
@@ -110,6 +110,9 @@ struct WavePlanes {
     asm volatile("" ::: "memory");   // (read where they are wanted, and not kept)
     return *reinterpret_cast<const uint32_t*>(lds + mine + 4 * k);
   }
+  // the spare word, and the planes of the lane's wavefront
+  __device__ __forceinline__ float& spare(uint32_t tid) const { return *reinterpret_cast<float*>(lds + tid * kPlaneBytes + 32); }
+  __device__ __forceinline__ char* wave(uint32_t tid) const { return lds + (tid & ~63u) * kPlaneBytes; }
 };
 
 // Shape of the matrix and of the walk over its blocks; the same for every lane.
@@ -290,7 +293,10 @@ __global__ __launch_bounds__(kThreads) void compress2d_kernel(const void* __rest
 // blocks.  Rows of lanes (lane / 16) and registers change places on the way in, so that lane 16*j + i
 // has the digits of four coefficients (word j of planes_to_digits) of block i of each group; of the
 // result it has row j of these blocks, four values that lie together in the matrix.  From there they
-// are stored as they are, or change places back to a block per lane.
+// are stored as they are, or change places back to a block per lane.  All of these changes go through LDS: it is
+// idle three quarters of the time, and an instruction that swaps rows of two registers takes a SIMD 8 of the cycles
+// that these kernels are bound by (with such instructions, 59 or 91 cycles per chunk and 130 for the way back, and now, us of a
+// 2-way reduce of 8192 x 32768 values at rate 4 403 and 396, at rate 8 541 and 524).
 // (What bounds these kernels is their VALU cycles.  The lifting's way, transpose of 16 planes, xor,
 // shifts, lifting, conversions and scaling, takes about 250 instructions per block, this one about 100, 150
 // with more than eight planes.  With the loop and the planes' layout as they are now, us before and after:
@@ -305,42 +311,75 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 __device__ __align__(16) const zc2d::MatrixOperands g_matrix = zc2d::build_matrix_operands();
 constexpr int kMatrixWords = sizeof(zc2d::MatrixOperands) / 4;
 
-// Rows of lanes and registers change places: what lane 16*j + i has in register g goes to lane 16*g + i,
-// register j.
-__device__ __forceinline__ void swap_rows(uint32_t& a0, uint32_t& a1, uint32_t& a2, uint32_t& a3) {
-  u32x2 r = __builtin_amdgcn_permlane32_swap(a0, a2, false, false);
-  a0 = r.x; a2 = r.y;
-  r = __builtin_amdgcn_permlane32_swap(a1, a3, false, false);
-  a1 = r.x; a3 = r.y;
-  r = __builtin_amdgcn_permlane16_swap(a0, a1, false, false);
-  a0 = r.x; a1 = r.y;
-  r = __builtin_amdgcn_permlane16_swap(a2, a3, false, false);
-  a2 = r.x; a3 = r.y;
+// Values of a block per lane, row-major, from and to rows: rows[g] = row lane/16 of block lane%16 of
+// group g.  `area` is the wavefront's own planes, which nobody needs any more; half of the values at a time take 2048 of
+// its 2304 bytes.  Two values of row j of block b are at 512 * j + 8 * b, but with neighbouring groups exchanged in odd rows:
+// then neither side's accesses meet in a bank.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+struct RowExchange {
+  char *row, *row1, *block, *block1;   // of groups 0 and 1, of rows 0 and 1
+  __device__ __forceinline__ RowExchange(char* area, uint32_t tid) {
+    const uint32_t at = (tid & 15) * 8 + (tid & 48) * 32 + (tid & 16) * 8, mine = (tid & 63) * 8;
+    row = area + at;
+    row1 = area + (at ^ 128u);
+    block = area + mine;
+    block1 = area + (mine ^ 128u);
+  }
+  __device__ __forceinline__ f32x2& by_row(int g) const { return *reinterpret_cast<f32x2*>((g & 1 ? row1 : row) + 256 * (g >> 1)); }
+  __device__ __forceinline__ f32x2& by_block(int r) const { return *reinterpret_cast<f32x2*>((r & 1 ? block1 : block) + 512 * r); }
+};
+// (what LDS holds changes places between a wavefront's lanes, in the order of the program)
+__device__ __forceinline__ void lds_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ void blocks_to_rows(const float (&y)[16], f32x4 (&rows)[4], char* area, uint32_t tid) {
+  const RowExchange at(area, tid);
+#pragma unroll
+  for (int h = 0; h < 4; h += 2) {
+    lds_order();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) at.by_block(r) = f32x2{y[4 * r + h], y[4 * r + h + 1]};
+    lds_order();
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x2 v = at.by_row(g);
+      rows[g][h] = v.x;
+      rows[g][h + 1] = v.y;
+    }
+  }
+  lds_order();
+}
+__device__ __forceinline__ void rows_to_blocks(const f32x4 (&rows)[4], float (&y)[16], char* area, uint32_t tid) {
+  const RowExchange at(area, tid);
+#pragma unroll
+  for (int h = 0; h < 4; h += 2) {
+    lds_order();
+#pragma unroll
+    for (int g = 0; g < 4; ++g) at.by_row(g) = f32x2{rows[g][h], rows[g][h + 1]};
+    lds_order();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const f32x2 v = at.by_block(r);
+      y[4 * r + h] = v.x;
+      y[4 * r + h + 1] = v.y;
+    }
+  }
+  lds_order();
 }
 
-// Values of a block per lane, row-major, from and to rows: rows[g] = row lane/16 of block lane%16 of
-// group g.
-__device__ __forceinline__ void blocks_to_rows(const float (&y)[16], f32x4 (&rows)[4]) {
+// Four words of a block per lane to the word lane/16 of block lane%16 of each group.  `area` has the words of the
+// workgroup's blocks, word by word.
+__device__ __forceinline__ void words_to_rows(uint32_t (&x)[4], char* area, uint32_t tid) {
+  uint32_t* const mine = reinterpret_cast<uint32_t*>(area) + tid;
+  const uint32_t* const theirs = reinterpret_cast<const uint32_t*>(area) + (tid & 48) * (kDecodeThreads / 16) + (tid & ~48u);
+  lds_order();
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    uint32_t a[4];
+  for (int w = 0; w < 4; ++w) mine[w * kDecodeThreads] = x[w];
+  lds_order();
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a[r] = __float_as_uint(y[4 * r + q]);
-    swap_rows(a[0], a[1], a[2], a[3]);
-#pragma unroll
-    for (int g = 0; g < 4; ++g) rows[g][q] = __uint_as_float(a[g]);
-  }
-}
-__device__ __forceinline__ void rows_to_blocks(const f32x4 (&rows)[4], float (&y)[16]) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    uint32_t a[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) a[g] = __float_as_uint(rows[g][q]);
-    swap_rows(a[0], a[1], a[2], a[3]);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) y[4 * r + q] = __uint_as_float(a[r]);
-  }
+  for (int g = 0; g < 4; ++g) x[g] = theirs[16 * g];
+  lds_order();
 }
 
 // The lane's number in the workgroup, anew in each pass of a loop: what is worked out from it, some dozen
@@ -353,7 +392,7 @@ __device__ __forceinline__ uint32_t fresh_tid() {
 
 // The wavefront's blocks as rows, unscaled, and each group's scale; false if some block is not covered.
 // All 64 lanes take part.
-__device__ __forceinline__ bool matrix_product(const WavePlanes& planes, uint32_t E, uint32_t lead, const uint32_t* matrix, uint32_t tid,
+__device__ __forceinline__ bool matrix_product(const WavePlanes& planes, uint32_t E, uint32_t lead, const uint32_t* matrix, char* digits, uint32_t tid,
                                                f32x4 (&d)[4], float (&scale)[4]) {
   uint32_t x[4], lower[4];
 #pragma unroll
@@ -365,7 +404,10 @@ __device__ __forceinline__ bool matrix_product(const WavePlanes& planes, uint32_
   // (the sixteenth would make the sums too long for a float)
   if (AnyLane()(!zc2d::matrix_covers(E, lead, x[3] & 0xFFFFu, more ? 15u : 8u) || (lower[0] >> 16) != 0u)) return false;
   zc2d::planes_to_digits<true>(x);
-  swap_rows(x[0], x[1], x[2], x[3]);
+  planes.spare(tid) = zc2d::matrix_scale(E, lead);
+  words_to_rows(x, digits, tid);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) scale[g] = planes.spare((tid & ~48u) + 16 * g);
   if (!more) {
     const f32x4 bias = *reinterpret_cast<const f32x4*>(matrix + 256 + ((tid & 48) >> 2));
     const f16x4 weight = __builtin_bit_cast(f16x4, *reinterpret_cast<const u32x2*>(matrix + 4 * (tid & 63)));
@@ -378,7 +420,7 @@ __device__ __forceinline__ bool matrix_product(const WavePlanes& planes, uint32_
     zc2d::planes_to_digits(lower);
 #pragma unroll
     for (int w = 0; w < 4; ++w) lower[w] ^= zc2d::kDigitSigns;
-    swap_rows(lower[0], lower[1], lower[2], lower[3]);
+    words_to_rows(lower, digits, tid);
     const f32x4 bias = *reinterpret_cast<const f32x4*>(matrix + 272 + ((tid & 48) >> 2));
     const f16x8 weight = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(matrix + 4 * (tid & 63)));
 #pragma unroll
@@ -387,14 +429,6 @@ __device__ __forceinline__ bool matrix_product(const WavePlanes& planes, uint32_
                        zc::permute_bytes(0u, lower[g], 0x0c010c00u), zc::permute_bytes(0u, lower[g], 0x0c030c02u)};
       d[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(weight, __builtin_bit_cast(f16x8, v), bias, 0, 0, 0);
     }
-  }
-  {
-    uint32_t s = __float_as_uint(zc2d::matrix_scale(E, lead));
-    u32x2 r = __builtin_amdgcn_permlane32_swap(s, s, false, false);
-    const u32x2 lo = __builtin_amdgcn_permlane16_swap(r.x, r.x, false, false);
-    const u32x2 hi = __builtin_amdgcn_permlane16_swap(r.y, r.y, false, false);
-    scale[0] = __uint_as_float(lo.x); scale[1] = __uint_as_float(lo.y);
-    scale[2] = __uint_as_float(hi.x); scale[3] = __uint_as_float(hi.y);
   }
   // values that the lifting's sums may not have room for, in blocks where they could be
   const uint64_t early = __builtin_amdgcn_ballot_w64(lead <= 2u);
@@ -514,7 +548,7 @@ __device__ __forceinline__ void store_row(void* out, size_t at, const f32x4& y) 
 // KiB of a row at a time, or, where a block row is a few blocks long (kNarrowPieces), as they are with a place worked out for
 // each.  Which, the host says (see store_form).
 template <int DT>
-__device__ __forceinline__ void store_rows(void* out, const Walk& w, const WaveCursor& cur, uint32_t tid, const f32x4 (&rows)[4]) {
+__device__ __forceinline__ void store_rows(void* out, const Walk& w, const WaveCursor& cur, const WavePlanes& planes, uint32_t tid, const f32x4 (&rows)[4]) {
   if (cur.whole(w) && (w.pieces & kPieces)) {
     const size_t at = cur.row(w, tid);
 #pragma unroll
@@ -548,7 +582,7 @@ __device__ __forceinline__ void store_rows(void* out, const Walk& w, const WaveC
     }
   } else {
     float y[16];
-    rows_to_blocks(rows, y);
+    rows_to_blocks(rows, y, planes.wave(tid), tid);
     if ((tid & 63) < cur.count(w)) store_block<DT>(out, w, cur.lane(w, tid), y);
   }
 }
@@ -565,17 +599,17 @@ __device__ __forceinline__ void store_rows(void* out, const Walk& w, const WaveC
 constexpr uint32_t kByMatrix = 1u, kLiftedFirst = 2u;
 template <int RATE>
 __device__ __forceinline__ uint32_t add_blocks(uint32_t (&W)[zc2d::Traits<RATE>::kWords], const uint32_t* token, WavePlanes& planes,
-                                           const uint32_t* matrix, uint32_t tid, bool first, f32x4 (&sum)[4]) {
+                                           const uint32_t* matrix, char* digits, uint32_t tid, bool first, f32x4 (&sum)[4]) {
   auto b = zc2d::read_block<RATE>(W, token, AnyLane(), planes);
   f32x4 d[4];
   float scale[4];
   uint32_t how = kByMatrix;
-  if (AnyLane()(b.r.left > 0) || !matrix_product(planes, b.E, b.lead, matrix, tid, d, scale)) {
+  if (AnyLane()(b.r.left > 0) || !matrix_product(planes, b.E, b.lead, matrix, digits, tid, d, scale)) {
     int32_t q[16];
     float y[16];
     zc2d::finish_block<RATE>(b, token, q, AnyLane(), planes);
     zc2d::scale_block(q, b.E, y);
-    blocks_to_rows(y, d);
+    blocks_to_rows(y, d, planes.wave(tid), tid);
     how = first ? kLiftedFirst : 0u;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -607,10 +641,12 @@ struct DecodeLds {
   char unused[ENCODER && kBefore < kTokenBias ? kTokenBias - kBefore : 16];
   uint32_t token[zc2d::kTokenRows << zc2d::kLookahead];
   uint32_t matrix[MATRIX ? kMatrixWords : 4];
+  char digits[MATRIX ? 16 * THREADS : 16];
 };
 
 template <int RATE, int DT, int THREADS>
-__global__ __launch_bounds__(THREADS) void decompress2d_kernel(const uint8_t* __restrict__ in, Walk w, void* __restrict__ out) {
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(as_matrix(RATE, THREADS) ? 6 : 1)))
+void decompress2d_kernel(const uint8_t* __restrict__ in, Walk w, void* __restrict__ out) {
   __shared__ __attribute__((aligned(16))) DecodeLds<THREADS, as_matrix(RATE, THREADS), false> lds;
   char* const plane_lds = lds.planes;
   uint32_t *const token = lds.token, *const matrix = lds.matrix;
@@ -635,8 +671,8 @@ __global__ __launch_bounds__(THREADS) void decompress2d_kernel(const uint8_t* __
       uint32_t Wn[NW];
       if (more) load_block_words<RATE>(in, next, w, tid, Wn);   // the next blocks' stream, ahead of time
       f32x4 y[4] = {};
-      add_blocks<RATE>(W, token, planes, matrix, tid, true, y);
-      store_rows<DT>(out, w, cur, tid, y);
+      add_blocks<RATE>(W, token, planes, matrix, lds.digits, tid, true, y);
+      store_rows<DT>(out, w, cur, planes, tid, y);
       if (!more) break;
 #pragma unroll
       for (int i = 0; i < NW; ++i) W[i] = Wn[i];
@@ -747,18 +783,19 @@ void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, 
         for (int i = 0; i < NW; ++i) W[i] = Wn[i];
         if (j + 1 < k) load_block_words<RATE>(chunks.p[j + 1], cur, w, tid, Wn);
         else if (next.inside(w)) load_block_words<RATE>(chunks.p[0], next, w, tid, Wn);
-        how |= add_blocks<RATE>(W, token, planes, matrix, tid, j == 0, rows);
+        how |= add_blocks<RATE>(W, token, planes, matrix, lds.digits, tid, j == 0, rows);
       } while (++j < k);
       const uint32_t tid = fresh_tid();
+      const WavePlanes planes(plane_lds, tid);
       if constexpr (RAW_OUT) {
         if (how == (kByMatrix | kLiftedFirst)) {
 #pragma unroll
           for (int g = 0; g < 4; ++g) rows[g] += 0.0f;
         }
-        store_rows<kF32>(out_raw, w, cur, tid, rows);
+        store_rows<kF32>(out_raw, w, cur, planes, tid, rows);
       } else {
         float sum[16];
-        rows_to_blocks(rows, sum);
+        rows_to_blocks(rows, sum, planes.wave(tid), tid);
         uint32_t x[16], W[NW];
         if (cur.whole(w)) {
 #pragma unroll
