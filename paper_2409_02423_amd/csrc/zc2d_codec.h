@@ -208,19 +208,20 @@ constexpr ExpandTable build_expand_table() {
 // An entry holds all the tokens that lie whole within the look-ahead: group bit, zeros,
 // closing one; a run that reaches the last coefficient needs no closing one, and the plane is
 // closed after it; a group bit 0 closes the plane.
-// Byte 0: how many bits of budget the entry must find; from bit kIndexShift on, where n is kept: how many coefficients were
-// passed; byte 2: the ones, as positions past the current coefficient; byte 3: how many stream bits were used, and
-// bit 31 if the plane is closed (bits 29 and 30 are zeros).
+// Where these are a group bit 1 and zeros only, and the last coefficient is not among them, the entry passes the eight zeros and
+// leaves the group bit to the next step, in the place of the last of them.
+// Byte 0: how many bits of budget the entry must find, and kTokenGoesOn if a group bit has to be put back; from bit
+// kIndexShift on, where n is kept: how many coefficients were passed; byte 2: the ones, as positions past the current
+// coefficient; byte 3: how many stream bits were used, and bit 31 if the plane is closed (bits 29 and 30 are zeros).
 // Bits past the budget are zeros in the decoder's window, and what they decode to there is right
 // everywhere but in one place: zeros after a group bit 1 would put the one on the last
 // coefficient, where a run cut by the budget has it at the lowest index still possible.  So
-// byte 0 is the bits used if the entry holds a run that reaches the last coefficient without a
-// closing one, kTokenNone (more than any budget) if it holds no whole token at all (or one whose
-// position byte 2 has no room for), and zero otherwise.
+// byte 0 is not zero if the entry holds a run that reaches the last coefficient without a closing one, or does not reach
+// its end: no less than the bits used (4 to 7 count as 8, which leaves kTokenGoesOn its bit).
 constexpr int kLookahead = 9;
 constexpr int kTokenRows = 11;
 constexpr uint32_t kTokenFirstRowIndex = 6;
-constexpr uint32_t kTokenClosed = 0x80000000u, kTokenNone = 255;
+constexpr uint32_t kTokenClosed = 0x80000000u, kTokenGoesOn = 4u;
 constexpr int kIndexShift = kLookahead + 2;   // n, times the bytes of a row
 struct TokenTable { uint32_t v[kTokenRows << kLookahead]; };
 constexpr TokenTable build_token_table() {
@@ -247,7 +248,11 @@ constexpr TokenTable build_token_table() {
         used += 1 + z + (passed + z == room ? 0 : 1);       // no closing one at the last coefficient
         passed += z + 1;
       }
-      const uint32_t need = used == 0u ? kTokenNone : (to_last ? used : 0u);
+      uint32_t need = to_last ? (used & kTokenGoesOn ? 8u : used) : 0u;
+      if (used == 0u) {   // (s is 1)
+        passed = used = kLookahead - 1;
+        need = kLookahead | kTokenGoesOn;
+      }
       t.v[(row << kLookahead) + s] = need | passed << kIndexShift | ones << 16 | used << 24 | closed;
     }
   }
@@ -574,8 +579,9 @@ struct PlaneReader {
 template <bool CAREFUL, int NW, class AnyActive, class Planes>
 ZC_DEV void read_planes(const uint32_t* token, PlaneReader<NW>& r, Planes& planes, AnyActive any_lane_active) {
   // byte offset of the entry: (clamped index - first row's index) rows, then the next bits
-  uint32_t bits_mask = ((1u << kLookahead) - 1u) << 2;
-  zc::materialise(bits_mask);   // (in a vector register, see SwapMasks)
+  uint32_t bits_mask = ((1u << kLookahead) - 1u) << 2, goes_on = kTokenGoesOn;   // (the next bit is bit 2 of the window)
+  zc::materialise(bits_mask);   // (in vector registers, see SwapMasks)
+  zc::materialise(goes_on);
   // Up to rate 8 (NW <= 4) few blocks take sixteen steps, and in as many no lane can pass its
   // sixteenth place: the plain form counts them.  At rate 16 it asks whether some lane has got there.
   constexpr bool kCounted = !CAREFUL && NW <= 4;
@@ -594,7 +600,10 @@ ZC_DEV void read_planes(const uint32_t* token, PlaneReader<NW>& r, Planes& plane
     }
     if (any_lane_active(cut)) {
       // zeros up to the one; the run ends at the last coefficient or at the budget (of which some is
-      // left: the group bit is a one).  The one may be too far on for an entry.
+      // left: the group bit is a one).  The one may be too far on for an entry.  (Runs that are longer than the look-ahead did not
+      // have entries: 2.2 of the 5.7 steps of a wavefront at rate 4, and of the 9.4 at rate 8, came here for such a
+      // one, at 54 cycles; now it is 1.1 at rate 4 and hardly any at rate 8: 2-way reduce of 8192 x 32768 values at rate 4
+      // 396 -> 380 us, at rate 8 524 -> 510, decompress2d of 8192 x 6144 bf16 values at rate 8 43.2 -> 42.4.)
       const uint32_t room = umin(15u - n, (uint32_t)r.left - 1u);
       const uint32_t z = umin(count_trailing_zeros(r.W[0] >> 3), room);
       const uint32_t made = (z + 1u) << kIndexShift | (1u + z + (z < room ? 1u : 0u)) << 24;
@@ -615,6 +624,7 @@ ZC_DEV void read_planes(const uint32_t* token, PlaneReader<NW>& r, Planes& plane
       r.at += e >> 30;
       const uint32_t taken = used + verbatim;
       drop_bits<NW>(r.W, taken);
+      r.W[0] = zc::and_or(e, goes_on, r.W[0]);
       r.left -= (int32_t)(taken & 31u);
     }
   };
@@ -661,7 +671,6 @@ ZC_DEV BlockReading<Traits<RATE>::kWords> read_block(uint32_t (&W)[Traits<RATE>:
                                                      AnyActive any_lane_active, Planes& planes) {
   constexpr int NW = Traits<RATE>::kWords;
   constexpr int kPayload = Traits<RATE>::kPayloadBits;
-  static_assert(kPayload < (int)kTokenNone, "no budget lets an entry without a token pass (it would be read for ever)");
   uint32_t E = W[0] & 0xFFu;
   // empty planes before the first one: zeros from bit 8 on, which seldom pass the first word
   const uint32_t top = W[0] & 0xFFFFFF00u;
