@@ -275,7 +275,8 @@ constexpr Enc4Table build_enc4_table() {
 //
 // Entry (both tables): bits 1:0 of byte i = the bits of coefficient i in the planes read
 // (the earlier plane in the higher bit) | planes read << 2 | stream bits used << 4 |
-// (next state's row: 0, 1, 2 or 3 = idle) << 11.
+// (next state's row: 0, 1, 2 or 3 = idle) << 11; in the look-ahead table's row 0, kDecCrowded if the first plane has more than
+// a single one.
 //
 // Look-ahead table: index = row*512 + next 9 stream bits, used when every lane that still
 // reads has at least 9 bits of budget left, so that the budget cannot cut what an entry reads.
@@ -295,6 +296,7 @@ constexpr int kDecLook = 9;
 constexpr int kDecLookEntries = 4 << kDecLook;
 constexpr int kDecBudgetEntries = 4 * 256;
 constexpr int kDecPlaneEntries = kDecLookEntries + kDecBudgetEntries;
+constexpr uint32_t kDecCrowded = 0x80000000u;
 constexpr uint32_t kDecIdle = 3u << 11;   // state code of the idle row (the codes are the rows' byte offsets in the look-ahead table)
 struct DecTable { uint32_t v[kDecPlaneEntries + 256]; };
 
@@ -324,7 +326,8 @@ constexpr DecTable build_dec_table() {
           next = b.next;
         }
       }
-      t.v[(n << kDecLook) + s] = bits | planes << 2 | used << 4 | (next < 3 ? (uint32_t)next << 11 : idle);
+      const uint32_t crowded = n == 0 && (a.p & (a.p - 1u)) != 0 ? kDecCrowded : 0u;
+      t.v[(n << kDecLook) + s] = bits | planes << 2 | used << 4 | (next < 3 ? (uint32_t)next << 11 : idle) | crowded;
     }
   for (int s = 0; s < (1 << kDecLook); ++s) t.v[(3 << kDecLook) + s] = idle;
   for (int n = 0; n < 3; ++n)
@@ -563,7 +566,7 @@ ZC_DEV void encode_block(const uint32_t (&x)[4], const Tables& tab, uint32_t (&W
   // (at rate 4 the count only serves as a shift of the words and of the table's entry, which are
   // zero when all words are)
   const uint32_t lead = RATE == 4 ? count_leading_zeros_nonzero(u[0] | u[1] | u[2] | u[3])
-                                  : count_leading_zeros(u[0] | u[1] | u[2] | u[3]);
+                                  : count_leading_zeros(or3(u[0], u[1], u[2] | u[3]));
   const int32_t avail = kPayload - (int32_t)lead;
   uint32_t left = avail > 0 ? (uint32_t)avail : 0u;
 #pragma unroll
@@ -586,8 +589,9 @@ ZC_DEV void encode_block(const uint32_t (&x)[4], const Tables& tab, uint32_t (&W
     uint32_t lit[kLitWords];
     auto make_word = [&](int j) {
       const int sh = 24 - 8 * j;
-      lit[j] = spread[(u[0] >> sh) & 0xFFu] | spread[(u[1] >> sh) & 0xFFu] << 1 | spread[(u[2] >> sh) & 0xFFu] << 2 |
-               spread[(u[3] >> sh) & 0xFFu] << 3;
+      // (three instructions that shift and combine)
+      lit[j] = (spread[(u[0] >> sh) & 0xFFu] | spread[(u[1] >> sh) & 0xFFu] << 1) |
+               (spread[(u[2] >> sh) & 0xFFu] | spread[(u[3] >> sh) & 0xFFu] << 1) << 2;
     };
     make_word(0);
 #pragma unroll
@@ -616,7 +620,7 @@ ZC_DEV void encode_block(const uint32_t (&x)[4], const Tables& tab, uint32_t (&W
           materialise(byte);   // (so that the address is this byte shifted and added to the row's offset in one instruction)
           const uint32_t e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(tab.enc) + state + (byte << 2));
           z >>= 8;
-          const uint32_t len = umin((e >> 14) & 15u, left);
+          const uint32_t len = umin16((e >> 14) & 15u, left);
           shift_in<NW>(P, e, len);  // only the low `len` bits of e enter the window
           left -= len;
           state = e >> 18;
@@ -719,6 +723,102 @@ ZC_DEV void scale_values(const int32_t (&q)[4], uint32_t E, bool all_common, flo
   }
 }
 
+// ---- rate 8: the inverse transform as a matrix ---------------------------------------------
+// The inverse lifting halves with floors, but a halving that leaves no remainder is linear, and a coefficient that
+// ends three digits above the lowest leaves none (the steps divide by 8 in all).  At rate 8 no block has coefficients that end lower:
+// each empty plane takes one of the 24 payload bits, each other one at least one and a literal one four, so the last of the planes is
+// the 24th at most, which is bit 8.  Then the four values are a fixed 4 x 4 matrix times the coefficients, and a matrix
+// instruction of the GPU multiplies each lane's own four by it, exactly: the digits that have been read, in bytes, are small whole
+// numbers, and so are the sums.  What else that needs:
+//   * no sum of the lifting wraps.  Its sums are at most 2.25 times the largest coefficient.  With two empty planes or more,
+//     coefficients are within -715827882..357913941; with one they are up to 1431655765 where the digit of bit 30 is set, and
+//     the largest sum, a + c/2 - b/8 - 5d/8, is below 2^31 if one of the four has it: the first plane must have a single one;
+//   * the scaling by the exponent byte is exact and finite.
+constexpr int kInverse8[4][4] = {{8, 3, -4, -1}, {8, 1, 4, 5}, {8, -1, 4, -5}, {8, -3, -4, 1}};   // 8 x what inverse_lift does
+
+namespace selfcheck {
+constexpr bool inverse8_ok() {
+  for (int c = 0; c < 4; ++c)
+    for (int sign = -1; sign <= 1; sign += 2) {
+      int32_t q[4] = {};
+      q[c] = sign * 8;
+      inverse_lift(q[0], q[1], q[2], q[3]);
+      for (int i = 0; i < 4; ++i)
+        if (q[i] != sign * kInverse8[i][c]) return false;
+    }
+  return true;
+}
+static_assert(inverse8_ok(), "the inverse transform as a matrix");
+}  // namespace selfcheck
+
+// The digits of coefficient i of the planes read through the tables (`upper`, at most eight) and of the eight literal ones behind them
+// (`lower`) are byte i of two words.  A byte d stands for (d ^ 0xAA) - 0xAA (negabinary, the lowest digit positive); d ^ 0xAA goes into
+// the product as the half-precision number of the same bits, times 2^-24 (the matrix instructions take subnormal halves as
+// they are), bytes 0 and 2 as one pair and 1 and 3 as the other.  With the weights below the result is 8 x value / (the place of the
+// lowest digit) * 2^-20.  bias: what takes the offset away.
+constexpr uint32_t kDigitBytes = 0x00FF00FFu, kDigitSigns = 0xAAAAAAAAu;
+struct Operands8 { uint32_t upper[4][2], lower[4][2]; float bias[4]; };   // weights by value
+constexpr uint32_t half_of_weight(int w, int lg) {   // w * 2^lg, |w| <= 8
+  return w == 0 ? 0u : (uint32_t)small_int_as_half(w) + ((uint32_t)lg << 10);
+}
+constexpr int digit_byte(int pair, int half) { return pair + 2 * half; }
+constexpr Operands8 build_operands8() {
+  Operands8 t{};
+  for (int i = 0; i < 4; ++i) {
+    int sum = 0;
+    for (int p = 0; p < 2; ++p)
+      for (int h = 0; h < 2; ++h) {
+        const int w = kInverse8[i][digit_byte(p, h)];
+        sum += w;
+        t.upper[i][p] |= half_of_weight(w, 12) << (16 * h);
+        t.lower[i][p] |= half_of_weight(w, 4) << (16 * h);
+      }
+    t.bias[i] = (float)(-0xAA * 257 * sum) / 1048576.0f;
+  }
+  return t;
+}
+namespace selfcheck {
+// No sum of the product's terms and its bias, taken in any order, is longer than a float holds.
+constexpr bool sums8_ok() {
+  for (int i = 0; i < 4; ++i) {
+    int64_t up = 0, down = 0, sum = 0;
+    for (int c = 0; c < 4; ++c) {
+      const int w = kInverse8[i][c];
+      (w > 0 ? up : down) += 255 * 257 * w;
+      sum += w;
+    }
+    (sum < 0 ? up : down) -= 0xAA * 257 * sum;
+    if (up >= 1 << 24 || -down >= 1 << 24) return false;
+  }
+  return true;
+}
+static_assert(sums8_ok(), "the matrix product's sums are exact");
+}  // namespace selfcheck
+
+// Without a matrix product (the host, and kernels that do not have it).
+struct NoProduct {
+  static constexpr bool kHere = false;
+  ZC_DEV void operator()(uint32_t, uint32_t, float (&)[4]) const {}
+};
+
+// Whether the matrix does not cover a block with these, whatever its planes.
+ZC_DEV bool outside_matrix(uint32_t E, uint32_t lead) { return E - 29u > 211u || lead - 1u > 13u; }
+// A zero block goes as one without digits; this many empty planes make the scale of exponent byte 0 a zero.
+constexpr uint32_t kZeroBlockLead = 13u;
+
+// The values of the digits `upper` and `lower` of blocks with `above` planes above `lower`, stored in `out` (FIRST) or added to it.
+// A product that is zero times a negative scale is - 0.  A value read is never - 0, so + 0 is added first, which changes a sum of - 0 only,
+// unless the sum becomes a stream, which has no sign for a zero (SIGNED_ZEROS).
+template <bool FIRST, bool SIGNED_ZEROS, class Product>
+ZC_DEV void values_by_matrix(uint32_t E, uint32_t above, uint32_t upper, uint32_t lower, const Product& product, float (&out)[4]) {
+  float d[4];
+  product(upper, lower, d);
+  // 2^-3 (the matrix), 2^20, the place of the lowest digit, 24 - above, with its sign, and 2^(E - 155)
+  const float scale = bits_to_float((E + 13u - above) << 23 | above << 31);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) out[i] = __builtin_fmaf(d[i], scale, FIRST ? 0.0f : (SIGNED_ZEROS ? out[i] + 0.0f : out[i]));
+}
+
 // W holds the block (bits beyond 4*RATE zero).
 //
 // Rates above 4 decode in two phases.  (1) While any lane of the wavefront is in a state
@@ -738,11 +838,12 @@ ZC_DEV void scale_values(const int32_t (&q)[4], uint32_t E, bool all_common, flo
 // 70.9 and 68.6, at rate 16 1.5e8 322 and 307, at rate 24 2^25 97.5 and 92.8, 8-way at rate 8 194 and 186, one chunk and local
 // values at rate 8 58.1 and 55.1, decompress at rate 24 5e7 bf16 values 57.0 and 54.3; on small ones: 2^17 values at rate 16
 // 2-way reduce 4.49 and 4.65, decompress 3.11 and 3.17.)
-template <int RATE, bool FIRST, bool BRANCHES, class AnyActive>
+template <int RATE, bool FIRST, bool BRANCHES, bool SIGNED_ZEROS, class AnyActive, class Product>
 ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& tab, float (&out)[4],
-                            AnyActive any_lane_active) {
+                            AnyActive any_lane_active, const Product& product) {
   constexpr int NW = Traits<RATE>::kWords;
   constexpr int kPayload = Traits<RATE>::kPayloadBits;
+  constexpr bool kMatrix = RATE == 8 && Product::kHere;
   uint32_t E = W[0] & 0xFFu;
   if constexpr (RATE == 4) {
     // one lookup for the whole payload byte (entry 0 is the zero block, which ignores
@@ -760,13 +861,24 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
     // leading empty planes = zero bits at the start of the payload, which seldom pass the first word
     const uint32_t top = W[0] & 0xFFFFFF00u;
     uint32_t lead = count_trailing_zeros_nonzero(top) - 8u;
-    if constexpr (NW == 1) lead = umin(lead, (uint32_t)kPayload);   // (for an empty payload too)
+    if constexpr (NW == 1 && !kMatrix) lead = umin(lead, (uint32_t)kPayload);   // (for an empty payload too)
     constexpr bool kZeroApart = BRANCHES && NW > 1;
     bool none = false;   // nothing to decode
-    auto uncommon = any_lane_active.lanes(!common_exponent(E));
+    auto uncommon = any_lane_active.lanes(kMatrix ? E - 29u > 211u : !common_exponent(E));
     auto look_closer = uncommon;
-    if constexpr (NW > 1) look_closer = look_closer | any_lane_active.lanes(top == 0u);
+    bool outside = false;   // of what the matrix covers (the same in every lane)
+    if constexpr (kMatrix) look_closer = look_closer | any_lane_active.lanes(lead - 1u > 13u);
+    else if constexpr (NW > 1) look_closer = look_closer | any_lane_active.lanes(top == 0u);
     if (!BRANCHES || any_lane_active.some(look_closer)) {
+      if constexpr (kMatrix) {
+        if (!any_lane_active(E != 0u)) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) out[i] = FIRST ? 0.0f : out[i] + 0.0f;
+          return;
+        }
+        uncommon = any_lane_active.lanes(!common_exponent(E));
+        outside = any_lane_active(E != 0u && outside_matrix(E, lead));
+      }
       // most often for zero blocks, whose scale does not matter and whose planes are not looked at.  (us of 98 % zeros
       // without and with this: 2-way reduce of 2^25 values at rate 12 73.2 and 71.1, at rate 16 96.5 and 94.1, decompress of 5e6 at
       // rate 20 8.42 and 8.14; at rate 8, where there is little to save, 58.6 and 59.3)
@@ -785,6 +897,7 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
       }
       // a zero block ignores its payload; after 32 empty planes nothing is left to decode
       none = E == 0u || (kPayload > 32 && lead >= 32u);
+      if constexpr (kMatrix) lead = umin(lead, (uint32_t)kPayload);
     }
     uint32_t left = (uint32_t)kPayload - lead;
     // keep the next stream bit at bit 2 of the window: bits 10..2 index the look-ahead table directly.
@@ -798,7 +911,11 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
         left = 0u;
         lead = 0u;
         state = kDecIdle;
-        if constexpr (kZeroApart) E = 127u;   // (the scale of a zero: any positive one)
+        if constexpr (kMatrix) {
+          lead = E == 0u ? kZeroBlockLead : 0u;
+        } else if constexpr (kZeroApart) {
+          E = 127u;   // (the scale of a zero: any positive one)
+        }
 #pragma unroll
         for (int j = 0; j < NW; ++j) W[j] = 0u;
       }
@@ -817,7 +934,7 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
         // table, eight times the row's in the budget table; the next stream bit is bit 2 of W[0])
         uint32_t at;
         if (any_lane_active.some(reading & any_lane_active.lanes(left < (uint32_t)kDecLook))) {
-          const uint32_t mask4 = (4u << umin(left, 7u)) - 4u;   // the next min(left, 7) stream bits, in place
+          const uint32_t mask4 = (4u << (BRANCHES ? umin16(left, 7u) : umin(left, 7u))) - 4u;   // the next min(left, 7) stream bits, in place
           at = 4u * kDecLookEntries + (state >> 1) + mask4 + (W[0] & mask4);
         } else {
           at = state | (W[0] & (((1u << kDecLook) - 1u) << 2));
@@ -834,7 +951,47 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
     };
     {
       uint32_t acc = 0;
-      bool open = group(acc, m);
+      bool open = true;
+      if constexpr (kMatrix) {
+        // where the matrix may cover the wavefront's blocks, the first step is every lane's, with enough budget for a look-ahead
+        uint32_t crowded = 0, s = 0;
+        auto take = [&](uint32_t at) {
+          const uint32_t e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(tab.dec) + at);
+          const uint32_t planes = (e >> 2) & 3u, used = (e >> 4) & 15u;
+          acc = (acc << planes) | (e & 0x03030303u);
+          m += planes;
+          W[0] >>= used;
+          left -= used;
+          state = e & kDecIdle;
+          return e;
+        };
+        constexpr uint32_t kLookMask = ((1u << kDecLook) - 1u) << 2;
+        if (!outside) {
+          crowded = (lead - 2u) & take(state | (W[0] & kLookMask));   // (negative: one empty plane and a crowded one)
+          s = 1;
+        }
+#pragma unroll 1
+        for (;; ++s) {
+          const auto reading = any_lane_active.lanes(state < kDecIdle);
+          open = any_lane_active.some(reading);
+          if (!open || s == 4u) break;
+          if (any_lane_active.some(reading & any_lane_active.lanes(left < (uint32_t)kDecLook))) {
+            const uint32_t mask4 = (4u << umin16(left, 7u)) - 4u;
+            take(4u * kDecLookEntries + (state >> 1) + mask4 + (W[0] & mask4));
+          } else {
+            take(state | (W[0] & kLookMask));
+          }
+        }
+        if (!open && !outside && !any_lane_active((int32_t)crowded < 0)) {
+          const uint32_t* pair = tab.dec + kDecPlaneEntries;
+          const uint32_t bits = W[0] >> 2;   // (23 bits at most)
+          values_by_matrix<FIRST, SIGNED_ZEROS>(E, m + lead, acc, (pair[bits & 0xFFu] << 2 | pair[(bits >> 8) & 0xFFu]) << 4 | pair[bits >> 16] << 2,
+                                                product, out);
+          return;
+        }
+      } else {
+        open = group(acc, m);
+      }
 #pragma unroll
       for (int i = 0; i < 4; ++i) A[i] = (acc >> (8 * i)) & 0xFFu;
       // more groups only for blocks that stay below three significant coefficients for long; no
@@ -862,7 +1019,7 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
       for (int j = 0; j < kLiteral; ++j) {
         uint32_t bits = W[j] >> 2;
         if (j + 1 < NW) bits = alignbit(W[j + 1], W[j], 2);
-        G[j] = pair[bits & 0xFFu] << 6 | pair[(bits >> 8) & 0xFFu] << 4 | pair[(bits >> 16) & 0xFFu] << 2 | pair[bits >> 24];
+        G[j] = (pair[bits & 0xFFu] << 2 | pair[(bits >> 8) & 0xFFu]) << 4 | (pair[(bits >> 16) & 0xFFu] << 2 | pair[bits >> 24]);
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -894,13 +1051,16 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
   }
 }
 
-template <int RATE, bool BRANCHES = true, class AnyActive>
-ZC_DEV void decode_block(uint32_t (&W)[Traits<RATE>::kWords], const Tables& tab, float (&out)[4], AnyActive any_lane_active) {
-  decode_block_to<RATE, true, BRANCHES>(W, tab, out, any_lane_active);
+// SIGNED_ZEROS: the sign of a sum that is zero matters (see values_by_matrix).
+template <int RATE, bool BRANCHES = true, class AnyActive, class Product = NoProduct>
+ZC_DEV void decode_block(uint32_t (&W)[Traits<RATE>::kWords], const Tables& tab, float (&out)[4], AnyActive any_lane_active,
+                         const Product& product = Product()) {
+  decode_block_to<RATE, true, BRANCHES, true>(W, tab, out, any_lane_active, product);
 }
-template <int RATE, bool BRANCHES = true, class AnyActive>
-ZC_DEV void decode_block_add(uint32_t (&W)[Traits<RATE>::kWords], const Tables& tab, float (&sum)[4], AnyActive any_lane_active) {
-  decode_block_to<RATE, false, BRANCHES>(W, tab, sum, any_lane_active);
+template <int RATE, bool BRANCHES = true, bool SIGNED_ZEROS = true, class AnyActive, class Product = NoProduct>
+ZC_DEV void decode_block_add(uint32_t (&W)[Traits<RATE>::kWords], const Tables& tab, float (&sum)[4], AnyActive any_lane_active,
+                             const Product& product = Product()) {
+  decode_block_to<RATE, false, BRANCHES, SIGNED_ZEROS>(W, tab, sum, any_lane_active, product);
 }
 
 // Rate 4 in the fused reduce: sum = (FIRST) or sum += (otherwise) the decoded block, with one

@@ -6,10 +6,13 @@
 // messages of one block per lane, which asks for its block before it stages its tables (see "small messages").
 // All are specialised per rate.  Each lane reads 16 contiguous bytes of fp32 (compress) or RATE/2 contiguous
 // bytes of stream (decompress, reduce), so a wavefront touches one contiguous span per access; the code
-// tables are staged in LDS once per workgroup.  No matrix cores: nothing here is a contraction.
+// tables are staged in LDS once per workgroup.  The decoder's inverse transform is a product of matrices in the 2-way reduce at rate 8,
+// and runs on the matrix cores there (see LaneProduct).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
+
+#include <type_traits>
 
 #include "../../include/zc.h"
 #include "zc_codec.h"
@@ -23,6 +26,7 @@ __device__ __align__(16) const zc::DecTable g_dec_table = zc::build_dec_table();
 __device__ __align__(16) const zc::Dec4Table g_dec4_table = zc::build_dec4_table();
 __device__ __align__(16) const zc::Dec4HalfTable g_dec4_half_table = zc::build_dec4_half_table();
 __device__ __align__(16) const zc::Enc4Table g_enc4_table = zc::build_enc4_table();
+__device__ __align__(16) const zc::Operands8 g_operands8 = zc::build_operands8();
 
 constexpr int kThreads = 256;          // 4 wavefronts
 constexpr int kEncWords = zc::kEncPlaneEntries + 256;
@@ -41,6 +45,46 @@ struct AnyLane {
   __device__ bool some(uint64_t set) const { return set != 0; }
   __device__ bool operator()(bool p) const { return __builtin_amdgcn_ballot_w64(p) != 0; }
 };
+
+// The decoder's inverse transform at rate 8 as a product of matrices (see "the inverse transform as a matrix" in zc_codec.h): the
+// 16 fours of lanes of a wavefront are 16 products of 4 x 4 weights and four blocks, of which a lane holds one, as its coefficients and
+// then as its values.  Lane l has the weights of value l mod 4.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+struct LaneProduct {
+  static constexpr bool kHere = true;
+  f16x4 upper, lower;
+  f32x4 bias;
+  uint32_t bytes, signs;   // (in vector registers: an operation of three operands with a scalar one takes the GPU twice as long)
+  __device__ __forceinline__ LaneProduct() {
+    typedef uint32_t pair __attribute__((ext_vector_type(2)));
+    upper = __builtin_bit_cast(f16x4, *reinterpret_cast<const pair*>(g_operands8.upper[threadIdx.x & 3]));
+    lower = __builtin_bit_cast(f16x4, *reinterpret_cast<const pair*>(g_operands8.lower[threadIdx.x & 3]));
+    bias = *reinterpret_cast<const f32x4*>(g_operands8.bias);
+    bytes = zc::kDigitBytes;
+    signs = zc::kDigitSigns;
+    zc::materialise(bytes);
+    zc::materialise(signs);
+  }
+  __device__ __forceinline__ f16x4 halves(uint32_t digits) const {
+    typedef uint32_t pair __attribute__((ext_vector_type(2)));
+    // (digits ^ signs) & bytes; signs are the same in every byte
+    const pair v = {(uint32_t)__builtin_amdgcn_bitop3_b32(digits, signs, bytes, 0x28), (uint32_t)__builtin_amdgcn_bitop3_b32(digits >> 8, signs, bytes, 0x28)};
+    return __builtin_bit_cast(f16x4, v);
+  }
+  __device__ __forceinline__ void operator()(uint32_t up, uint32_t low, float (&d)[4]) const {
+    f32x4 v = __builtin_amdgcn_mfma_f32_4x4x4f16(lower, halves(low), bias, 0, 0, 0);
+    v = __builtin_amdgcn_mfma_f32_4x4x4f16(upper, halves(up), v, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d[i] = v[i];
+  }
+};
+// The reduce kernels that have it: two chunks without local values.  (With local values, or for any number of chunks, where 16 blocks'
+// decoders follow one another, the operands and the general form behind each product took the registers from 64 to 72 and
+// to 120: 8-way reduce of 2^25 values 186 and 221 us, one chunk and local values 60 and 83.)
+constexpr bool has_product(int rate, bool local, int k) { return rate == 8 && k == 2 && !local; }
+template <bool HAS>
+using Product = std::conditional_t<HAS, LaneProduct, zc::NoProduct>;
 
 // Copy a code table into LDS, 16 bytes per lane and step.
 template <int WORDS>
@@ -506,13 +550,14 @@ struct ChunkPointers {
 // and the next one in that order is fetched before the current one is decoded; the
 // local values of a tile are requested before its first chunk is decoded.
 template <int RATE, int U, bool LOCAL, bool RAW_OUT, int K>
-__global__ __launch_bounds__(kThreads) void reduce_kernel(ChunkPointers chunks, int k_given, const float* local, size_t n,
-                                                          uint8_t* out, float* out_raw) {
+__device__ __forceinline__ void reduce_tiles(const ChunkPointers& chunks, int k_given, const float* local, size_t n,
+                                             uint8_t* out, float* out_raw) {
   const int k = K > 0 ? K : k_given;   // K > 0: the number of chunks is known when the kernel is compiled
   __shared__ __align__(16) uint32_t dec[decoder_table_words<RATE>()];
   __shared__ __align__(16) uint32_t dec_half[RATE == 4 ? kDec4HalfWords : 4];
   __shared__ __align__(16) uint32_t enc[RAW_OUT ? 4 : encoder_table_words<RATE>()];
   const zc::Tables tab = stage_reduce_tables<RATE, !RAW_OUT, (RATE == 4)>(dec, dec_half, enc);
+  const Product<has_product(RATE, LOCAL, K)> product;
   __syncthreads();
   constexpr int NW = zc::Traits<RATE>::kWords;
   constexpr size_t kTile = (size_t)U * kThreads;
@@ -577,7 +622,7 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(ChunkPointers chunks, 
                 if (first) zc::accumulate_plain4<true>(W[g][u][0], tab, s[u]);
                 else zc::accumulate_plain4<false>(W[g][u][0], tab, s[u]);
               } else {
-                zc::decode_block_add<RATE>(W[g][u], tab, s[u], AnyLane());
+                zc::decode_block_add<RATE, true, RAW_OUT>(W[g][u], tab, s[u], AnyLane(), product);
               }
             }
           }
@@ -636,8 +681,8 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(ChunkPointers chunks, 
         } else {
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            if (c == 0) zc::decode_block<RATE>(W[u], tab, s[u], AnyLane());
-            else zc::decode_block_add<RATE>(W[u], tab, s[u], AnyLane());
+            if (c == 0) zc::decode_block<RATE>(W[u], tab, s[u], AnyLane(), product);
+            else zc::decode_block_add<RATE, true, RAW_OUT>(W[u], tab, s[u], AnyLane(), product);
           }
         }
         if (!last || more) {
@@ -711,6 +756,20 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(ChunkPointers chunks, 
       store_stream<RATE>(out, whole, Wo);
     }
   }
+}
+
+template <int RATE, int U, bool LOCAL, bool RAW_OUT, int K>
+__global__ __launch_bounds__(kThreads) void reduce_kernel(ChunkPointers chunks, int k, const float* local, size_t n, uint8_t* out, float* out_raw) {
+  reduce_tiles<RATE, U, LOCAL, RAW_OUT, K>(chunks, k, local, n, out, out_raw);
+}
+// With the product (told that eight wavefronts fit a SIMD, the compiler keeps its results out of the accumulation registers).  us without and
+// with it: 2-way reduce of 2^27 + 4099 values 239 and 218, of 2^25 69.3 and 65.6, to fp32 52.8 and 50.8; of wavefronts of zero blocks 48 and 34, but of
+// constant values, whose blocks take the general form behind the first four steps, 118 and 120, to fp32 91.8 and 93.5.
+template <int RATE, int U, bool RAW_OUT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8)))
+void reduce_product_kernel(ChunkPointers chunks, size_t n, uint8_t* out, float* out_raw) {
+  static_assert(has_product(RATE, false, 2), "two chunks");
+  reduce_tiles<RATE, U, false, RAW_OUT, 2>(chunks, 2, nullptr, n, out, out_raw);
 }
 
 // ---- small messages -------------------------------------------------------------------
@@ -1047,6 +1106,21 @@ int zc_decompress_half(const void* d_in, size_t n, int rate, int dtype, void* d_
   return launch_decompress(d_in, n, rate, dtype, d_out, stream);
 }
 
+}  // extern "C"
+
+namespace {
+template <int RATE, bool LOCAL, bool RAW>
+void launch_reduce2(const ChunkPointers& chunks, const float* local, size_t n, uint8_t* out, float* out_raw, hipStream_t s) {
+  const dim3 grid(grid_for(n, RAW ? kReduceRaw : kReduce, RATE, reduce_unroll<RATE>()));
+  if constexpr (has_product(RATE, LOCAL, 2))
+    hipLaunchKernelGGL((reduce_product_kernel<RATE, reduce_unroll<RATE>(), RAW>), grid, dim3(kThreads), 0, s, chunks, n, out, out_raw);
+  else
+    hipLaunchKernelGGL((reduce_kernel<RATE, reduce_unroll<RATE>(), LOCAL, RAW, 2>), grid, dim3(kThreads), 0, s, chunks, 2, local, n, out, out_raw);
+}
+}  // namespace
+
+extern "C" {
+
 static int launch_reduce(const void* const* d_in, int k, const float* d_local, size_t n, int rate, void* d_out,
                          size_t out_cap, float* d_out_raw, void* stream) {
   const bool raw_out = d_out_raw != nullptr;
@@ -1067,15 +1141,15 @@ static int launch_reduce(const void* const* d_in, int k, const float* d_local, s
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint8_t* out = static_cast<uint8_t*>(d_out);
   const unsigned small = small_grid(n, raw_out ? kReduceRaw : kReduce, rate, k == 2 && !d_local);
-#define LAUNCH_K(R, LOCAL, RAW, K)                                                                            \
-  hipLaunchKernelGGL((reduce_kernel<R, reduce_unroll<R>(), LOCAL, RAW, K>), dim3(grid_for(n, RAW ? kReduceRaw : kReduce, R, reduce_unroll<R>())),    \
+#define LAUNCH_K(R, LOCAL, RAW)                                                                               \
+  hipLaunchKernelGGL((reduce_kernel<R, reduce_unroll<R>(), LOCAL, RAW, 0>), dim3(grid_for(n, RAW ? kReduceRaw : kReduce, R, reduce_unroll<R>())),    \
                      dim3(kThreads), 0, s, chunks, k, d_local, n, out, d_out_raw)
 #define LAUNCH(R, LOCAL, RAW)                 \
   do {                                        \
     if (small)                                \
       hipLaunchKernelGGL((reduce_small_kernel<R, LOCAL, RAW>), dim3(small), dim3(kThreads), 0, s, chunks, k, d_local, n, out, d_out_raw); \
-    else if (k == 2) LAUNCH_K(R, LOCAL, RAW, 2);   \
-    else LAUNCH_K(R, LOCAL, RAW, 0);          \
+    else if (k == 2) launch_reduce2<R, LOCAL, RAW>(chunks, d_local, n, out, d_out_raw, s);   \
+    else LAUNCH_K(R, LOCAL, RAW);          \
   } while (0)
 #define CALL(R)                                   \
   do {                                            \

@@ -144,6 +144,63 @@ extern "C" int zc_host_add_blocks(int rate, int branches, const uint8_t* in, siz
   return 0;
 }
 
+// Rate 8 with the inverse transform as a matrix: the halves, weights and biases that the kernels put into their matrix
+// instructions, multiplied and summed in fp32 from either end, which has to give the same (every sum is exact).
+namespace {
+constexpr zc::Operands8 kOperands8 = zc::build_operands8();
+
+float half_to_float(uint32_t h) {   // (exact; no infinities here)
+  const int e = (int)((h >> 10) & 31u);
+  const float m = e ? __builtin_ldexpf((float)(1024u + (h & 1023u)), e - 25) : __builtin_ldexpf((float)(h & 1023u), -24);
+  return (h & 0x8000u) ? -m : m;
+}
+
+struct HostProduct {
+  static constexpr bool kHere = true;
+  bool* used;
+  bool* exact;
+  void operator()(uint32_t up, uint32_t low, float (&d)[4]) const {
+    *used = true;
+    for (int i = 0; i < 4; ++i) {
+      float term[8];
+      int n = 0;
+      for (int p = 0; p < 2; ++p)
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t upper = (((up ^ zc::kDigitSigns) >> (8 * p)) & zc::kDigitBytes) >> (16 * h) & 0xFFFFu;
+          const uint32_t lower = (((low ^ zc::kDigitSigns) >> (8 * p)) & zc::kDigitBytes) >> (16 * h) & 0xFFFFu;
+          term[n++] = half_to_float(upper) * half_to_float((kOperands8.upper[i][p] >> (16 * h)) & 0xFFFFu);
+          term[n++] = half_to_float(lower) * half_to_float((kOperands8.lower[i][p] >> (16 * h)) & 0xFFFFu);
+        }
+      float v = kOperands8.bias[i], back = 0.0f;
+      for (int t = 0; t < n; ++t) v += term[t];
+      for (int t = n; t-- > 0;) back += term[t];
+      back += kOperands8.bias[i];
+      *exact = *exact && v == back;
+      d[i] = v;
+    }
+  }
+};
+}  // namespace
+
+// first: sum = the decoded blocks, otherwise sum += (stream: the sign of a zero does not matter).  covered[j]: by the matrix.
+extern "C" int zc_host_matrix8(int first, int stream, const uint8_t* in, size_t blocks, float* sum, uint8_t* covered) {
+  bool exact = true;
+  for (size_t j = 0; j < blocks; ++j) {
+    uint32_t W[1];
+    float s[4];
+    bool used = false;
+    std::memcpy(W, in + 4 * j, 4);
+    std::memcpy(s, sum + 4 * j, 16);
+    const HostProduct product{&used, &exact};
+    if (first) zc::decode_block<8>(W, kTables, s, always, product);
+    else if (stream) zc::decode_block_add<8, true, false>(W, kTables, s, always, product);
+    else zc::decode_block_add<8, true, true>(W, kTables, s, always, product);
+    std::memcpy(sum + 4 * j, s, 16);
+    covered[j] = used;
+  }
+  return exact ? 0 : -1;
+}
+
 extern "C" int zc_host_decode_blocks(int rate, const uint8_t* in, size_t blocks, float* x) {
   for (size_t j = 0; j < blocks; ++j) switch (rate) {
 #define F(R) case R: dec<R>(in + j * (R / 2), x + 4 * j); break;

@@ -431,3 +431,42 @@ def test_both_sides_of_the_line_for_small_messages(gpu, oracle, rate, per_cu):
 def test_both_sides_of_the_line_for_two_raw_chunks(gpu, oracle):
     """Two chunks without local values to fp32 at rate 4: the line lies at 3.5 workgroups of 256 blocks per CU."""
     test_both_sides_of_the_line_for_small_messages(gpu, oracle, 4, 3.5)
+
+
+@pytest.mark.parametrize("raw", (False, True))
+def test_two_chunks_at_rate_8_by_matrix_and_not(gpu, oracle, raw):
+    """The 2-way reduce at rate 8 with whole tiles, whose decoder multiplies by a matrix where that covers all of a wavefront's
+    blocks: wavefronts of ordinary blocks, with one block in 64 that is not covered, of zero blocks, of constant ones (many
+    planes) and of arbitrary bytes, each kind beside each other in the two chunks."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 4 * 256 * 9 * cus + 4 * 777 + 3     # past the line for small messages, with blocks after the last tile and a ragged one
+    blocks = n // 4 + 1
+    rng = np.random.default_rng(8)
+    chunks = []
+    for shift in range(2):
+        x = (rng.standard_normal(n + 1) * 1e-3).astype(np.float32)
+        kind = (np.arange(blocks) // 64 + np.arange(blocks) // 4096 * shift) % 5   # of a wavefront
+        per_value = np.repeat(kind, 4)[:n + 1]
+        x[per_value == 2] = 0.0
+        x[per_value == 3] = 0.3
+        s = oracle.compress(x[:n], 8).reshape(-1, 4).copy()
+        odd = (kind == 1) & (np.arange(blocks) % 64 == 17 * shift + 5)
+        s[odd] = rng.integers(0, 256, size=(int(odd.sum()), 4), dtype=np.uint8)
+        s[odd, 0] = np.minimum(s[odd, 0], 250)   # (no sum overflows)
+        junk = kind == 4
+        s[junk, 1:] = rng.integers(0, 256, size=(int(junk.sum()), 3), dtype=np.uint8)
+        s[junk, 0] = rng.choice([0, 20, 29, 100, 240, 241, 250], size=int(junk.sum()))
+        chunks.append(np.ascontiguousarray(s.reshape(-1)))
+    dev = [torch.from_numpy(c).cuda() for c in chunks]
+    with np.errstate(all="ignore"):
+        if raw:
+            got = gpu.zc_reduce_decompress(dev, None, n, 8).cpu().numpy()
+            want = oracle.decompress(chunks[0], n, 8) + oracle.decompress(chunks[1], n, 8)
+            same = (got.view(np.uint32) == want.view(np.uint32)) | (np.isnan(got) & np.isnan(want))
+            assert same.all(), np.flatnonzero(~same)[:5]
+        else:
+            got = gpu.zc_reduce_compressed(dev, n, 8).cpu().numpy()
+            want = oracle.reduce_compressed(chunks, n, 8)
+            bad = np.flatnonzero(got != want)
+            assert bad.size == 0, (bad.size, bad[:5] // 4)

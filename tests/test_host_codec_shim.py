@@ -222,3 +222,50 @@ def test_zero_blocks_side_by_side_with_others(oracle, shim, rate, share):
         assert shim.zc_host_decode_wave(rate, s.ctypes.data, n, got.ctypes.data, lanes) == 0
         bad = np.flatnonzero((got.view(np.uint32) != want.view(np.uint32)).reshape(-1, 4).any(axis=1))
         assert bad.size == 0, (rate, share, lanes, bad[:5])
+
+
+def _rate8_blocks(rng):
+    """Arbitrary blocks by the number of empty planes (the first plane crowded or not), dense and sparse, under exponent
+    bytes of every kind, and what the encoder makes of ordinary values."""
+    bits = rng.integers(0, 2, size=(24 * 1500, 24), dtype=np.uint8)
+    for k in range(3):
+        bits[k::4] &= rng.integers(0, 2, size=bits[k::4].shape, dtype=np.uint8)
+    for lead in range(24):
+        part = bits[1500 * lead:1500 * (lead + 1)]
+        part[:, :lead] = 0
+        part[:, lead] = 1
+    s = np.zeros((len(bits), 4), dtype=np.uint8)
+    s[:, 1:] = np.packbits(bits, axis=1, bitorder="little")
+    s[:, 0] = np.where(rng.random(len(s)) < 0.3, rng.choice([0, 1, 28, 29, 30, 239, 240, 241, 251, 252, 255], size=len(s)), rng.integers(29, 241, size=len(s)))
+    return s
+
+
+@pytest.mark.parametrize("stream", (0, 1))
+def test_rate8_matrix_matches_reference(oracle, shim, stream):
+    """The decoder's inverse transform as a matrix product at rate 8, alone and added to sums (zeros of both signs among
+    them, whose sign a stream does not keep), against the reference decoder and an addition in fp32; and that the matrix covers
+    what it is for: nearly all of the encoder's blocks, and none without an empty plane."""
+    shim.zc_host_matrix8.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_void_p]
+    rng = np.random.default_rng(88 + stream)
+    s = _rate8_blocks(rng)
+    ordinary = oracle.compress(workloads.gradient_lowrank(64, 1024).reshape(-1), 8).reshape(-1, 4)
+    rows = np.ascontiguousarray(np.concatenate([s, ordinary]))
+    n = len(rows)
+    with np.errstate(all="ignore"):
+        y = oracle.decompress(rows.reshape(-1), 4 * n, 8)
+        start = (rng.standard_normal(4 * n) * np.ldexp(1.0, rng.integers(-140, 120, size=4 * n))).astype(np.float32)
+        start[::9], start[4::9] = 0.0, -0.0
+        start[1::3] = (y[1::3] * rng.uniform(-2, 2, size=y[1::3].size)).astype(np.float32)
+        want = start + y
+    covered = np.zeros(n, dtype=np.uint8)
+    got = np.zeros(4 * n, dtype=np.float32)
+    assert shim.zc_host_matrix8(1, 0, rows.ctypes.data, n, got.ctypes.data, covered.ctypes.data) == 0
+    bad = np.flatnonzero(got.view(np.uint32) != y.view(np.uint32))
+    assert bad.size == 0, (bad[:5], rows[bad[:1] // 4])
+    got = start.copy()
+    assert shim.zc_host_matrix8(0, stream, rows.ctypes.data, n, got.ctypes.data, covered.ctypes.data) == 0
+    ok = (got.view(np.uint32) == want.view(np.uint32)) | (np.isnan(got) & np.isnan(want)) | ((stream != 0) & (got == 0) & (want == 0))
+    assert ok.all(), np.flatnonzero(~ok)[:5]
+    by_lead = covered[:24 * 1500].reshape(24, 1500).mean(axis=1)
+    assert by_lead[0] == 0 and 0 < by_lead[1] < by_lead[3] and (by_lead[15:] == 0).all(), by_lead
+    assert covered[len(s):].mean() > 0.98
