@@ -122,6 +122,18 @@ ZC_DEV uint32_t umin16(uint32_t a, uint32_t b) {
   return umin(a & 0xFFFFu, b & 0xFFFFu);
 #endif
 }
+// (the same with a number, which takes no register: one more in the decoder was the 65th of four of the k-way reduces,
+// and a SIMD held seven wavefronts of these instead of eight)
+template <uint32_t B>
+ZC_DEV uint32_t umin16(uint32_t a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  uint32_t r;
+  asm("v_min_u16 %0, %2, %1" : "=v"(r) : "v"(a), "n"(B));
+  return r;
+#else
+  return umin(a & 0xFFFFu, B);
+#endif
+}
 // (the larger of a's and a number, and the sum)
 template <uint32_t B>
 ZC_DEV uint32_t umax16(uint32_t a) {
@@ -934,7 +946,7 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
         // table, eight times the row's in the budget table; the next stream bit is bit 2 of W[0])
         uint32_t at;
         if (any_lane_active.some(reading & any_lane_active.lanes(left < (uint32_t)kDecLook))) {
-          const uint32_t mask4 = (4u << (BRANCHES ? umin16(left, 7u) : umin(left, 7u))) - 4u;   // the next min(left, 7) stream bits, in place
+          const uint32_t mask4 = (4u << (BRANCHES ? umin16<7>(left) : umin(left, 7u))) - 4u;   // the next min(left, 7) stream bits, in place
           at = 4u * kDecLookEntries + (state >> 1) + mask4 + (W[0] & mask4);
         } else {
           at = state | (W[0] & (((1u << kDecLook) - 1u) << 2));
@@ -976,7 +988,7 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
           open = any_lane_active.some(reading);
           if (!open || s == 4u) break;
           if (any_lane_active.some(reading & any_lane_active.lanes(left < (uint32_t)kDecLook))) {
-            const uint32_t mask4 = (4u << umin16(left, 7u)) - 4u;
+            const uint32_t mask4 = (4u << umin16<7>(left)) - 4u;
             take(4u * kDecLookEntries + (state >> 1) + mask4 + (W[0] & mask4));
           } else {
             take(state | (W[0] & kLookMask));

@@ -2,30 +2,54 @@
 make of their sources; no GPU.
 
 The lossless calls use no memory besides their buffers (include/zc.h): none of their kernels keeps anything in
-scratch memory, which the runtime would have to allocate.  And no inline assembly of the 4 x 4 kernels reads a
+scratch memory, which the runtime would have to allocate.  Kernels that just fit a number of wavefronts per SIMD do not
+outgrow it.  And no inline assembly of the 4 x 4 kernels reads a
 register that a matrix instruction wrote: how long a reader has to wait for it, the compiler sees to for the
 instructions that it knows only."""
+import os
 import re
 import subprocess
+
+import pytest
 
 from paper_2409_02423_amd import build
 
 
-def _assembly(tmp_path, name):
-    source = [s for s in build.SOURCES if s.endswith(name)][0]
-    out = str(tmp_path / "kernels.s")
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    """The assembly of each source by its name, all of them made side by side."""
+    work = tmp_path_factory.mktemp("asm")
     flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
-    subprocess.check_call([build.HIPCC] + flags + ["-S", "--cuda-device-only", source, "-o", out],
-                          stderr=subprocess.DEVNULL)
-    return open(out).read()
+    running = []
+    for source in build.SOURCES:
+        out = str(work / (os.path.basename(source) + ".s"))
+        running.append((os.path.basename(source), out, subprocess.Popen(
+            [build.HIPCC] + flags + ["-S", "--cuda-device-only", source, "-o", out], stderr=subprocess.DEVNULL)))
+    texts = {}
+    for name, out, process in running:
+        assert process.wait() == 0, name
+        with open(out) as f:
+            texts[name] = f.read()
+    return texts
 
 
-def test_lossless_kernels_use_no_scratch(tmp_path):
-    text = _assembly(tmp_path, "zl_kernels.hip")
+def test_lossless_kernels_use_no_scratch(assembly):
+    text = assembly["zl_kernels.hip"]
     kernels = re.findall(r"\.amdhsa_kernel (\S+)\n(.*?)\.end_amdhsa_kernel", text, flags=re.S)
     assert sum("zl_compress_kernel" in name for name, _ in kernels) == 2
     for name, meta in kernels:
         assert re.search(r"\.amdhsa_private_segment_fixed_size (\d+)", meta).group(1) == "0", name
+
+
+# Kernels whose registers are just few enough for so many wavefronts per SIMD: template arguments as they are mangled.
+@pytest.mark.parametrize("source, kernel, waves", [
+    ("zc_kernels.hip", "reduce_kernelILi12ELi2ELb0ELb1ELi0E", 8),
+    ("zc_kernels.hip", "reduce_kernelILi24ELi2ELb1ELb0ELi0E", 8),
+    ("zc_kernels.hip", "reduce_kernelILi28ELi2ELb0ELb1ELi0E", 8),
+])
+def test_kernels_that_just_fit_do(assembly, source, kernel, waves):
+    m = re.search(r"^_Z\w*%s\w*:.*?; Occupancy: (\d+)" % kernel, assembly[source], flags=re.S | re.M)
+    assert int(m.group(1)) >= waves
 
 
 def _registers(operand):
@@ -36,9 +60,9 @@ def _registers(operand):
     return {int(m.group(1))} if m else set()
 
 
-def test_inline_assembly_reads_no_matrix_results(tmp_path):
+def test_inline_assembly_reads_no_matrix_results(assembly):
     from_matrix, inline, products, blocks = set(), False, 0, 0
-    for line in _assembly(tmp_path, "zc2d_kernels.hip").splitlines():
+    for line in assembly["zc2d_kernels.hip"].splitlines():
         line = line.strip()
         if line in (";;#ASMSTART", ";;#ASMEND"):
             inline = line == ";;#ASMSTART"
