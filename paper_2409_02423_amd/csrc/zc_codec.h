@@ -59,6 +59,16 @@ ZC_DEV void materialise(uint32_t& v) {
 #endif
 }
 
+// The same for a value of a branch that few wavefronts take, which so stays one: the compiler would work out short ones always
+// and select.
+ZC_DEV void materialise_seldom(uint32_t& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("; seldom" : "+v"(v));
+#else
+  (void)v;
+#endif
+}
+
 // ({hi,lo} >> (s & 31)) truncated to 32 bits.
 ZC_DEV uint32_t alignbit(uint32_t hi, uint32_t lo, uint32_t s) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -895,7 +905,15 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
       // without and with this: 2-way reduce of 2^25 values at rate 12 73.2 and 71.1, at rate 16 96.5 and 94.1, decompress of 5e6 at
       // rate 20 8.42 and 8.14; at rate 8, where there is little to save, 58.6 and 59.3)
       if constexpr (kZeroApart) uncommon = any_lane_active.lanes(E != 0u && !common_exponent(E));
+      // (The count stays a branch.  us of zeros before it was none, with none and now: 2-way reduce to fp32 of 2^25 values at rate 12 35.6,
+      // 38.0 and 35.3, to a stream 59.2, 61.7 and 58.6, 3-way reduce at rate 12 78.2, 82.1 and 77.4, at rate 16 101.5, 103.9 and 99.4;
+      // ordinary values alike.)
       if (NW > 1 && (!kZeroApart || any_lane_active(E != 0u && top == 0u))) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        // (at rate 32 this one keeps a register: 64 instead of 65 of the reduce of any number of chunks to fp32, eight wavefronts
+        // per SIMD instead of seven, 3-way 2^25 values 121 and 118 us; at the other rates it takes one or two per cent of two chunks)
+        if constexpr (kZeroApart && RATE == 32) asm volatile("");
+#endif
         lead = 0;
         bool found = false;
 #pragma unroll
@@ -906,6 +924,7 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
           found = found || (w != 0);
         }
         lead = umin(lead - 8u, (uint32_t)kPayload);   // (the header byte)
+        if constexpr (kZeroApart) materialise_seldom(lead);
       }
       // a zero block ignores its payload; after 32 empty planes nothing is left to decode
       none = E == 0u || (kPayload > 32 && lead >= 32u);

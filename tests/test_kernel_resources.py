@@ -46,10 +46,19 @@ def test_lossless_kernels_use_no_scratch(assembly):
     ("zc_kernels.hip", "reduce_kernelILi12ELi2ELb0ELb1ELi0E", 8),
     ("zc_kernels.hip", "reduce_kernelILi24ELi2ELb1ELb0ELi0E", 8),
     ("zc_kernels.hip", "reduce_kernelILi28ELi2ELb0ELb1ELi0E", 8),
+    ("zc_kernels.hip", "reduce_kernelILi32ELi2ELb0ELb1ELi0E", 8),
 ])
 def test_kernels_that_just_fit_do(assembly, source, kernel, waves):
     m = re.search(r"^_Z\w*%s\w*:.*?; Occupancy: (\d+)" % kernel, assembly[source], flags=re.S | re.M)
     assert int(m.group(1)) >= waves
+
+
+# What few wavefronts need is branched around (materialise_seldom in zc_codec.h), for zero blocks' sake.
+@pytest.mark.parametrize("kernel", ["reduce_kernelILi12ELi2ELb0ELb1ELi2E", "reduce_kernelILi16ELi2ELb0ELb1ELi0E"])
+def test_seldom_wanted_counts_are_branched_around(assembly, kernel):
+    code = re.search(r"^_Z\w*%s\w*:.*?s_endpgm" % kernel, assembly["zc_kernels.hip"], flags=re.S | re.M).group(0)
+    around = re.findall(r"s_cbranch_\w+ (\.LBB\w+)\n(?:(?!\.LBB|\s+s_cbranch).*\n)+?\s+; seldom\n\s+;;#ASMEND\n\1:", code)
+    assert 0 < len(around) == code.count("; seldom")
 
 
 def _registers(operand):
