@@ -744,8 +744,10 @@ __device__ __forceinline__ void fill_block(const Walk& w, const Cursor& cur, con
 // (Where local values are added the lifting's way is kept: a block per lane is what they are added to, and
 // the matrix product, the rows' way back and the local values together took 88 registers and four
 // wavefronts per SIMD: 23.8 against 22.4 us for one chunk and fp32 output, 2048 x 6144 values at rate 4.)
+// (Six wavefronts per SIMD also for one that adds local values and encodes, which at rate 4 took 82 registers and five: one chunk and local
+// values to a stream, 8192 x 8192 values at rate 4, 99.5 and 91.9 us.)
 template <int RATE, bool LOCAL, bool RAW_OUT, int THREADS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(as_matrix(RATE, THREADS) && !LOCAL ? 6 : 1)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(as_matrix(RATE, THREADS) && !(LOCAL && RAW_OUT) ? 6 : 1)))
 void reduce2d_kernel(ChunkPointers2d chunks, int k, const float* local, Walk w, uint8_t* out, float* out_raw) {
   constexpr bool kMatrix = as_matrix(RATE, THREADS) && !LOCAL;
   __shared__ __attribute__((aligned(16))) DecodeLds<THREADS, kMatrix, !RAW_OUT> lds;

@@ -47,6 +47,9 @@ def test_lossless_kernels_use_no_scratch(assembly):
     ("zc_kernels.hip", "reduce_kernelILi24ELi2ELb1ELb0ELi0E", 8),
     ("zc_kernels.hip", "reduce_kernelILi28ELi2ELb0ELb1ELi0E", 8),
     ("zc_kernels.hip", "reduce_kernelILi32ELi2ELb0ELb1ELi0E", 8),
+    ("zc2d_kernels.hip", "reduce2d_kernelILi2ELb1ELb0ELi512E", 6),
+    ("zc2d_kernels.hip", "reduce2d_kernelILi4ELb1ELb0ELi512E", 6),
+    ("zc2d_kernels.hip", "reduce2d_kernelILi8ELb1ELb0ELi512E", 6),
 ])
 def test_kernels_that_just_fit_do(assembly, source, kernel, waves):
     m = re.search(r"^_Z\w*%s\w*:.*?; Occupancy: (\d+)" % kernel, assembly[source], flags=re.S | re.M)
