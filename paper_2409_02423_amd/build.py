@@ -6,7 +6,7 @@ import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = [os.path.join(HERE, "csrc", f) for f in ("zc_kernels.hip", "zc2d_kernels.hip", "zl_kernels.hip")]
-DEPS = SOURCES + [os.path.join(HERE, "csrc", f) for f in ("zc_codec.h", "zc_half.h", "zc2d_codec.h", "zl_codec.h")] + [
+DEPS = SOURCES + [os.path.join(HERE, "csrc", f) for f in ("zc_codec.h", "zc_half.h", "zc2d_codec.h", "zc2d_grid.h", "zl_codec.h")] + [
                   os.path.join(HERE, "..", "include", "zc.h")]
 LIB = os.path.join(HERE, "libzc.so")
 STAMP = LIB + ".stamp"   # digest of what the library was built from (file times do not survive every copy)

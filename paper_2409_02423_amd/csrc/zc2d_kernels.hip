@@ -13,6 +13,7 @@
 
 #include "../../include/zc.h"
 #include "zc2d_codec.h"
+#include "zc2d_grid.h"
 #include "zc_half.h"
 
 namespace {
@@ -59,25 +60,17 @@ __device__ __forceinline__ void stage_table(const uint32_t* __restrict__ src, ui
 // four wavefronts: 0.530 against 0.496 ms for the 2-way reduce of 8192 x 32768 values at rate 4).  (256 lanes, as
 // the kernels were before: 0.270 against 0.248 ms for decompress2d, 0.613 against 0.583 ms for the reduce;
 // 1024: 0.599 ms.)
-// Their grid, us of 8192 x 32768 values at rate 4: decompress2d 234, 222 and 222 at 16, 24 and 32, the 2-way reduce
-// with fp32 output 384, 357, 362 and 386 at 24, 48, 64 and 96.  With fp32 rows that are aligned to
-// their elements only, at rates 2 and 4 also with those that do not start at 64 bytes, decompress2d gains from more:
-// neighbouring wavefronts write to the same cache lines and should do so at the same time (6144 x 43690 values at rate 4: 279
-// at 48, 250 at 64; at rate 8 274 and 277; 6144 x 43688 at rate 4 309 at 24, 255 at 64).  Where memory is waited for less it does
-// so from where the output is larger than the last-level cache: at rate 8 rows that do not start at 64 bytes (8192 x 12292 values 91 at
-// 24, 96 at 64; 10000 x 12292 136 and 113; 6144 x 43688 298 and 240), at rate 2 half-precision ones that do not start at cache lines
-// (12288 x 12292 97 and 107, 8192 x 24580 141 and 134, 8192 x 28676 201 and 152; at rate 4 98 and 109, 132 and 139, 155 and 159).  The
-// reduce with local values and fp32 output is like it (522 at 24, 457 at 64).  The reduces that write streams have
-// 24: 469 at 16, 24 and 32.  Matrices of fewer than twice these many workgroups' blocks get fewer (see decode_grid_for).
+// Their grids and the figures behind them are in zc2d_grid.h.
 // The compress kernel has 16, and 64 where that leaves a lane four blocks or more: with one block per lane a
 // workgroup stages its table and asks for its values for nothing else (8192 x 32768 values at rate 4: 238 at 16, 224 at
 // 64, 229 at 128; 8192 x 8192 at rate 2: 48.9 at 16, four blocks per lane, 55.8 at 64, one block; 6144 x 43690 at rate 8
 // 296 and 265).
 // Only a build with -DZC_TUNING_KNOBS lets ZC2D_WORKGROUPS_PER_CU override these; the shipped library reads
 // no environment variable.
-constexpr int kCompressWorkgroupsPerCU = 16, kCompressWorkgroupsPerCUMost = 64, kDecodeWorkgroupsPerCU = 24, kDecodeWorkgroupsPerCUWide = 64,
-              kDecodeWorkgroupsPerCULeast = 12;
-constexpr size_t kDecodeBytesLarge = (size_t)448 << 20;   // of output
+constexpr int kCompressWorkgroupsPerCU = 16, kCompressWorkgroupsPerCUMost = 64;
+using zc2d::kDecodeWorkgroupsPerCU;
+using zc2d::kDecodeWorkgroupsPerCULeast;
+using zc2d::kDecodeWorkgroupsPerCUWide;
 
 // The wavefront-wide vote of the codec: whether p holds in some lane.
 struct AnyLane {
@@ -994,11 +987,8 @@ int launch_decompress2d(const void* d_in, size_t rows, size_t cols, int rate, vo
   const size_t blocks = ((rows + 3) / 4) * ((cols + 3) / 4);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int cus = compute_units(), threads = decode_threads(blocks, rate, false, cus);
-  const bool large = blocks * 16 * (DT == kF32 ? 4 : 2) >= kDecodeBytesLarge;
-  const bool wide = DT == kF32 ? (cols & 3) != 0 || ((cols & 15) != 0 && (rate <= 4 || (rate == 8 && large)))
-                               : rate == 2 && (cols & 31) != 0 && large;
-  const unsigned grid = wide ? grid_for(blocks, kDecodeWorkgroupsPerCUWide, threads, cus)
-                        : decode_grid_for(blocks, (cols & 3) ? kDecodeWorkgroupsPerCUWide : kDecodeWorkgroupsPerCU, threads, cus);
+  const zc2d::DecompressGrid g = zc2d::decompress_grid(blocks, cols, DT != kF32, rate);
+  const unsigned grid = g.at_once ? grid_for(blocks, g.per_cu, threads, cus) : decode_grid_for(blocks, g.per_cu, threads, cus);
   const Walk w = walk_for(rows, cols, grid, threads, store_form(cols, DT != kF32, rate <= 4 ? 16 : 4));
 #define LAUNCH(R, T) hipLaunchKernelGGL((decompress2d_kernel<R, DT, T>), dim3(grid), dim3(T), 0, s, static_cast<const uint8_t*>(d_in), w, d_out)
 #define CALL(R)                                                                \

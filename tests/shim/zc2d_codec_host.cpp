@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "../../paper_2409_02423_amd/csrc/zc2d_codec.h"
+#include "../../paper_2409_02423_amd/csrc/zc2d_grid.h"
 
 namespace {
 // one lane alone: its own predicate is the vote
@@ -190,4 +191,10 @@ extern "C" int zc2d_host_decode_blocks(int rate, const uint8_t* in, size_t block
       default: return -2;
     }
   return 0;
+}
+
+// Workgroups per CU of decompress2d, negative if the grid may be made smaller for want of blocks per lane.
+extern "C" int zc2d_host_decompress_grid(size_t rows, size_t cols, int half, int rate) {
+  const zc2d::DecompressGrid g = zc2d::decompress_grid(((rows + 3) / 4) * ((cols + 3) / 4), cols, half != 0, rate);
+  return g.at_once ? g.per_cu : -g.per_cu;
 }

@@ -12,7 +12,7 @@ from paper_2409_02423_amd import workloads
 HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "shim", "zc2d_codec_host.cpp")
 LIB = os.path.join(HERE, "shim", "libzc2d_codec_host.so")
-HDRS = [os.path.join(HERE, "..", "paper_2409_02423_amd", "csrc", f) for f in ("zc2d_codec.h", "zc_codec.h")]
+HDRS = [os.path.join(HERE, "..", "paper_2409_02423_amd", "csrc", f) for f in ("zc2d_codec.h", "zc2d_grid.h", "zc_codec.h")]
 RATES = (2, 4, 8, 16)
 
 
@@ -25,6 +25,7 @@ def shim():
     L = ctypes.CDLL(LIB)
     L.zc2d_host_encode_blocks.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     L.zc2d_host_decode_blocks.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+    L.zc2d_host_decompress_grid.argtypes = [ctypes.c_size_t, ctypes.c_size_t, ctypes.c_int, ctypes.c_int]
     L.zc2d_host_wave.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_int]
     return L
 
@@ -193,3 +194,19 @@ def test_matrix_form_matches_reference_where_it_covers(o2, shim, rate):
         shares[lead] = covered(s[s[:, 0] != 0], lead)
     assert shares[0] == 0 and 0 < shares[1] < shares[3] and shares[3] > 0.8, shares
     assert all(shares[lead] == 0 for lead in shares if lead > 18), shares
+
+
+# At rate 8 no lane takes a second block where neighbouring wavefronts share the ends of fp32 rows.
+@pytest.mark.parametrize("cols", [28, 260, 10004, 10008, 43688])
+@pytest.mark.parametrize("rows", [64, 5000, 6144])
+def test_rows_off_64_bytes_are_decoded_at_once(shim, rows, cols):
+    blocks = (rows + 3) // 4 * ((cols + 3) // 4)
+    assert shim.zc2d_host_decompress_grid(rows, cols, 0, 8) * 256 * 512 >= blocks
+
+
+@pytest.mark.parametrize("rows, cols, half, rate, grid", [
+    (5000, 10016, 0, 8, -24), (5000, 10000, 0, 8, -24), (4000000, 12, 0, 8, -24), (20000000, 12, 0, 8, 64),
+    (5000, 10004, 0, 4, 64), (5000, 10004, 0, 16, -24), (5000, 10003, 0, 16, 64), (5000, 10003, 0, 8, 64),
+    (8192, 12292, 1, 2, -24), (8192, 28676, 1, 2, 64), (8192, 28676, 1, 4, -24), (8192, 6145, 1, 8, -64)])
+def test_other_decompress_grids(shim, rows, cols, half, rate, grid):
+    assert shim.zc2d_host_decompress_grid(rows, cols, half, rate) == grid
