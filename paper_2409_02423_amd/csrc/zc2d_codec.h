@@ -210,19 +210,23 @@ constexpr ExpandTable build_expand_table() {
 // closed after it; a group bit 0 closes the plane.
 // Where these are a group bit 1 and zeros only, and the last coefficient is not among them, the entry passes the eight zeros and
 // leaves the group bit to the next step, in the place of the last of them.
-// Byte 0: how many bits of budget the entry must find, and kTokenGoesOn if a group bit has to be put back; from bit
-// kIndexShift on, where n is kept: how many coefficients were passed; byte 2: the ones, as positions past the current
-// coefficient; byte 3: how many stream bits were used, and bit 31 if the plane is closed (bits 29 and 30 are zeros).
+// Byte 0: how many bits of budget the entry must find; kTokenGoesOn, which is where the window has the last of the eight zeros, if a
+// group bit has to be put there; from bit kIndexShift on, where n is kept: how many coefficients were passed; byte 2: the ones, as
+// positions past the current coefficient; byte 3: how many stream bits were used, and bit 31 if the plane is closed (bits 29 and 30
+// are zeros).
+// (What lies below kIndexShift adds up in n's lower bits over a block, and must not reach kIndexShift: kTokenGoesOn occurs once
+// at most, since it passes eight of sixteen coefficients and leaves the last, and each entry with a byte 0 passes one at least.)
 // Bits past the budget are zeros in the decoder's window, and what they decode to there is right
 // everywhere but in one place: zeros after a group bit 1 would put the one on the last
 // coefficient, where a run cut by the budget has it at the lowest index still possible.  So
-// byte 0 is not zero if the entry holds a run that reaches the last coefficient without a closing one, or does not reach
-// its end: no less than the bits used (4 to 7 count as 8, which leaves kTokenGoesOn its bit).
+// byte 0 is the bits looked at if the entry holds a run that reaches the last coefficient without a closing one, or does not
+// reach its end, and zero otherwise.
 constexpr int kLookahead = 9;
 constexpr int kTokenRows = 11;
 constexpr uint32_t kTokenFirstRowIndex = 6;
-constexpr uint32_t kTokenClosed = 0x80000000u, kTokenGoesOn = 4u;
+constexpr uint32_t kTokenClosed = 0x80000000u, kTokenGoesOn = 4u << (kLookahead - 1);
 constexpr int kIndexShift = kLookahead + 2;   // n, times the bytes of a row
+static_assert(kTokenGoesOn + 16 * kLookahead < 1u << kIndexShift, "nothing is carried into n");
 struct TokenTable { uint32_t v[kTokenRows << kLookahead]; };
 constexpr TokenTable build_token_table() {
   TokenTable t{};
@@ -248,7 +252,7 @@ constexpr TokenTable build_token_table() {
         used += 1 + z + (passed + z == room ? 0 : 1);       // no closing one at the last coefficient
         passed += z + 1;
       }
-      uint32_t need = to_last ? (used & kTokenGoesOn ? 8u : used) : 0u;
+      uint32_t need = to_last ? used : 0u;
       if (used == 0u) {   // (s is 1)
         passed = used = kLookahead - 1;
         need = kLookahead | kTokenGoesOn;
@@ -623,8 +627,8 @@ ZC_DEV void read_planes(const uint32_t* token, PlaneReader<NW>& r, Planes& plane
       zc::materialise(r.pattern);   // (before the window moves)
       r.at += e >> 30;
       const uint32_t taken = used + verbatim;
+      r.W[0] = zc::and_or(e, goes_on, r.W[0]);   // (behind the shift it cost a wait for that: 64 x 256 constant values at rate 16 8.68 and 8.41 us)
       drop_bits<NW>(r.W, taken);
-      r.W[0] = zc::and_or(e, goes_on, r.W[0]);
       r.left -= (int32_t)(taken & 31u);
     }
   };

@@ -64,6 +64,16 @@ def test_seldom_wanted_counts_are_branched_around(assembly, kernel):
     assert 0 < len(around) == code.count("; seldom")
 
 
+# The step through a block's planes waits for nothing between the window's shift, which is inline assembly, and the
+# next look-up: what reads such a result at once gets an idle cycle in front of it.
+@pytest.mark.parametrize("kernel", ["reduce2d_kernelILi4ELb0ELb0ELi256E", "reduce2d_kernelILi4ELb0ELb0ELi512E"])
+def test_nothing_waits_for_the_windows_shift(assembly, kernel):
+    code = re.search(r"^_Z\w*%s\w*:.*?s_endpgm" % kernel, assembly["zc2d_kernels.hip"], flags=re.S | re.M).group(0)
+    lines = [l.strip() for l in code.splitlines() if l.strip() and not l.strip().startswith((";", "."))]
+    after = [b for a, b in zip(lines, lines[1:]) if a.startswith("v_lshrrev_b64")]
+    assert after and not any(b.startswith("s_nop") for b in after)
+
+
 def _registers(operand):
     m = re.fullmatch(r"[-|]*v\[(\d+):(\d+)\][|]*", operand)
     if m:
