@@ -1,6 +1,7 @@
 // Host build of the per-block codec that the GPU kernels run (csrc/zc_codec.h), so
 // that its logic can be checked on the CPU against the reference codec and under
 // host sanitizers before it runs on a GPU.  Test-only: the library never runs this.
+#include <atomic>
 #include <condition_variable>
 #include <cstring>
 #include <mutex>
@@ -69,25 +70,31 @@ struct Ballot {
   unsigned long round = 0;
 };
 
+// a thread's share of a set of lanes is its own predicate; the vote joins them
+struct Vote {
+  Ballot* b;
+  bool lanes(bool p) const { return p; }
+  bool some(bool set) const { return b->vote(set); }
+  bool operator()(bool p) const { return b->vote(p); }
+};
+
+// one(j, whether there is a block j) for as many blocks at a time as there are lanes
+template <class One>
+void in_lockstep(int lanes, size_t blocks, One one) {
+  std::vector<std::thread> pool;
+  for (int t = 0; t < lanes; ++t)
+    pool.emplace_back([&, t] {
+      for (size_t j = t; j < (blocks + lanes - 1) / lanes * lanes; j += lanes) one(j, j < blocks);
+    });
+  for (auto& th : pool) th.join();
+}
+
 template <int RATE>
 void wave(bool encode, const uint8_t* in, size_t blocks, uint8_t* out, int lanes) {
   constexpr int B = zc::Traits<RATE>::kBlockBytes;
   Ballot ballot(lanes);
-  // a thread's share of a set of lanes is its own predicate; the vote joins them
-  struct Vote {
-    Ballot* b;
-    bool lanes(bool p) const { return p; }
-    bool some(bool set) const { return b->vote(set); }
-    bool operator()(bool p) const { return b->vote(p); }
-  };
   const Vote vote{&ballot};
-  const size_t waves = (blocks + lanes - 1) / lanes;
-  std::vector<std::thread> pool;
-  for (int t = 0; t < lanes; ++t)
-    pool.emplace_back([&, t] {
-      for (size_t w = 0; w < waves; ++w) {
-        const size_t j = w * lanes + t;
-        const bool real = j < blocks;   // lanes past the end code a zero block and drop the result
+  in_lockstep(lanes, blocks, [&](size_t j, bool real) {   // (lanes past the end code a zero block and drop the result)
         if (encode) {
           uint32_t b[4] = {0, 0, 0, 0}, W[zc::Traits<RATE>::kWords];
           if (real) std::memcpy(b, in + 16 * j, 16);
@@ -100,9 +107,7 @@ void wave(bool encode, const uint8_t* in, size_t blocks, uint8_t* out, int lanes
           zc::decode_block<RATE>(W, kTables, o, vote);
           if (real) std::memcpy(out + 16 * j, o, 16);
         }
-      }
-    });
-  for (auto& th : pool) th.join();
+  });
 }
 }  // namespace
 
@@ -183,21 +188,37 @@ struct HostProduct {
 }  // namespace
 
 // first: sum = the decoded blocks, otherwise sum += (stream: the sign of a zero does not matter).  covered[j]: by the matrix.
+namespace {
+template <class AnyActive>
+bool matrix8(bool first, bool stream, const uint8_t* in, float* sum, uint8_t* covered, AnyActive vote) {
+  bool used = false, exact = true;
+  uint32_t W[1];
+  float s[4];
+  std::memcpy(W, in, 4);
+  std::memcpy(s, sum, 16);
+  const HostProduct product{&used, &exact};
+  if (first) zc::decode_block<8>(W, kTables, s, vote, product);
+  else if (stream) zc::decode_block_add<8, true, false>(W, kTables, s, vote, product);
+  else zc::decode_block_add<8, true, true>(W, kTables, s, vote, product);
+  std::memcpy(sum, s, 16);
+  *covered = used;
+  return exact;
+}
+}  // namespace
 extern "C" int zc_host_matrix8(int first, int stream, const uint8_t* in, size_t blocks, float* sum, uint8_t* covered) {
   bool exact = true;
-  for (size_t j = 0; j < blocks; ++j) {
-    uint32_t W[1];
-    float s[4];
-    bool used = false;
-    std::memcpy(W, in + 4 * j, 4);
-    std::memcpy(s, sum + 4 * j, 16);
-    const HostProduct product{&used, &exact};
-    if (first) zc::decode_block<8>(W, kTables, s, always, product);
-    else if (stream) zc::decode_block_add<8, true, false>(W, kTables, s, always, product);
-    else zc::decode_block_add<8, true, true>(W, kTables, s, always, product);
-    std::memcpy(sum + 4 * j, s, 16);
-    covered[j] = used;
-  }
+  for (size_t j = 0; j < blocks; ++j) exact = matrix8(first != 0, stream != 0, in + 4 * j, sum + 4 * j, covered + j, always) && exact;
+  return exact ? 0 : -1;
+}
+// The same with `lanes` blocks, of which there is a multiple, in lockstep (see Ballot).
+extern "C" int zc_host_matrix8_wave(int first, int stream, const uint8_t* in, size_t blocks, float* sum, uint8_t* covered, int lanes) {
+  if (blocks % lanes != 0) return -2;
+  Ballot ballot(lanes);
+  const Vote vote{&ballot};
+  std::atomic<bool> exact{true};
+  in_lockstep(lanes, blocks, [&](size_t j, bool) {
+    if (!matrix8(first != 0, stream != 0, in + 4 * j, sum + 4 * j, covered + j, vote)) exact = false;
+  });
   return exact ? 0 : -1;
 }
 

@@ -269,3 +269,65 @@ def test_rate8_matrix_matches_reference(oracle, shim, stream):
     by_lead = covered[:24 * 1500].reshape(24, 1500).mean(axis=1)
     assert by_lead[0] == 0 and 0 < by_lead[1] < by_lead[3] and (by_lead[15:] == 0).all(), by_lead
     assert covered[len(s):].mean() > 0.98
+
+
+@pytest.mark.parametrize("lanes", (4, 16))
+def test_rate8_matrix_in_lockstep(oracle, shim, lanes):
+    """The same with lanes that vote: whether the matrix is taken, whether all are zero blocks, whether some lane is near its
+    budget and whether some goes on past four steps is decided for all of them.  Wavefronts of blocks that the matrix covers, alone
+    and with zero blocks, with one other block (an uncommon exponent byte, no empty plane, a crowded first plane after
+    one, many empty planes), with constant blocks, whose steps are many, of zero blocks only and of any blocks."""
+    shim.zc_host_matrix8.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_void_p]
+    shim.zc_host_matrix8_wave.argtypes = shim.zc_host_matrix8.argtypes + [ctypes.c_int]
+    rng = np.random.default_rng(800 + lanes)
+    ordinary = oracle.compress(workloads.gradient_lowrank(64, 1024).reshape(-1), 8).reshape(-1, 4)
+    alone = np.zeros(len(ordinary), dtype=np.uint8)
+    assert shim.zc_host_matrix8(1, 0, ordinary.ctypes.data, len(ordinary), np.zeros(4 * len(ordinary), np.float32).ctypes.data,
+                                alone.ctypes.data) == 0
+    ordinary = ordinary[alone == 1]
+    constant = oracle.compress(np.repeat(rng.standard_normal(256).astype(np.float32), 4), 8).reshape(-1, 4)
+    any_block = _rate8_blocks(rng)
+    def planes(first, *rest):   # a payload of 24 bits from its first ones
+        bits = np.array(list(first) + list(rest) + [0] * 24, dtype=np.uint8)[:24]
+        return np.packbits(bits, bitorder="little")
+    other = np.concatenate([np.concatenate([[e], p])[None] for e, p in (
+        (252, planes([0, 0, 1, 0, 0, 0])), (28, planes([0, 0, 1, 0, 0, 0])), (127, planes([1, 0, 0, 0])), (127, planes([0] + [1] * 12)),
+        (127, planes([0] * 15 + [1])), (127, planes([0] * 24)), (255, planes([1] * 24)))]).astype(np.uint8)
+    def wave(kind):
+        w = ordinary[rng.integers(0, len(ordinary), size=lanes)].copy()
+        at = rng.permutation(lanes)
+        if kind == "zeros":     # with and without a payload
+            zero = at[:rng.integers(1, lanes)]
+            w[zero, 0] = 0
+            w[zero[::2], 1:] = 0
+        elif kind == "other":
+            w[at[0]] = other[rng.integers(0, len(other))]
+        elif kind == "constant":
+            n = rng.integers(1, lanes + 1)
+            w[at[:n]] = constant[rng.integers(0, len(constant), size=n)]
+        elif kind == "none":
+            w[:, 0] = 0
+        elif kind == "any":
+            w = any_block[rng.integers(0, len(any_block), size=lanes)].copy()
+            w[rng.random(lanes) < 0.3, 0] = 0
+        return w
+    kinds = ["ordinary", "zeros", "other", "constant", "none", "any"] * 24
+    rows = np.ascontiguousarray(np.concatenate([wave(k) for k in kinds]))
+    n = len(rows)
+    with np.errstate(all="ignore"):
+        y = oracle.decompress(rows.reshape(-1), 4 * n, 8)
+        start = (rng.standard_normal(4 * n) * np.ldexp(1.0, rng.integers(-140, 120, size=4 * n))).astype(np.float32)
+        start[::9], start[4::9] = 0.0, -0.0
+        want = start + y
+    covered = np.zeros(n, dtype=np.uint8)
+    for first, stream in ((1, 0), (0, 0), (0, 1)):
+        got = start.copy()
+        assert shim.zc_host_matrix8_wave(first, stream, rows.ctypes.data, n, got.ctypes.data, covered.ctypes.data, lanes) == 0
+        expect = y if first else want
+        ok = (got.view(np.uint32) == expect.view(np.uint32)) | (np.isnan(got) & np.isnan(expect)) | ((stream != 0) & (got == 0) & (expect == 0))
+        assert ok.all(), (first, stream, np.flatnonzero(~ok)[:5], kinds[np.flatnonzero(~ok)[0] // 4 // lanes])
+    by_wave = covered.reshape(-1, lanes)
+    assert (by_wave == by_wave[:, :1]).all()
+    share = {k: by_wave[[j for j, kind in enumerate(kinds) if kind == k], 0].mean() for k in set(kinds)}
+    assert share["ordinary"] > 0.75 and share["zeros"] > 0.75, share
+    assert share["other"] < 0.2 and share["none"] == 0 and 0 <= share["constant"] < 0.75, share

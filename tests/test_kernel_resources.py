@@ -3,9 +3,8 @@ make of their sources; no GPU.
 
 The lossless calls use no memory besides their buffers (include/zc.h): none of their kernels keeps anything in
 scratch memory, which the runtime would have to allocate.  Kernels that just fit a number of wavefronts per SIMD do not
-outgrow it.  And no inline assembly of the 4 x 4 kernels reads a
-register that a matrix instruction wrote: how long a reader has to wait for it, the compiler sees to for the
-instructions that it knows only."""
+outgrow it.  And inline assembly, whose waits the compiler does not know of, keeps away from matrix
+instructions and is not waited for where it is."""
 import os
 import re
 import subprocess
@@ -82,23 +81,40 @@ def _registers(operand):
     return {int(m.group(1))} if m else set()
 
 
-def test_inline_assembly_reads_no_matrix_results(assembly):
-    from_matrix, inline, products, blocks = set(), False, 0, 0
-    for line in assembly["zc2d_kernels.hip"].splitlines():
+# How long a matrix instruction and its neighbours have to wait for each other, the compiler sees to for the instructions that it
+# knows.  Inline assembly reads no matrix result, writes no operand of a matrix instruction within the last few
+# instructions before it, and none of its operands or results within the time that it takes.
+kBefore, kAfter = 4, 20
+
+
+@pytest.mark.parametrize("source, least", [("zc_kernels.hip", 16), ("zc2d_kernels.hip", 8)])
+def test_inline_assembly_keeps_away_from_matrix_instructions(assembly, source, least):
+    from_matrix, inline, products, blocks, at = set(), False, 0, 0, 0
+    written, busy = [], []   # (place, registers) of what inline assembly wrote, and of matrix instructions
+    for line in assembly[source].splitlines():
         line = line.strip()
         if line in (";;#ASMSTART", ";;#ASMEND"):
             inline = line == ";;#ASMSTART"
             continue
+        if not re.match(r"[a-z]\w+(\s|$)", line):
+            continue
+        at += 1
         m = re.match(r"(v_\w+|ds_read\w*|global_load\w*|scratch_load\w*)\s+([^;]*)", line)
         if not m:
             continue
-        operands = [o.strip().split(" ")[0] for o in m.group(2).split(",")]
+        operands = [_registers(o.strip().split(" ")[0]) for o in m.group(2).split(",")]
         if inline:
             blocks += 1
-            assert not any(_registers(o) & from_matrix for o in operands[1:]), line
+            assert not any(o & from_matrix for o in operands[1:]), line
+            busy = [(p, r) for p, r in busy if at - p <= kAfter]
+            assert not any(operands[0] & r for _, r in busy), line
+            written.append((at, operands[0]))
         if m.group(1).startswith("v_mfma"):
             products += 1
-            from_matrix |= _registers(operands[0])
+            written = [(p, r) for p, r in written if at - p <= kBefore]
+            assert not any(o & r for o in operands[1:] for _, r in written), line
+            busy.append((at, set().union(*operands)))
+            from_matrix |= operands[0]
         elif not m.group(1).startswith("v_cmp"):
-            from_matrix -= _registers(operands[0])
-    assert products >= 8 and blocks > 0
+            from_matrix -= operands[0]
+    assert products >= least and blocks > 0
