@@ -954,9 +954,20 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
     // phase 1.  A[i] collects the planes of coefficient i, the latest in bit 0; m counts them
     // (per lane: a step reads one or two planes, or none in a lane that is idle).
     uint32_t A[4] = {0u, 0u, 0u, 0u}, m = 0;
-    // one group of up to four steps: byte i of acc = the group's planes of coefficient i (at most eight)
-    auto group = [&](uint32_t& acc, uint32_t& mg) {
-      uint32_t s = 0;
+    // one step: the entry, whose planes go to acc (byte i: the planes of coefficient i) and their number to mg
+    auto take = [&](uint32_t at, uint32_t& acc, uint32_t& mg) {
+      const uint32_t e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(tab.dec) + at);
+      const uint32_t planes = (e >> 2) & 3u, used = (e >> 4) & 15u;
+      acc = (acc << planes) | (e & 0x03030303u);
+      mg += planes;
+      shift_out<NW>(W, used);
+      left -= used;
+      state = e & kDecIdle;
+      return e;
+    };
+    // up to four steps (at most eight planes), `s` of them taken already; whether some lane goes on
+    constexpr uint32_t kLookMask = ((1u << kDecLook) - 1u) << 2;
+    auto group = [&](uint32_t& acc, uint32_t& mg, uint32_t s = 0) {
 #pragma unroll 1
       for (; s < 4u; ++s) {
         const auto reading = any_lane_active.lanes(state < kDecIdle);
@@ -968,15 +979,9 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
           const uint32_t mask4 = (4u << (BRANCHES ? umin16<7>(left) : umin(left, 7u))) - 4u;   // the next min(left, 7) stream bits, in place
           at = 4u * kDecLookEntries + (state >> 1) + mask4 + (W[0] & mask4);
         } else {
-          at = state | (W[0] & (((1u << kDecLook) - 1u) << 2));
+          at = state | (W[0] & kLookMask);
         }
-        const uint32_t e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(tab.dec) + at);
-        const uint32_t planes = (e >> 2) & 3u, used = (e >> 4) & 15u;
-        acc = (acc << planes) | (e & 0x03030303u);
-        mg += planes;
-        shift_out<NW>(W, used);
-        left -= used;
-        state = e & kDecIdle;
+        take(at, acc, mg);
       }
       return s == 4u;
     };
@@ -986,33 +991,11 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
       if constexpr (kMatrix) {
         // where the matrix may cover the wavefront's blocks, the first step is every lane's, with enough budget for a look-ahead
         uint32_t crowded = 0, s = 0;
-        auto take = [&](uint32_t at) {
-          const uint32_t e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(tab.dec) + at);
-          const uint32_t planes = (e >> 2) & 3u, used = (e >> 4) & 15u;
-          acc = (acc << planes) | (e & 0x03030303u);
-          m += planes;
-          W[0] >>= used;
-          left -= used;
-          state = e & kDecIdle;
-          return e;
-        };
-        constexpr uint32_t kLookMask = ((1u << kDecLook) - 1u) << 2;
         if (!outside) {
-          crowded = (lead - 2u) & take(state | (W[0] & kLookMask));   // (negative: one empty plane and a crowded one)
+          crowded = (lead - 2u) & take(state | (W[0] & kLookMask), acc, m);   // (negative: one empty plane and a crowded one)
           s = 1;
         }
-#pragma unroll 1
-        for (;; ++s) {
-          const auto reading = any_lane_active.lanes(state < kDecIdle);
-          open = any_lane_active.some(reading);
-          if (!open || s == 4u) break;
-          if (any_lane_active.some(reading & any_lane_active.lanes(left < (uint32_t)kDecLook))) {
-            const uint32_t mask4 = (4u << umin16<7>(left)) - 4u;
-            take(4u * kDecLookEntries + (state >> 1) + mask4 + (W[0] & mask4));
-          } else {
-            take(state | (W[0] & kLookMask));
-          }
-        }
+        open = group(acc, m, s) && any_lane_active(state < kDecIdle);
         if (!open && !outside && !any_lane_active((int32_t)crowded < 0)) {
           const uint32_t* pair = tab.dec + kDecPlaneEntries;
           const uint32_t bits = W[0] >> 2;   // (23 bits at most)

@@ -763,8 +763,9 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(ChunkPointers chunks, 
   reduce_tiles<RATE, U, LOCAL, RAW_OUT, K>(chunks, k, local, n, out, out_raw);
 }
 // With the product (told that eight wavefronts fit a SIMD, the compiler keeps its results out of the accumulation registers).  us without and
-// with it: 2-way reduce of 2^27 + 4099 values 239 and 218, of 2^25 69.3 and 65.6, to fp32 52.8 and 50.8; of wavefronts of zero blocks 48 and 34, but of
-// constant values, whose blocks take the general form behind the first four steps, 118 and 120, to fp32 91.8 and 93.5.
+// with it: 2-way reduce of 2^27 + 4099 values 240 and 207, to fp32 175 and 154, of 2^25 68.4 and 62.0, to fp32 51.9 and 48.3; of wavefronts of zero
+// blocks 45.4 and 32.9; of constant values, whose blocks take the general form behind the first four steps, 117.5 and 116.0, to fp32 91.4 and 90.4.
+// With a loop of its own for the first four steps, beside the general form's, these were 217, 161, 64.5, 49.8 and, constant, 119.6 and 93.0.
 template <int RATE, int U, bool RAW_OUT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8)))
 void reduce_product_kernel(ChunkPointers chunks, size_t n, uint8_t* out, float* out_raw) {
