@@ -32,6 +32,7 @@
 #ifndef ZC2D_CODEC_H
 #define ZC2D_CODEC_H
 
+#include <assert.h>
 #include "zc_codec.h"
 
 namespace zc2d {
@@ -395,10 +396,14 @@ ZC_DEV void encode_block(const uint32_t (&x)[16], const uint32_t* expand, uint32
   if (any_lane_active(left > 0)) {
     uint32_t h[8], sig = 0u;
     // the first non-empty plane to bit 31, or, where mostly sixteen planes or less are coded, to bit 15: shifts to the right take the
-    // GPU half as long, and but for tiny blocks (and zero ones) lead is 13 at most: the largest of the 16 numbers is 2^26 or
-    // more, and coefficients below 2^16 would make them 2^19 at most
+    // GPU half as long.  These need lead to be 16 at most, and but for tiny blocks (and zero ones) it is 8: the largest of the 16
+    // numbers is 2^26 or more, the inverse transform makes no number larger than 2.25 times 2.25 times the largest coefficient (but for
+    // what the halvings drop, less than 2^5), so that one coefficient is 2^23 or more, which takes a digit at bit 23 or above.
     constexpr bool kDown = RATE <= 8;
     if constexpr (kDown) {
+#if !defined(__HIP_DEVICE_COMPILE__)
+      assert(tiny || raw >= 32u || raw <= 8u);
+#endif
       if (tiny) {
 #pragma unroll
         for (int c = 0; c < 16; ++c) u[c] <<= umax(lead & 31u, 16u) - 16u;

@@ -637,6 +637,8 @@ struct DecodeLds {
   char digits[MATRIX ? 16 * THREADS : 16];
 };
 
+// (Six wavefronts per SIMD for the forms with the matrix product, which at rate 8 would take 82 registers and leave five.  For the others 1
+// says nothing: the compiler makes the same of them without.)
 template <int RATE, int DT, int THREADS>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(as_matrix(RATE, THREADS) ? 6 : 1)))
 void decompress2d_kernel(const uint8_t* __restrict__ in, Walk w, void* __restrict__ out) {

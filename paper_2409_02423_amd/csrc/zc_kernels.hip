@@ -914,11 +914,12 @@ unsigned grid_for(size_t n, Kernel kernel, int rate, int blocks_per_lane) {
 }
 
 // Workgroups of a small message's kernel (one block per lane), or 0 if the message is not small.
-// The line is where the two forms meet, in workgroups of one block per lane and CU.  (us with tiles and with
+// The line is where the two forms meet, in workgroups of one block per lane and CU.  (Reduces at rate 8: three sets of
+// buffers in turn, 1572864 values to fp32, on the line, 6.1 and 5.9.  us with tiles and with
 // one block per lane, as one of 30 launches in a graph: compress at rate 8 2^18 values, one such workgroup per CU,
 // 4.3 and 2.5, 2^20 5.0 and 3.6, 2^21 5.9 and 4.9, 2^22 7.5 and 7.7; decompress 5.1 and 3.2, 5.4 and 3.8, 6.0 and
-// 5.0, 7.2 and 8.4; 2-way reduce 6.0 and 4.6, 6.6 and 5.8, 8.3 and 8.0, 12.3 and 13.0, at rate 24 18.8 and 11.5 for 300001 values
-// but 11.3 and 11.6 for 2^21; with raw output 4.0 and 3.4, 5.0 and 4.5, 5.9 and 6.1, for 1500001 values 6.9 and 5.5.  At rate 4,
+// 5.0, 7.2 and 8.4; 2-way reduce 6.1 and 4.6, 6.7 and 5.9, 8.1 and 8.0, 11.3 and 12.6, at rate 24 18.8 and 11.5 for 300001 values
+// but 11.3 and 11.6 for 2^21; at rate 8 with raw output 5.0 and 4.0, 5.7 and 5.1, 6.7 and 6.8, 8.7 and 11.0, for 1500001 values 9.5 and 6.7.  At rate 4,
 // whose wide kernels take 512 blocks per wavefront: compress 2^18 3.2 and 2.4, 2^20 3.4 and 2.9, 2^22 4.9 and 6.4;
 // decompress 2.3 and 2.1, 2^19 2.38 and 2.36, 2^20 2.5 and 2.6; reduces 2^18 2.9 and 2.6, 2^20 3.0 and 3.1, of two chunks
 // to a stream 2^17 2.44 and 2.42, 2^18 2.44 and 2.49, to fp32 700001 values 2.76 and 2.55 but 2^20 2.65 and 2.78.)
