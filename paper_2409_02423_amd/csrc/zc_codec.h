@@ -907,12 +907,13 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
       if constexpr (kZeroApart) uncommon = any_lane_active.lanes(E != 0u && !common_exponent(E));
       // (The count stays a branch.  us of zeros before it was none, with none and now: 2-way reduce to fp32 of 2^25 values at rate 12 35.6,
       // 38.0 and 35.3, to a stream 59.2, 61.7 and 58.6, 3-way reduce at rate 12 78.2, 82.1 and 77.4, at rate 16 101.5, 103.9 and 99.4;
-      // ordinary values alike.)
+      // ordinary values alike.  Not where rate 16 stores its values: decompress of 3000001 constant ones 16.8 without and 17.2 with it.)
       if (NW > 1 && (!kZeroApart || any_lane_active(E != 0u && top == 0u))) {
 #if defined(__HIP_DEVICE_COMPILE__)
-        // (at rate 32 this one keeps a register: 64 instead of 65 of the reduce of any number of chunks to fp32, eight wavefronts
-        // per SIMD instead of seven, 3-way 2^25 values 121 and 118 us; at the other rates it takes one or two per cent of two chunks)
-        if constexpr (kZeroApart && RATE == 32) asm volatile("");
+        // (at rate 32 this keeps it, and a register: 64 instead of 65 of the reduce of any number of chunks to fp32, eight wavefronts
+        // per SIMD instead of seven, 3-way 2^25 values 121 and 118 us; with the other one as well, 8-way 3000001 values 72.1 and 73.7; at the
+        // other rates it takes one or two per cent of two chunks)
+        if constexpr (kZeroApart && RATE == 32) asm volatile("; seldom");
 #endif
         lead = 0;
         bool found = false;
@@ -924,7 +925,7 @@ ZC_DEV void decode_block_to(uint32_t (&W)[Traits<RATE>::kWords], const Tables& t
           found = found || (w != 0);
         }
         lead = umin(lead - 8u, (uint32_t)kPayload);   // (the header byte)
-        if constexpr (kZeroApart) materialise_seldom(lead);
+        if constexpr (kZeroApart && RATE != 32 && !(FIRST && RATE == 16)) materialise_seldom(lead);
       }
       // a zero block ignores its payload; after 32 empty planes nothing is left to decode
       none = E == 0u || (kPayload > 32 && lead >= 32u);
